@@ -287,8 +287,17 @@ uint64_t exe_op_gemm_workspace(int32_t dtype, int32_t M, int32_t N, int32_t K);
 int exe_op_gemm_noalloc(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
                         const void* bias, int32_t act, float alpha, int32_t out_mode, void* out);
 uint64_t exe_op_gemm_noalloc_max_workspace(void);
+/* The GEMM for few rows that the model calls use where it is the faster one (decode iterations, small batches; float also up
+ * to about 2000 rows): streams the weights, the waves of a workgroup split K and add up in LDS.  A workgroup computes
+ * nt x 16 output features (nt in {1, 2, 4, 5}) of ma x 8 rows (ma in {1, 2, 4, 6, 8}); nt = 0 lets the library choose nt, ma
+ * and splits.  splits > 1 (bf16 only): K split over workgroups as well, partial sums in the workspace
+ * (splits x M x N floats), added by a second kernel.  K a multiple of 64 (bf16) or 32 (float), N of 4, operands 16-byte
+ * aligned, else EXE_ERR_SHAPE / EXE_ERR_ARG. */
+int exe_op_gemm_stream(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
+                       const void* bias, int32_t act, float alpha, int32_t out_mode, void* out, int32_t nt, int32_t ma,
+                       int32_t splits, void* workspace, uint64_t workspace_bytes);
 /* How exe_op_gemm launches a shape (host function; lets a test assert that its cases cover every kernel
- * instantiation): *route 0 = MFMA tile kernel, 2 = plain-FMA kernel; *cfg = tile configuration (0 64x256, 1 128x256,
+ * instantiation): *route 0 = MFMA tile kernel, 1 = streaming kernel (float), 2 = plain-FMA kernel; *cfg = tile configuration (0 64x256, 1 128x256,
  * 2 256x256, 3 64x128, 4 128x128, 5 256x128 rows x features); *splits = split-K parts (> 1: float partials in the
  * workspace, summed in split order by a second kernel); *rows_first = rows of the first launch (M, unless the rows
  * beyond whole rounds of 256 x 256 tiles go to a second, separately planned launch: ask again with M - *rows_first). */

@@ -1,0 +1,64 @@
+// What the GEMM kernels share: the MFMA step over 64 bytes of K, and the epilogue (alpha, bias, activation, and the store
+// in one of the three output modes).
+#pragma once
+#include "common.h"
+
+namespace exe {
+
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+
+template <typename T> struct Vec4;                     // four consecutive elements in one access
+template <> struct Vec4<float> { typedef f32x4 type; };
+template <> struct Vec4<bf16_t> { typedef bf16x4 type; };
+
+// 64 bytes of K of 16 weight rows times 16 activation rows: lane l holds 16 bytes of row l % 16, the k-values of lane group
+// l / 16.  Which k a lane group holds does not matter as long as both operands agree.  The weights are the MFMA's A
+// operand: the accumulator of lane l is output features 4 * (l / 16) .. +3 of row l % 16.
+template <typename T> struct HalfUnit;
+template <> struct HalfUnit<bf16_t> {
+    static __device__ __forceinline__ f32x4 mma(u32x4 w, u32x4 a, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+    }
+};
+template <> struct HalfUnit<float> {
+    static __device__ __forceinline__ f32x4 mma(u32x4 w, u32x4 a, f32x4 c)
+    {
+        f32x4 wf = __builtin_bit_cast(f32x4, w), af = __builtin_bit_cast(f32x4, a);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[i], af[i], c, 0, 0, 0);
+        return c;
+    }
+};
+
+// Stores 4 consecutive output features n..n+3 of row m.  v = raw accumulators.
+template <typename T>
+__device__ __forceinline__ void epilogue_store4(f32x4 v, int m, int n, int N, const T* __restrict__ bias, int act,
+                                                float alpha, int out_mode, void* __restrict__ out)
+{
+    f32x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = v[j] * alpha + (bias ? to_f32(bias[n + j]) : 0.f);
+    int64_t o = (int64_t)m * N + n;
+    if (out_mode == OUT_T) {
+        T* p = (T*)out + o;
+        if constexpr (sizeof(T) == 2) {
+            bf16x4 w;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = (bf16_t)act_apply(r[j], act);
+            *(bf16x4*)p = w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = act_apply(r[j], act);
+            *(f32x4*)p = r;
+        }
+    } else if (out_mode == OUT_RESID) {
+        f32x4* p = (f32x4*)((float*)out + o);
+        f32x4 h = *p;
+        *p = h + r;
+    } else {
+        *(f32x4*)((float*)out + o) = r;
+    }
+}
+
+}  // namespace exe

@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+#include <vector>
+
 namespace exe {
 
 struct GemmArgs {
@@ -18,15 +21,37 @@ struct GemmArgs {
     float* workspace;     // split-K partial sums
     size_t workspace_bytes;
     int lda = 0, ldw = 0; // row strides of A and W in elements (0 = K); the generic kernel takes dense rows only
+    // Launches of few rows may run on the streaming kernel (the model's do; exe_op_gemm serves bf16 with the tile kernel
+    // alone, whose launch plans exe_op_gemm_plan reports).
+    bool few_rows = false;
 };
-size_t gemm_workspace_bytes(int dtype, int M, int N, int K);
-// which kernel family a shape runs on: 0 tile (MFMA), 2 generic (plain FMA)
-int gemm_route(int dtype, int M, int N, int K);
-// how a shape is launched: route (as gemm_route), tile configuration (0 64x256, 1 128x256, 2 256x256, 3 64x128,
+size_t gemm_workspace_bytes(int dtype, int M, int N, int K, bool few_rows);
+// how a shape is launched with few_rows = (dtype is float): route (0 tile kernel, 1 streaming kernel, 2 generic), tile configuration (0 64x256, 1 128x256, 2 256x256, 3 64x128,
 // 4 128x128, 5 256x128), split-K parts, and the leading rows that the first launch takes (M unless the rows beyond
 // whole rounds of tiles go to a second launch)
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+
+// The streaming kernel (kernels_gemm_stream.hip): nt * 16 output features of ma * 8 rows per workgroup, K in `splits` parts of
+// units_per_split units (128 bytes of a row each); nt = 0: a shape it does not take.  launch_gemm_stream leaves float
+// partials in a.workspace if splits > 1.
+struct StreamPlan { int nt = 0, ma = 0, splits = 1, units_per_split = 0; double cost = 0.0; };
+StreamPlan gemm_stream_plan(int dtype, int M, int N, int K);
+StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K);    // nt in {1, 2, 4, 5}, ma in {1, 2, 4, 6, 8}
+hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
+hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t s);
+
+// A kernel's dynamic LDS limit, raised once per kernel and device.
+constexpr int MAX_DEVICES = 64;
+struct LdsLimit {
+    std::once_flag once;
+    hipError_t err = hipSuccess;
+    hipError_t raise(const void* kern, int bytes)
+    {
+        std::call_once(once, [&]() { err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+        return err;
+    }
+};
 
 hipError_t launch_embed(int dtype, const int32_t* tokens, const int32_t* pos, int T, int d, const void* tok_emb,
                         const void* pos_emb, float* h, hipStream_t s);

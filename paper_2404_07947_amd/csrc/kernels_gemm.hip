@@ -1,10 +1,11 @@
 // GEMM kernels for the projections of a Transformer layer: out = epilogue(alpha * A[M,K] . W[N,K]^T + bias).
 //
-//  * gemm_tile_kernel    bf16, MFMA 16x16x32.  Macro tiles (BM x 256 or BM x 128, 64 k per LDS stage) filled by
-//                        direct global->LDS loads into a ring of stages; software-pipelined fragment fetch;
-//                        optional split-K into float partials, finished by splitk_reduce_kernel.
-//                        Large M (encode) is MFMA / LDS-fill bound; small M (decode) streams the weights.
-//  * gemm_generic_kernel float or bf16 inputs, plain FMA in float, any shape (tiny fp32 config, odd shapes).
+//  * gemm_tile_kernel    MFMA 16x16x32 (bf16) or 16x16x4 (float).  Macro tiles (BM x 256 or BM x 128, 128 bytes of K
+//                        per LDS stage) filled by direct global->LDS loads into a ring of stages; software-pipelined
+//                        fragment fetch; optional split-K into float partials (bf16), finished by splitk_reduce_kernel.
+//                        Large M (encode) is MFMA / LDS-fill bound.
+//  * gemm_stream_kernel  (kernels_gemm_stream.hip) few rows: streams the weights, the waves of a workgroup split K.
+//  * gemm_generic_kernel float or bf16 inputs, plain FMA in float, any shape (depths and widths the others do not take).
 //
 // Both A and W are K-contiguous, so both MFMA operands are 16-byte vectors along K.  The MFMA "A" operand
 // is fed with weight rows and the "B" operand with activation rows: the accumulator then holds 4
@@ -22,7 +23,7 @@
 #include <type_traits>
 #include <unordered_map>
 
-#include "common.h"
+#include "gemm_epilogue.h"
 #include "kernels.h"
 
 #ifndef EXE_GEMM_ABLATE
@@ -37,42 +38,12 @@
 
 namespace exe {
 
-// ---------------------------------------------------------------- shared epilogue
-// Stores 4 consecutive output features n..n+3 of row m.  v = raw accumulators.
-template <typename T>
-__device__ __forceinline__ void epilogue_store4(f32x4 v, int m, int n, int N, const T* __restrict__ bias, int act,
-                                                float alpha, int out_mode, void* __restrict__ out)
-{
-    f32x4 r;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = v[j] * alpha + (bias ? to_f32(bias[n + j]) : 0.f);
-    int64_t o = (int64_t)m * N + n;
-    if (out_mode == OUT_T) {
-        T* p = (T*)out + o;
-        if constexpr (sizeof(T) == 2) {
-            bf16x4 w;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = (bf16_t)act_apply(r[j], act);
-            *(bf16x4*)p = w;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) r[j] = act_apply(r[j], act);
-            *(f32x4*)p = r;
-        }
-    } else if (out_mode == OUT_RESID) {
-        f32x4* p = (f32x4*)((float*)out + o);
-        f32x4 h = *p;
-        *p = h + r;
-    } else {
-        *(f32x4*)((float*)out + o) = r;
-    }
-}
-
-// ---------------------------------------------------------------- tile kernel (bf16, MFMA 16x16x32): LDS layout
-// LDS tile layout for a stage of 64 bf16 along K: row r is 128 bytes = 8 chunks of 16 bytes; chunk c is
+// ---------------------------------------------------------------- tile kernel: LDS layout
+// LDS tile layout for a stage of 64 bf16 (32 float) along K: row r is 128 bytes = 8 chunks of 16 bytes; chunk c is
 // stored at slot c ^ ((r>>1)&7), so that 16 consecutive rows read at the same chunk index touch 16 distinct
 // 16-byte bank groups (256 bytes of banks; measured: zero LDS bank conflicts).
-constexpr int TBK = 64;
+constexpr int TROW = 128;                                   // bytes of K per stage
+template <typename T> constexpr int tbk() { return TROW / (int)sizeof(T); }
 __device__ __forceinline__ int lds_swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int lds_off(int row, int chunk) { return row * 128 + ((chunk ^ lds_swz(row)) << 4); }
 
@@ -124,10 +95,10 @@ template <> struct LdsTurn<2> {
 // acc[i][j]: the wave's accumulator tiles (i: 16 output features, j: 16 rows); stg: LDS byte address of the wave's
 // buffer (EN * 128 bytes); (row0, col0): output coordinates of the wave's first element; fout: float destination
 // of EPI_PARTIAL / EPI_F32 / EPI_RESID; tout: bf16 destination of EPI_T*.
-template <int TM, int TN, int EN, int MODE>
+template <typename T, int TM, int TN, int EN, int MODE>
 __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsigned stg, int lane, int row0, int col0,
-                                               int M, int N, const bf16_t* __restrict__ bias, float alpha,
-                                               float* __restrict__ fout, bf16_t* __restrict__ tout)
+                                               int M, int N, const T* __restrict__ bias, float alpha,
+                                               float* __restrict__ fout, T* __restrict__ tout)
 {
     static_assert(TM % 2 == 0 && TN % 2 == 0, "groups are 2 tiles high");
     constexpr int QW = EN / 8;                  // 16-byte slots a lane writes, and reads, per group
@@ -158,7 +129,7 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
             int n = g_col(x);
             bv[x] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (bias && n < N) {
-                bf16x4 b = *(const bf16x4*)(bias + n);
+                typename Vec4<T>::type b = *(const typename Vec4<T>::type*)(bias + n);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) bv[x][e] = (float)b[e];
             }
@@ -200,11 +171,11 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
                 if (MODE == EPI_F32) *(f32x4*)(fout + o) = r;
                 else if (MODE == EPI_RESID) *(f32x4*)(fout + o) = res[g % D][p] + r;
                 else {
-                    bf16x4 w;
+                    typename Vec4<T>::type w;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        w[e] = (bf16_t)(MODE == EPI_T_RELU ? act_apply(r[e], 0) : MODE == EPI_T_GELU ? act_apply(r[e], 1) : r[e]);
-                    *(bf16x4*)(tout + o) = w;
+                        w[e] = (T)(MODE == EPI_T_RELU ? act_apply(r[e], 0) : MODE == EPI_T_GELU ? act_apply(r[e], 1) : r[e]);
+                    *(typename Vec4<T>::type*)(tout + o) = w;
                 }
             }
         }
@@ -217,7 +188,7 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
 // room within the 160 KB of a CU, else 16 (2 KB per wave).
 constexpr int epilogue_cols(int BM, int BN, int WM, int WN, int ST)
 {
-    return ST * (BM + BN) * TBK * 2 + (BM / WM) * (BN / WN) * 4096 <= 160 * 1024 ? 32 : 16;
+    return ST * (BM + BN) * TROW + (BM / WM) * (BN / WN) * 4096 <= 160 * 1024 ? 32 : 16;
 }
 
 // ---------------------------------------------------------------- tile kernel
@@ -240,10 +211,9 @@ constexpr int epilogue_cols(int BM, int BN, int WM, int WN, int ST)
 // Workgroups are persistent (one per CU) and the loader runs ahead across items, so that a tile's epilogue and
 // the first loads of the next tile overlap.  Split-K (n_split > 1): every item writes its float partial tile;
 // splitk_reduce_kernel finishes.
-template <int BM, int BN, int WM, int WN, int ST>
+template <typename T, int BM, int BN, int WM, int WN, int ST>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
-    int M, int N, int K, const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias,
-    int act, float alpha, int out_mode, void* __restrict__ out, float* __restrict__ partial, int tiles_m, int tiles_n,
+    int M, int N, int K, const T* __restrict__ A, const T* __restrict__ W, const T* __restrict__ bias, int act, float alpha, int out_mode, void* __restrict__ out, float* __restrict__ partial, int tiles_m, int tiles_n,
     int k_per_split, int n_split, int flags, int lda, int ldw)
 {
     // flags: bit 0 = spread the loads of a k-tile over the MFMAs (see below); bit 1 = the weights are read once
@@ -262,7 +232,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0, "tile/waves mismatch");
     static_assert(LPT * (ST - 1) <= 63, "vmcnt range");
     extern __shared__ __align__(16) unsigned char lds[];
-    constexpr int STAGE = (BM + BN) * TBK * 2;     // bytes per LDS stage: A tile then W tile
+    constexpr int STAGE = (BM + BN) * TROW;        // bytes per LDS stage: A tile then W tile
+    constexpr int TBK = tbk<T>();
+    constexpr unsigned ESZ = sizeof(T);
     constexpr int EN = epilogue_cols(BM, BN, WM, WN, ST);
 
     // Work items are (split, output tile) pairs, numbered split-major.  The workgroups are persistent: workgroup b
@@ -311,13 +283,13 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
         for (int p = 0; p < A_PASSES; ++p) {
             int rl = (p * NW + wave) * 8 + (lane >> 3);
             int r = m0 + rl < M ? rl : M - 1 - m0;
-            off_a[p] = (unsigned)r * (unsigned)(lda * 2) + (((lane & 7) ^ lds_swz(rl)) << 4);
+            off_a[p] = (unsigned)r * (unsigned)lda * ESZ + (((lane & 7) ^ lds_swz(rl)) << 4);
         }
 #pragma unroll
         for (int p = 0; p < B_PASSES; ++p) {
             int rl = (p * NW + wave) * 8 + (lane >> 3);
             int r = n0 + rl < N ? rl : N - 1 - n0;
-            off_w[p] = (unsigned)r * (unsigned)(ldw * 2) + (((lane & 7) ^ lds_swz(rl)) << 4);
+            off_w[p] = (unsigned)r * (unsigned)ldw * ESZ + (((lane & 7) ^ lds_swz(rl)) << 4);
         }
     };
     set_src(ld_v);
@@ -339,15 +311,15 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
 #pragma clang diagnostic pop
     auto issue_range = [&](int stage, auto x0, auto x1) {
         unsigned base = lds_base + stage * STAGE + wave * 1024;
-        const char* ka = base_a + ld_kt * (TBK * 2);
-        const char* kw = base_w + ld_kt * (TBK * 2);
+        const char* ka = base_a + ld_kt * TROW;
+        const char* kw = base_w + ld_kt * TROW;
 #pragma unroll
         for (int x = decltype(x0)::value; x < decltype(x1)::value; ++x) {
             if ((EXE_GEMM_ABLATE & 2) && x < A_PASSES) continue;
             if ((EXE_GEMM_ABLATE & 4) && x >= A_PASSES) continue;
             if (x < A_PASSES) load_to_lds(ka, off_a[x], base + x * NW * 1024);
-            else if (w_once) load_to_lds_nt(kw, off_w[x - A_PASSES], base + BM * TBK * 2 + (x - A_PASSES) * NW * 1024);
-            else load_to_lds(kw, off_w[x - A_PASSES], base + BM * TBK * 2 + (x - A_PASSES) * NW * 1024);
+            else if (w_once) load_to_lds_nt(kw, off_w[x - A_PASSES], base + BM * TROW + (x - A_PASSES) * NW * 1024);
+            else load_to_lds(kw, off_w[x - A_PASSES], base + BM * TROW + (x - A_PASSES) * NW * 1024);
         }
     };
     // moves the loader to the next k-tile; past the last item the last k-tile is loaded again, which keeps the
@@ -371,23 +343,24 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
     using X3 = std::integral_constant<int, Q3>;
     using X4 = std::integral_constant<int, LPX>;
 
-    // MFMA operands (16x16x32): lane l holds row l%16 and the 8 k-values 8*(l/16) .. +7 of a 32-k step, i.e.
-    // 16-byte chunk 4*ks + l/16 of the stage row.  The W fragments of a 32-k step are kept for all its row parts.
+    // MFMA operands: lane l holds 16-byte chunk 4*ks + l/16 of stage row l%16: the 8 k-values 8*(l/16) .. +7 of a 32-k step
+    // (16x16x32 bf16), or 4 k-values of a 16-k step, one for each of four MFMAs (16x16x4 float).  The W fragments of a step
+    // are kept for all its row parts.
     f32x4 acc[TN][TM];
     int frow = lane & 15, fk = lane >> 4;
-    bf16x8 fa[2][TMH], fw[2][TN];
+    u32x4 fa[2][TMH], fw[2][TN];
     // fragments of sub-step s of the k-tile in `stage`: activation rows of its row part, and (first row part of a
     // 32-k step only) the weight rows
     auto fetch = [&](int stage, int s) {
         const unsigned char* sa = lds + stage * STAGE;
-        const unsigned char* sw = sa + BM * TBK * 2;
+        const unsigned char* sw = sa + BM * TROW;
         int ks = s / MH, mh = s % MH;
 #pragma unroll
         for (int j = 0; j < TMH; ++j)
-            fa[s & 1][j] = *(const bf16x8*)(sa + lds_off(wm * WM + (mh * TMH + j) * 16 + frow, ks * 4 + fk));
+            fa[s & 1][j] = *(const u32x4*)(sa + lds_off(wm * WM + (mh * TMH + j) * 16 + frow, ks * 4 + fk));
         if (mh == 0) {
 #pragma unroll
-            for (int i = 0; i < TN; ++i) fw[ks & 1][i] = *(const bf16x8*)(sw + lds_off(wn * WN + i * 16 + frow, ks * 4 + fk));
+            for (int i = 0; i < TN; ++i) fw[ks & 1][i] = *(const u32x4*)(sw + lds_off(wn * WN + i * 16 + frow, ks * 4 + fk));
         }
     };
     // the MFMAs of sub-step s in two halves, so that the next sub-step's fragment fetch can be issued between them
@@ -399,7 +372,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
         for (int x = 0; x < NM; ++x) {
             if ((x < NM / 2) != (half == 0)) continue;
             int i = x / TMH, j = x % TMH;
-            acc[i][mh * TMH + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks & 1][i], fa[s & 1][j], acc[i][mh * TMH + j], 0, 0, 0);
+            acc[i][mh * TMH + j] = HalfUnit<T>::mma(fw[ks & 1][i], fa[s & 1][j], acc[i][mh * TMH + j]);
         }
     };
 #define EXE_SB __builtin_amdgcn_sched_barrier(0)
@@ -480,17 +453,17 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
 #pragma unroll
                     for (int j = 0; j < TM; ++j) asm volatile("" ::"v"(acc[i][j]));
             } else if (n_split > 1)
-                epilogue_tiles<TM, TN, EN, EPI_PARTIAL>(acc, stg, lane, row0, col0, M, N, nullptr, 1.f, partial + (int64_t)z * M * N, nullptr);
+                epilogue_tiles<T, TM, TN, EN, EPI_PARTIAL>(acc, stg, lane, row0, col0, M, N, nullptr, 1.f, partial + (int64_t)z * M * N, nullptr);
             else if (out_mode == OUT_RESID)
-                epilogue_tiles<TM, TN, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+                epilogue_tiles<T, TM, TN, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (out_mode == OUT_F32)
-                epilogue_tiles<TM, TN, EN, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+                epilogue_tiles<T, TM, TN, EN, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (act == 0)
-                epilogue_tiles<TM, TN, EN, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (bf16_t*)out);
+                epilogue_tiles<T, TM, TN, EN, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out);
             else if (act == 1)
-                epilogue_tiles<TM, TN, EN, EPI_T_GELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (bf16_t*)out);
+                epilogue_tiles<T, TM, TN, EN, EPI_T_GELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out);
             else
-                epilogue_tiles<TM, TN, EN, EPI_T>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (bf16_t*)out);
+                epilogue_tiles<T, TM, TN, EN, EPI_T>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out);
         }
         // first fragments of the next item (not held across the epilogue: it needs the registers)
         if (v + (int)gridDim.x < items) fetch(st, 0);
@@ -568,7 +541,10 @@ enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, N_CFG }
 struct CfgInfo { int bm, bn; };
 static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}};
 
-struct Plan { int route; int cfg; int splits; int k_per_split; int tiles; int spread; double cost; };
+static int k_tile(int dtype) { return dtype == DT_F32 ? tbk<float>() : tbk<bf16_t>(); }
+
+// route: 0 tile kernel, 1 streaming kernel (then `stream` says how), 2 generic kernel
+struct Plan { int route; int cfg; int splits; int k_per_split; int tiles; int spread; double cost; StreamPlan stream; };
 
 static int env_int(const char* name, int dflt)
 {
@@ -591,118 +567,130 @@ static const Knobs& knobs()
 // MI355X with the weights coming from HBM (the GEMM shapes of three models, 16 <= M <= 1024; the time of its picks
 // is within 1 % of the time of the best picks in total, 13 % at worst): a workgroup's time is the larger of its
 // LDS-fill traffic at the rate one CU sustains through its vector L1 (about 35 GB/s) and its MFMA work at the rate
-// the tile loop reaches on such short runs (about 3.5 TFLOP/s per CU; the 128 x 256 shape 0.8 of that); workgroups
-// run in rounds of one per CU; the whole launch cannot beat streaming W once from HBM; split-K adds the float
+// the tile loop reaches on such short runs (about 3.5 TFLOP/s per CU; the 128 x 256 shape 0.8 of that; float 0.45);
+// workgroups run in rounds of one per CU; the whole launch cannot beat streaming W once from HBM; split-K adds the float
 // partials' round trip and a second launch.
-static double plan_cost(int cfg, int splits, int M, int N, int K)
+static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K)
 {
-    int bm = CFG[cfg].bm, bn = CFG[cfg].bn;
+    int bm = CFG[cfg].bm, bn = CFG[cfg].bn, bk = k_tile(dtype), esz = TROW / bk;
     int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     int64_t wgs = tiles * splits;
     double rounds = (double)((wgs + 255) / 256);
-    double ktiles = (double)((K / TBK + splits - 1) / splits);
-    double fill = ktiles * (bm + bn) * TBK * 2 / 35e9;
-    double mfma = ktiles * 2.0 * bm * bn * TBK / (cfg == C128x256 ? 2.8e12 : 3.5e12);
+    double ktiles = (double)((K / bk + splits - 1) / splits);
+    double fill = ktiles * (bm + bn) * TROW / 35e9;
+    double mfma = ktiles * 2.0 * bm * bn * bk / (dtype == DT_F32 ? 0.45e12 : cfg == C128x256 ? 2.8e12 : 3.5e12);
     double t = rounds * (fill > mfma ? fill : mfma);
-    double hbm = (double)N * K * 2 / 5.5e12;
+    double hbm = (double)N * K * esz / 5.5e12;
     if (t < hbm) t = hbm;
     t += 4e-6;
     if (splits > 1) t += 2.0 * splits * M * N * 4 / 3e12 + 1e-6;
     return t;
 }
 
-// Split-K over `s` parts: every part but the last takes ceil(k-tiles / s) k-tiles, the last one the rest, which must
-// be at least 4 k-tiles.
-static int split_k_tiles(int K, int s) { return (K / TBK + s - 1) / s; }
-static bool split_ok(int K, int s)
+// Split-K over `s` parts (bf16): every part but the last takes ceil(k-tiles / s) k-tiles, the last one the rest, which
+// must be at least 4 k-tiles.  Float is not split: its callers need no workspace, and the few-row shapes that would
+// want it run on the streaming kernel.
+static int split_k_tiles(int dtype, int K, int s) { return (K / k_tile(dtype) + s - 1) / s; }
+static bool split_ok(int dtype, int K, int s)
 {
     if (s == 1) return true;
-    int per = split_k_tiles(K, s), last = K / TBK - per * (s - 1);
+    if (dtype == DT_F32) return false;
+    int per = split_k_tiles(dtype, K, s), last = K / k_tile(dtype) - per * (s - 1);
     return per >= 4 && last >= 4;
 }
 
-static Plan make_plan(int dtype, int M, int N, int K)
+// The streaming kernel is taken when its estimate is clearly below the tile kernel's (both are within 10-20 %): the tile
+// kernel's is a few per cent high where both stream from HBM.
+constexpr double STREAM_MARGIN = 0.92;
+
+// `few_rows`: the caller may be served by the streaming kernel (see GemmArgs).
+static Plan make_plan(int dtype, int M, int N, int K, bool few_rows)
 {
-    Plan p{2, 0, 1, K, 0, 0, 0.0};
-    if (dtype != DT_BF16 || N % 4 != 0 || K % TBK != 0 || M < 1) return p;
+    Plan p{2, 0, 1, K, 0, 0, 0.0, StreamPlan{}};
+    if (N % 4 != 0 || K % k_tile(dtype) != 0 || M < 1) return p;
     p.route = 0;
-    p.cfg = C256x256;
+    p.cfg = dtype == DT_F32 ? C128x128 : C256x256;
     // the model's choice per shape is remembered (a decode iteration asks for the same few shapes 4 times per layer)
-    struct Choice { int cfg, splits; double cost; };
+    struct Choice { int cfg, splits; double cost; StreamPlan stream; };
     thread_local std::unordered_map<uint64_t, Choice> memo;
-    uint64_t key = ((uint64_t)M << 44) ^ ((uint64_t)N << 22) ^ (uint64_t)K;
+    uint64_t key = ((uint64_t)M << 44) ^ ((uint64_t)N << 22) ^ ((uint64_t)K << 2) ^ (dtype == DT_F32 ? 2 : 0) ^ (few_rows ? 1 : 0);
     auto hit = memo.find(key);
     if (hit != memo.end()) {
         p.cfg = hit->second.cfg;
         p.splits = hit->second.splits;
         p.cost = hit->second.cost;
-    } else if (M > 1024) {
-        p.cost = plan_cost(C256x256, 1, M, N, K);
+        p.stream = hit->second.stream;
+    } else if (M > 1024 && dtype == DT_BF16) {
+        p.cost = plan_cost(dtype, C256x256, 1, M, N, K);
     } else {
         double best = 1e30;
         for (int cfg = 0; cfg < N_CFG; ++cfg) {
             if (CFG[cfg].bm >= 2 * M && CFG[cfg].bm > 64) continue;     // more than half the rows would be padding
+            if (dtype == DT_F32 && cfg != C64x128 && cfg != C128x128) continue;
             for (int s = 1; s <= 16; ++s) {
-                if (!split_ok(K, s)) continue;
-                double c = plan_cost(cfg, s, M, N, K);
+                if (!split_ok(dtype, K, s)) continue;
+                double c = plan_cost(dtype, cfg, s, M, N, K);
                 if (c < best) { best = c; p.cfg = cfg; p.splits = s; }
             }
         }
         p.cost = best;
+        if (few_rows && M <= (dtype == DT_F32 ? 2048 : 256)) {
+            p.stream = gemm_stream_plan(dtype, M, N, K);
+            if (p.stream.nt && p.stream.cost > STREAM_MARGIN * best) p.stream = StreamPlan{};
+            if (p.stream.nt) p.cost = p.stream.cost;
+        }
         if (memo.size() > 4096) memo.clear();
-        memo[key] = Choice{p.cfg, p.splits, p.cost};
+        memo[key] = Choice{p.cfg, p.splits, p.cost, p.stream};
+    }
+    if (p.stream.nt) {
+        p.route = 1;
+        p.splits = p.stream.splits;
+        return p;
     }
     const Knobs& kn = knobs();
-    if (kn.cfg >= 0 && kn.cfg < N_CFG) p.cfg = kn.cfg;
-    if (kn.split > 0 && split_ok(K, kn.split)) p.splits = kn.split;
+    if (kn.cfg >= 0 && kn.cfg < N_CFG && dtype == DT_BF16) p.cfg = kn.cfg;
+    if (kn.split > 0 && split_ok(dtype, K, kn.split)) p.splits = kn.split;
     p.spread = 1;     // never slower than issuing a k-tile's loads at once in that sweep, up to 15 % faster from M = 128 on
     if (kn.spread >= 0) p.spread = kn.spread != 0;
     p.tiles = ((M + CFG[p.cfg].bm - 1) / CFG[p.cfg].bm) * ((N + CFG[p.cfg].bn - 1) / CFG[p.cfg].bn);
-    p.k_per_split = split_k_tiles(K, p.splits) * TBK;
+    p.k_per_split = split_k_tiles(dtype, K, p.splits) * k_tile(dtype);
     return p;
 }
 
-int gemm_route(int dtype, int M, int N, int K) { return make_plan(dtype, M, N, K).route; }
-
-
 // Per-device launch state: the number of persistent workgroups of a tile GEMM (one per compute unit: every
 // configuration takes more than half of a CU's LDS, so one workgroup is resident per CU; rounded down to a
-// multiple of 8 for the XCD mapping) and, per tile configuration, whether the kernel's dynamic LDS limit has been
-// raised on that device.
-constexpr int MAX_DEVICES = 64;
-struct DeviceState { std::once_flag grid_once; int grid = 0; std::once_flag attr_once[8]; hipError_t attr_err[8]; };
-static DeviceState& device_state()
+// multiple of 8 for the XCD mapping).
+static int current_device()
 {
-    static DeviceState st[MAX_DEVICES];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
-    return st[dev];
+    return dev;
 }
 static int persistent_grid()
 {
-    DeviceState& d = device_state();
-    std::call_once(d.grid_once, [&]() {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-            cus = 256;
-        d.grid = cus / 8 * 8;
-        if (knobs().grid >= 8) d.grid = knobs().grid / 8 * 8;
+    static std::once_flag once[MAX_DEVICES];
+    static int grid[MAX_DEVICES];
+    int dev = current_device();
+    std::call_once(once[dev], [&]() {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) cus = 256;
+        grid[dev] = cus / 8 * 8;
+        if (knobs().grid >= 8) grid[dev] = knobs().grid / 8 * 8;
     });
-    return d.grid;
+    return grid[dev];
 }
 
 // A launch of many 256 x 256 tiles runs in rounds of one tile per CU, and a last round that fills few CUs costs as
 // much as a full one.  split_rows returns the number of leading rows whose tiles fill whole rounds when handing the
 // remaining rows (a few hundred) to a second, separately planned launch is cheaper by the cost model, else M.
-static int split_rows(int dtype, int M, int N, int K)
+static int split_rows(int dtype, int M, int N, int K, bool few_rows)
 {
-    if (M <= 1024 || make_plan(dtype, M, N, K).route != 0) return M;
+    if (M <= 1024 || dtype != DT_BF16 || make_plan(dtype, M, N, K, false).route != 0) return M;
     int G = persistent_grid();
     int tn = (N + 255) / 256, tm = (M + 255) / 256, total = tm * tn;
     int rounds = total / G;
     if (rounds < 1 || total == rounds * G) return M;
-    double whole = plan_cost(C256x256, 1, M, N, K);
+    double whole = plan_cost(dtype, C256x256, 1, M, N, K);
     // Candidates for the first launch: the most row tiles that fill whole rounds, and the largest multiple of 64 row
     // tiles.  With a multiple of 64 every XCD keeps one group of 8 row tiles for the whole launch and all eight walk
     // the weight columns in step; measured, a round of such a launch takes 3-6 % less (16 384 rows against 17 120 -
@@ -713,9 +701,9 @@ static int split_rows(int dtype, int M, int N, int K)
     for (int tm1 : cand) {
         if (tm1 < 1 || tm1 >= tm) continue;
         int M1 = tm1 * 256;
-        double first = plan_cost(C256x256, 1, M1, N, K);
+        double first = plan_cost(dtype, C256x256, 1, M1, N, K);
         if (tm1 % 64 == 0) first *= 0.95;
-        double parts = first + make_plan(dtype, M - M1, N, K).cost;
+        double parts = first + make_plan(dtype, M - M1, N, K, few_rows).cost;
         if (parts < best_cost) { best_cost = parts; best = M1; }
     }
     return best;
@@ -723,54 +711,57 @@ static int split_rows(int dtype, int M, int N, int K)
 
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first)
 {
-    int M1 = split_rows(dtype, M, N, K);
-    Plan p = make_plan(dtype, M1, N, K);
+    int M1 = split_rows(dtype, M, N, K, dtype == DT_F32);
+    Plan p = make_plan(dtype, M1, N, K, dtype == DT_F32);
     *route = p.route;
     *cfg = p.cfg;
     *splits = p.splits;
     *rows_first = M1;
 }
 
-size_t gemm_workspace_bytes(int dtype, int M, int N, int K)
+size_t gemm_workspace_bytes(int dtype, int M, int N, int K, bool few_rows)
 {
-    int M1 = split_rows(dtype, M, N, K);
-    if (M1 < M) return gemm_workspace_bytes(dtype, M - M1, N, K);
-    Plan p = make_plan(dtype, M, N, K);
+    int M1 = split_rows(dtype, M, N, K, few_rows);
+    if (M1 < M) return gemm_workspace_bytes(dtype, M - M1, N, K, few_rows);
+    Plan p = make_plan(dtype, M, N, K, few_rows);
     return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
 }
 
-template <int BM, int BN, int WM, int WN, int ST>
-static hipError_t launch_tile(const GemmArgs& a, const Plan& p, int cfg_index, hipStream_t s)
+hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s)
 {
-    auto kern = gemm_tile_kernel<BM, BN, WM, WN, ST>;
+    int64_t quads = ((int64_t)a.M * a.N) / 4;
+    splitk_reduce_kernel<bf16_t><<<(unsigned)((quads + 255) / 256), 256, 0, s>>>(
+        a.M, a.N, splits, a.workspace, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
+    return hipGetLastError();
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int ST>
+static hipError_t launch_tile(const GemmArgs& a, const Plan& p, hipStream_t s)
+{
+    auto kern = gemm_tile_kernel<T, BM, BN, WM, WN, ST>;
     constexpr int threads = (BM / WM) * (BN / WN) * 64;
-    size_t lds = (size_t)ST * (BM + BN) * TBK * 2 + (size_t)(threads / 64) * epilogue_cols(BM, BN, WM, WN, ST) * 128;
-    static_assert(ST * (BM + BN) * TBK * 2 + (BM / WM) * (BN / WN) * epilogue_cols(BM, BN, WM, WN, ST) * 128 <= 160 * 1024, "LDS budget");
-    DeviceState& d = device_state();
-    std::call_once(d.attr_once[cfg_index], [&]() {
-        d.attr_err[cfg_index] = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
-    if (d.attr_err[cfg_index] != hipSuccess) return d.attr_err[cfg_index];
+    constexpr int lds = ST * (BM + BN) * TROW + (threads / 64) * epilogue_cols(BM, BN, WM, WN, ST) * 128;
+    static_assert(lds <= 160 * 1024, "LDS budget");
+    static LdsLimit limit[MAX_DEVICES];
+    hipError_t e = limit[current_device()].raise((const void*)kern, lds);
+    if (e != hipSuccess) return e;
     int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
     int items = tm * tn * p.splits;
     int grid = items < persistent_grid() ? items : persistent_grid();
     int w_once = tm == 1 && a.M <= 64;      // measured: 7-10 % faster up to 32 rows, even from 96 rows on
     if (knobs().nt >= 0) w_once = knobs().nt != 0;
-    kern<<<grid, threads, lds, s>>>(a.M, a.N, a.K, (const bf16_t*)a.A, (const bf16_t*)a.W, (const bf16_t*)a.bias, a.act,
-                                    a.alpha, a.out_mode, a.out, a.workspace, tm, tn, p.k_per_split, p.splits,
+    kern<<<grid, threads, lds, s>>>(a.M, a.N, a.K, (const T*)a.A, (const T*)a.W, (const T*)a.bias, a.act, a.alpha, a.out_mode,
+                                    a.out, a.workspace, tm, tn, p.k_per_split, p.splits,
                                     (p.spread ? 1 : 0) | (w_once ? 2 : 0), a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.splits == 1) return e;
-    int64_t quads = ((int64_t)a.M * a.N) / 4;
-    splitk_reduce_kernel<bf16_t><<<(unsigned)((quads + 255) / 256), 256, 0, s>>>(
-        a.M, a.N, p.splits, a.workspace, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
     return hipGetLastError();
 }
+
+static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
 {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    int M1 = split_rows(a.dtype, a.M, a.N, a.K);
+    int M1 = split_rows(a.dtype, a.M, a.N, a.K, a.few_rows);
     if (M1 < a.M) {
         GemmArgs head = a, tail = a;
         head.M = M1;
@@ -781,9 +772,9 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         hipError_t e = launch_gemm(head, s);
         return e != hipSuccess ? e : launch_gemm(tail, s);
     }
-    Plan p = make_plan(a.dtype, a.M, a.N, a.K);
-    if (p.splits > 1 && (!a.workspace || a.workspace_bytes < gemm_workspace_bytes(a.dtype, a.M, a.N, a.K)))
-        return hipErrorInvalidValue;
+    Plan p = make_plan(a.dtype, a.M, a.N, a.K, a.few_rows);
+    // the generic kernel is the only one that reads and writes float operands element by element
+    if (a.dtype == DT_F32 && !(aligned16(a.A) && aligned16(a.W) && aligned16(a.out) && aligned16(a.bias))) p.route = 2;
     if (p.route == 2) {
         dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
         if (a.dtype == DT_F32)
@@ -794,14 +785,23 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
                                                              (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
         return hipGetLastError();
     }
-    switch (p.cfg) {
-        case C64x256: return launch_tile<64, 256, 32, 64, 3>(a, p, C64x256, s);
-        case C128x256: return launch_tile<128, 256, 64, 64, 3>(a, p, C128x256, s);
-        case C256x256: return launch_tile<256, 256, 128, 64, 2>(a, p, C256x256, s);
-        case C64x128: return launch_tile<64, 128, 32, 64, 4>(a, p, C64x128, s);
-        case C128x128: return launch_tile<128, 128, 64, 64, 3>(a, p, C128x128, s);
-        default: return launch_tile<256, 128, 64, 64, 3>(a, p, C256x128, s);
+    if (p.splits > 1 && (!a.workspace || a.workspace_bytes < (size_t)p.splits * a.M * a.N * sizeof(float)))
+        return hipErrorInvalidValue;
+    hipError_t e;
+    if (p.route == 1) e = launch_gemm_stream(a, p.stream, s);
+    else if (a.dtype == DT_F32) {
+        e = p.cfg == C64x128 ? launch_tile<float, 64, 128, 32, 64, 4>(a, p, s) : launch_tile<float, 128, 128, 64, 64, 3>(a, p, s);
+    } else {
+        switch (p.cfg) {
+            case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;
+            case C128x256: e = launch_tile<bf16_t, 128, 256, 64, 64, 3>(a, p, s); break;
+            case C256x256: e = launch_tile<bf16_t, 256, 256, 128, 64, 2>(a, p, s); break;
+            case C64x128: e = launch_tile<bf16_t, 64, 128, 32, 64, 4>(a, p, s); break;
+            case C128x128: e = launch_tile<bf16_t, 128, 128, 64, 64, 3>(a, p, s); break;
+            default: e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);
+        }
     }
+    return e != hipSuccess || p.splits == 1 ? e : launch_splitk_reduce(a, p.splits, s);
 }
 
 }  // namespace exe

@@ -337,9 +337,10 @@ extern "C" int exe_model_free(exe_model_t* m)
 
 static size_t gemm_ws_need(const exe_model* m, int N, int K)
 {
+    if (m->c.dtype == EXE_DTYPE_F32) return 0;             // float launches are not split
     size_t need = 0;
-    int lim = std::min(m->rows_cap, 4096);
-    for (int M = 1; M <= lim; ++M) need = std::max(need, gemm_workspace_bytes(m->c.dtype, M, N, K));
+    int lim = std::min(m->rows_cap, 1024);                 // more rows are split-K only in a remainder launch of at most 1024
+    for (int M = 1; M <= lim; ++M) need = std::max(need, gemm_workspace_bytes(m->c.dtype, M, N, K, true));
     return need;
 }
 
@@ -486,6 +487,7 @@ static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void
                     float alpha, int out_mode, void* out)
 {
     GemmArgs g{m->c.dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, m->gemm_ws, m->gemm_ws_bytes};
+    g.few_rows = true;
     double e = esz_of(m);
     double bytes = ((double)M * K + (double)N * K) * e +
                    (double)M * N * (out_mode == OUT_T ? e : (out_mode == OUT_RESID ? 8.0 : 4.0));
@@ -1626,7 +1628,7 @@ extern "C" int exe_run_rra(exe_model_t* m, const exe_rra_config_t* cfg, int32_t 
 // ---------------------------------------------------------------- single-operation entry points
 extern "C" uint64_t exe_op_gemm_workspace(int32_t dtype, int32_t M, int32_t N, int32_t K)
 {
-    return gemm_workspace_bytes(dtype, M, N, K);
+    return gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32);
 }
 
 extern "C" int exe_op_gemm(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A,
@@ -1637,9 +1639,36 @@ extern "C" int exe_op_gemm(void* hip_stream, int32_t dtype, int32_t M, int32_t N
     if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
     if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
     if (K % 8 || N % 4) return fail(EXE_ERR_SHAPE, "K must be a multiple of 8 and N of 4");
-    if (gemm_workspace_bytes(dtype, M, N, K) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
+    if (gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
     GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)workspace, (size_t)workspace_bytes};
+    g.few_rows = dtype == DT_F32;
     HIP_TRY(launch_gemm(g, (hipStream_t)hip_stream));
+    return EXE_OK;
+}
+
+extern "C" int exe_op_gemm_stream(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
+                                  const void* bias, int32_t act, float alpha, int32_t out_mode, void* out, int32_t nt, int32_t ma,
+                                  int32_t splits, void* workspace, uint64_t workspace_bytes)
+{
+    if (M < 1 || N < 1 || K < 1 || !A || !W || !out) return fail(EXE_ERR_ARG, "bad gemm arguments");
+    if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
+    if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
+    const void* ptrs[] = {A, W, bias, out};
+    for (const void* p : ptrs)
+        if ((uintptr_t)p & 15) return fail(EXE_ERR_ARG, "operands must be 16-byte aligned");
+    StreamPlan p;
+    if (nt == 0) p = gemm_stream_plan(dtype, M, N, K);
+    else {
+        if ((nt != 1 && nt != 2 && nt != 4 && nt != 5) || (ma != 1 && ma != 2 && ma != 4 && ma != 6 && ma != 8))
+            return fail(EXE_ERR_ARG, "no streaming GEMM of %d x 16 features and %d x 8 rows", nt, ma);
+        p = gemm_stream_candidate(dtype, nt, ma, splits, M, N, K);
+    }
+    if (!p.nt) return fail(EXE_ERR_SHAPE, "shape not served by the streaming kernel");
+    if (p.splits > 1 && (!workspace || workspace_bytes < (uint64_t)p.splits * M * N * sizeof(float)))
+        return fail(EXE_ERR_ARG, "workspace too small");
+    GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)workspace, (size_t)workspace_bytes};
+    HIP_TRY(launch_gemm_stream(g, p, (hipStream_t)hip_stream));
+    if (p.splits > 1) HIP_TRY(launch_splitk_reduce(g, p.splits, (hipStream_t)hip_stream));
     return EXE_OK;
 }
 
@@ -1679,7 +1708,7 @@ extern "C" int exe_op_gemm_noalloc(void* hip_stream, int32_t dtype, int32_t M, i
     if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
     if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
     if (K % 8 || N % 4) return fail(EXE_ERR_SHAPE, "K must be a multiple of 8 and N of 4");
-    size_t need = gemm_workspace_bytes(dtype, M, N, K);
+    size_t need = gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32);
     if (need > EXE_NOALLOC_SCRATCH_BYTES)
         return fail(EXE_ERR_SHAPE, "this shape's split-K partial sums take %llu bytes, the static scratch holds %llu",
                     (unsigned long long)need, (unsigned long long)EXE_NOALLOC_SCRATCH_BYTES);
@@ -1689,6 +1718,7 @@ extern "C" int exe_op_gemm_noalloc(void* hip_stream, int32_t dtype, int32_t M, i
     // every partial sum that the reduction reads is written by the GEMM launch before it, so nothing left in the
     // array by an earlier call is ever read and nothing needs clearing
     GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)ws, (size_t)EXE_NOALLOC_SCRATCH_BYTES};
+    g.few_rows = dtype == DT_F32;
     HIP_TRY(launch_gemm(g, (hipStream_t)hip_stream));
     return EXE_OK;
 }
@@ -1719,8 +1749,8 @@ extern "C" int exe_op_gemm_ld(void* hip_stream, int32_t dtype, int32_t M, int32_
     if (dtype != DT_BF16) return fail(EXE_ERR_ARG, "strided rows are a bf16 feature");
     if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
     if (K % 64 || N % 4 || lda < K || ldw < K || lda % 8 || ldw % 8) return fail(EXE_ERR_SHAPE, "K must be a multiple of 64, N of 4, strides of 8 and >= K");
-    if (gemm_route(dtype, M, N, K) != 0) return fail(EXE_ERR_SHAPE, "shape not served by the tile kernel");
-    if (gemm_workspace_bytes(dtype, M, N, K) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
+    if (M < 1) return fail(EXE_ERR_SHAPE, "shape not served by the tile kernel");
+    if (gemm_workspace_bytes(dtype, M, N, K, false) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
     GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)workspace, (size_t)workspace_bytes};
     g.lda = lda;
     g.ldw = ldw;
