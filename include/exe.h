@@ -313,6 +313,12 @@ int exe_op_gemm_ld(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_
 int exe_op_norm(void* hip_stream, int32_t dtype, int32_t rms, const float* x, const int32_t* row_index,
                 int32_t rows, int32_t d, const void* gain, const void* shift, float eps, float out_scale,
                 void* out);
+/* The same behind a projection whose split-K partial sums still lie in memory (the model's norms take them so): row src
+ * of x becomes x[src] + sum over splits of partial[s][src] (+ bias) first, then is normalised.  partial [splits,
+ * partial_rows, d] float, bias nullable in dtype; rows named by row_index must differ. */
+int exe_op_resid_norm(void* hip_stream, int32_t dtype, int32_t rms, float* x, const int32_t* row_index, int32_t rows,
+                      int32_t d, const float* partial, int32_t splits, int32_t partial_rows, const void* bias,
+                      const void* gain, const void* shift, float eps, float out_scale, void* out);
 /* Ragged prefill attention over packed qkv [T, 3*H*dh] (dtype): cu_seqlens [n_seqs+1] host.
  * causal 0/1; bias_by_dist nullable device float [H, 2*bias_radius+1] indexed by clamp(key-query)+radius.
  * out [T, H*dh] dtype. */

@@ -24,8 +24,12 @@ struct GemmArgs {
     // Launches of few rows may run on the streaming kernel (the model's do; exe_op_gemm serves bf16 with the tile kernel
     // alone, whose launch plans exe_op_gemm_plan reports).
     bool few_rows = false;
+    // OUT_RESID only: the caller's next kernel can add split-K partials to the residual stream itself.  launch_gemm then
+    // leaves them in the workspace, *pending = their number (0: the result is complete), and plans with the cheaper split.
+    int* pending = nullptr;
 };
-size_t gemm_workspace_bytes(int dtype, int M, int N, int K, bool few_rows);
+enum GemmMode { GEMM_TILE_ONLY = 0, GEMM_FEW_ROWS = 1, GEMM_DEFER = 2 };       // flags, as the two members above
+size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode);
 // how a shape is launched with few_rows = (dtype is float): route (0 tile kernel, 1 streaming kernel, 2 generic), tile configuration (0 64x256, 1 128x256, 2 256x256, 3 64x128,
 // 4 128x128, 5 256x128), split-K parts, and the leading rows that the first launch takes (M unless the rows beyond
 // whole rounds of tiles go to a second launch)
@@ -36,8 +40,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // units_per_split units (128 bytes of a row each); nt = 0: a shape it does not take.  launch_gemm_stream leaves float
 // partials in a.workspace if splits > 1.
 struct StreamPlan { int nt = 0, ma = 0, splits = 1, units_per_split = 0; double cost = 0.0; };
-StreamPlan gemm_stream_plan(int dtype, int M, int N, int K);
-StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K);    // nt in {1, 2, 4, 5}, ma in {1, 2, 4, 6, 8}
+StreamPlan gemm_stream_plan(int dtype, int M, int N, int K, bool defer);
+StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K, bool defer);    // nt in {1, 2, 4, 5}, ma in {1, 2, 4, 6, 8}
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t s);
 
@@ -57,8 +61,20 @@ hipError_t launch_embed(int dtype, const int32_t* tokens, const int32_t* pos, in
                         const void* pos_emb, float* h, hipStream_t s);
 hipError_t launch_load_hidden(int dtype, const void* x, int64_t n, float* h, hipStream_t s);
 hipError_t launch_store_hidden(int dtype, const float* h, int64_t n, void* out, hipStream_t s);
-hipError_t launch_norm(int dtype, int rms, const float* x, const int32_t* row_index, int rows, int d,
-                       const void* gain, const void* shift, float eps, float out_scale, void* out, hipStream_t s);
+struct NormArgs {
+    int dtype, rms;
+    float* x;                    // residual rows; written only with `partial`
+    const int32_t* row_index;    // nullable: selects rows of x (and of the partials)
+    int rows, d;
+    const void *gain, *shift;    // shift: LayerNorm only
+    float eps, out_scale;
+    void* out;                   // [rows, d] in dtype
+    // split-K partials [splits][partial_rows][d] of the projection that ends in x, and its bias (nullable): added to x first
+    const float* partial = nullptr;
+    int splits = 0, partial_rows = 0;
+    const void* bias = nullptr;
+};
+hipError_t launch_norm(const NormArgs& a, hipStream_t s);
 // copies K and V rows of `src` (row stride ld, K at column k_off, V at v_off) into the cache:
 // token t belongs to batch entry tok_b[t] (t itself if nullptr) at position tok_pos[t];
 // K of (b, head, pos) lives at pool + base[b] + ((layer*2+0)*H + head)*cap[b]*dh + pos*dh, V at kv index 1.

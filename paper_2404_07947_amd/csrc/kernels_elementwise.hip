@@ -67,17 +67,26 @@ hipError_t launch_store_hidden(int dtype, const float* h, int64_t n, void* out, 
 }
 
 // ---------------------------------------------------------------- norms
-// One workgroup per row.  The row is kept in LDS as float, statistics are exact two-pass in float:
+// One workgroup per row, the row in registers (Q groups of 4 elements per thread); statistics are exact two-pass in float:
 // LayerNorm: mean, then the mean of squared deviations; RMSNorm: mean of squares.
-__device__ __forceinline__ float block_sum(float v, float* red)
+//
+// With `partial` the kernel first finishes the product that ends in the residual stream: x += sum of the split-K partials
+// (in split order, then the bias), which saves the reduction kernel between a projection and the norm behind it.
+//
+// What bounds it: few rows are a chain of latencies (loads, two reductions, store), so every load is issued before the
+// first reduction; many rows are a stream.  Measured against a kernel that keeps the row in LDS, us per launch:
+//   1 x 5120 3.7 -> 3.1, with 4 partials (reduction + norm before) 8.3 -> 4.2; 32 x 5120 with 4 7.4 -> 4.5; 256 x 5120 with 4
+//   10.4 -> 5.7; 512 x 5120 with 2 15.3 -> 7.7; 64 x 1024 with 8 5.7 -> 3.0; 16384 x 5120 108 -> 90 (5.6 TB/s);
+//   8192 x 1024 16.8 -> 9.8; float 12288 x 256 15.5 -> 6.2
+template <int NT> __device__ __forceinline__ float block_sum(float v, float* red)
 {
     v = wave_sum(v);
-    int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
+    if (NT == 64) return v;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     float t = 0.f;
-    for (int i = 0; i < nw; ++i) t += red[i];
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) t += red[i];
     return t;
 }
 
@@ -97,61 +106,109 @@ __device__ __forceinline__ void store4(bf16_t* p, f32x4 v)
     *(bf16x4*)p = w;
 }
 
-template <typename T, bool RMS>
-__global__ void norm_kernel(const float* __restrict__ x, const int32_t* __restrict__ row_index, int d,
-                            const T* __restrict__ gain, const T* __restrict__ shift, float eps, float out_scale,
-                            T* __restrict__ out)
+template <typename T, bool RMS, int NT, int Q>
+__global__ __launch_bounds__(NT) void norm_kernel(float* __restrict__ x, const int32_t* __restrict__ row_index, int d,
+                                                  const float* __restrict__ partial, int splits, int64_t slice,
+                                                  const T* __restrict__ bias, const T* __restrict__ gain,
+                                                  const T* __restrict__ shift, float eps, float out_scale, T* __restrict__ out)
 {
-    extern __shared__ float row[];
-    __shared__ float red[16];
+    __shared__ float red[2][16];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     int r = blockIdx.x;
     int64_t src = row_index ? row_index[r] : r;
-    const float* xr = x + src * d;
-    float s = 0.f;
-    for (int k = threadIdx.x * 4; k < d; k += blockDim.x * 4) {
-        f32x4 v = *(const f32x4*)(xr + k);
-        *(f32x4*)(row + k) = v;
-        s += RMS ? (v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w) : (v.x + v.y + v.z + v.w);
+    float* xr = x + src * d;
+    f32x4 v[Q], g[Q], b[Q];
+    auto at = [&](int q) { return (q * NT + (int)threadIdx.x) * 4; };
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        int k = at(q);
+        v[q] = k < d ? load4(xr + k) : zero;
+        g[q] = k < d ? load4(gain + k) : zero;
+        b[q] = !RMS && k < d ? load4(shift + k) : zero;
     }
-    float tot = block_sum(s, red);
+    if (partial) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            int k = at(q);
+            if (k >= d) continue;
+            const float* p = partial + src * d + k;
+            f32x4 sum = load4(p);
+            int s = 1;
+            for (; s + 3 <= splits; s += 3) {
+                f32x4 p0 = load4(p + s * slice), p1 = load4(p + (s + 1) * slice), p2 = load4(p + (s + 2) * slice);
+                sum += p0;
+                sum += p1;
+                sum += p2;
+            }
+            for (; s < splits; ++s) sum += load4(p + s * slice);
+            if (bias) sum += load4(bias + k);
+            v[q] += sum;
+            store4(xr + k, v[q]);
+        }
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        s += RMS ? (v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w) : (v[q].x + v[q].y + v[q].z + v[q].w);
+    float tot = block_sum<NT>(s, red[0]);
     float mean = 0.f, rstd;
     if (RMS) {
         rstd = 1.f / sqrtf(tot / d + eps);
     } else {
         mean = tot / d;
-        float q = 0.f;
-        for (int k = threadIdx.x * 4; k < d; k += blockDim.x * 4) {
-            f32x4 v = *(const f32x4*)(row + k);
-            float a = v.x - mean, b = v.y - mean, c = v.z - mean, e = v.w - mean;
-            q += a * a + b * b + c * c + e * e;
+        float sq = 0.f;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            float e0 = v[q].x - mean, e1 = v[q].y - mean, e2 = v[q].z - mean, e3 = v[q].w - mean;
+            if (at(q) < d) sq += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
         }
-        float var = block_sum(q, red) / d;
-        rstd = 1.f / sqrtf(var + eps);
+        rstd = 1.f / sqrtf(block_sum<NT>(sq, red[1]) / d + eps);
     }
     T* o = out + (int64_t)r * d;
-    for (int k = threadIdx.x * 4; k < d; k += blockDim.x * 4) {
-        f32x4 v = *(const f32x4*)(row + k);
-        f32x4 g = load4(gain + k), b = RMS ? f32x4{0.f, 0.f, 0.f, 0.f} : load4(shift + k), y;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = ((v[j] - mean) * rstd * g[j] + b[j]) * out_scale;
+    for (int q = 0; q < Q; ++q) {
+        int k = at(q);
+        if (k >= d) continue;
+        f32x4 y;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = ((v[q][j] - mean) * rstd * g[q][j] + b[q][j]) * out_scale;
         store4(o + k, y);
     }
 }
 
-hipError_t launch_norm(int dtype, int rms, const float* x, const int32_t* row_index, int rows, int d,
-                       const void* gain, const void* shift, float eps, float out_scale, void* out, hipStream_t s)
+template <typename T, bool RMS, int NT, int Q> static hipError_t norm_go(const NormArgs& a, hipStream_t s)
 {
-    if (rows <= 0) return hipSuccess;
-    if (d % 4 != 0 || d > 36864) return hipErrorInvalidValue;
-    size_t lds = (size_t)d * sizeof(float);
-    int threads = d >= 4096 ? 512 : 256;
-#define EXE_NORM(T, R)                                                                                       \
-    norm_kernel<T, R><<<rows, threads, lds, s>>>(x, row_index, d, (const T*)gain, (const T*)shift, eps,      \
-                                                 out_scale, (T*)out)
-    if (dtype == DT_F32) { if (rms) EXE_NORM(float, true); else EXE_NORM(float, false); }
-    else { if (rms) EXE_NORM(bf16_t, true); else EXE_NORM(bf16_t, false); }
-#undef EXE_NORM
+    norm_kernel<T, RMS, NT, Q><<<a.rows, NT, 0, s>>>(a.x, a.row_index, a.d, a.partial, a.splits, (int64_t)a.partial_rows * a.d,
+                                                     (const T*)a.bias, (const T*)a.gain, (const T*)a.shift, a.eps, a.out_scale,
+                                                     (T*)a.out);
     return hipGetLastError();
+}
+
+// Launch shape.  Few rows: as many threads as keep a thread at one or two groups, for the latency of the chain.  From 2048
+// rows on the chip is full whatever the shape, and small workgroups with more per thread are the faster stream (12288 x 256:
+// 64 threads 6.2 us, 256 11.1; 8192 x 1024: 64 threads 9.8 us, 256 13.6; 16384 x 5120: 512 threads 90 us, 1024 123).
+template <typename T, bool RMS> static hipError_t norm_shape(const NormArgs& a, hipStream_t s)
+{
+    int q = a.d / 4;
+    bool many = a.rows >= 2048;
+    if (q <= 64) return norm_go<T, RMS, 64, 1>(a, s);
+    if (q <= 128 && many) return norm_go<T, RMS, 64, 2>(a, s);
+    if (q <= 256) return many ? norm_go<T, RMS, 64, 4>(a, s) : norm_go<T, RMS, 256, 1>(a, s);
+    if (q <= 512) return norm_go<T, RMS, 256, 2>(a, s);
+    if (q <= 1024) return many ? norm_go<T, RMS, 256, 4>(a, s) : norm_go<T, RMS, 512, 2>(a, s);
+    if (q <= 1280) return many ? norm_go<T, RMS, 512, 3>(a, s) : norm_go<T, RMS, 640, 2>(a, s);
+    if (q <= 2048) return norm_go<T, RMS, 512, 4>(a, s);
+    if (q <= 3072) return norm_go<T, RMS, 768, 4>(a, s);
+    if (q <= 4096) return norm_go<T, RMS, 1024, 4>(a, s);
+    return norm_go<T, RMS, 1024, 9>(a, s);
+}
+
+hipError_t launch_norm(const NormArgs& a, hipStream_t s)
+{
+    if (a.rows <= 0) return hipSuccess;
+    if (a.d % 4 != 0 || a.d > 36864) return hipErrorInvalidValue;
+    if (a.dtype == DT_F32) return a.rms ? norm_shape<float, true>(a, s) : norm_shape<float, false>(a, s);
+    return a.rms ? norm_shape<bf16_t, true>(a, s) : norm_shape<bf16_t, false>(a, s);
 }
 
 // ---------------------------------------------------------------- K/V append

@@ -569,8 +569,8 @@ static const Knobs& knobs()
 // LDS-fill traffic at the rate one CU sustains through its vector L1 (about 35 GB/s) and its MFMA work at the rate
 // the tile loop reaches on such short runs (about 3.5 TFLOP/s per CU; the 128 x 256 shape 0.8 of that; float 0.45);
 // workgroups run in rounds of one per CU; the whole launch cannot beat streaming W once from HBM; split-K adds the float
-// partials' round trip and a second launch.
-static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K)
+// partials' round trip and a second launch (`defer`: the next kernel of the residual stream adds them up, see norm_kernel).
+static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, bool defer)
 {
     int bm = CFG[cfg].bm, bn = CFG[cfg].bn, bk = k_tile(dtype), esz = TROW / bk;
     int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -583,7 +583,7 @@ static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K)
     double hbm = (double)N * K * esz / 5.5e12;
     if (t < hbm) t = hbm;
     t += 4e-6;
-    if (splits > 1) t += 2.0 * splits * M * N * 4 / 3e12 + 1e-6;
+    if (splits > 1) t += defer ? 2.0 * splits * M * N * 4 / 8e12 - 1e-6 : 2.0 * splits * M * N * 4 / 3e12 + 1e-6;
     return t;
 }
 
@@ -603,8 +603,8 @@ static bool split_ok(int dtype, int K, int s)
 // kernel's is a few per cent high where both stream from HBM.
 constexpr double STREAM_MARGIN = 0.92;
 
-// `few_rows`: the caller may be served by the streaming kernel (see GemmArgs).
-static Plan make_plan(int dtype, int M, int N, int K, bool few_rows)
+// mode: what the caller allows (GemmMode)
+static Plan make_plan(int dtype, int M, int N, int K, int mode)
 {
     Plan p{2, 0, 1, K, 0, 0, 0.0, StreamPlan{}};
     if (N % 4 != 0 || K % k_tile(dtype) != 0 || M < 1) return p;
@@ -613,7 +613,7 @@ static Plan make_plan(int dtype, int M, int N, int K, bool few_rows)
     // the model's choice per shape is remembered (a decode iteration asks for the same few shapes 4 times per layer)
     struct Choice { int cfg, splits; double cost; StreamPlan stream; };
     thread_local std::unordered_map<uint64_t, Choice> memo;
-    uint64_t key = ((uint64_t)M << 44) ^ ((uint64_t)N << 22) ^ ((uint64_t)K << 2) ^ (dtype == DT_F32 ? 2 : 0) ^ (few_rows ? 1 : 0);
+    uint64_t key = ((uint64_t)M << 46) ^ ((uint64_t)N << 24) ^ ((uint64_t)K << 3) ^ (dtype == DT_F32 ? 4 : 0) ^ (uint64_t)mode;
     auto hit = memo.find(key);
     if (hit != memo.end()) {
         p.cfg = hit->second.cfg;
@@ -621,7 +621,7 @@ static Plan make_plan(int dtype, int M, int N, int K, bool few_rows)
         p.cost = hit->second.cost;
         p.stream = hit->second.stream;
     } else if (M > 1024 && dtype == DT_BF16) {
-        p.cost = plan_cost(dtype, C256x256, 1, M, N, K);
+        p.cost = plan_cost(dtype, C256x256, 1, M, N, K, false);
     } else {
         double best = 1e30;
         for (int cfg = 0; cfg < N_CFG; ++cfg) {
@@ -629,13 +629,13 @@ static Plan make_plan(int dtype, int M, int N, int K, bool few_rows)
             if (dtype == DT_F32 && cfg != C64x128 && cfg != C128x128) continue;
             for (int s = 1; s <= 16; ++s) {
                 if (!split_ok(dtype, K, s)) continue;
-                double c = plan_cost(dtype, cfg, s, M, N, K);
+                double c = plan_cost(dtype, cfg, s, M, N, K, mode & GEMM_DEFER);
                 if (c < best) { best = c; p.cfg = cfg; p.splits = s; }
             }
         }
         p.cost = best;
-        if (few_rows && M <= (dtype == DT_F32 ? 2048 : 256)) {
-            p.stream = gemm_stream_plan(dtype, M, N, K);
+        if ((mode & GEMM_FEW_ROWS) && M <= (dtype == DT_F32 ? 2048 : 256)) {
+            p.stream = gemm_stream_plan(dtype, M, N, K, mode & GEMM_DEFER);
             if (p.stream.nt && p.stream.cost > STREAM_MARGIN * best) p.stream = StreamPlan{};
             if (p.stream.nt) p.cost = p.stream.cost;
         }
@@ -683,14 +683,14 @@ static int persistent_grid()
 // A launch of many 256 x 256 tiles runs in rounds of one tile per CU, and a last round that fills few CUs costs as
 // much as a full one.  split_rows returns the number of leading rows whose tiles fill whole rounds when handing the
 // remaining rows (a few hundred) to a second, separately planned launch is cheaper by the cost model, else M.
-static int split_rows(int dtype, int M, int N, int K, bool few_rows)
+static int split_rows(int dtype, int M, int N, int K, int mode)
 {
-    if (M <= 1024 || dtype != DT_BF16 || make_plan(dtype, M, N, K, false).route != 0) return M;
+    if (M <= 1024 || dtype != DT_BF16 || make_plan(dtype, M, N, K, GEMM_TILE_ONLY).route != 0) return M;
     int G = persistent_grid();
     int tn = (N + 255) / 256, tm = (M + 255) / 256, total = tm * tn;
     int rounds = total / G;
     if (rounds < 1 || total == rounds * G) return M;
-    double whole = plan_cost(dtype, C256x256, 1, M, N, K);
+    double whole = plan_cost(dtype, C256x256, 1, M, N, K, false);
     // Candidates for the first launch: the most row tiles that fill whole rounds, and the largest multiple of 64 row
     // tiles.  With a multiple of 64 every XCD keeps one group of 8 row tiles for the whole launch and all eight walk
     // the weight columns in step; measured, a round of such a launch takes 3-6 % less (16 384 rows against 17 120 -
@@ -701,29 +701,32 @@ static int split_rows(int dtype, int M, int N, int K, bool few_rows)
     for (int tm1 : cand) {
         if (tm1 < 1 || tm1 >= tm) continue;
         int M1 = tm1 * 256;
-        double first = plan_cost(dtype, C256x256, 1, M1, N, K);
+        double first = plan_cost(dtype, C256x256, 1, M1, N, K, false);
         if (tm1 % 64 == 0) first *= 0.95;
-        double parts = first + make_plan(dtype, M - M1, N, K, few_rows).cost;
+        double parts = first + make_plan(dtype, M - M1, N, K, mode & ~GEMM_DEFER).cost;
         if (parts < best_cost) { best_cost = parts; best = M1; }
     }
     return best;
 }
 
+// exe_op_gemm's mode: bf16 by the tile kernel alone
+static int op_mode(int dtype) { return dtype == DT_F32 ? GEMM_FEW_ROWS : GEMM_TILE_ONLY; }
+
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first)
 {
-    int M1 = split_rows(dtype, M, N, K, dtype == DT_F32);
-    Plan p = make_plan(dtype, M1, N, K, dtype == DT_F32);
+    int M1 = split_rows(dtype, M, N, K, op_mode(dtype));
+    Plan p = make_plan(dtype, M1, N, K, op_mode(dtype));
     *route = p.route;
     *cfg = p.cfg;
     *splits = p.splits;
     *rows_first = M1;
 }
 
-size_t gemm_workspace_bytes(int dtype, int M, int N, int K, bool few_rows)
+size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode)
 {
-    int M1 = split_rows(dtype, M, N, K, few_rows);
-    if (M1 < M) return gemm_workspace_bytes(dtype, M - M1, N, K, few_rows);
-    Plan p = make_plan(dtype, M, N, K, few_rows);
+    int M1 = split_rows(dtype, M, N, K, mode);
+    if (M1 < M) return gemm_workspace_bytes(dtype, M - M1, N, K, mode & ~GEMM_DEFER);
+    Plan p = make_plan(dtype, M, N, K, mode);
     return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
 }
 
@@ -760,10 +763,13 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
 {
+    if (a.pending) *a.pending = 0;
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    int M1 = split_rows(a.dtype, a.M, a.N, a.K, a.few_rows);
+    int mode = (a.few_rows ? GEMM_FEW_ROWS : 0) | (a.pending && a.out_mode == OUT_RESID && a.alpha == 1.f ? GEMM_DEFER : 0);
+    int M1 = split_rows(a.dtype, a.M, a.N, a.K, mode);
     if (M1 < a.M) {
         GemmArgs head = a, tail = a;
+        head.pending = tail.pending = nullptr;
         head.M = M1;
         tail.M = a.M - M1;
         size_t esz = a.dtype == DT_BF16 ? 2 : 4, osz = a.out_mode == OUT_T ? esz : 4;
@@ -772,7 +778,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         hipError_t e = launch_gemm(head, s);
         return e != hipSuccess ? e : launch_gemm(tail, s);
     }
-    Plan p = make_plan(a.dtype, a.M, a.N, a.K, a.few_rows);
+    Plan p = make_plan(a.dtype, a.M, a.N, a.K, mode);
     // the generic kernel is the only one that reads and writes float operands element by element
     if (a.dtype == DT_F32 && !(aligned16(a.A) && aligned16(a.W) && aligned16(a.out) && aligned16(a.bias))) p.route = 2;
     if (p.route == 2) {
@@ -785,8 +791,17 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
                                                              (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
         return hipGetLastError();
     }
-    if (p.splits > 1 && (!a.workspace || a.workspace_bytes < (size_t)p.splits * a.M * a.N * sizeof(float)))
-        return hipErrorInvalidValue;
+    if (p.splits > 1 && (size_t)p.splits * a.M * a.N * sizeof(float) > (a.workspace ? a.workspace_bytes : 0)) {
+        // fewer parts than planned, as the workspace allows (a model's is sized from every eighth row count)
+        if (p.route == 1) {
+            p.stream = gemm_stream_candidate(a.dtype, p.stream.nt, p.stream.ma, 1, a.M, a.N, a.K, false);
+            p.splits = 1;
+        } else {
+            size_t fit = a.workspace ? a.workspace_bytes / ((size_t)a.M * a.N * sizeof(float)) : 0;
+            while (p.splits > 1 && ((size_t)p.splits > fit || !split_ok(a.dtype, a.K, p.splits))) --p.splits;
+            p.k_per_split = split_k_tiles(a.dtype, a.K, p.splits) * k_tile(a.dtype);
+        }
+    }
     hipError_t e;
     if (p.route == 1) e = launch_gemm_stream(a, p.stream, s);
     else if (a.dtype == DT_F32) {
@@ -801,7 +816,12 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
             default: e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);
         }
     }
-    return e != hipSuccess || p.splits == 1 ? e : launch_splitk_reduce(a, p.splits, s);
+    if (e != hipSuccess || p.splits == 1) return e;
+    if (mode & GEMM_DEFER) {
+        *a.pending = p.splits;
+        return hipSuccess;
+    }
+    return launch_splitk_reduce(a, p.splits, s);
 }
 
 }  // namespace exe

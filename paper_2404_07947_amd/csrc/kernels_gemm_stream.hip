@@ -175,8 +175,8 @@ static const int STREAM_NT[] = {1, 2, 4, 5}, STREAM_MA[] = {1, 2, 4, 6, 8};
 // Seconds of a launch with these parameters.  Two rates, fitted to the launches named at the top of this file and to 6
 // row counts x 16 weight shapes around them (within 10 % of the measured time for most, 20 % at worst): the weights come
 // from memory at 6.9 TB/s, and a CU takes in the rows of its workgroups, activations included, at 50 GB/s; the two overlap
-// for the most part (third-power mean).  Float adds the MFMA rate of a CU (0.55 TFLOP/s).  2.5 us are paid by every launch.
-static double stream_cost(int dtype, int nt, int ma, int splits, int M, int N, int K)
+// for the most part (third-power mean).  Partial sums cost their round trip, and a reduction launch unless the next kernel takes them (`defer`).  Float adds the MFMA rate of a CU (0.55 TFLOP/s).  2.5 us are paid by every launch.
+static double stream_cost(int dtype, int nt, int ma, int splits, int M, int N, int K, bool defer)
 {
     double e = dtype == DT_F32 ? 4.0 : 2.0;
     double wgs = (double)((N + nt * 16 - 1) / (nt * 16)) * ((M + ma * 8 - 1) / (ma * 8)) * splits;
@@ -187,28 +187,28 @@ static double stream_cost(int dtype, int nt, int ma, int splits, int M, int N, i
     double c = dtype == DT_F32 ? rounds * 2.0 * nt * 16 * ((ma + 1) / 2 * 16) * per / 0.55e12 : 0.0;
     double t = 2.5e-6 + cbrt(a * a * a + b * b * b + c * c * c);
     if (stream_waves(nt, ma) * 2 * (nt * 2 + ma) > 80) t += (rounds - 1) * 2e-6;       // one workgroup per CU: rounds do not overlap
-    if (splits > 1) t += 3.5e-6 + 2.0 * splits * M * N * 4 / 4e12;
+    if (splits > 1) t += defer ? 0.5e-6 + 2.0 * splits * M * N * 4 / 8e12 : 3.5e-6 + 2.0 * splits * M * N * 4 / 4e12;
     return t;
 }
 
 // the parameters of one candidate; nt = 0 if the shape does not allow it.  Float is not split over workgroups (no workspace
 // is asked of its callers); a bf16 part keeps at least 16 units, 4 for each wave.
-StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K)
+StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K, bool defer)
 {
     int ue = dtype == DT_F32 ? 32 : 64, units = K / ue, per = splits < 1 ? 0 : (units + splits - 1) / splits;
     if (M < 1 || N % 4 != 0 || K % ue != 0 || splits < 1) return StreamPlan{};
     if (splits > 1 && (dtype == DT_F32 || per < 16 || per * (splits - 1) >= units)) return StreamPlan{};
-    return StreamPlan{nt, ma, splits, per, stream_cost(dtype, nt, ma, splits, M, N, K)};
+    return StreamPlan{nt, ma, splits, per, stream_cost(dtype, nt, ma, splits, M, N, K, defer)};
 }
 
-StreamPlan gemm_stream_plan(int dtype, int M, int N, int K)
+StreamPlan gemm_stream_plan(int dtype, int M, int N, int K, bool defer)
 {
     StreamPlan best;
     for (int nt : STREAM_NT)
         for (int ma : STREAM_MA) {
             if (ma > 1 && (ma - 1) * 8 >= M + 7) continue;            // rows that do not exist
             for (int s = 1; s <= 8; s *= 2) {
-                StreamPlan p = gemm_stream_candidate(dtype, nt, ma, s, M, N, K);
+                StreamPlan p = gemm_stream_candidate(dtype, nt, ma, s, M, N, K, defer);
                 if (!p.nt) break;
                 if (!best.nt || p.cost < best.cost) best = p;
             }

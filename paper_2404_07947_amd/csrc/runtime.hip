@@ -190,6 +190,9 @@ struct exe_model {
     std::vector<int32_t> mark;            // duplicate detection
     int32_t mark_gen = 0;
     KTimer timer;
+    // Split-K partial sums of the last projection into the residual stream h that still lie in gemm_ws (splits > 0): the
+    // norm that follows adds them (run_norm), finish_resid does where none follows.
+    struct Pending { int splits = 0, rows = 0; const void* bias = nullptr; } pend;
 };
 
 // ---------------------------------------------------------------- timing helpers
@@ -340,7 +343,8 @@ static size_t gemm_ws_need(const exe_model* m, int N, int K)
     if (m->c.dtype == EXE_DTYPE_F32) return 0;             // float launches are not split
     size_t need = 0;
     int lim = std::min(m->rows_cap, 1024);                 // more rows are split-K only in a remainder launch of at most 1024
-    for (int M = 1; M <= lim; ++M) need = std::max(need, gemm_workspace_bytes(m->c.dtype, M, N, K, true));
+    for (int M = lim; M >= 1; M = (M - 1) / 8 * 8)         // row counts between these fit, or split less
+        for (int mode : {GEMM_FEW_ROWS | 0, GEMM_FEW_ROWS | GEMM_DEFER}) need = std::max(need, gemm_workspace_bytes(m->c.dtype, M, N, K, mode));
     return need;
 }
 
@@ -488,6 +492,11 @@ static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void
 {
     GemmArgs g{m->c.dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, m->gemm_ws, m->gemm_ws_bytes};
     g.few_rows = true;
+    if (out_mode == OUT_RESID) {
+        g.pending = &m->pend.splits;
+        m->pend.rows = M;
+        m->pend.bias = bias;
+    }
     double e = esz_of(m);
     double bytes = ((double)M * K + (double)N * K) * e +
                    (double)M * N * (out_mode == OUT_T ? e : (out_mode == OUT_RESID ? 8.0 : 4.0));
@@ -499,9 +508,25 @@ static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void
 static int run_norm(exe_model* m, const int32_t* row_index, int rows, const void* g, const void* b, float out_scale,
                     void* out)
 {
-    LAUNCH(m, EXE_K_NORM, (double)rows * m->c.d_model * (4.0 + esz_of(m)), 0.0,
-           launch_norm(m->c.dtype, m->c.norm == EXE_NORM_RMSNORM, m->h, row_index, rows, m->c.d_model, g, b,
-                       m->c.norm_eps, out_scale, out, m->stream));
+    NormArgs a{m->c.dtype, m->c.norm == EXE_NORM_RMSNORM, m->h, row_index, rows, m->c.d_model, g, b, m->c.norm_eps, out_scale, out};
+    if (m->pend.splits) {
+        a.partial = m->gemm_ws;
+        a.splits = m->pend.splits;
+        a.partial_rows = m->pend.rows;
+        a.bias = m->pend.bias;
+        m->pend.splits = 0;
+    }
+    LAUNCH(m, EXE_K_NORM, (double)rows * m->c.d_model * (4.0 + esz_of(m)), 0.0, launch_norm(a, m->stream));
+    return EXE_OK;
+}
+
+// completes h where no norm follows (hidden states out)
+static int finish_resid(exe_model* m)
+{
+    if (!m->pend.splits) return EXE_OK;
+    GemmArgs g{m->c.dtype, m->pend.rows, m->c.d_model, 0, nullptr, nullptr, m->pend.bias, -1, 1.f, OUT_RESID, m->h, m->gemm_ws, m->gemm_ws_bytes};
+    LAUNCH(m, EXE_K_OTHER, 0.0, 0.0, launch_splitk_reduce(g, m->pend.splits, m->stream));
+    m->pend.splits = 0;
     return EXE_OK;
 }
 
@@ -773,6 +798,7 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
     }
     if (st.off > m->stage_bytes) { rollback(); return fail(EXE_ERR_ARG, "descriptor staging overflow"); }
 
+    m->pend.splits = 0;                    // h is about to be written anew
     auto body = [&]() -> int {
         HIP_TRY(hipMemcpyAsync(m->stage_d, m->stage_h, st.off, hipMemcpyHostToDevice, m->stream));
         if (c.has_embed)
@@ -798,6 +824,7 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
             return EXE_OK;
         }
         if (c.has_lm_head) return run_head(m, d.last, n, next_tokens, out_device);
+        if ((r = finish_resid(m))) return r;
         if (out_device)
             LAUNCH(m, EXE_K_OTHER, (double)T * c.d_model * (esz_of(m) + 4.0), 0.0,
                    launch_store_hidden(c.dtype, m->h, (int64_t)T * c.d_model, out_device, m->stream));
@@ -967,6 +994,7 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
         dd.table_w = stage_block_table(m, st, sp, &dd.table);
         if (st.off > m->stage_bytes) return fail(EXE_ERR_ARG, "descriptor staging overflow");
     }
+    m->pend.splits = 0;                    // h is about to be written anew
     HIP_TRY(hipMemcpyAsync(m->stage_d, m->stage_h, st.off, hipMemcpyHostToDevice, m->stream));
     int r;
     if ((r = decode_input(m, dd, n, hidden_in))) return r;
@@ -976,6 +1004,7 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
     if (c.has_lm_head) {
         if ((r = run_head(m, nullptr, n, next_tokens, out_device))) return r;
     } else {
+        if ((r = finish_resid(m))) return r;
         if (out_device)
             LAUNCH(m, EXE_K_OTHER, (double)n * c.d_model * (e + 4.0), 0.0,
                    launch_store_hidden(c.dtype, m->h, (int64_t)n * c.d_model, out_device, m->stream));
@@ -1329,6 +1358,7 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
     if (he == hipSuccess) he = hipMemsetAsync(m->h, 0, (size_t)m->rows_cap * c.d_model * sizeof(float), m->stream);
     if (he != hipSuccess) { rollback(); return fail(EXE_ERR_HIP, "profile memset: %s", hipGetErrorString(he)); }
 
+    m->pend.splits = 0;
     Stager st{m};
     EncodeDesc ed{};
     DecodeDesc dd{};
@@ -1628,7 +1658,7 @@ extern "C" int exe_run_rra(exe_model_t* m, const exe_rra_config_t* cfg, int32_t 
 // ---------------------------------------------------------------- single-operation entry points
 extern "C" uint64_t exe_op_gemm_workspace(int32_t dtype, int32_t M, int32_t N, int32_t K)
 {
-    return gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32);
+    return gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32 ? GEMM_FEW_ROWS : GEMM_TILE_ONLY);
 }
 
 extern "C" int exe_op_gemm(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A,
@@ -1639,7 +1669,7 @@ extern "C" int exe_op_gemm(void* hip_stream, int32_t dtype, int32_t M, int32_t N
     if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
     if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
     if (K % 8 || N % 4) return fail(EXE_ERR_SHAPE, "K must be a multiple of 8 and N of 4");
-    if (gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
+    if (gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32 ? GEMM_FEW_ROWS : GEMM_TILE_ONLY) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
     GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)workspace, (size_t)workspace_bytes};
     g.few_rows = dtype == DT_F32;
     HIP_TRY(launch_gemm(g, (hipStream_t)hip_stream));
@@ -1657,11 +1687,11 @@ extern "C" int exe_op_gemm_stream(void* hip_stream, int32_t dtype, int32_t M, in
     for (const void* p : ptrs)
         if ((uintptr_t)p & 15) return fail(EXE_ERR_ARG, "operands must be 16-byte aligned");
     StreamPlan p;
-    if (nt == 0) p = gemm_stream_plan(dtype, M, N, K);
+    if (nt == 0) p = gemm_stream_plan(dtype, M, N, K, false);
     else {
         if ((nt != 1 && nt != 2 && nt != 4 && nt != 5) || (ma != 1 && ma != 2 && ma != 4 && ma != 6 && ma != 8))
             return fail(EXE_ERR_ARG, "no streaming GEMM of %d x 16 features and %d x 8 rows", nt, ma);
-        p = gemm_stream_candidate(dtype, nt, ma, splits, M, N, K);
+        p = gemm_stream_candidate(dtype, nt, ma, splits, M, N, K, false);
     }
     if (!p.nt) return fail(EXE_ERR_SHAPE, "shape not served by the streaming kernel");
     if (p.splits > 1 && (!workspace || workspace_bytes < (uint64_t)p.splits * M * N * sizeof(float)))
@@ -1708,7 +1738,7 @@ extern "C" int exe_op_gemm_noalloc(void* hip_stream, int32_t dtype, int32_t M, i
     if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
     if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
     if (K % 8 || N % 4) return fail(EXE_ERR_SHAPE, "K must be a multiple of 8 and N of 4");
-    size_t need = gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32);
+    size_t need = gemm_workspace_bytes(dtype, M, N, K, dtype == DT_F32 ? GEMM_FEW_ROWS : GEMM_TILE_ONLY);
     if (need > EXE_NOALLOC_SCRATCH_BYTES)
         return fail(EXE_ERR_SHAPE, "this shape's split-K partial sums take %llu bytes, the static scratch holds %llu",
                     (unsigned long long)need, (unsigned long long)EXE_NOALLOC_SCRATCH_BYTES);
@@ -1750,7 +1780,7 @@ extern "C" int exe_op_gemm_ld(void* hip_stream, int32_t dtype, int32_t M, int32_
     if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
     if (K % 64 || N % 4 || lda < K || ldw < K || lda % 8 || ldw % 8) return fail(EXE_ERR_SHAPE, "K must be a multiple of 64, N of 4, strides of 8 and >= K");
     if (M < 1) return fail(EXE_ERR_SHAPE, "shape not served by the tile kernel");
-    if (gemm_workspace_bytes(dtype, M, N, K, false) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
+    if (gemm_workspace_bytes(dtype, M, N, K, GEMM_TILE_ONLY) > workspace_bytes) return fail(EXE_ERR_ARG, "workspace too small");
     GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)workspace, (size_t)workspace_bytes};
     g.lda = lda;
     g.ldw = ldw;
@@ -1763,7 +1793,20 @@ extern "C" int exe_op_norm(void* hip_stream, int32_t dtype, int32_t rms, const f
                            void* out)
 {
     if (!x || !gain || !out || rows < 0 || d < 1 || (!rms && !shift)) return fail(EXE_ERR_ARG, "bad norm arguments");
-    HIP_TRY(launch_norm(dtype, rms, x, row_index, rows, d, gain, shift, eps, out_scale, out, (hipStream_t)hip_stream));
+    NormArgs a{dtype, rms, const_cast<float*>(x), row_index, rows, d, gain, shift, eps, out_scale, out};    // x is not written
+    HIP_TRY(launch_norm(a, (hipStream_t)hip_stream));
+    return EXE_OK;
+}
+
+extern "C" int exe_op_resid_norm(void* hip_stream, int32_t dtype, int32_t rms, float* x, const int32_t* row_index, int32_t rows,
+                                 int32_t d, const float* partial, int32_t splits, int32_t partial_rows, const void* bias,
+                                 const void* gain, const void* shift, float eps, float out_scale, void* out)
+{
+    if (!x || !gain || !out || rows < 0 || d < 1 || (!rms && !shift) || !partial || splits < 1 || partial_rows < 1)
+        return fail(EXE_ERR_ARG, "bad norm arguments");
+    if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
+    NormArgs a{dtype, rms, x, row_index, rows, d, gain, shift, eps, out_scale, out, partial, splits, partial_rows, bias};
+    HIP_TRY(launch_norm(a, (hipStream_t)hip_stream));
     return EXE_OK;
 }
 

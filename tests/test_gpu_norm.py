@@ -1,0 +1,69 @@
+"""Norms at the edges of the kernel's launch shapes, and the form that finishes a split-K projection into the residual stream
+first (exe_op_resid_norm), against the oracle's primitives."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2404_07947_amd as exe
+import workload as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+F32, BF16 = wl.DTYPE_F32, wl.DTYPE_BF16
+
+
+def rnd(shape, seed, scale=1.0, dtype=torch.float32):
+    return (torch.randn(shape, generator=torch.Generator().manual_seed(seed)) * scale).to(dtype)
+
+
+def reference(rms, x, g, b, eps, scale):
+    P, e = oracle.Primitives("double"), float(np.float32(eps))
+    return (P.rmsnorm(x, g.float().numpy(), e) if rms else P.layernorm(x, g.float().numpy(), b.float().numpy(), e)) * scale
+
+
+def relerr(got, ref):
+    return float(np.max(np.abs(got - ref)) / np.max(np.abs(ref)))
+
+
+# widths on both sides of every step of the launch rule, for few rows and for many (the rule changes at 2048 rows)
+@pytest.mark.parametrize("rows", [3, 2050])
+@pytest.mark.parametrize("d", [8, 256, 260, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 5120, 5124, 8192, 8196, 12288, 16384, 16392])
+def test_norm_launch_shapes(rows, d):
+    dtype, rms = (BF16, 0) if d % 512 else (F32, 1)
+    td = torch.float32 if dtype == F32 else torch.bfloat16
+    x, g, b = rnd((rows, d), 1, 2.0) + 0.3, (1 + rnd((d,), 2, 0.1)).to(td), rnd((d,), 3, 0.1).to(td)
+    out = torch.zeros((rows, d), dtype=td, device=DEV)
+    exe.exe_op_norm(dtype, rms, x.to(DEV), None, rows, d, g.to(DEV), b.to(DEV), 1e-5, 0.5, out)
+    torch.cuda.synchronize()
+    pick = np.unique([0, rows // 2, rows - 1])
+    ref = reference(rms, x.numpy()[pick], g, b, 1e-5, 0.5)
+    # float statistics and one rounding of the result: 2^-9 relative in bf16
+    assert relerr(out.float().cpu().numpy()[pick], ref) < (2e-6 if dtype == F32 else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("dtype,rms", [(BF16, 0), (BF16, 1), (F32, 0)])
+@pytest.mark.parametrize("splits", [1, 2, 3, 4, 7, 8, 16])
+@pytest.mark.parametrize("d", [64, 1024, 5120])
+def test_resid_norm(dtype, rms, splits, d):
+    td = torch.float32 if dtype == F32 else torch.bfloat16
+    rows_all, idx = 9, [8, 0, 3, 5]
+    x, part = rnd((rows_all, d), 4, 2.0), rnd((splits, rows_all, d), 5, 1.0)
+    g, b, bias = (1 + rnd((d,), 6, 0.1)).to(td), rnd((d,), 7, 0.1).to(td), rnd((d,), 8, 0.5).to(td)
+    for row_index in (None, idx):
+        n = rows_all if row_index is None else len(idx)
+        bv = bias if row_index is None else None
+        xd, out = x.to(DEV).clone(), torch.zeros((n, d), dtype=td, device=DEV)
+        ri = None if row_index is None else torch.tensor(row_index, dtype=torch.int32, device=DEV)
+        exe.exe_op_resid_norm(dtype, rms, xd, ri, n, d, part.to(DEV), splits, rows_all, None if bv is None else bv.to(DEV),
+                              g.to(DEV), b.to(DEV), 1e-6, 1.0, out)
+        torch.cuda.synchronize()
+        pick = np.arange(rows_all) if row_index is None else np.array(idx)
+        full = x.double().numpy() + part.double().numpy().sum(0) + (0 if bv is None else bv.double().numpy())
+        got = xd.cpu().numpy()
+        # splits + 2 float additions of values of order 1: (splits + 2) * 2^-24 of the largest
+        assert relerr(got[pick], full[pick]) < (splits + 2) * 2.0 ** -24 * 2
+        rest = np.setdiff1d(np.arange(rows_all), pick)
+        assert np.array_equal(got[rest], x.numpy()[rest])
+        ref = reference(rms, full[pick].astype(np.float32), g, b, 1e-6, 1.0)
+        assert relerr(out.float().cpu().numpy(), ref) < (1e-5 if dtype == F32 else 2.0 ** -8)
