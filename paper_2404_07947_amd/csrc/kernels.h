@@ -134,7 +134,6 @@ struct AttnPackedArgs {      // ragged prefill over packed qkv [T, 3*H*dh]
     int force_generic;
     int max_len = 0;         // longest sequence of the batch (0 = unknown: T is taken)
 };
-bool prefill_mfma_supported(int dtype, int dh);
 constexpr int PREFILL_TILE_Q = 128;
 // Appends the (seq, first query row) pairs of a batch's 128-row query tiles to `tiles`: sequences longest first, the
 // tiles of one sequence together, last rows (causal: most keys) first.  The tiles of a sequence read the same keys

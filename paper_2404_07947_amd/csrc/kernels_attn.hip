@@ -5,11 +5,11 @@
 //    softmax whose partial results are merged across the workgroup at the end.
 //      PACKED = false: decode / cross attention -- keys and values come from a sequence's cache extent
 //                      ([head][capacity][dh] per layer, keys then values).  HBM-bandwidth bound.
-//      PACKED = true : ragged prefill straight from the packed qkv activations (float configs, unusual
-//                      head sizes); the MFMA kernel below replaces it for bf16 with head size 128.
-//  * prefill_mfma_kernel<CAUSAL, BIAS>: flash-style ragged prefill for bf16, head size 128.  A workgroup
+//      PACKED = true : ragged prefill straight from the packed qkv activations, for what the MFMA kernel below does
+//                      not take (bias tables beyond its LDS copy, sequences beyond 32-bit offsets).
+//  * prefill_mfma_kernel<T, DH, CAUSAL, BIAS>: flash-style ragged prefill.  A workgroup
 //    owns 128 query rows of one (sequence, head); keys/values go through LDS in tiles of 64.
-//    S^T = K.Q^T and O^T = V^T.P^T are both computed with MFMA 16x16x32 so that softmax statistics of a
+//    S^T = K.Q^T and O^T = V^T.P^T are both computed with MFMA 16x16 tiles so that softmax statistics of a
 //    query live in the lanes of one accumulator column and P feeds the second MFMA straight from the first
 //    one's accumulators.
 #include <stdio.h>
@@ -18,7 +18,7 @@
 #include <mutex>
 #include <vector>
 
-#include "common.h"
+#include "gemm_epilogue.h"
 #include "kernels.h"
 
 namespace exe {
@@ -368,7 +368,7 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- MFMA prefill (bf16, head size 128)
+// ---------------------------------------------------------------- MFMA prefill (described for bf16, head size 128)
 // A workgroup of 4 waves owns PREFILL_TILE_Q = 128 query rows of one (sequence, head), 32 per wave as two 16-row
 // blocks; three workgroups fit a CU (48 KB of LDS each, at most 168 registers; the variants with a bias table need
 // more registers than that without spilling, and a spill in the tile loop waits for the tile loads in flight, so
@@ -381,13 +381,25 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
 // so a query's softmax statistics live in the four lanes that share its column, and the probabilities never leave
 // registers.  Two barriers per tile (the value tile is loaded behind the scores).  The workgroups of a CU drift
 // apart, so one wave's softmax (vector ALU) overlaps another's MFMAs on the same SIMD.
-constexpr int PF_NW = 4, PF_DH = 128, PF_KT = 64, PF_THREADS = PF_NW * 64, PF_QT = PF_NW * 32;
-constexpr int PF_LPT = 16 / PF_NW;                                // direct-to-LDS loads per wave and tile
-constexpr int PF_TILE = 16384, PF_LDS = 3 * PF_TILE;              // key tiles 0 and 1, then the value tile
+constexpr int PF_NW = 4, PF_KT = 64, PF_THREADS = PF_NW * 64, PF_QT = PF_NW * 32;
 static_assert(PF_QT == PREFILL_TILE_Q, "the tile list is built for PREFILL_TILE_Q query rows per workgroup");
+constexpr int pf_tile_bytes(int row_bytes) { return PF_KT * row_bytes; }
+template <typename T, int DH> constexpr int pf_v_tiles() { return sizeof(T) == 2 && DH == 128 ? 1 : 2; }
+template <typename T, int DH> constexpr int pf_lds()              // two key tiles, then the value tile(s)
+{
+    return (2 + pf_v_tiles<T, DH>()) * pf_tile_bytes(DH * (int)sizeof(T));
+}
+// workgroups per CU that the registers must leave room for (LDS does)
+template <typename T, int DH, bool BIAS> constexpr int pf_per_cu()
+{
+    if (sizeof(T) == 4) return DH == 64 ? 2 : 1;
+    return (DH == 64 ? 4 : 3) - (BIAS ? 1 : 0);
+}
 
-// A key or value tile [64 rows][128] in LDS: 256-byte rows of 16 chunks, chunk c of row r stored at slot c ^ (r & 15).
-__device__ __forceinline__ int pf_off(int row, int chunk) { return row * 256 + ((chunk ^ (row & 15)) << 4); }
+// A key or value tile [64 rows] in LDS, row-major in 16-byte chunks.  Rows of 256 bytes and more keep chunk c of row r at
+// slot c ^ (r & 15), rows of 128 bytes at slot c ^ ((r >> 1) & 7): the fragment reads below touch every bank group
+// equally.  Rows 16 apart share their swizzle.
+template <int RB> __device__ __forceinline__ int pf_swz(int row) { return RB >= 256 ? row & 15 : (row >> 1) & 7; }
 
 typedef __attribute__((ext_vector_type(4))) short pf_v4s;
 // Transposing LDS read (ds_read_b64_tr_b16).  Within each block of 16 lanes, lane L points at 4 consecutive 16-bit
@@ -420,14 +432,31 @@ __device__ __forceinline__ float rows_sum(float x)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-template <bool CAUSAL, bool BIAS>
-__global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(const bf16_t* __restrict__ qkv,
+//
+// Head size 64: half the bytes per tile, so the value tiles are double buffered too and one barrier per tile is enough.
+// Its probabilities enter the second product as the sum of two bf16 values (the rounded one and the rounded rest, 2^-17
+// relative): before this kernel the row kernel, with float probabilities, served that head size, and the second set of
+// MFMAs hides behind the exponentials.
+//
+// Float: the same tiles and softmax with 16x16x4 MFMAs, four per 16-byte fragment; the second product takes one key per lane
+// group and MFMA, so P again goes from accumulator to operand without moving, and V is read 4 bytes per lane.
+//
+// Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 39;
+// float x 64, 32 sequences of 384, 4 heads, 192 -> 75.
+template <typename T, int DH, bool CAUSAL, bool BIAS>
+__global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefill_mfma_kernel(const T* __restrict__ qkv,
                                                                   const int32_t* __restrict__ cu,
                                                                   const int32_t* __restrict__ tiles, int H,
                                                                   float scale, const float* __restrict__ bias_by_dist,
-                                                                  int radius, bf16_t* __restrict__ out)
+                                                                  int radius, T* __restrict__ out)
 {
-    extern __shared__ __align__(16) unsigned char pf_smem[];      // 2 key tiles, then 1 value tile
+    constexpr int RB = DH * (int)sizeof(T), RPL = 1024 / RB;                   // bytes per row; rows per wave-load
+    constexpr int PF_LPT = PF_KT / RPL / PF_NW;                   // direct-to-LDS loads per wave and tile
+    constexpr int PF_TILE = pf_tile_bytes(RB);
+    constexpr int DS = RB / 64, DT = DH / 16;                     // 64-byte steps of the first product, feature tiles of the second
+    constexpr bool V2 = pf_v_tiles<T, DH>() == 2;
+    constexpr bool SPLIT_P = sizeof(T) == 2 && DH == 64;
+    extern __shared__ __align__(16) unsigned char pf_smem[];      // 2 key tiles, then the value tile(s)
     __shared__ float sbias[BIAS ? 1024 : 1];
 
     // Workgroup -> (tile, head).  Workgroups go to the 8 XCDs round-robin in launch order.  With a multiple of 8 heads,
@@ -445,34 +474,34 @@ __global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(
     }
     int sb = tiles[tile * 2], q0 = tiles[tile * 2 + 1];
     int t0 = cu[sb], n = cu[sb + 1] - t0;
-    int inner = H * PF_DH;
+    int inner = H * DH;
     int64_t ld = 3 * (int64_t)inner;
     int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int qi = lane & 15, g = lane >> 4;
     int wq0 = q0 + wave * 32;                                     // this wave's first query row
-    const bf16_t* seq = qkv + (int64_t)t0 * ld + h * PF_DH;
+    const T* seq = qkv + (int64_t)t0 * ld + h * DH;
 
     if (BIAS) {
         for (int i = tid; i < 2 * radius + 1; i += PF_THREADS)
             sbias[i] = bias_by_dist[(int64_t)h * (2 * radius + 1) + i] * LOG2E;
     }
 
-    // query fragments (B operand): lane (query qi, lane group g) holds features 32*ds + 8*g .. +7
-    bf16x8 qf[2][4];
+    // query fragments (B operand): lane (query qi, lane group g) holds 16-byte chunk 4*ds + g of its query row
+    u32x4 qf[2][DS];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
         int qr = wq0 + qb * 16 + qi;
         qr = qr < n ? qr : n - 1;
-        const bf16_t* qp = seq + (int64_t)qr * ld + g * 8;
+        const u32x4* qp = (const u32x4*)(seq + (int64_t)qr * ld) + g;
 #pragma unroll
-        for (int ds = 0; ds < 4; ++ds) qf[qb][ds] = *(const bf16x8*)(qp + ds * 32);
+        for (int ds = 0; ds < DS; ++ds) qf[qb][ds] = qp[ds * 4];
     }
     int kend = n;
     if (CAUSAL) kend = q0 + PF_QT < n ? q0 + PF_QT : n;
     int n_tiles = (kend + PF_KT - 1) / PF_KT;
 
-    // ---- loaders.  Per tile of keys and of values a wave issues two 1 KB direct-to-LDS loads of 4 rows each; a
-    // lane fills slot lane%16 of its row with the chunk that the swizzle puts there.  Written as inline assembly
+    // ---- loaders.  Per tile of keys and of values a wave issues PF_LPT 1 KB direct-to-LDS loads of RPL rows each; a
+    // lane fills a slot of its row with the chunk that the swizzle puts there.  Written as inline assembly
     // so that the compiler does not order every later LDS read behind them.
     unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)pf_smem;
     const char* kbase = (const char*)(seq + inner);
@@ -485,23 +514,24 @@ __global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(
     const char* vbase = (const char*)(seq + 2 * inner);
     auto load_tile = [&](const char* base, int kt, unsigned dst) {
 #pragma unroll
-        for (int p = 0; p < 16 / PF_NW; ++p) {
-            int row = (p * PF_NW + wave) * 4;                       // first of the 4 tile rows of this load
-            int key = row + (lane >> 4);
+        for (int p = 0; p < PF_LPT; ++p) {
+            constexpr int CPR = RB / 16;                            // chunks per row
+            int row = (p * PF_NW + wave) * RPL;                     // first of the tile rows of this load
+            int key = row + lane / CPR;
             int kg = kt * PF_KT + key;
             kg = kg < n ? kg : n - 1;
-            unsigned voff = (unsigned)kg * (unsigned)(ld * 2) + (((lane & 15) ^ (key & 15)) << 4);
-            load_to_lds(base, voff, dst + row * 256);
+            unsigned voff = (unsigned)kg * (unsigned)(ld * (int)sizeof(T)) + (((lane & (CPR - 1)) ^ pf_swz<RB>(key)) << 4);
+            load_to_lds(base, voff, dst + row * RB);
         }
     };
     auto load_k = [&](int kt) { load_tile(kbase, kt, lds_base + (kt & 1) * PF_TILE); };
-    auto load_v = [&](int kt) { load_tile(vbase, kt, lds_base + 2 * PF_TILE); };
+    auto load_v = [&](int kt) { load_tile(vbase, kt, lds_base + (2 + (V2 ? kt & 1 : 0)) * PF_TILE); };
 
-    f32x4 o_acc[2][8];
+    f32x4 o_acc[2][DT];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) o_acc[qb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int dt = 0; dt < DT; ++dt) o_acc[qb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
     float sc = scale * LOG2E;
     f32x4 s_acc[2][4];
@@ -516,17 +546,17 @@ __global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(
         // The four swizzled chunk offsets of a lane ((4 ds + g) ^ qi for ds = 0..3) are recomputed per tile from one
         // register: held across the tile loop they cost four, and a register spilled in this loop puts a full wait
         // for the tile loads in flight in front of its reload (scratch reloads count with them).
-        int qx = qi;
+        int qx = pf_swz<RB>(qi);
         asm volatile("" : "+v"(qx));
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
             s_acc[0][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
             s_acc[1][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ds = 0; ds < 4; ++ds) {
-                bf16x8 fk = *(const bf16x8*)(sK + (kb * 16 + qi) * 256 + (((ds * 4 + g) ^ qx) << 4));
-                s_acc[0][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fk, qf[0][ds], s_acc[0][kb], 0, 0, 0);
-                s_acc[1][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fk, qf[1][ds], s_acc[1][kb], 0, 0, 0);
+            for (int ds = 0; ds < DS; ++ds) {
+                u32x4 fk = *(const u32x4*)(sK + (kb * 16 + qi) * RB + (((ds * 4 + g) ^ qx) << 4));
+                s_acc[0][kb] = HalfUnit<T>::mma(fk, qf[0][ds], s_acc[0][kb]);
+                s_acc[1][kb] = HalfUnit<T>::mma(fk, qf[1][ds], s_acc[1][kb]);
             }
         }
     };
@@ -606,7 +636,7 @@ __global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt)
+                for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o_acc[qb][dt][r] *= alpha[qb];
         }
@@ -617,48 +647,91 @@ __global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(
     // L = 4*j + q points at columns 16*dt + 4*q .. +3 of key 4*g + j.
     int v_row = 4 * g + (qi >> 2), v_q = qi & 3;
     auto phase_pv = [&](int kt) {
-        const unsigned char* sV = pf_smem + 2 * PF_TILE + v_row * 256 + (v_q & 1) * 8;
+        const unsigned char* tV = pf_smem + (2 + (V2 ? kt & 1 : 0)) * PF_TILE;
+        if constexpr (sizeof(T) == 4) {
+            // lane group g supplies key 4*g + r of key block kb, for feature 16*dt + qi
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    int row = kb * 16 + 4 * g + r;
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) {
+                        float fv = *(const float*)(tV + row * RB + (((4 * dt + (qi >> 2)) ^ pf_swz<RB>(row)) << 4) + (qi & 3) * 4);
+                        o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[0][kb][r], o_acc[0][dt], 0, 0, 0);
+                        o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[1][kb][r], o_acc[1][dt], 0, 0, 0);
+                    }
+                }
+            return;
+        }
+        const unsigned char* sV = tV + v_row * RB + (v_q & 1) * 8;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 pf[2];
+            bf16x8 pf[2], pr[2];                     // probabilities, and (head size 64) what their rounding left over
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[qb][e] = (bf16_t)s_acc[qb][2 * ks + (e >> 2)][e & 3];
+                for (int e = 0; e < 8; ++e) {
+                    float p = s_acc[qb][2 * ks + (e >> 2)][e & 3];
+                    pf[qb][e] = (bf16_t)p;
+                    if (SPLIT_P) pr[qb][e] = (bf16_t)(p - (float)pf[qb][e]);
+                }
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-                int slot = ((2 * dt + (v_q >> 1)) ^ v_row) << 4;     // rows v_row, +16, +32, +48 share their low 4 bits
-                uint2 lo = pf_read_tr(sV + ks * 32 * 256 + slot);
-                uint2 hi = pf_read_tr(sV + (ks * 32 + 16) * 256 + slot);
+            for (int dt = 0; dt < DT; ++dt) {
+                int slot = ((2 * dt + (v_q >> 1)) ^ pf_swz<RB>(v_row)) << 4;
+                uint2 lo = pf_read_tr(sV + ks * 32 * RB + slot);
+                uint2 hi = pf_read_tr(sV + (ks * 32 + 16) * RB + slot);
                 uint4 both = {lo.x, lo.y, hi.x, hi.y};
                 bf16x8 fv = __builtin_bit_cast(bf16x8, both);
                 o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[0], o_acc[0][dt], 0, 0, 0);
                 o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[1], o_acc[1][dt], 0, 0, 0);
+                if (SPLIT_P) {
+                    o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pr[0], o_acc[0][dt], 0, 0, 0);
+                    o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pr[1], o_acc[1][dt], 0, 0, 0);
+                }
             }
         }
     };
 
-    // Key tiles are double buffered; the single value tile is loaded at the start of its own iteration, behind
-    // the scores and the softmax, which costs a second barrier per tile but lets three workgroups share a CU.
-    load_k(0);
-    __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));               // vmcnt(0)
-    __syncthreads();
-
-    for (int kt = 0; kt < n_tiles; ++kt) {
-        load_v(kt);                                               // PF_LPT loads
-        bool more = kt + 1 < n_tiles;
-        if (more) load_k(kt + 1);                                 // PF_LPT loads, into the buffer tile kt-1 has left
-        bool act = active(kt);
-        if (act) {
-            phase_s(kt);
-            phase_softmax(kt);
+    if constexpr (V2) {
+        load_k(0);
+        load_v(0);
+        for (int kt = 0; kt < n_tiles; ++kt) {
+            __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));       // vmcnt(0): this wave's part of tile kt has landed
+            __syncthreads();
+            if (kt + 1 < n_tiles) {                               // into the buffers that tile kt - 1 has left
+                load_k(kt + 1);
+                load_v(kt + 1);
+            }
+            if (active(kt)) {
+                phase_s(kt);
+                phase_softmax(kt);
+                phase_pv(kt);
+            }
         }
-        if (more) __builtin_amdgcn_s_waitcnt(0x0070 | PF_LPT | (15 << 8));   // the value tile: all but the key loads
-        else __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));
+    } else {
+        // Key tiles are double buffered; the single value tile is loaded at the start of its own iteration, behind
+        // the scores and the softmax, which costs a second barrier per tile but lets three workgroups share a CU.
+        load_k(0);
+        __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));           // vmcnt(0)
         __syncthreads();
-        if (act) phase_pv(kt);
-        __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));           // this wave's part of the next key tile has landed
-        __syncthreads();
+
+        for (int kt = 0; kt < n_tiles; ++kt) {
+            load_v(kt);                                           // PF_LPT loads
+            bool more = kt + 1 < n_tiles;
+            if (more) load_k(kt + 1);                             // PF_LPT loads, into the buffer tile kt-1 has left
+            bool act = active(kt);
+            if (act) {
+                phase_s(kt);
+                phase_softmax(kt);
+            }
+            if (more) __builtin_amdgcn_s_waitcnt(0x0070 | PF_LPT | (15 << 8));   // the value tile: all but the key loads
+            else __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));
+            __syncthreads();
+            if (act) phase_pv(kt);
+            __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));       // this wave's part of the next key tile has landed
+            __syncthreads();
+        }
     }
 
     // lane (qi, g) holds features 16*dt + 4*g .. +3 of its query
@@ -667,19 +740,19 @@ __global__ __launch_bounds__(PF_THREADS, BIAS ? 2 : 3) void prefill_mfma_kernel(
         int qpos = wq0 + qb * 16 + qi;
         if (qpos < n) {
             float inv = 1.f / l_run[qb];
-            bf16_t* op = out + (int64_t)(t0 + qpos) * inner + h * PF_DH + 4 * g;
+            T* op = out + (int64_t)(t0 + qpos) * inner + h * DH + 4 * g;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-                bf16x4 w;
+            for (int dt = 0; dt < DT; ++dt) {
+                typename Vec4<T>::type w;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) w[j] = (bf16_t)(o_acc[qb][dt][j] * inv);
-                *(bf16x4*)(op + dt * 16) = w;
+                for (int j = 0; j < 4; ++j) w[j] = (T)(o_acc[qb][dt][j] * inv);
+                *(typename Vec4<T>::type*)(op + dt * 16) = w;
             }
         }
     }
 }
 
-bool prefill_mfma_supported(int dtype, int dh) { return dtype == DT_BF16 && dh == PF_DH; }
+
 
 void prefill_tile_order(const int32_t* lens, int n_seqs, std::vector<int32_t>& tiles)
 {
@@ -693,53 +766,46 @@ void prefill_tile_order(const int32_t* lens, int n_seqs, std::vector<int32_t>& t
         }
 }
 
+template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
+{
+    auto kern = prefill_mfma_kernel<T, DH, CAUSAL, BIAS>;
+    constexpr int lds = pf_lds<T, DH>();
+    static LdsLimit limit[MAX_DEVICES];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
+    hipError_t e = limit[dev].raise((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    kern<<<(unsigned)(a.n_tiles * a.H), PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
+                                                             BIAS ? a.bias_radius : 0, (T*)a.out);
+    return hipGetLastError();
+}
+template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
+{
+    if (a.causal) return a.bias_by_dist ? launch_prefill<T, DH, true, true>(a, s) : launch_prefill<T, DH, true, false>(a, s);
+    return a.bias_by_dist ? launch_prefill<T, DH, false, true>(a, s) : launch_prefill<T, DH, false, false>(a, s);
+}
+
 hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
+    if ((a.dtype != DT_F32 && a.dtype != DT_BF16) || (a.dh != 64 && a.dh != 128)) return hipErrorInvalidValue;
     // The key loader addresses the rows of one sequence with 32-bit byte offsets, and a head's bias table must fit
     // the kernel's LDS copy; a batch outside these limits runs on the row kernel, which is correct but far slower,
     // so say so (once).
-    const bool mfma_shape = !a.force_generic && prefill_mfma_supported(a.dtype, a.dh) && a.n_tiles > 0;
-    const int64_t longest = a.max_len > 0 ? a.max_len : a.T;
-    const bool mfma_fits = longest * 3 * a.H * a.dh * 2 < ((int64_t)1 << 32) && (!a.bias_by_dist || 2 * a.bias_radius + 1 <= 1024);
+    const bool mfma_shape = !a.force_generic && a.n_tiles > 0;
+    const int64_t longest = a.max_len > 0 ? a.max_len : a.T, row_bytes = (int64_t)3 * a.H * a.dh * (a.dtype == DT_F32 ? 4 : 2);
+    const bool mfma_fits = longest * row_bytes < ((int64_t)1 << 32) && (!a.bias_by_dist || 2 * a.bias_radius + 1 <= 1024);
     if (mfma_shape && !mfma_fits) {
         static std::once_flag warned;
         std::call_once(warned, [&]() {
-            fprintf(stderr, "exe: prefill attention falls back to the row kernel (longest sequence %lld rows of %d bytes, bias "
-                            "radius %d): expect it to be much slower\n", (long long)longest, 3 * a.H * a.dh * 2, a.bias_radius);
+            fprintf(stderr, "exe: prefill attention falls back to the row kernel (longest sequence %lld rows of %lld bytes, bias "
+                            "radius %d): expect it to be much slower\n", (long long)longest, (long long)row_bytes, a.bias_radius);
         });
     }
     if (mfma_shape && mfma_fits) {
         if ((int64_t)a.n_tiles * a.H > 0x7fffffff) return hipErrorInvalidValue;
-        dim3 grid((unsigned)(a.n_tiles * a.H));
-        const bf16_t* qkv = (const bf16_t*)a.qkv;
-        bf16_t* out = (bf16_t*)a.out;
-        constexpr int lds = PF_LDS;
-        // the kernels' dynamic LDS limit is raised once per device
-        static std::once_flag attr_once[64];
-        static hipError_t attr_err[64];
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-        std::call_once(attr_once[dev], [&]() {
-            const void* kerns[4] = {(const void*)prefill_mfma_kernel<true, true>, (const void*)prefill_mfma_kernel<true, false>,
-                                    (const void*)prefill_mfma_kernel<false, true>, (const void*)prefill_mfma_kernel<false, false>};
-            attr_err[dev] = hipSuccess;
-            for (const void* k : kerns) {
-                hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-                if (e != hipSuccess) attr_err[dev] = e;
-            }
-        });
-        if (attr_err[dev] != hipSuccess) return attr_err[dev];
-        auto launch = [&](auto kern, const float* bias, int radius) -> hipError_t {
-            kern<<<grid, PF_THREADS, lds, s>>>(qkv, a.cu, a.tiles, a.H, a.scale, bias, radius, out);
-            return hipGetLastError();
-        };
-        if (a.causal) {
-            if (a.bias_by_dist) return launch(prefill_mfma_kernel<true, true>, a.bias_by_dist, a.bias_radius);
-            return launch(prefill_mfma_kernel<true, false>, nullptr, 0);
-        }
-        if (a.bias_by_dist) return launch(prefill_mfma_kernel<false, true>, a.bias_by_dist, a.bias_radius);
-        return launch(prefill_mfma_kernel<false, false>, nullptr, 0);
+        if (a.dtype == DT_F32) return a.dh == 64 ? launch_prefill<float, 64>(a, s) : launch_prefill<float, 128>(a, s);
+        return a.dh == 64 ? launch_prefill<bf16_t, 64>(a, s) : launch_prefill<bf16_t, 128>(a, s);
     }
     dim3 grid(a.H, a.T);
 #define EXE_ROW(T, DH)                                                                                           \
@@ -749,8 +815,7 @@ hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
     if (a.dtype == DT_F32 && a.dh == 64) EXE_ROW(float, 64);
     else if (a.dtype == DT_F32 && a.dh == 128) EXE_ROW(float, 128);
     else if (a.dtype == DT_BF16 && a.dh == 64) EXE_ROW(bf16_t, 64);
-    else if (a.dtype == DT_BF16 && a.dh == 128) EXE_ROW(bf16_t, 128);
-    else return hipErrorInvalidValue;
+    else EXE_ROW(bf16_t, 128);
 #undef EXE_ROW
     return hipGetLastError();
 }
