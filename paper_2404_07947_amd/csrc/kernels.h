@@ -29,9 +29,10 @@ struct GemmArgs {
     int* pending = nullptr;
 };
 enum GemmMode { GEMM_TILE_ONLY = 0, GEMM_FEW_ROWS = 1, GEMM_DEFER = 2 };       // flags, as the two members above
+constexpr int MAX_SPLIT_ROWS = 4096;      // no launch of more rows is split over K
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode);
 // how a shape is launched with few_rows = (dtype is float): route (0 tile kernel, 1 streaming kernel, 2 generic), tile configuration (0 64x256, 1 128x256, 2 256x256, 3 64x128,
-// 4 128x128, 5 256x128), split-K parts, and the leading rows that the first launch takes (M unless the rows beyond
+// 4 128x128, 5 256x128, 6 192x256), split-K parts, and the leading rows that the first launch takes (M unless the rows beyond
 // whole rounds of tiles go to a second launch)
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
@@ -42,6 +43,9 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 struct StreamPlan { int nt = 0, ma = 0, splits = 1, units_per_split = 0; double cost = 0.0; };
 StreamPlan gemm_stream_plan(int dtype, int M, int N, int K, bool defer);
 StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K, bool defer);    // nt in {1, 2, 4, 5}, ma in {1, 2, 4, 6, 8}
+// The large tile kernel (kernels_gemm_large.hip, bf16): bm (256, 192 or 128) x 256 tiles, persistent on at most grid_max
+// workgroups, K in `splits` parts of k_per_split (every part at least 2 k-tiles of 64).
+hipError_t launch_gemm_large(const GemmArgs& a, int bm, int k_per_split, int splits, int grid_max, hipStream_t s);
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t s);
 

@@ -3,7 +3,7 @@
 //  * gemm_tile_kernel    MFMA 16x16x32 (bf16) or 16x16x4 (float).  Macro tiles (BM x 256 or BM x 128, 128 bytes of K
 //                        per LDS stage) filled by direct global->LDS loads into a ring of stages; software-pipelined
 //                        fragment fetch; optional split-K into float partials (bf16), finished by splitk_reduce_kernel.
-//                        Large M (encode) is MFMA / LDS-fill bound.
+//  * gemm_large_kernel   (kernels_gemm_large.hip) bf16, tiles 256 features wide: encode, and decode batches of 100 rows and more.
 //  * gemm_stream_kernel  (kernels_gemm_stream.hip) few rows: streams the weights, the waves of a workgroup split K.
 //  * gemm_generic_kernel float or bf16 inputs, plain FMA in float, any shape (depths and widths the others do not take).
 //
@@ -23,7 +23,7 @@
 #include <type_traits>
 #include <unordered_map>
 
-#include "gemm_epilogue.h"
+#include "gemm_tile.h"
 #include "kernels.h"
 
 #ifndef EXE_GEMM_ABLATE
@@ -37,152 +37,6 @@
 #endif
 
 namespace exe {
-
-// ---------------------------------------------------------------- tile kernel: LDS layout
-// LDS tile layout for a stage of 64 bf16 (32 float) along K: row r is 128 bytes = 8 chunks of 16 bytes; chunk c is
-// stored at slot c ^ ((r>>1)&7), so that 16 consecutive rows read at the same chunk index touch 16 distinct
-// 16-byte bank groups (256 bytes of banks; measured: zero LDS bank conflicts).
-constexpr int TROW = 128;                                   // bytes of K per stage
-template <typename T> constexpr int tbk() { return TROW / (int)sizeof(T); }
-__device__ __forceinline__ int lds_swz(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int lds_off(int row, int chunk) { return row * 128 + ((chunk ^ lds_swz(row)) << 4); }
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef __attribute__((address_space(1))) const void* gbl_ptr_t;
-
-// s_waitcnt vmcnt(N) lgkmcnt(L) with expcnt at its maximum; vmcnt is split over bits [3:0] and [15:14],
-// lgkmcnt is bits [11:8]
-template <int N, int L> __device__ __forceinline__ void wait_cnt()
-{
-    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14) | (L << 8));
-}
-
-// ---------------------------------------------------------------- tile epilogue
-// A lane of a 16x16 accumulator tile holds 4 consecutive output features n = 4*(l/16) .. +3 of one row m = l%16:
-// stored as it lies, a wave-wide store would scatter 16-byte pieces over 16 output rows.  Each wave therefore
-// turns its tiles through a private LDS buffer, a "group" of 32 rows x EN columns (2 x EN/16 tiles) at a time,
-// with the 16-byte slots XOR-swizzled by row so that neither side has bank conflicts, and then stores whole
-// row segments.
-//
-// The LDS accesses are written as inline assembly on purpose: the compiler assumes that a DS read may alias the
-// destination of the direct global->LDS loads still in flight for the next item and would put a vmcnt(0) in
-// front of every one of them, which also waits for the stores of the previous group.  The buffer is private to
-// the wave and is never a destination of those loads; DS operations of one wave execute in order, and the
-// lgkmcnt(0) after the reads completes them before the next group's writes.
-enum EpiMode { EPI_PARTIAL = 0, EPI_F32, EPI_RESID, EPI_T, EPI_T_RELU, EPI_T_GELU };
-
-template <int QW> struct LdsTurn;
-template <> struct LdsTurn<4> {
-    static __device__ __forceinline__ void read(f32x4 (&v)[4], const unsigned (&a)[4])
-    {
-        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-                     : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
-                     : "memory");
-    }
-};
-template <> struct LdsTurn<2> {
-    static __device__ __forceinline__ void read(f32x4 (&v)[2], const unsigned (&a)[2])
-    {
-        asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(v[0]), "=&v"(v[1])
-                     : "v"(a[0]), "v"(a[1])
-                     : "memory");
-    }
-};
-
-// acc[i][j]: the wave's accumulator tiles (i: 16 output features, j: 16 rows); stg: LDS byte address of the wave's
-// buffer (EN * 128 bytes); (row0, col0): output coordinates of the wave's first element; fout: float destination
-// of EPI_PARTIAL / EPI_F32 / EPI_RESID; tout: bf16 destination of EPI_T*.
-template <typename T, int TM, int TN, int EN, int MODE>
-__device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsigned stg, int lane, int row0, int col0,
-                                               int M, int N, const T* __restrict__ bias, float alpha,
-                                               float* __restrict__ fout, T* __restrict__ tout)
-{
-    static_assert(TM % 2 == 0 && TN % 2 == 0, "groups are 2 tiles high");
-    constexpr int QW = EN / 8;                  // 16-byte slots a lane writes, and reads, per group
-    constexpr int IW = EN / 16;                 // tiles side by side in a group
-    constexpr int NG = TN / IW;                 // groups per 32 rows
-    constexpr int G = (TM / 2) * NG;
-    constexpr int RPP = EN == 32 ? 8 : 16;      // output rows covered by one wave-wide read
-    constexpr int D = G < 2 ? G : 2;            // residual prefetch depth in groups (registers: D * QW * 4)
-    int lm = lane & 15, lq = lane >> 4;
-    int rc = EN == 32 ? (lane & 7) : (lane & 3);
-    int rr = EN == 32 ? (lane >> 3) : (lane >> 2);
-    // slot of (row m, 16-byte column c) in the buffer
-    auto slot = [](int m, int c) { return EN == 32 ? m * 8 + (c ^ ((m >> 1) & 7)) : m * 4 + (c ^ ((m >> 2) & 3)); };
-    unsigned waddr[QW], raddr[QW];
-#pragma unroll
-    for (int x = 0; x < QW; ++x) {
-        int jj = x / IW, ii = x % IW;           // tile (ii, jj) of the group
-        waddr[x] = stg + slot(jj * 16 + lm, ii * 4 + lq) * 16;
-        raddr[x] = stg + slot(x * RPP + rr, rc) * 16;
-    }
-    // group g = jp * NG + ig covers rows row0 + 32 jp .. +31 and columns col0 + EN ig .. + EN - 1
-    auto g_row = [&](int g, int p) { return row0 + (g / NG) * 32 + p * RPP + rr; };
-    auto g_col = [&](int g) { return col0 + (g % NG) * EN + rc * 4; };
-    f32x4 bv[NG];
-    if (MODE != EPI_PARTIAL) {
-#pragma unroll
-        for (int x = 0; x < NG; ++x) {
-            int n = g_col(x);
-            bv[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (bias && n < N) {
-                typename Vec4<T>::type b = *(const typename Vec4<T>::type*)(bias + n);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) bv[x][e] = (float)b[e];
-            }
-        }
-    }
-    f32x4 res[D][QW];
-    auto load_res = [&](int g) {
-        int n = g_col(g);
-#pragma unroll
-        for (int p = 0; p < QW; ++p) {
-            int m = g_row(g, p);
-            res[g % D][p] = (m < M && n < N) ? *(const f32x4*)(fout + (int64_t)m * N + n) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    };
-    if (MODE == EPI_RESID) {
-#pragma unroll
-        for (int g = 0; g < D; ++g) load_res(g);
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        int jp = g / NG, ig = g % NG;
-#pragma unroll
-        for (int x = 0; x < QW; ++x) {
-            f32x4 vv = acc[ig * IW + x % IW][jp * 2 + x / IW];
-            asm volatile("ds_write_b128 %0, %1" ::"v"(waddr[x]), "v"(vv) : "memory");
-        }
-        f32x4 v[QW];
-        LdsTurn<QW>::read(v, raddr);
-        int n = g_col(g);
-#pragma unroll
-        for (int p = 0; p < QW; ++p) {
-            int m = g_row(g, p);
-            if (m >= M || n >= N) continue;
-            int64_t o = (int64_t)m * N + n;
-            if (MODE == EPI_PARTIAL) {
-                *(f32x4*)(fout + o) = v[p];
-            } else {
-                f32x4 r = v[p] * alpha + bv[ig];
-                if (MODE == EPI_F32) *(f32x4*)(fout + o) = r;
-                else if (MODE == EPI_RESID) *(f32x4*)(fout + o) = res[g % D][p] + r;
-                else {
-                    typename Vec4<T>::type w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        w[e] = (T)(MODE == EPI_T_RELU ? act_apply(r[e], 0) : MODE == EPI_T_GELU ? act_apply(r[e], 1) : r[e]);
-                    *(typename Vec4<T>::type*)(tout + o) = w;
-                }
-            }
-        }
-        if (MODE == EPI_RESID && g + D < G) load_res(g + D);
-        __builtin_amdgcn_sched_barrier(0);      // keeps the groups in order: hoisted loads would cost registers
-    }
-}
 
 // Columns that a wave turns through LDS at a time in the epilogue: 32 (4 KB per wave) where the stages leave
 // room within the 160 KB of a CU, else 16 (2 KB per wave).
@@ -536,10 +390,15 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(int M, int N, int K, 
 // ---------------------------------------------------------------- host-side routing
 // Tile configurations.  The first three have BN = 256 (the weight share of the LDS fill traffic is
 // BN / (BM + BN), which is what a weight-streaming decode GEMM wants large); the last three halve BN for
-// matrices with few output features, where more tiles beat deeper split-K.
-enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, N_CFG };
+// matrices with few output features, where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows run on
+// gemm_large_kernel, the others on gemm_tile_kernel.
+enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, C192x256, N_CFG };
 struct CfgInfo { int bm, bn; };
-static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}};
+static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}, {192, 256}};
+
+// gemm_large_kernel needs a few k-tiles per item (its loads run two ahead and its waits are counted in them)
+static bool is_large(int cfg) { return cfg == C256x256 || cfg == C128x256 || cfg == C192x256; }
+constexpr int LARGE_MIN_K = 256;
 
 static int k_tile(int dtype) { return dtype == DT_F32 ? tbk<float>() : tbk<bf16_t>(); }
 
@@ -563,27 +422,43 @@ static const Knobs& knobs()
     return k;
 }
 
-// Cost model behind the choice of tile shape and split count, fitted to sweeps of the six shapes x 1..16 splits on
-// MI355X with the weights coming from HBM (the GEMM shapes of three models, 16 <= M <= 1024; the time of its picks
-// is within 1 % of the time of the best picks in total, 13 % at worst): a workgroup's time is the larger of its
-// LDS-fill traffic at the rate one CU sustains through its vector L1 (about 35 GB/s) and its MFMA work at the rate
-// the tile loop reaches on such short runs (about 3.5 TFLOP/s per CU; the 128 x 256 shape 0.8 of that; float 0.45);
-// workgroups run in rounds of one per CU; the whole launch cannot beat streaming W once from HBM; split-K adds the float
-// partials' round trip and a second launch (`defer`: the next kernel of the residual stream adds them up, see norm_kernel).
-static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, bool defer)
+// Cost model behind the choice of tile shape and split count: a workgroup's time is the larger of its LDS-fill traffic and
+// its MFMA work, in rounds of one workgroup per CU; the whole launch cannot beat streaming W once from HBM; split-K adds the
+// float partials' round trip and a second launch (`defer`: the next kernel of the residual stream adds them up, see
+// norm_kernel).
+//
+// Two sets of rates.  A model's launches (`model`): fitted to 2800 launches on MI355X, 13 row counts from 24 to 2048 x 11
+// weight shapes of 1024 to 49152 features, six tile shapes x 1..8 splits, weights from HBM: the picks take 0.7 % more than
+// the best measured choice on average, 11 % at worst.  gemm_large_kernel is priced by its time per k-tile there (1.03 us for
+// 256 rows, 0.93 for 192, 0.80 for 128, 16 % more when every CU runs it: the clock falls) and per tile.  Up to 192
+// rows, where the estimate also has to compare with the streaming kernel's, the rates of an earlier fit stay (within 2 % of
+// the best choice on average), and so they do for exe_op_gemm's launches up to 1024 rows: its callers have been given these
+// plans' workspace sizes.
+struct Rates { double fill, mfma, hbm, partial, reduce; };
+static const Rates MODEL_RATES{44e9, 3.5e12, 6.5e12, 5.3e12, 4.5e-6}, OP_RATES{35e9, 3.5e12, 5.5e12, 3e12, 1e-6};
+
+static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, bool defer, bool model)
 {
     int bm = CFG[cfg].bm, bn = CFG[cfg].bn, bk = k_tile(dtype), esz = TROW / bk;
+    const Rates& r = model ? MODEL_RATES : OP_RATES;
     int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     int64_t wgs = tiles * splits;
     double rounds = (double)((wgs + 255) / 256);
     double ktiles = (double)((K / bk + splits - 1) / splits);
-    double fill = ktiles * (bm + bn) * TROW / 35e9;
-    double mfma = ktiles * 2.0 * bm * bn * bk / (dtype == DT_F32 ? 0.45e12 : cfg == C128x256 ? 2.8e12 : 3.5e12);
-    double t = rounds * (fill > mfma ? fill : mfma);
-    double hbm = (double)N * K * esz / 5.5e12;
+    double t;
+    if (model && is_large(cfg)) {
+        double busy = wgs / rounds / 256;
+        double per = bm == 256 ? 1.03e-6 : bm == 192 ? 0.93e-6 : 0.80e-6, fixed = bm == 256 ? 5e-6 : bm == 192 ? 4.5e-6 : 3e-6;
+        t = rounds * (ktiles * per * (1.0 + 0.16 * busy) + fixed);
+    } else {
+        double fill = ktiles * (bm + bn) * TROW / r.fill;
+        double mfma = ktiles * 2.0 * bm * bn * bk / (dtype == DT_F32 ? 0.45e12 : cfg == C128x256 ? 2.8e12 : r.mfma);
+        t = rounds * (fill > mfma ? fill : mfma);
+    }
+    double hbm = (double)N * K * esz / r.hbm;
     if (t < hbm) t = hbm;
     t += 4e-6;
-    if (splits > 1) t += defer ? 2.0 * splits * M * N * 4 / 8e12 - 1e-6 : 2.0 * splits * M * N * 4 / 3e12 + 1e-6;
+    if (splits > 1) t += defer ? 2.0 * splits * M * N * 4 / 8e12 - 1e-6 : 2.0 * splits * M * N * 4 / r.partial + r.reduce;
     return t;
 }
 
@@ -603,6 +478,9 @@ static bool split_ok(int dtype, int K, int s)
 // kernel's is a few per cent high where both stream from HBM.
 constexpr double STREAM_MARGIN = 0.92;
 
+constexpr int64_t MANY_ROWS_PARTIALS = 128 << 20;
+constexpr int OP_RATE_ROWS = 192;
+
 // mode: what the caller allows (GemmMode)
 static Plan make_plan(int dtype, int M, int N, int K, int mode)
 {
@@ -620,16 +498,23 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         p.splits = hit->second.splits;
         p.cost = hit->second.cost;
         p.stream = hit->second.stream;
-    } else if (M > 1024 && dtype == DT_BF16) {
-        p.cost = plan_cost(dtype, C256x256, 1, M, N, K, false);
     } else {
+        // Beyond 1024 rows a launch has many tiles and only the large shapes are worth a look; split-K still pays where they
+        // leave most of the chip idle (1500 x 1024, K 16384: 239 us in 24 tiles, 60 us in six parts), with partial sums
+        // bounded, and for a model's launches only (others would have to bring a workspace that they need not have now).
+        const bool many = M > 1024 && dtype == DT_BF16, model = many || ((mode & GEMM_FEW_ROWS) && M > OP_RATE_ROWS);
+        const int max_splits = !many ? 16 : (mode & GEMM_FEW_ROWS) && M <= MAX_SPLIT_ROWS ? 8 : 1;
         double best = 1e30;
         for (int cfg = 0; cfg < N_CFG; ++cfg) {
             if (CFG[cfg].bm >= 2 * M && CFG[cfg].bm > 64) continue;     // more than half the rows would be padding
             if (dtype == DT_F32 && cfg != C64x128 && cfg != C128x128) continue;
-            for (int s = 1; s <= 16; ++s) {
+            if (is_large(cfg) && K < LARGE_MIN_K) continue;
+            if (cfg == C192x256 && !model) continue;
+            if (many && !is_large(cfg) && !(K < LARGE_MIN_K && cfg == C256x128)) continue;
+            for (int s = 1; s <= max_splits; ++s) {
                 if (!split_ok(dtype, K, s)) continue;
-                double c = plan_cost(dtype, cfg, s, M, N, K, mode & GEMM_DEFER);
+                if (many && s > 1 && (int64_t)s * M * N * 4 > MANY_ROWS_PARTIALS) break;
+                double c = plan_cost(dtype, cfg, s, M, N, K, mode & GEMM_DEFER, model && dtype == DT_BF16);
                 if (c < best) { best = c; p.cfg = cfg; p.splits = s; }
             }
         }
@@ -648,7 +533,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         return p;
     }
     const Knobs& kn = knobs();
-    if (kn.cfg >= 0 && kn.cfg < N_CFG && dtype == DT_BF16) p.cfg = kn.cfg;
+    if (kn.cfg >= 0 && kn.cfg < N_CFG && dtype == DT_BF16 && !(is_large(kn.cfg) && K < LARGE_MIN_K)) p.cfg = kn.cfg;
     if (kn.split > 0 && split_ok(dtype, K, kn.split)) p.splits = kn.split;
     p.spread = 1;     // never slower than issuing a k-tile's loads at once in that sweep, up to 15 % faster from M = 128 on
     if (kn.spread >= 0) p.spread = kn.spread != 0;
@@ -685,23 +570,24 @@ static int persistent_grid()
 // remaining rows (a few hundred) to a second, separately planned launch is cheaper by the cost model, else M.
 static int split_rows(int dtype, int M, int N, int K, int mode)
 {
-    if (M <= 1024 || dtype != DT_BF16 || make_plan(dtype, M, N, K, GEMM_TILE_ONLY).route != 0) return M;
+    if (M <= 1024 || dtype != DT_BF16 || K < LARGE_MIN_K) return M;
+    Plan all = make_plan(dtype, M, N, K, mode);
+    if (all.route != 0) return M;
     int G = persistent_grid();
     int tn = (N + 255) / 256, tm = (M + 255) / 256, total = tm * tn;
     int rounds = total / G;
     if (rounds < 1 || total == rounds * G) return M;
-    double whole = plan_cost(dtype, C256x256, 1, M, N, K, false);
     // Candidates for the first launch: the most row tiles that fill whole rounds, and the largest multiple of 64 row
     // tiles.  With a multiple of 64 every XCD keeps one group of 8 row tiles for the whole launch and all eight walk
     // the weight columns in step; measured, a round of such a launch takes 3-6 % less (16 384 rows against 17 120 -
     // 17 352 at the OPT-13B shape: 1826 us + 127 us for the rest against 2049 us in one launch of 16 rounds).
     int best = M;
-    double best_cost = whole;
+    double best_cost = all.cost;
     int cand[2] = {rounds * G / tn, tm / 64 * 64};
     for (int tm1 : cand) {
         if (tm1 < 1 || tm1 >= tm) continue;
         int M1 = tm1 * 256;
-        double first = plan_cost(dtype, C256x256, 1, M1, N, K, false);
+        double first = plan_cost(dtype, C256x256, 1, M1, N, K, false, true);
         if (tm1 % 64 == 0) first *= 0.95;
         double parts = first + make_plan(dtype, M - M1, N, K, mode & ~GEMM_DEFER).cost;
         if (parts < best_cost) { best_cost = parts; best = M1; }
@@ -809,8 +695,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     } else {
         switch (p.cfg) {
             case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;
-            case C128x256: e = launch_tile<bf16_t, 128, 256, 64, 64, 3>(a, p, s); break;
-            case C256x256: e = launch_tile<bf16_t, 256, 256, 128, 64, 2>(a, p, s); break;
+            case C128x256: case C256x256: case C192x256: e = launch_gemm_large(a, CFG[p.cfg].bm, p.k_per_split, p.splits, persistent_grid(), s); break;
             case C64x128: e = launch_tile<bf16_t, 64, 128, 32, 64, 4>(a, p, s); break;
             case C128x128: e = launch_tile<bf16_t, 128, 128, 64, 64, 3>(a, p, s); break;
             default: e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);

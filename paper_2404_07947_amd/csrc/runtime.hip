@@ -342,8 +342,8 @@ static size_t gemm_ws_need(const exe_model* m, int N, int K)
 {
     if (m->c.dtype == EXE_DTYPE_F32) return 0;             // float launches are not split
     size_t need = 0;
-    int lim = std::min(m->rows_cap, 1024);                 // more rows are split-K only in a remainder launch of at most 1024
-    for (int M = lim; M >= 1; M = (M - 1) / 8 * 8)         // row counts between these fit, or split less
+    int lim = std::min(m->rows_cap, MAX_SPLIT_ROWS);       // more rows are split-K only in a remainder launch
+    for (int M = lim; M >= 1; M = M > 1024 ? std::max((M - 1) / 64 * 64, 1024) : (M - 1) / 8 * 8)     // row counts between these fit, or split less
         for (int mode : {GEMM_FEW_ROWS | 0, GEMM_FEW_ROWS | GEMM_DEFER}) need = std::max(need, gemm_workspace_bytes(m->c.dtype, M, N, K, mode));
     return need;
 }
