@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "gemm_epilogue.h"
@@ -25,9 +26,34 @@ namespace exe {
 
 constexpr float LOG2E = 1.44269504088896340736f;
 constexpr int ATTN_BIAS_LDS = 1024;       // entries of a head's bias table that the row kernel keeps in LDS
-constexpr int ATTN_SHORT_LEN = 320;      // decode attention: mean rows per sequence up to which 4 waves serve a row
+constexpr int ATTN_U = 2;                 // decode attention: row blocks in flight per wave
+constexpr int ATTN_LONG_BYTES = 256 << 10;
+constexpr int ATTN_LONG_LDS = 88 << 10;   // dynamic LDS that leaves room for one workgroup on a CU
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Sum over the W lanes (8 or 16) that share a cached row, in every one of them: DPP moves inside a row of 16 lanes, a few
+// cycles each where a shuffle takes a trip through the LDS pipe.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int W> __device__ __forceinline__ float row_sum(float d)
+{
+    static_assert(W == 8 || W == 16 || W == 32, "lanes per row");
+    d += dpp_move<0xB1>(d);                  // quad_perm: lane ^ 1
+    d += dpp_move<0x4E>(d);                  // quad_perm: lane ^ 2
+    d += dpp_move<0x141>(d);                 // row_half_mirror: the other four of eight
+    if (W >= 16) d += dpp_move<0x140>(d);    // row_mirror: the other eight of sixteen
+    if (W == 32) d += __shfl_xor(d, 16, WAVE);
+    return d;
+}
+// the value of the lane `lane ^ O`
+template <int O> __device__ __forceinline__ float lane_xor(float x)
+{
+    if (O == 8) return dpp_move<0x128>(x);   // row_ror:8
+    return __shfl_xor(x, O, WAVE);
+}
 
 template <typename T, int EPL> struct Chunk;
 template <> struct Chunk<float, 4> {
@@ -88,11 +114,10 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
     constexpr int EPL = 16 / sizeof(T);      // elements per 16-byte chunk
     constexpr int LPR = DH / EPL;            // lanes that share one key/value row
     constexpr int RPW = 64 / LPR;            // rows per wave per load
-    constexpr int G = NWV * RPW;             // partial softmax states per workgroup (U row blocks in flight per wave)
     constexpr int NL = (PAGED && RPW * U > 8) ? U : 1;   // PAGED: table look-ups per step
     static_assert(RPW <= 8, "the rows of one load must fit the smallest block");
-    __shared__ float s_m[G], s_l[G];
-    __shared__ float s_acc[G][DH];
+    __shared__ float s_m[NWV], s_l[NWV];
+    __shared__ __align__(16) float s_acc[NWV][DH];
 
     int h = blockIdx.x, r = blockIdx.y;
     int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -220,8 +245,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
             float d = 0.f;
 #pragma unroll
             for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
-#pragma unroll
-            for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, WAVE);
+            d = row_sum<LPR>(d);
             int j = j0 + u * RPW + rg;
             if (bias) d += bias_at(j - qpos);
             s[u] = j < nc ? d : -INFINITY;
@@ -253,8 +277,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
         float d = 0.f;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
-#pragma unroll
-        for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, WAVE);
+        d = row_sum<LPR>(d);
         if (bias) d += bias_at(nk - 1 - qpos);
         float mx = fmaxf(m_run, d);
         float alpha = fast_exp2(m_run - mx), p = fast_exp2(d - mx);
@@ -264,18 +287,35 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
         m_run = mx;
     }
 
-    // merge the G partial states (wave, row group) of this workgroup
-    int gi = wave * RPW + rg;
-    if (cl == 0) { s_m[gi] = m_run; s_l[gi] = l_run; }
+    // Merge the partial states: the row groups of a wave across its lanes, then the waves through LDS.  (All NWV * RPW states
+    // through LDS, added up by DH threads, took 2-4 us of every launch.)
+    auto merge_lanes = [&](auto xo) {
+        constexpr int O = decltype(xo)::value;
+        float mo = lane_xor<O>(m_run), lo = lane_xor<O>(l_run);
+        float mx = fmaxf(m_run, mo), mref = mx == -INFINITY ? 0.f : mx;
+        float wa = fast_exp2(m_run - mref), wb = fast_exp2(mo - mref);       // 0 for a side that saw no key
+        l_run = l_run * wa + lo * wb;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) s_acc[gi][cl * EPL + e] = acc[e];
+        for (int e = 0; e < EPL; ++e) acc[e] = acc[e] * wa + lane_xor<O>(acc[e]) * wb;
+        m_run = mx;
+    };
+    if constexpr (LPR <= 8) merge_lanes(std::integral_constant<int, 8>{});
+    if constexpr (LPR <= 16) merge_lanes(std::integral_constant<int, 16>{});
+    if constexpr (LPR <= 32) merge_lanes(std::integral_constant<int, 32>{});
+    if (lane == 0) { s_m[wave] = m_run; s_l[wave] = l_run; }
+    if (rg == 0) {
+#pragma unroll
+        for (int e = 0; e < EPL; e += 4) *(f32x4*)&s_acc[wave][cl * EPL + e] = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+    }
     __syncthreads();
     for (int c = threadIdx.x; c < DH; c += NWV * 64) {
-        float M = -INFINITY;
-        for (int g = 0; g < G; ++g) M = fmaxf(M, s_m[g]);
+        float M = s_m[0];
+#pragma unroll
+        for (int g = 1; g < NWV; ++g) M = fmaxf(M, s_m[g]);
         float L = 0.f, o = 0.f;
-        for (int g = 0; g < G; ++g) {
-            float w = fast_exp2(s_m[g] - M);      // 0 for groups that saw no key
+#pragma unroll
+        for (int g = 0; g < NWV; ++g) {
+            float w = fast_exp2(s_m[g] - M);      // 0 for waves that saw no key
             L += s_l[g] * w;
             o += s_acc[g][c] * w;
         }
@@ -283,33 +323,56 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
     }
 }
 
+// Launch shape of a decode attention launch whose sequences have mean_len rows on average (0 = unknown), 2 row blocks in
+// flight per wave: measured best of a sweep over {1,2,4,8,16} waves x {1,2,3,4,8} blocks.
+//  * 16 waves per (sequence, head), fewer where the rows would leave some without a step: 8 up to 12 steps, 4 up to 4
+//    (16 x 128 heads of 8 rows: 4 waves 6.8, 8 waves 9.0, 16 waves 14.5 us; 32 x 40 heads of 200 rows: 21.9, 21.8, 21.0).
+//  * Long streams run one workgroup per CU (dynamic LDS that nothing uses keeps a second one out): with two, twice as many
+//    streams are open in memory (256 x 40 heads of 576 rows x 128: 432 us with two, 420 with one, 8 x 96 of 1024 58.2 and
+//    56.7; short ones need the second to cover their start and end: 48 x 16 of 430 rows x 64 15.7 us with two, 17.5 with
+//    one; 32 x 40 of 576 x 128 55.0 either way).
+template <typename T, int DH> static int attn_waves(int mean_len)
+{
+    constexpr int step = 64 / (DH / (16 / (int)sizeof(T))) * ATTN_U;         // rows that a wave takes at a time
+    return mean_len <= 0 || mean_len > 12 * step ? 16 : mean_len > 4 * step ? 8 : 4;
+}
+
+template <typename T, int DH, bool PAGED, typename... Args>
+static hipError_t launch_attn_row(int mean_len, dim3 grid, hipStream_t s, Args... args)
+{
+    auto k16 = attn_row_kernel<T, DH, false, 16, ATTN_U, PAGED>;
+    switch (attn_waves<T, DH>(mean_len)) {
+        case 4: attn_row_kernel<T, DH, false, 4, ATTN_U, PAGED><<<grid, 256, 0, s>>>(args...); break;
+        case 8: attn_row_kernel<T, DH, false, 8, ATTN_U, PAGED><<<grid, 512, 0, s>>>(args...); break;
+        default: {
+            int lds = (int64_t)mean_len * 2 * DH * (int)sizeof(T) >= ATTN_LONG_BYTES ? ATTN_LONG_LDS : 0;
+            static LdsLimit limit[MAX_DEVICES];
+            int dev = 0;
+            if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
+            hipError_t e = limit[dev].raise((const void*)k16, ATTN_LONG_LDS);
+            if (e != hipSuccess) return e;
+            k16<<<grid, 1024, lds, s>>>(args...);
+        }
+    }
+    return hipGetLastError();
+}
+
+template <typename T, int DH> static hipError_t launch_attn_cache_t(const AttnCacheArgs& a, hipStream_t s)
+{
+    const int32_t* none = nullptr;
+    return launch_attn_row<T, DH, false>(a.mean_len, dim3(a.H, a.B), s, (const T*)a.q, a.q_stride, (const T*)a.pool, a.base, a.cap, a.len,
+                                         a.qpos, none, none, a.layer, a.H, 0, a.scale, a.bias_by_dist, a.bias_radius, (T*)a.out,
+                                         a.new_k_off, a.new_v_off, none, 0, 0);
+}
+
 hipError_t launch_attn_cache(const AttnCacheArgs& a, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
-    dim3 grid(a.H, a.B);
-    // 16 waves per (sequence, head), 2 row blocks in flight per wave: measured best of a sweep over
-    // {1,2,4,8,16} waves x {1,2,3,4,8} blocks (6.4 TB/s at batch 256, 6.0 at batch 32; 4 waves x 4: 6.0 / 5.3).
-    // Short sequences (mean_len rows on average, 0 = unknown) leave most of 16 waves without a row: 4 waves serve
-    // them better (32 rows: 6.3 against 2.2 TB/s, cache-assisted; even at about 300 rows).
-    int nwv = a.mean_len > 0 && a.mean_len <= ATTN_SHORT_LEN ? 4 : 16;
-#define EXE_ROW_N(T, DH, NWV)                                                                                   \
-    attn_row_kernel<T, DH, false, NWV, 2><<<grid, NWV * 64, 0, s>>>((const T*)a.q, a.q_stride, (const T*)a.pool, \
-                                                               a.base, a.cap, a.len, a.qpos, nullptr, nullptr,  \
-                                                               a.layer, a.H, 0, a.scale, a.bias_by_dist,        \
-                                                               a.bias_radius, (T*)a.out, a.new_k_off, a.new_v_off)
-#define EXE_ROW(T, DH)                                                                                          \
-    do {                                                                                                        \
-        if (nwv == 4) EXE_ROW_N(T, DH, 4);                                                                      \
-        else EXE_ROW_N(T, DH, 16);                                                                              \
-    } while (0)
-    if (a.dtype == DT_F32 && a.dh == 64) EXE_ROW(float, 64);
-    else if (a.dtype == DT_F32 && a.dh == 128) EXE_ROW(float, 128);
-    else if (a.dtype == DT_BF16 && a.dh == 64) EXE_ROW(bf16_t, 64);
-    else if (a.dtype == DT_BF16 && a.dh == 128) EXE_ROW(bf16_t, 128);
-    else return hipErrorInvalidValue;
-#undef EXE_ROW
-#undef EXE_ROW_N
-    return hipGetLastError();
+    if (a.dtype == DT_F32 && a.dh == 64) return launch_attn_cache_t<float, 64>(a, s);
+    if (a.dtype == DT_F32 && a.dh == 128) return launch_attn_cache_t<float, 128>(a, s);
+    if (a.dtype == DT_BF16 && a.dh == 64) return launch_attn_cache_t<bf16_t, 64>(a, s);
+    if (a.dtype == DT_BF16 && a.dh == 128) return launch_attn_cache_t<bf16_t, 128>(a, s);
+    return hipErrorInvalidValue;
 }
 
 // Host-side replay of the paged kernel's row indexing for one sequence of `len` cached rows (the rows a launch with
@@ -319,7 +382,7 @@ hipError_t launch_attn_cache(const AttnCacheArgs& a, hipStream_t s)
 int paged_index_check(int dtype, int dh, int block_shift, int nwv, int len)
 {
     int epl = dtype == DT_F32 ? 4 : 8, lpr = dh / epl, rpw = 64 / lpr;
-    constexpr int U = 2;                       // as launched below
+    constexpr int U = ATTN_U;
     int nl = rpw * U > 8 ? U : 1, block_rows = 1 << block_shift, bad = 0;
     if (len < 1 || rpw > 8) return -1;
     int n_blocks = (len + block_rows - 1) >> block_shift;
@@ -342,30 +405,24 @@ int paged_index_check(int dtype, int dh, int block_shift, int nwv, int len)
     return bad;
 }
 
+template <typename T, int DH> static hipError_t launch_attn_paged_t(const AttnPagedArgs& a, hipStream_t s)
+{
+    const int32_t* none = nullptr;
+    const int64_t* none64 = nullptr;
+    return launch_attn_row<T, DH, true>(a.mean_len, dim3(a.H, a.B), s, (const T*)a.q, a.q_stride, (const T*)a.pool, none64, none, a.len,
+                                        a.qpos, none, none, 0, a.H, 0, a.scale, a.bias_by_dist, a.bias_radius, (T*)a.out,
+                                        a.new_k_off, a.new_v_off, a.block_table, a.max_blocks, a.block_shift);
+}
+
 hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
 {
     if (a.B <= 0) return hipSuccess;
     if (a.block_shift < 3 || a.block_shift > 12 || a.max_blocks < 1) return hipErrorInvalidValue;
-    dim3 grid(a.H, a.B);
-    int nwv = a.mean_len > 0 && a.mean_len <= ATTN_SHORT_LEN ? 4 : 16;
-#define EXE_ROW_N(T, DH, NWV)                                                                                       \
-    attn_row_kernel<T, DH, false, NWV, 2, true><<<grid, NWV * 64, 0, s>>>(                                          \
-        (const T*)a.q, a.q_stride, (const T*)a.pool, nullptr, nullptr, a.len, a.qpos, nullptr, nullptr, 0, a.H, 0,  \
-        a.scale, a.bias_by_dist, a.bias_radius, (T*)a.out, a.new_k_off, a.new_v_off, a.block_table, a.max_blocks,   \
-        a.block_shift)
-#define EXE_ROW(T, DH)                                                                                              \
-    do {                                                                                                            \
-        if (nwv == 4) EXE_ROW_N(T, DH, 4);                                                                          \
-        else EXE_ROW_N(T, DH, 16);                                                                                  \
-    } while (0)
-    if (a.dtype == DT_F32 && a.dh == 64) EXE_ROW(float, 64);
-    else if (a.dtype == DT_F32 && a.dh == 128) EXE_ROW(float, 128);
-    else if (a.dtype == DT_BF16 && a.dh == 64) EXE_ROW(bf16_t, 64);
-    else if (a.dtype == DT_BF16 && a.dh == 128) EXE_ROW(bf16_t, 128);
-    else return hipErrorInvalidValue;
-#undef EXE_ROW
-#undef EXE_ROW_N
-    return hipGetLastError();
+    if (a.dtype == DT_F32 && a.dh == 64) return launch_attn_paged_t<float, 64>(a, s);
+    if (a.dtype == DT_F32 && a.dh == 128) return launch_attn_paged_t<float, 128>(a, s);
+    if (a.dtype == DT_BF16 && a.dh == 64) return launch_attn_paged_t<bf16_t, 64>(a, s);
+    if (a.dtype == DT_BF16 && a.dh == 128) return launch_attn_paged_t<bf16_t, 128>(a, s);
+    return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------- MFMA prefill (described for bf16, head size 128)
