@@ -61,6 +61,8 @@ struct LdsLimit {
     }
 };
 
+// copies a call's descriptors (16-byte aligned buffers of a multiple of 16 bytes) from pinned host memory
+hipError_t launch_stage(const void* host, void* dev, size_t bytes, hipStream_t s);
 hipError_t launch_embed(int dtype, const int32_t* tokens, const int32_t* pos, int T, int d, const void* tok_emb,
                         const void* pos_emb, float* h, hipStream_t s);
 hipError_t launch_load_hidden(int dtype, const void* x, int64_t n, float* h, hipStream_t s);

@@ -4,66 +4,126 @@
 
 namespace exe {
 
+// V consecutive elements, from storage to float and back
+template <typename T, int V> __device__ __forceinline__ void load_f32(const T* p, float (&f)[V])
+{
+    typedef __attribute__((ext_vector_type(V))) T vec;
+    vec v = *(const vec*)p;
+#pragma unroll
+    for (int i = 0; i < V; ++i) f[i] = to_f32(v[i]);
+}
+template <typename T, int V> __device__ __forceinline__ void store_f32(T* p, const float (&f)[V])
+{
+    typedef __attribute__((ext_vector_type(V))) T vec;
+    vec v;
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = from_f32<T>(f[i]);
+    *(vec*)p = v;
+}
+// V of the kernels below: 4 where every row and pointer allows it, else 1
+static bool vec4_ok(int dtype, int64_t row, const float* f, const void* a, const void* b = nullptr)
+{
+    uintptr_t m = dtype == DT_F32 ? 15 : 7;
+    return row % 4 == 0 && ((uintptr_t)f & 15) == 0 && ((uintptr_t)a & m) == 0 && ((uintptr_t)b & m) == 0;
+}
+
+// ---------------------------------------------------------------- descriptors
+// A call's descriptors from pinned host memory to the device.  A kernel in the stream, not a copy command: the copy engine's
+// hand-over to the kernels behind it took longer than either.
+__global__ void stage_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int n)
+{
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
+hipError_t launch_stage(const void* host, void* dev, size_t bytes, hipStream_t s)
+{
+    int n = (int)((bytes + 15) / 16);
+    if (n <= 0) return hipSuccess;
+    stage_kernel<<<(n + 255) / 256, 256, 0, s>>>((const uint4*)host, (uint4*)dev, n);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- embedding
-// h[t][:] = tok_emb[tokens[t]][:] (+ pos_emb[pos[t]][:]); the residual stream h is float.
-template <typename T>
+// h[t][:] = tok_emb[tokens[t]][:] (+ pos_emb[pos[t]][:]); the residual stream h is float.  One element group per thread: with
+// one workgroup per row each of its 20 rounds (d = 5120) waited for memory in turn, 17 us for a single row (now 4).
+template <typename T, int V>
 __global__ void embed_kernel(const int32_t* __restrict__ tokens, const int32_t* __restrict__ pos, int d,
                              const T* __restrict__ tok_emb, const T* __restrict__ pos_emb, float* __restrict__ h)
 {
-    int t = blockIdx.x;
-    const T* e = tok_emb + (int64_t)tokens[t] * d;
-    const T* p = pos_emb ? pos_emb + (int64_t)pos[t] * d : nullptr;
-    float* o = h + (int64_t)t * d;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) {
-        float v = to_f32(e[k]);
-        if (p) v += to_f32(p[k]);
-        o[k] = v;
+    int t = blockIdx.x, k = (blockIdx.y * blockDim.x + threadIdx.x) * V;
+    if (k >= d) return;
+    float v[V], p[V];
+    load_f32<T, V>(tok_emb + (int64_t)tokens[t] * d + k, v);
+    if (pos_emb) {
+        load_f32<T, V>(pos_emb + (int64_t)pos[t] * d + k, p);
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] += p[i];
+    }
+    store_f32<float, V>(h + (int64_t)t * d + k, v);
+}
+
+template <typename T, int V> __global__ void load_hidden_kernel(const T* __restrict__ x, int64_t n, float* __restrict__ h)
+{
+    int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+    int64_t stride = (int64_t)gridDim.x * blockDim.x * V;
+    for (; i < n; i += stride) {
+        float v[V];
+        load_f32<T, V>(x + i, v);
+        store_f32<float, V>(h + i, v);
     }
 }
 
-template <typename T>
-__global__ void load_hidden_kernel(const T* __restrict__ x, int64_t n, float* __restrict__ h)
+template <typename T, int V> __global__ void store_hidden_kernel(const float* __restrict__ h, int64_t n, T* __restrict__ out)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) h[i] = to_f32(x[i]);
+    int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+    int64_t stride = (int64_t)gridDim.x * blockDim.x * V;
+    for (; i < n; i += stride) {
+        float v[V];
+        load_f32<float, V>(h + i, v);
+        store_f32<T, V>(out + i, v);
+    }
 }
 
-template <typename T>
-__global__ void store_hidden_kernel(const float* __restrict__ h, int64_t n, T* __restrict__ out)
+template <typename T, int V>
+static hipError_t embed_shape(const int32_t* tokens, const int32_t* pos, int T_, int d, const void* te, const void* pe, float* h, hipStream_t s)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) out[i] = from_f32<T>(h[i]);
+    int groups = (d + V - 1) / V, threads = groups >= 256 ? 256 : 64;
+    embed_kernel<T, V><<<dim3(T_, (groups + threads - 1) / threads), threads, 0, s>>>(tokens, pos, d, (const T*)te, (const T*)pe, h);
+    return hipGetLastError();
 }
 
 hipError_t launch_embed(int dtype, const int32_t* tokens, const int32_t* pos, int T, int d, const void* tok_emb,
                         const void* pos_emb, float* h, hipStream_t s)
 {
     if (T <= 0) return hipSuccess;
-    if (dtype == DT_F32)
-        embed_kernel<float><<<T, 256, 0, s>>>(tokens, pos, d, (const float*)tok_emb, (const float*)pos_emb, h);
-    else
-        embed_kernel<bf16_t><<<T, 256, 0, s>>>(tokens, pos, d, (const bf16_t*)tok_emb, (const bf16_t*)pos_emb, h);
+    bool v4 = vec4_ok(dtype, d, h, tok_emb, pos_emb);
+    if (dtype == DT_F32) return v4 ? embed_shape<float, 4>(tokens, pos, T, d, tok_emb, pos_emb, h, s) : embed_shape<float, 1>(tokens, pos, T, d, tok_emb, pos_emb, h, s);
+    return v4 ? embed_shape<bf16_t, 4>(tokens, pos, T, d, tok_emb, pos_emb, h, s) : embed_shape<bf16_t, 1>(tokens, pos, T, d, tok_emb, pos_emb, h, s);
+}
+
+template <typename T, int V> static hipError_t hidden_shape(const void* x, float* h, void* out, int64_t n, hipStream_t s)
+{
+    int64_t want = (n + 256 * V - 1) / (256 * V);
+    int blocks = (int)(want < 8192 ? want : 8192);
+    if (x) load_hidden_kernel<T, V><<<blocks, 256, 0, s>>>((const T*)x, n, h);
+    else store_hidden_kernel<T, V><<<blocks, 256, 0, s>>>(h, n, (T*)out);
     return hipGetLastError();
 }
 
-hipError_t launch_load_hidden(int dtype, const void* x, int64_t n, float* h, hipStream_t s)
+static hipError_t hidden_any(int dtype, const void* x, float* h, void* out, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    int blocks = (int)((n + 1023) / 1024 < 8192 ? (n + 1023) / 1024 : 8192);
-    if (dtype == DT_F32) load_hidden_kernel<float><<<blocks, 256, 0, s>>>((const float*)x, n, h);
-    else load_hidden_kernel<bf16_t><<<blocks, 256, 0, s>>>((const bf16_t*)x, n, h);
-    return hipGetLastError();
+    bool v4 = vec4_ok(dtype, n, h, x, out);
+    if (dtype == DT_F32) return v4 ? hidden_shape<float, 4>(x, h, out, n, s) : hidden_shape<float, 1>(x, h, out, n, s);
+    return v4 ? hidden_shape<bf16_t, 4>(x, h, out, n, s) : hidden_shape<bf16_t, 1>(x, h, out, n, s);
 }
+
+hipError_t launch_load_hidden(int dtype, const void* x, int64_t n, float* h, hipStream_t s) { return hidden_any(dtype, x, h, nullptr, n, s); }
 
 hipError_t launch_store_hidden(int dtype, const float* h, int64_t n, void* out, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    int blocks = (int)((n + 1023) / 1024 < 8192 ? (n + 1023) / 1024 : 8192);
-    if (dtype == DT_F32) store_hidden_kernel<float><<<blocks, 256, 0, s>>>(h, n, (float*)out);
-    else store_hidden_kernel<bf16_t><<<blocks, 256, 0, s>>>(h, n, (bf16_t*)out);
-    return hipGetLastError();
+    return hidden_any(dtype, nullptr, const_cast<float*>(h), out, n, s);
 }
 
 // ---------------------------------------------------------------- norms
@@ -291,17 +351,30 @@ hipError_t launch_kv_append_paged(int dtype, const void* src, int ld, int k_off,
 }
 
 // ---------------------------------------------------------------- greedy argmax
-// One workgroup per row; ties resolve to the lowest index at every level of the reduction.
-__global__ void argmax_kernel(const float* __restrict__ logits, int n, int32_t* __restrict__ out)
+// One workgroup per row; ties resolve to the lowest index at every level of the reduction.  Four loads in flight per thread:
+// one at a time, a row of 50 272 logits took 20 us (now 7).  `out` may be pinned host memory.
+template <int V> __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int n, int32_t* __restrict__ out)
 {
     __shared__ float bv[16];
     __shared__ int bi[16];
     const float* x = logits + (int64_t)blockIdx.x * n;
     float best = -INFINITY;
     int idx = 0x7fffffff;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        float v = x[i];
-        if (v > best || (v == best && i < idx)) { best = v; idx = i; }
+    constexpr int D = 4;
+    for (int i0 = threadIdx.x * V; i0 < n; i0 += 1024 * V * D) {
+        float v[D][V];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            int i = i0 + d * 1024 * V;
+            load_f32<float, V>(x + (i < n ? i : i0), v[d]);
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                int i = i0 + d * 1024 * V + e;
+                if (i < n && (v[d][e] > best || (v[d][e] == best && i < idx))) { best = v[d][e]; idx = i; }
+            }
     }
     if (idx == 0x7fffffff) { best = -INFINITY; }
 #pragma unroll
@@ -323,7 +396,8 @@ __global__ void argmax_kernel(const float* __restrict__ logits, int n, int32_t* 
 hipError_t launch_argmax(const float* logits, int rows, int n, int32_t* out, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
-    argmax_kernel<<<rows, 1024, 0, s>>>(logits, n, out);
+    if (n % 4 == 0 && ((uintptr_t)logits & 15) == 0) argmax_kernel<4><<<rows, 1024, 0, s>>>(logits, n, out);
+    else argmax_kernel<1><<<rows, 1024, 0, s>>>(logits, n, out);
     return hipGetLastError();
 }
 

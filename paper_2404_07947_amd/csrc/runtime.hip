@@ -180,13 +180,12 @@ struct exe_model {
     float* h = nullptr;
     void *a = nullptr, *qkv = nullptr, *ctx = nullptr, *u = nullptr, *a_last = nullptr;
     float* logits = nullptr;
-    int32_t* d_next = nullptr;
     float* gemm_ws = nullptr;
     size_t gemm_ws_bytes = 0;
     // descriptor staging
     unsigned char *stage_h = nullptr, *stage_d = nullptr;
     size_t stage_bytes = 0;
-    int32_t* h_next = nullptr;            // pinned
+    int32_t* h_next = nullptr;            // pinned; argmax writes it
     std::vector<int32_t> mark;            // duplicate detection
     int32_t mark_gen = 0;
     KTimer timer;
@@ -321,7 +320,7 @@ static void free_model(exe_model* m)
 {
     if (!m) return;
     (void)hipStreamSynchronize(m->stream);
-    void* ptrs[] = {m->pool.ptr, m->h, m->a, m->qkv, m->ctx, m->u, m->a_last, m->logits, m->d_next, m->gemm_ws,
+    void* ptrs[] = {m->pool.ptr, m->h, m->a, m->qkv, m->ctx, m->u, m->a_last, m->logits, m->gemm_ws,
                     m->stage_d, m->bias_enc, m->bias_dec, m->bias_x};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -442,8 +441,7 @@ extern "C" int exe_model_load(const exe_config_t* cfg, const exe_tensor_t* weigh
     if (c.has_lm_head) {
         LOAD_TRY(hipMalloc(&m->a_last, (size_t)c.max_batch_seqs * d * e));
         LOAD_TRY(hipMalloc((void**)&m->logits, (size_t)c.max_batch_seqs * c.vocab * sizeof(float)));
-        LOAD_TRY(hipMalloc((void**)&m->d_next, (size_t)c.max_batch_seqs * sizeof(int32_t)));
-        LOAD_TRY(hipHostMalloc((void**)&m->h_next, (size_t)c.max_batch_seqs * sizeof(int32_t), hipHostMallocDefault));
+        LOAD_TRY(hipHostMalloc((void**)&m->h_next, (size_t)c.max_batch_seqs * sizeof(int32_t), hipHostMallocCoherent));
     }
     size_t ws = 0;
     ws = std::max(ws, gemm_ws_need(m, 3 * m->inner, c.d_model));
@@ -463,7 +461,8 @@ extern "C" int exe_model_load(const exe_config_t* cfg, const exe_tensor_t* weigh
     size_t tiles_max = (size_t)c.max_batch_tokens / PREFILL_TILE_Q + c.max_batch_seqs + 1;
     m->stage_bytes = 3 * (size_t)rows * 4 + tiles_max * 8 + (size_t)(c.max_batch_seqs + 1) * (2 * 8 + 6 * 4) + 256 +
                      table_max * 4 + 16;
-    LOAD_TRY(hipHostMalloc((void**)&m->stage_h, m->stage_bytes, hipHostMallocDefault));
+    m->stage_bytes = (m->stage_bytes + 15) & ~(size_t)15;
+    LOAD_TRY(hipHostMalloc((void**)&m->stage_h, m->stage_bytes, hipHostMallocCoherent));
     LOAD_TRY(hipMalloc((void**)&m->stage_d, m->stage_bytes));
 #undef LOAD_TRY
     *out = m;
@@ -544,26 +543,26 @@ static float attn_scale(const exe_model* m)
     return m->c.scale_mode == EXE_SCALE_RSQRT_DH ? 1.f / sqrtf((float)m->c.head_dim) : 1.f;
 }
 
-// final norm of selected rows, LM head, argmax (launches only)
-static int head_launches(exe_model* m, const int32_t* row_index_dev, int n)
+// final norm of selected rows, LM head into `logits`, argmax into h_next if tokens are wanted (launches only)
+static int head_launches(exe_model* m, const int32_t* row_index_dev, int n, float* logits, bool tokens)
 {
     const exe_config_t& c = m->c;
     int r;
     float out_scale = c.arch == EXE_ARCH_ENC_DEC ? 1.f / sqrtf((float)c.d_model) : 1.f;
     if ((r = run_norm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last))) return r;
-    if ((r = run_gemm(m, n, c.vocab, c.d_model, m->a_last, m->tok_emb, nullptr, -1, 1.f, OUT_F32, m->logits))) return r;
-    LAUNCH(m, EXE_K_OTHER, (double)n * c.vocab * 4.0, 0.0, launch_argmax(m->logits, n, c.vocab, m->d_next, m->stream));
+    if ((r = run_gemm(m, n, c.vocab, c.d_model, m->a_last, m->tok_emb, nullptr, -1, 1.f, OUT_F32, logits))) return r;
+    if (tokens) LAUNCH(m, EXE_K_OTHER, (double)n * c.vocab * 4.0, 0.0, launch_argmax(logits, n, c.vocab, m->h_next, m->stream));
     return EXE_OK;
 }
 
-// head, then tokens to the host and logits to out_device; synchronises the stream
+// head, with the logits straight to out_device where its alignment allows the kernels' stores; synchronises the stream
 static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* next_tokens, void* out_device)
 {
     const exe_config_t& c = m->c;
-    int r = head_launches(m, row_index_dev, n);
+    bool direct = out_device && ((uintptr_t)out_device & 15) == 0;
+    int r = head_launches(m, row_index_dev, n, direct ? (float*)out_device : m->logits, next_tokens != nullptr);
     if (r) return r;
-    if (next_tokens) HIP_TRY(hipMemcpyAsync(m->h_next, m->d_next, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
-    if (out_device)
+    if (out_device && !direct)
         HIP_TRY(hipMemcpyAsync(out_device, m->logits, (size_t)n * c.vocab * 4, hipMemcpyDeviceToDevice, m->stream));
     HIP_TRY(hipStreamSynchronize(m->stream));
     if (next_tokens) memcpy(next_tokens, m->h_next, (size_t)n * 4);
@@ -800,7 +799,7 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
 
     m->pend.splits = 0;                    // h is about to be written anew
     auto body = [&]() -> int {
-        HIP_TRY(hipMemcpyAsync(m->stage_d, m->stage_h, st.off, hipMemcpyHostToDevice, m->stream));
+        HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
         if (c.has_embed)
             LAUNCH(m, EXE_K_OTHER, (double)T * c.d_model * (esz_of(m) + 4.0), 0.0,
                    launch_embed(c.dtype, d.tok, d.tok_pos, T, c.d_model, m->tok_emb, m->pos_emb, m->h, m->stream));
@@ -995,7 +994,7 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
         if (st.off > m->stage_bytes) return fail(EXE_ERR_ARG, "descriptor staging overflow");
     }
     m->pend.splits = 0;                    // h is about to be written anew
-    HIP_TRY(hipMemcpyAsync(m->stage_d, m->stage_h, st.off, hipMemcpyHostToDevice, m->stream));
+    HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
     int r;
     if ((r = decode_input(m, dd, n, hidden_in))) return r;
     for (size_t l = 0; l < m->dec.size(); ++l)
@@ -1384,7 +1383,7 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
     };
     auto body = [&]() -> int {
         if (st.off > m->stage_bytes) return fail(EXE_ERR_ARG, "descriptor staging overflow");
-        HIP_TRY(hipMemcpyAsync(m->stage_d, m->stage_h, st.off, hipMemcpyHostToDevice, m->stream));
+        HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
         EventTimer t;
         HIP_TRY(t.init());
         int r;
@@ -1438,7 +1437,7 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
         } else if (c.has_lm_head) {
             HIP_TRY(hipEventRecord(t.a, m->stream));
             for (int i = 0; i < n_steps; ++i)
-                if ((r = head_launches(m, phase == 0 ? ed.last : nullptr, n))) return r;
+                if ((r = head_launches(m, phase == 0 ? ed.last : nullptr, n, m->logits, true))) return r;
             HIP_TRY(hipEventRecord(t.b, m->stream));
             HIP_TRY(hipEventSynchronize(t.b));
             float ms = 0.f;
