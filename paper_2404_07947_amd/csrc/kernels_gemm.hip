@@ -487,7 +487,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
     Plan p{2, 0, 1, K, 0, 0, 0.0, StreamPlan{}};
     if (N % 4 != 0 || K % k_tile(dtype) != 0 || M < 1) return p;
     p.route = 0;
-    p.cfg = dtype == DT_F32 ? C128x128 : C256x256;
+    p.cfg = dtype == DT_F32 ? C64x128 : C256x256;
     // the model's choice per shape is remembered (a decode iteration asks for the same few shapes 4 times per layer)
     struct Choice { int cfg, splits; double cost; StreamPlan stream; };
     thread_local std::unordered_map<uint64_t, Choice> memo;
@@ -507,7 +507,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         double best = 1e30;
         for (int cfg = 0; cfg < N_CFG; ++cfg) {
             if (CFG[cfg].bm >= 2 * M && CFG[cfg].bm > 64) continue;     // more than half the rows would be padding
-            if (dtype == DT_F32 && cfg != C64x128 && cfg != C128x128) continue;
+            if (dtype == DT_F32 && cfg != C64x128) continue;
             if (is_large(cfg) && K < LARGE_MIN_K) continue;
             if (cfg == C192x256 && !model) continue;
             if (many && !is_large(cfg) && !(K < LARGE_MIN_K && cfg == C256x128)) continue;
@@ -542,7 +542,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
     return p;
 }
 
-// Per-device launch state: the number of persistent workgroups of a tile GEMM (one per compute unit: every
+// Per-device launch state: the number of persistent workgroups of a tile GEMM (one per compute unit: every bf16
 // configuration takes more than half of a CU's LDS, so one workgroup is resident per CU; rounded down to a
 // multiple of 8 for the XCD mapping).
 static int current_device()
@@ -636,7 +636,9 @@ static hipError_t launch_tile(const GemmArgs& a, const Plan& p, hipStream_t s)
     if (e != hipSuccess) return e;
     int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
     int items = tm * tn * p.splits;
-    int grid = items < persistent_grid() ? items : persistent_grid();
+    constexpr int per_cu = 160 * 1024 / lds;         // float: 2 or 3 workgroups share a CU
+    int gmax = persistent_grid() * per_cu;
+    int grid = items < gmax ? items : gmax;
     int w_once = tm == 1 && a.M <= 64;      // measured: 7-10 % faster up to 32 rows, even from 96 rows on
     if (knobs().nt >= 0) w_once = knobs().nt != 0;
     kern<<<grid, threads, lds, s>>>(a.M, a.N, a.K, (const T*)a.A, (const T*)a.W, (const T*)a.bias, a.act, a.alpha, a.out_mode,
@@ -691,7 +693,11 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     hipError_t e;
     if (p.route == 1) e = launch_gemm_stream(a, p.stream, s);
     else if (a.dtype == DT_F32) {
-        e = p.cfg == C64x128 ? launch_tile<float, 64, 128, 32, 64, 4>(a, p, s) : launch_tile<float, 128, 128, 64, 64, 3>(a, p, s);
+        // Two or three workgroups on a CU hide each other's starts, epilogues and barriers (one, of 4 waves, ran at 60-70 TFLOP/s):
+        // 12288 x 768, K 256 81 -> 61 us, x 1024 93 -> 72; the smaller tile where the larger makes no more than a round:
+        // 12288 x 256, K 256 35 -> 23 (27 with the larger), K 1024 89 -> 63 (74).
+        int64_t tiles = (int64_t)((a.M + 63) / 64) * ((a.N + 127) / 128);
+        e = tiles <= 2 * persistent_grid() ? launch_tile<float, 64, 64, 32, 32, 2>(a, p, s) : launch_tile<float, 64, 128, 32, 32, 2>(a, p, s);
     } else {
         switch (p.cfg) {
             case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;

@@ -59,3 +59,22 @@ def test_large_gemm_every_row(cfg, M, N, K, mode):
     torch.cuda.synchronize()
     err = np.max(np.abs(out.float().cpu().numpy() - ref), axis=1) / np.max(np.abs(ref))
     assert float(err.max()) < TOL[mode], (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("M,N,K", [(8193, 1028, 64), (12289, 516, 96)])
+@pytest.mark.parametrize("mode", ["f32", "resid", "gelu"])
+def test_float_tiles_beyond_one_round(M, N, K, mode):
+    """The wider float tile (more tiles than two per CU; the smaller one is compared in test_gpu_gemm_stream.py)."""
+    assert exe.exe_op_gemm_plan(wl.DTYPE_F32, M, N, K)["route"] == 0
+    A, W, b = rnd((M, K), 1, 1.0, torch.float32), rnd((N, K), 2, 0.05, torch.float32), rnd((N,), 3, 0.5, torch.float32)
+    prim = oracle.Primitives("double")
+    ref, act, out_mode, out = prim.linear(A.numpy(), W.numpy(), None) + b.numpy(), -1, 2, torch.zeros((M, N), device=DEV)
+    if mode == "resid":
+        h = rnd((M, N), 4, 1.0, torch.float32)
+        ref, out_mode, out = ref + h.numpy(), 1, h.to(DEV)
+    elif mode == "gelu":
+        ref, act, out_mode = prim.act(ref, 1), 1, 0
+    exe.exe_op_gemm(wl.DTYPE_F32, M, N, K, A.to(DEV), W.to(DEV), b.to(DEV), act, 1.0, out_mode, out)
+    torch.cuda.synchronize()
+    err = np.max(np.abs(out.cpu().numpy() - ref), axis=1) / np.max(np.abs(ref))
+    assert float(err.max()) < 1e-5, (int(err.argmax()), float(err.max()))     # K <= 96 float additions: far below
