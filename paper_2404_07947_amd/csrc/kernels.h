@@ -81,6 +81,9 @@ struct NormArgs {
     const void* bias = nullptr;
 };
 hipError_t launch_norm(const NormArgs& a, hipStream_t s);
+// A norm and the product behind it in one launch of the streaming kernel (a.A is not read), where norm_gemm_fits says so.
+bool norm_gemm_fits(const NormArgs& n, const GemmArgs& a);
+hipError_t launch_norm_gemm(const NormArgs& n, const GemmArgs& a, hipStream_t s);
 // copies K and V rows of `src` (row stride ld, K at column k_off, V at v_off) into the cache:
 // token t belongs to batch entry tok_b[t] (t itself if nullptr) at position tok_pos[t];
 // K of (b, head, pos) lives at pool + base[b] + ((layer*2+0)*H + head)*cap[b]*dh + pos*dh, V at kv index 1.

@@ -519,6 +519,23 @@ static int run_norm(exe_model* m, const int32_t* row_index, int rows, const void
     return EXE_OK;
 }
 
+// out = epilogue(norm(h) . W^T): one launch for a few short rows, else the norm into `a` and the product
+static int run_norm_gemm(exe_model* m, const int32_t* row_index, int rows, const void* g, const void* b, float out_scale, void* a,
+                         int N, const void* W, const void* bias, int act, int out_mode, void* out)
+{
+    const exe_config_t& c = m->c;
+    NormArgs n{c.dtype, c.norm == EXE_NORM_RMSNORM, m->h, row_index, rows, c.d_model, g, b, c.norm_eps, out_scale, nullptr};
+    GemmArgs p{c.dtype, rows, N, c.d_model, nullptr, W, bias, act, 1.f, out_mode, out, nullptr, 0};
+    if (!m->pend.splits && norm_gemm_fits(n, p)) {
+        double e = esz_of(m);
+        LAUNCH(m, EXE_K_GEMM_SKINNY, ((double)rows + N) * c.d_model * e + (double)rows * N * (out_mode == OUT_T ? e : 4.0),
+               2.0 * rows * N * c.d_model, launch_norm_gemm(n, p, m->stream));
+        return EXE_OK;
+    }
+    int r = run_norm(m, row_index, rows, g, b, out_scale, a);
+    return r ? r : run_gemm(m, rows, N, c.d_model, a, W, bias, act, 1.f, out_mode, out);
+}
+
 // completes h where no norm follows (hidden states out)
 static int finish_resid(exe_model* m)
 {
@@ -533,8 +550,7 @@ static int finish_resid(exe_model* m)
 static int run_ffn(exe_model* m, int rows, const DecLayerW& L)
 {
     int r;
-    if ((r = run_norm(m, nullptr, rows, L.n2_g, L.n2_b, 1.f, m->a))) return r;
-    if ((r = run_gemm(m, rows, m->c.d_ff, m->c.d_model, m->a, L.w_1, L.b_1, m->c.act, 1.f, OUT_T, m->u))) return r;
+    if ((r = run_norm_gemm(m, nullptr, rows, L.n2_g, L.n2_b, 1.f, m->a, m->c.d_ff, L.w_1, L.b_1, m->c.act, OUT_T, m->u))) return r;
     return run_gemm(m, rows, m->c.d_model, m->c.d_ff, m->u, L.w_2, L.b_2, -1, 1.f, OUT_RESID, m->h);
 }
 
@@ -549,8 +565,7 @@ static int head_launches(exe_model* m, const int32_t* row_index_dev, int n, floa
     const exe_config_t& c = m->c;
     int r;
     float out_scale = c.arch == EXE_ARCH_ENC_DEC ? 1.f / sqrtf((float)c.d_model) : 1.f;
-    if ((r = run_norm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last))) return r;
-    if ((r = run_gemm(m, n, c.vocab, c.d_model, m->a_last, m->tok_emb, nullptr, -1, 1.f, OUT_F32, logits))) return r;
+    if ((r = run_norm_gemm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last, c.vocab, m->tok_emb, nullptr, -1, OUT_F32, logits))) return r;
     if (tokens) LAUNCH(m, EXE_K_OTHER, (double)n * c.vocab * 4.0, 0.0, launch_argmax(logits, n, c.vocab, m->h_next, m->stream));
     return EXE_OK;
 }
@@ -625,8 +640,7 @@ static int encode_layer(exe_model* m, const DecLayerW& L, int layer, int n, int 
     bool encdec = c.arch == EXE_ARCH_ENC_DEC;
     int r;
     if (parts & 1) {
-        if ((r = run_norm(m, nullptr, T, L.n1_g, L.n1_b, 1.f, m->a))) return r;
-        if ((r = run_gemm(m, T, 3 * m->inner, c.d_model, m->a, L.w_qkv, L.b_qkv, -1, 1.f, OUT_T, m->qkv))) return r;
+        if ((r = run_norm_gemm(m, nullptr, T, L.n1_g, L.n1_b, 1.f, m->a, 3 * m->inner, L.w_qkv, L.b_qkv, -1, OUT_T, m->qkv))) return r;
         if (!encdec && d.table)
             LAUNCH(m, EXE_K_OTHER, 4.0 * T * m->inner * esz_of(m), 0.0,
                    launch_kv_append_paged(c.dtype, m->qkv, 3 * m->inner, m->inner, 2 * m->inner, T, d.tok_b, d.tok_pos,
@@ -908,8 +922,7 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
     double e = esz_of(m);
     int r;
     if (parts & 1) {
-        if ((r = run_norm(m, nullptr, n, L.n1_g, L.n1_b, 1.f, m->a))) return r;
-        if ((r = run_gemm(m, n, 3 * m->inner, c.d_model, m->a, L.w_qkv, L.b_qkv, -1, 1.f, OUT_T, m->qkv))) return r;
+        if ((r = run_norm_gemm(m, nullptr, n, L.n1_g, L.n1_b, 1.f, m->a, 3 * m->inner, L.w_qkv, L.b_qkv, -1, OUT_T, m->qkv))) return r;
         if (!(parts & 2))      // the attention kernel appends the new key/value rows itself when it runs
             LAUNCH(m, EXE_K_OTHER, 4.0 * n * m->inner * e, 0.0,
                    launch_kv_append(c.dtype, m->qkv, 3 * m->inner, m->inner, 2 * m->inner, n, nullptr, d.pos, d.base, d.cap,
@@ -934,8 +947,7 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
         if ((r = run_gemm(m, n, c.d_model, m->inner, m->ctx, L.w_o, L.b_o, -1, 1.f, OUT_RESID, m->h))) return r;
     if (encdec) {
         if (parts & 1) {
-            if ((r = run_norm(m, nullptr, n, L.nx_g, nullptr, 1.f, m->a))) return r;
-            if ((r = run_gemm(m, n, m->inner, c.d_model, m->a, L.w_xq, nullptr, -1, 1.f, OUT_T, m->qkv))) return r;
+            if ((r = run_norm_gemm(m, nullptr, n, L.nx_g, nullptr, 1.f, m->a, m->inner, L.w_xq, nullptr, -1, OUT_T, m->qkv))) return r;
         }
         if (parts & 2) {
             AttnCacheArgs x{c.dtype, n, c.n_heads, c.head_dim, m->qkv, m->inner, m->pool.ptr, d.xbase, d.xcap, d.xlen, d.pos,
