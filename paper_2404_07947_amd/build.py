@@ -12,7 +12,9 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libexe.so")
 SOURCES = ["kernels_elementwise.hip", "kernels_gemm.hip", "kernels_gemm_large.hip", "kernels_gemm_stream.hip", "kernels_attn.hip", "runtime.hip", "probe.hip", "sched.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
+# Kernel arguments preloaded into scalar registers instead of fetched by each wave's first instructions: decode iterations of
+# small models run 1-3 % faster (0.3 us of a 4-6 us launch).
+FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
