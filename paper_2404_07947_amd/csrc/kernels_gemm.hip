@@ -573,6 +573,7 @@ static int split_rows(int dtype, int M, int N, int K, int mode)
     if (M <= 1024 || dtype != DT_BF16 || K < LARGE_MIN_K) return M;
     Plan all = make_plan(dtype, M, N, K, mode);
     if (all.route != 0) return M;
+    const bool model = mode & GEMM_FEW_ROWS;          // exe_op_gemm's launches are cut where they were (see plan_cost)
     int G = persistent_grid();
     int tn = (N + 255) / 256, tm = (M + 255) / 256, total = tm * tn;
     int rounds = total / G;
@@ -582,14 +583,16 @@ static int split_rows(int dtype, int M, int N, int K, int mode)
     // the weight columns in step; measured, a round of such a launch takes 3-6 % less (16 384 rows against 17 120 -
     // 17 352 at the OPT-13B shape: 1826 us + 127 us for the rest against 2049 us in one launch of 16 rounds).
     int best = M;
-    double best_cost = all.cost;
+    double best_cost = model ? all.cost : plan_cost(dtype, C256x256, 1, M, N, K, false, false);
     int cand[2] = {rounds * G / tn, tm / 64 * 64};
     for (int tm1 : cand) {
         if (tm1 < 1 || tm1 >= tm) continue;
         int M1 = tm1 * 256;
-        double first = plan_cost(dtype, C256x256, 1, M1, N, K, false, true);
+        double first = plan_cost(dtype, C256x256, 1, M1, N, K, false, model);
         if (tm1 % 64 == 0) first *= 0.95;
-        double parts = first + make_plan(dtype, M - M1, N, K, mode & ~GEMM_DEFER).cost;
+        double rest = model || M - M1 <= 1024 ? make_plan(dtype, M - M1, N, K, mode & ~GEMM_DEFER).cost
+                                              : plan_cost(dtype, C256x256, 1, M - M1, N, K, false, false);
+        double parts = first + rest;
         if (parts < best_cost) { best_cost = parts; best = M1; }
     }
     return best;
