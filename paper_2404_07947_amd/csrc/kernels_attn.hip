@@ -489,7 +489,43 @@ __device__ __forceinline__ float rows_sum(float x)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-//
+// One query row by one wave, keys 0 .. nk - 1 in order, 64 at a time: a lane takes a key for the scores, and features lane,
+// lane + 64 of the result.  seq: the sequence's first row of this head's queries; sc: the scale for exp2.
+template <typename T, int DH, bool BIAS>
+__device__ __forceinline__ void prefill_row(const T* seq, int64_t ld, int inner, int qr, int nk, float sc, const float* sbias, int radius,
+                                            int lane, T* out)
+{
+    const T *q = seq + qr * ld, *keys = seq + inner, *values = seq + 2 * inner;
+    float m = -INFINITY, l = 0.f, acc[DH / 64] = {};
+    for (int j0 = 0; j0 < nk; j0 += 64) {
+        int j = j0 + lane, cnt = nk - j0 < 64 ? nk - j0 : 64;
+        const T* k = keys + (j < nk ? j : nk - 1) * ld;
+        float s = 0.f;
+#pragma unroll 4
+        for (int e = 0; e < DH; ++e) s = fmaf(to_f32(q[e]), to_f32(k[e]), s);
+        s *= sc;
+        if (BIAS) {
+            int rel = j - qr;
+            s += sbias[(rel < -radius ? -radius : (rel > radius ? radius : rel)) + radius];
+        }
+        if (j >= nk) s = -INFINITY;
+        float mx = wave_max(fmaxf(m, s)), mref = mx == -INFINITY ? 0.f : mx;
+        float alpha = fast_exp2(m - mref), p = fast_exp2(s - mref);
+        l = l * alpha + wave_sum(p);
+#pragma unroll
+        for (int f = 0; f < DH / 64; ++f) acc[f] *= alpha;
+        for (int t = 0; t < cnt; ++t) {
+            float pt = __shfl(p, t, WAVE);
+            const T* v = values + (j0 + t) * ld + lane;
+#pragma unroll
+            for (int f = 0; f < DH / 64; ++f) acc[f] = fmaf(pt, to_f32(v[f * 64]), acc[f]);
+        }
+        m = mx;
+    }
+#pragma unroll
+    for (int f = 0; f < DH / 64; ++f) out[lane + f * 64] = from_f32<T>(acc[f] / l);
+}
+
 // Head size 64: half the bytes per tile, so the value tiles are double buffered too and one barrier per tile is enough.
 // Its probabilities enter the second product as the sum of two bf16 values (the rounded one and the rounded rest, 2^-17
 // relative): before this kernel the row kernel, with float probabilities, served that head size, and the second set of
@@ -795,8 +831,18 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
         int qpos = wq0 + qb * 16 + qi;
-        if (qpos < n) {
-            float inv = 1.f / l_run[qb];
+        float inv = 1.f / l_run[qb];
+        bool nan = false;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) nan |= o_acc[qb][dt][j] != o_acc[qb][dt][j];
+        // The second product takes every key of a tile: 0 times the infinite or NaN value of a key that the mask keeps from this
+        // query is NaN.  Such a row is not stored, but computed again from its own keys alone (rare, so not for speed).
+        unsigned long long lanes = __builtin_amdgcn_ballot_w64(nan && qpos < n);
+        unsigned again = (unsigned)(lanes | lanes >> 32);
+        again = (again | again >> 16) & 0xffff;                   // bit qi: query row wq0 + 16 * qb + qi
+        if (qpos < n && !(again >> qi & 1)) {
             T* op = out + (int64_t)(t0 + qpos) * inner + h * DH + 4 * g;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
@@ -806,10 +852,13 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
                 *(typename Vec4<T>::type*)(op + dt * 16) = w;
             }
         }
+        for (; again; again &= again - 1) {
+            int qr = wq0 + qb * 16 + __builtin_ctz(again);
+            prefill_row<T, DH, BIAS>(seq, ld, inner, qr, CAUSAL ? qr + 1 : n, sc, sbias, radius, lane,
+                                     out + (int64_t)(t0 + qr) * inner + h * DH);
+        }
     }
 }
-
-
 
 void prefill_tile_order(const int32_t* lens, int n_seqs, std::vector<int32_t>& tiles)
 {

@@ -1,0 +1,76 @@
+"""Prefill attention on inputs that separate the MFMA kernel from plain arithmetic: what a row may not depend on, and what its
+probabilities have to keep."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2404_07947_amd as exe
+import workload as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+F32, BF16 = wl.DTYPE_F32, wl.DTYPE_BF16
+TYPES = [(BF16, 64), (BF16, 128), (F32, 64), (F32, 128)]
+
+
+def td(dtype):
+    return torch.float32 if dtype == F32 else torch.bfloat16
+
+
+def run(dtype, dh, H, lens, qkv, scale, causal, tab=None, R=0, generic=0):
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = torch.zeros((int(cu[-1]), H * dh), dtype=td(dtype), device=DEV)
+    exe.exe_op_prefill_attention(dtype, cu, qkv.to(DEV), H, dh, scale, causal, None if tab is None else tab.to(DEV), R, out,
+                                 force_generic=generic)
+    torch.cuda.synchronize()
+    return out.float().cpu().numpy()
+
+
+def reference(dh, H, lens, qkv, scale, causal, tab=None, R=0):
+    """Row by row in 64 bits, from the keys and values that a row attends to and no others."""
+    x, inner, t0, rows = qkv.double().numpy(), H * dh, 0, []
+    for L in lens:
+        s = x[t0:t0 + L]
+        for i in range(L):
+            n, row = (i + 1 if causal else L), []
+            for h in range(H):
+                q, k, v = (s[:, j * inner + h * dh:j * inner + (h + 1) * dh] for j in range(3))
+                sc = (k[:n] @ q[i]) * float(np.float32(scale))
+                if tab is not None:
+                    sc = sc + tab.double().numpy()[h][np.clip(np.arange(n) - i, -R, R) + R]
+                p = np.exp(sc - sc.max())
+                with np.errstate(invalid="ignore"):
+                    row.append((p / p.sum()) @ v[:n])
+            rows.append(np.concatenate(row))
+        t0 += L
+    return np.stack(rows)
+
+
+def tolerance(dtype):
+    return 1e-5 if dtype == F32 else 2.0 ** -7          # as in test_gpu_prefill_types.py; bf16 x 128 rounds the probabilities too
+
+
+@pytest.mark.parametrize("dtype,dh", TYPES)
+@pytest.mark.parametrize("use_bias", [0, 1])
+def test_causal_rows_do_not_see_later_values(dtype, dh, use_bias):
+    """Infinite and NaN value rows late in a sequence (and in its neighbour): every earlier row stays finite and right, the
+    rows from there on have them in the features that hold them and nowhere else."""
+    H, lens, R = 2, [200, 70], 40
+    g = torch.Generator().manual_seed(dh)
+    qkv = torch.randn((270, 3 * H * dh), generator=g).to(td(dtype))
+    tab = torch.randn((H, 2 * R + 1), generator=g) * 0.5 if use_bias else None
+    ref = reference(dh, H, lens, qkv, 0.1, 1, tab, R)
+    bad = qkv.clone()
+    bad[130, 2 * H * dh:] = float("inf")                # all features: row 130 is in the key tile of rows 128 .. 191
+    bad[199, 2 * H * dh + 3] = float("nan")             # the last row of the sequence
+    bad[200 + 33, 2 * H * dh + dh + 5] = float("-inf")  # one feature of head 1
+    got = run(dtype, dh, H, lens, bad, 0.1, 1, tab, R)
+    clean = np.ones(270, bool)
+    clean[130:200] = clean[233:] = False
+    err = np.abs(got[clean] - ref[clean]).max(axis=1) / np.abs(ref[clean]).max(axis=1)
+    assert err.max() < tolerance(dtype), (int(err.argmax()), float(err.max()))
+    assert np.all(np.isposinf(got[131:199])), "rows 131 .. 198 see the infinite row"
+    other = np.ones(H * dh, bool)
+    other[dh + 5] = False
+    err = np.abs(got[233:, other] - ref[233:, other]).max(axis=1) / np.abs(ref[233:]).max(axis=1)
+    assert err.max() < tolerance(dtype) and np.all(np.isneginf(got[234:, dh + 5]))
