@@ -589,6 +589,14 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) qf[qb][ds] = qp[ds * 4];
     }
+    // the softmax below takes the maximum of the raw scores, which wants a positive scale: the sign of a negative one goes to
+    // the queries
+    if (scale < 0.f) {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) qf[qb][ds] ^= sizeof(T) == 4 ? 0x80000000u : 0x80008000u;
+    }
     int kend = n;
     if (CAUSAL) kend = q0 + PF_QT < n ? q0 + PF_QT : n;
     int n_tiles = (kend + PF_KT - 1) / PF_KT;
@@ -626,7 +634,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) o_acc[qb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-    float sc = scale * LOG2E;
+    float sc = fabsf(scale) * LOG2E;
     f32x4 s_acc[2][4];
 
     // a wave whose queries all lie before a tile's first key (causal) or past the sequence end has nothing to
@@ -698,7 +706,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
                         mx = fmaxf(mx, v);
                     }
             } else {
-                // the scale is positive: take the maximum of the raw scores and fold the scale into the exponent
+                // sc is not negative: take the maximum of the raw scores and fold the scale into the exponent
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -854,7 +862,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         }
         for (; again; again &= again - 1) {
             int qr = wq0 + qb * 16 + __builtin_ctz(again);
-            prefill_row<T, DH, BIAS>(seq, ld, inner, qr, CAUSAL ? qr + 1 : n, sc, sbias, radius, lane,
+            prefill_row<T, DH, BIAS>(seq, ld, inner, qr, CAUSAL ? qr + 1 : n, scale * LOG2E, sbias, radius, lane,
                                      out + (int64_t)(t0 + qr) * inner + h * DH);
         }
     }

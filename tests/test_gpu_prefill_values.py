@@ -74,3 +74,18 @@ def test_causal_rows_do_not_see_later_values(dtype, dh, use_bias):
     other[dh + 5] = False
     err = np.abs(got[233:, other] - ref[233:, other]).max(axis=1) / np.abs(ref[233:]).max(axis=1)
     assert err.max() < tolerance(dtype) and np.all(np.isneginf(got[234:, dh + 5]))
+
+
+@pytest.mark.parametrize("dtype,dh", TYPES)
+@pytest.mark.parametrize("scale", [-3.0, 0.0])
+@pytest.mark.parametrize("causal,use_bias", [(1, 0), (0, 1)])
+def test_scales_that_are_not_positive(dtype, dh, scale, causal, use_bias):
+    H, lens, R = 2, [200, 17], 40
+    g = torch.Generator().manual_seed(7 + dh)
+    qkv = torch.randn((217, 3 * H * dh), generator=g).to(td(dtype))
+    tab = torch.randn((H, 2 * R + 1), generator=g) * 0.5 if use_bias else None
+    ref = reference(dh, H, lens, qkv, scale, causal, tab, R)
+    got = run(dtype, dh, H, lens, qkv, scale, causal, tab, R)
+    err = np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)
+    # a score is 3 times a float sum of dh products of up to about 10, |.| 150 at most in all: 3 * 150 * 2^-24 relative in p
+    assert err.max() < (5e-5 if dtype == F32 else 2.0 ** -7), (int(err.argmax()), float(err.max()))
