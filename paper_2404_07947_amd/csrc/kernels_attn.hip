@@ -768,15 +768,31 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         const unsigned char* sV = tV + v_row * RB + (v_q & 1) * 8;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 pf[2], pr[2];                     // probabilities, and (head size 64) what their rounding left over
+            // p, or (SPLIT_P) its first, second and third 8 bits: p = pf[0] + pf[1] + pf[2]
+            constexpr int NP = SPLIT_P ? 3 : 1;
+            bf16x8 pf[NP][2];
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+            for (int qb = 0; qb < 2; ++qb) {
+                if constexpr (!SPLIT_P) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float p = s_acc[qb][2 * ks + (e >> 2)][e & 3];
-                    pf[qb][e] = (bf16_t)p;
-                    if (SPLIT_P) pr[qb][e] = (bf16_t)(p - (float)pf[qb][e]);
+                    for (int e = 0; e < 8; ++e) pf[0][qb][e] = (bf16_t)s_acc[qb][2 * ks + (e >> 2)][e & 3];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NP; ++i) {
+                        u32x4 w;
+#pragma unroll
+                        for (int e = 0; e < 8; e += 2) {
+                            f32x4& sv = s_acc[qb][2 * ks + (e >> 2)];
+                            float a = sv[e & 3], b = sv[(e & 3) + 1];
+                            unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+                            w[e >> 1] = __builtin_amdgcn_perm(ub, ua, 0x07060302);          // their upper halves
+                            sv[e & 3] = a - __uint_as_float(ua & 0xffff0000u);
+                            sv[(e & 3) + 1] = b - __uint_as_float(ub & 0xffff0000u);
+                        }
+                        pf[i][qb] = __builtin_bit_cast(bf16x8, w);
+                    }
                 }
+            }
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
                 int slot = ((2 * dt + (v_q >> 1)) ^ pf_swz<RB>(v_row)) << 4;
@@ -784,11 +800,10 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
                 uint2 hi = pf_read_tr(sV + (ks * 32 + 16) * RB + slot);
                 uint4 both = {lo.x, lo.y, hi.x, hi.y};
                 bf16x8 fv = __builtin_bit_cast(bf16x8, both);
-                o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[0], o_acc[0][dt], 0, 0, 0);
-                o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[1], o_acc[1][dt], 0, 0, 0);
-                if (SPLIT_P) {
-                    o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pr[0], o_acc[0][dt], 0, 0, 0);
-                    o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pr[1], o_acc[1][dt], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < NP; ++i) {
+                    o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[i][0], o_acc[0][dt], 0, 0, 0);
+                    o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[i][1], o_acc[1][dt], 0, 0, 0);
                 }
             }
         }

@@ -89,3 +89,34 @@ def test_scales_that_are_not_positive(dtype, dh, scale, causal, use_bias):
     err = np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)
     # a score is 3 times a float sum of dh products of up to about 10, |.| 150 at most in all: 3 * 150 * 2^-24 relative in p
     assert err.max() < (5e-5 if dtype == F32 else 2.0 ** -7), (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("dtype,dh", [(BF16, 64), (F32, 64), (F32, 128)])
+def test_probabilities_keep_24_bits(dtype, dh):
+    """Two keys whose values nearly cancel: a feature's result is p0 * a - p1 * b with |result| down to 2^-16 of its terms, so
+    a probability rounded to fewer bits shows however the result itself is stored."""
+    n = 400                                              # sequences of two rows; the second row of each is compared
+    g = torch.Generator().manual_seed(3)
+    qkv = torch.zeros((2 * n, 3 * dh))
+    qkv[:, :2 * dh] = (torch.randn((2 * n, 2 * dh), generator=g) * 0.3).to(torch.bfloat16).float()
+    x = qkv.double().numpy().reshape(n, 2, 3 * dh)
+    s = np.einsum("nd,nkd->nk", x[:, 1, :dh], x[:, :, dh:2 * dh]) * 0.125
+    ratio = np.exp(s[:, 0] - s[:, 1])                    # p0 / p1
+    a = np.arange(128, 256) / 128.0                      # every bf16 value in [1, 2), and in [0.25, 4) for b
+    b = np.concatenate([a / 4, a / 2, a, a * 2])
+    V = np.zeros((n, 2, dh))
+    for i in range(n):
+        off = np.abs(ratio[i] * a[:, None] - b[None, :])
+        best = np.argsort(off, axis=None)[:dh]
+        V[i, 0], V[i, 1] = a[best // len(b)], -b[best % len(b)]
+    qkv = qkv.view(n, 2, 3 * dh)
+    qkv[:, :, 2 * dh:] = torch.from_numpy(V).float()
+    qkv = qkv.reshape(2 * n, 3 * dh).to(td(dtype))
+    lens = [2] * n
+    got, ref = run(dtype, dh, 1, lens, qkv, 0.125, 1)[1::2], reference(dh, 1, lens, qkv, 0.125, 1)[1::2]
+    p1 = 1.0 / (1.0 + ratio)
+    terms = (p1 * ratio)[:, None] * V[:, 0] - p1[:, None] * V[:, 1]                  # |p0 a| + |p1 b|
+    assert np.mean(np.abs(ref) / terms < 2.0 ** -11) > 0.25          # where the rounding of a bf16 result hides no 2^-18
+    # a float exponential and float sums are good to a few 2^-24 of the terms (2^-21 taken); 16-bit probabilities to 2^-18
+    bound = 2.0 ** -21 * terms + (0 if dtype == F32 else 2.0 ** -8) * np.abs(ref)
+    assert np.all(np.abs(got - ref) < bound), float(np.max(np.abs(got - ref) / terms))
