@@ -527,14 +527,15 @@ __device__ __forceinline__ void prefill_row(const T* seq, int64_t ld, int inner,
 }
 
 // Head size 64: half the bytes per tile, so the value tiles are double buffered too and one barrier per tile is enough.
-// Its probabilities enter the second product as the sum of two bf16 values (the rounded one and the rounded rest, 2^-17
-// relative): before this kernel the row kernel, with float probabilities, served that head size, and the second set of
-// MFMAs hides behind the exponentials.
+// Its probabilities enter the second product as the sum of three bf16 values, their first, second and third 8 bits, so no bit
+// of the float is lost: the row kernel, which served this head size before, multiplies floats too.  The two further sets of
+// MFMAs hide behind the exponentials for the most part (one set more and a rounded rest, 2^-17 relative: 40 us where three
+// take 43).
 //
 // Float: the same tiles and softmax with 16x16x4 MFMAs, four per 16-byte fragment; the second product takes one key per lane
 // group and MFMA, so P again goes from accumulator to operand without moving, and V is read 4 bytes per lane.
 //
-// Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 39;
+// Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 43;
 // float x 64, 32 sequences of 384, 4 heads, 192 -> 75.
 template <typename T, int DH, bool CAUSAL, bool BIAS>
 __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefill_mfma_kernel(const T* __restrict__ qkv,
@@ -855,14 +856,14 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     for (int qb = 0; qb < 2; ++qb) {
         int qpos = wq0 + qb * 16 + qi;
         float inv = 1.f / l_run[qb];
-        bool nan = false;
+        float most = o_acc[qb][0][0];                              // NaN if one of them is
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) nan |= o_acc[qb][dt][j] != o_acc[qb][dt][j];
+            for (int j = 0; j < 4; ++j) most = __builtin_elementwise_maximum(most, o_acc[qb][dt][j]);
         // The second product takes every key of a tile: 0 times the infinite or NaN value of a key that the mask keeps from this
         // query is NaN.  Such a row is not stored, but computed again from its own keys alone (rare, so not for speed).
-        unsigned long long lanes = __builtin_amdgcn_ballot_w64(nan && qpos < n);
+        unsigned long long lanes = __builtin_amdgcn_ballot_w64(most != most && qpos < n);
         unsigned again = (unsigned)(lanes | lanes >> 32);
         again = (again | again >> 16) & 0xffff;                   // bit qi: query row wq0 + 16 * qb + qi
         if (qpos < n && !(again >> qi & 1)) {
