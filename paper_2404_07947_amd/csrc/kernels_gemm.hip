@@ -481,6 +481,19 @@ constexpr double STREAM_MARGIN = 0.92;
 constexpr int64_t MANY_ROWS_PARTIALS = 128 << 20;
 constexpr int OP_RATE_ROWS = 192;
 
+struct PlanKey {
+    int M, N, K, flags;
+    bool operator==(const PlanKey& o) const { return M == o.M && N == o.N && K == o.K && flags == o.flags; }
+};
+struct PlanKeyHash {
+    size_t operator()(const PlanKey& k) const
+    {
+        uint64_t h = (((uint64_t)k.M << 32) ^ (uint64_t)k.N) * 0x9e3779b97f4a7c15ull ^ (((uint64_t)k.K << 3) + k.flags);
+        h *= 0x9e3779b97f4a7c15ull;
+        return (size_t)(h ^ h >> 32);
+    }
+};
+
 // mode: what the caller allows (GemmMode)
 static Plan make_plan(int dtype, int M, int N, int K, int mode)
 {
@@ -490,8 +503,8 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
     p.cfg = dtype == DT_F32 ? C64x128 : C256x256;
     // the model's choice per shape is remembered (a decode iteration asks for the same few shapes 4 times per layer)
     struct Choice { int cfg, splits; double cost; StreamPlan stream; };
-    thread_local std::unordered_map<uint64_t, Choice> memo;
-    uint64_t key = ((uint64_t)M << 46) ^ ((uint64_t)N << 24) ^ ((uint64_t)K << 3) ^ (dtype == DT_F32 ? 4 : 0) ^ (uint64_t)mode;
+    thread_local std::unordered_map<PlanKey, Choice, PlanKeyHash> memo;
+    const PlanKey key{M, N, K, mode | (dtype == DT_F32 ? 4 : 0)};
     auto hit = memo.find(key);
     if (hit != memo.end()) {
         p.cfg = hit->second.cfg;
