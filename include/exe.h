@@ -292,7 +292,7 @@ uint64_t exe_op_gemm_noalloc_max_workspace(void);
  * nt x 16 output features (nt in {1, 2, 4, 5}) of ma x 8 rows (ma in {1, 2, 4, 6, 8}); nt = 0 lets the library choose nt, ma
  * and splits.  splits > 1 (bf16 only): K split over workgroups as well, partial sums in the workspace
  * (splits x M x N floats), added by a second kernel.  K a multiple of 64 (bf16) or 32 (float), N of 4, operands 16-byte
- * aligned, else EXE_ERR_SHAPE / EXE_ERR_ARG. */
+ * aligned, the rows of a workgroup less than 4 GB in all, else EXE_ERR_SHAPE / EXE_ERR_ARG. */
 int exe_op_gemm_stream(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
                        const void* bias, int32_t act, float alpha, int32_t out_mode, void* out, int32_t nt, int32_t ma,
                        int32_t splits, void* workspace, uint64_t workspace_bytes);

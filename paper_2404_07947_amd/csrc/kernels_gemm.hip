@@ -499,6 +499,8 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
 {
     Plan p{2, 0, 1, K, 0, 0, 0.0, StreamPlan{}};
     if (N % 4 != 0 || K % k_tile(dtype) != 0 || M < 1) return p;
+    // the MFMA kernels address the rows of a tile by 32-bit byte offsets, in float up to 128 rows
+    if (dtype == DT_F32 && (int64_t)K * 128 * (int)sizeof(float) >= ((int64_t)1 << 32)) return p;
     p.route = 0;
     p.cfg = dtype == DT_F32 ? C64x128 : C256x256;
     // the model's choice per shape is remembered (a decode iteration asks for the same few shapes 4 times per layer)

@@ -300,6 +300,7 @@ StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, i
 {
     int ue = dtype == DT_F32 ? 32 : 64, units = K / ue, per = splits < 1 ? 0 : (units + splits - 1) / splits;
     if (M < 1 || N % 4 != 0 || K % ue != 0 || splits < 1) return StreamPlan{};
+    if ((int64_t)K * (dtype == DT_F32 ? 4 : 2) * (nt * 16 > ma * 8 ? nt * 16 : ma * 8) >= ((int64_t)1 << 32)) return StreamPlan{};    // row offsets are 32 bits
     if (splits > 1 && (dtype == DT_F32 || per < 16 || per * (splits - 1) >= units)) return StreamPlan{};
     return StreamPlan{nt, ma, splits, per, stream_cost(dtype, nt, ma, splits, M, N, K, defer)};
 }

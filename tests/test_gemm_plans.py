@@ -28,3 +28,17 @@ def test_a_plan_does_not_depend_on_the_shapes_planned_before(dtype, first, secon
         return exe.exe_op_gemm_plan(dtype, *shape), exe.exe_op_gemm_workspace(dtype, *shape)
     for a, b in ((first, second), (second, first)):
         assert in_a_new_thread(lambda: (ask(a), ask(b))[1]) == in_a_new_thread(lambda: ask(b))
+
+
+@pytest.mark.parametrize("M", [1, 7, 128, 1000, 5000])
+@pytest.mark.parametrize("N", [4, 128, 1024])
+def test_float_rows_beyond_32_bit_offsets_take_the_kernel_with_64_bit_ones(M, N):
+    """The MFMA kernels address a tile's rows by 32-bit byte offsets: 128 rows of 2^23 floats are 4 GB."""
+    assert exe.exe_op_gemm_plan(F32, M, N, (1 << 23) - 32)["route"] != 2
+    for K in (1 << 23, (1 << 23) + 32, 1 << 26):
+        assert exe.exe_op_gemm_plan(F32, M, N, K)["route"] == 2
+
+
+@pytest.mark.parametrize("dtype,K", [(F32, 1 << 24), (BF16, 1 << 25)])
+def test_the_streaming_gemm_refuses_80_such_rows(dtype, K):
+    assert exe.lib().exe_op_gemm_stream(None, dtype, 8, 128, K, 64, 64, None, -1, 1.0, 2, 64, 5, 1, 1, None, 0) == -2
