@@ -360,20 +360,20 @@ template <int V> __global__ __launch_bounds__(1024) void argmax_kernel(const flo
     const float* x = logits + (int64_t)blockIdx.x * n;
     float best = -INFINITY;
     int idx = 0x7fffffff;
-    constexpr int D = 4;
-    for (int i0 = threadIdx.x * V; i0 < n; i0 += 1024 * V * D) {
+    constexpr unsigned D = 4;
+    for (unsigned i0 = threadIdx.x * V; i0 < (unsigned)n; i0 += 1024 * V * D) {       // unsigned: i0 runs past n, which may be 2^31 - 1
         float v[D][V];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            int i = i0 + d * 1024 * V;
-            load_f32<float, V>(x + (i < n ? i : i0), v[d]);
+        for (unsigned d = 0; d < D; ++d) {
+            unsigned i = i0 + d * 1024 * V;
+            load_f32<float, V>(x + (i < (unsigned)n ? i : i0), v[d]);
         }
 #pragma unroll
-        for (int d = 0; d < D; ++d)
+        for (unsigned d = 0; d < D; ++d)
 #pragma unroll
             for (int e = 0; e < V; ++e) {
-                int i = i0 + d * 1024 * V + e;
-                if (i < n && (v[d][e] > best || (v[d][e] == best && i < idx))) { best = v[d][e]; idx = i; }
+                unsigned i = i0 + d * 1024 * V + e;
+                if (i < (unsigned)n && (v[d][e] > best || (v[d][e] == best && (int)i < idx))) { best = v[d][e]; idx = (int)i; }
             }
     }
     if (idx == 0x7fffffff) { best = -INFINITY; }
