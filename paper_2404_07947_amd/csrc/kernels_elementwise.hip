@@ -166,7 +166,7 @@ __device__ __forceinline__ void store4(bf16_t* p, f32x4 v)
     *(bf16x4*)p = w;
 }
 
-template <typename T, bool RMS, int NT, int Q>
+template <typename T, bool RMS, int NT, int Q, bool LATE>
 __global__ __launch_bounds__(NT) void norm_kernel(float* __restrict__ x, const int32_t* __restrict__ row_index, int d,
                                                   const float* __restrict__ partial, int splits, int64_t slice,
                                                   const T* __restrict__ bias, const T* __restrict__ gain,
@@ -183,8 +183,8 @@ __global__ __launch_bounds__(NT) void norm_kernel(float* __restrict__ x, const i
     for (int q = 0; q < Q; ++q) {
         int k = at(q);
         v[q] = k < d ? load4(xr + k) : zero;
-        g[q] = k < d ? load4(gain + k) : zero;
-        b[q] = !RMS && k < d ? load4(shift + k) : zero;
+        g[q] = !LATE && k < d ? load4(gain + k) : zero;
+        b[q] = !LATE && !RMS && k < d ? load4(shift + k) : zero;
     }
     if (partial) {
 #pragma unroll
@@ -229,16 +229,16 @@ __global__ __launch_bounds__(NT) void norm_kernel(float* __restrict__ x, const i
     for (int q = 0; q < Q; ++q) {
         int k = at(q);
         if (k >= d) continue;
-        f32x4 y;
+        f32x4 y, gq = LATE ? load4(gain + k) : g[q], bq = LATE && !RMS ? load4(shift + k) : b[q];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = ((v[q][j] - mean) * rstd * g[q][j] + b[q][j]) * out_scale;
+        for (int j = 0; j < 4; ++j) y[j] = ((v[q][j] - mean) * rstd * gq[j] + bq[j]) * out_scale;
         store4(o + k, y);
     }
 }
 
-template <typename T, bool RMS, int NT, int Q> static hipError_t norm_go(const NormArgs& a, hipStream_t s)
+template <typename T, bool RMS, int NT, int Q, bool LATE = false> static hipError_t norm_go(const NormArgs& a, hipStream_t s)
 {
-    norm_kernel<T, RMS, NT, Q><<<a.rows, NT, 0, s>>>(a.x, a.row_index, a.d, a.partial, a.splits, (int64_t)a.partial_rows * a.d,
+    norm_kernel<T, RMS, NT, Q, LATE><<<a.rows, NT, 0, s>>>(a.x, a.row_index, a.d, a.partial, a.splits, (int64_t)a.partial_rows * a.d,
                                                      (const T*)a.bias, (const T*)a.gain, (const T*)a.shift, a.eps, a.out_scale,
                                                      (T*)a.out);
     return hipGetLastError();
@@ -247,8 +247,13 @@ template <typename T, bool RMS, int NT, int Q> static hipError_t norm_go(const N
 // Launch shape.  Few rows: as many threads as keep a thread at one or two groups, for the latency of the chain.  From 2048
 // rows on the chip is full whatever the shape, and small workgroups with more per thread are the faster stream (12288 x 256:
 // 64 threads 6.2 us, 256 11.1; 8192 x 1024: 64 threads 9.8 us, 256 13.6; 16384 x 5120: 512 threads 90 us, 1024 123).
+// Rows of more than 5120: gain and shift are loaded behind the statistics (LATE).  Held from the start they cost 8 registers per
+// group, and with them the waves that hide the stream, or spills from 16384 on.  us per launch, kernel with the row in LDS /
+// loaded first / late: LayerNorm bf16 8192 x 12288 129 / 156 / 105, 8192 x 20480 351 / 461 / 181, float 2048 x 16388
+// 60 / 125 / 46, 16 x 16388 6.5 / 9.6 / 4.6; float RMSNorm, with one of the four arrays in play, is no faster late.
 template <typename T, bool RMS> static hipError_t norm_shape(const NormArgs& a, hipStream_t s)
 {
+    constexpr bool LATE = !RMS || sizeof(T) == 2;
     int q = a.d / 4;
     bool many = a.rows >= 2048;
     if (q <= 64) return norm_go<T, RMS, 64, 1>(a, s);
@@ -257,10 +262,12 @@ template <typename T, bool RMS> static hipError_t norm_shape(const NormArgs& a, 
     if (q <= 512) return norm_go<T, RMS, 256, 2>(a, s);
     if (q <= 1024) return many ? norm_go<T, RMS, 256, 4>(a, s) : norm_go<T, RMS, 512, 2>(a, s);
     if (q <= 1280) return many ? norm_go<T, RMS, 512, 3>(a, s) : norm_go<T, RMS, 640, 2>(a, s);
-    if (q <= 2048) return norm_go<T, RMS, 512, 4>(a, s);
-    if (q <= 3072) return norm_go<T, RMS, 768, 4>(a, s);
-    if (q <= 4096) return norm_go<T, RMS, 1024, 4>(a, s);
-    return norm_go<T, RMS, 1024, 9>(a, s);
+    if (q <= 2048) return norm_go<T, RMS, 512, 4, LATE>(a, s);
+    if (q <= 3072) return norm_go<T, RMS, 768, 4, LATE>(a, s);
+    if (q <= 4096) return norm_go<T, RMS, 1024, 4, LATE>(a, s);
+    if (q <= 5120) return norm_go<T, RMS, 1024, 5, LATE>(a, s);
+    if (q <= 7168) return norm_go<T, RMS, 1024, 7, LATE>(a, s);
+    return norm_go<T, RMS, 1024, 9, LATE>(a, s);
 }
 
 hipError_t launch_norm(const NormArgs& a, hipStream_t s)

@@ -28,7 +28,8 @@ def relerr(got, ref):
 
 # widths on both sides of every step of the launch rule, for few rows and for many (the rule changes at 2048 rows)
 @pytest.mark.parametrize("rows", [3, 2050])
-@pytest.mark.parametrize("d", [8, 256, 260, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 5120, 5124, 8192, 8196, 12288, 16384, 16392])
+@pytest.mark.parametrize("d", [8, 256, 260, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 5120, 5124, 8192, 8196, 12288, 12292, 16384, 16392, 20480, 20484,
+                               28672, 28676, 36864])
 def test_norm_launch_shapes(rows, d):
     dtype, rms = (BF16, 0) if d % 512 else (F32, 1)
     td = torch.float32 if dtype == F32 else torch.bfloat16
@@ -44,7 +45,7 @@ def test_norm_launch_shapes(rows, d):
 
 @pytest.mark.parametrize("dtype,rms", [(BF16, 0), (BF16, 1), (F32, 0)])
 @pytest.mark.parametrize("splits", [1, 2, 3, 4, 7, 8, 16])
-@pytest.mark.parametrize("d", [64, 1024, 5120])
+@pytest.mark.parametrize("d", [64, 1024, 5120, 16388])
 def test_resid_norm(dtype, rms, splits, d):
     td = torch.float32 if dtype == F32 else torch.bfloat16
     rows_all, idx = 9, [8, 0, 3, 5]
