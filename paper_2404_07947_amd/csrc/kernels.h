@@ -128,6 +128,13 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s);
 // host-side replay of the paged kernel's row indexing (0 = every row read lies in its block and is read once)
 int paged_index_check(int dtype, int dh, int block_shift, int nwv, int len);
 
+constexpr int PREFILL_TILE_Q = 128, PREFILL_TILE_K = 64;
+struct PrefillWork {         // of one head over a batch
+    int max_len = 0;         // longest sequence
+    int64_t pairs = 0;       // (query row, key) pairs
+    int64_t key_tiles = 0;   // key tiles of all query tiles
+};
+PrefillWork prefill_work(const int32_t* lens, int n_seqs, bool causal);
 struct AttnPackedArgs {      // ragged prefill over packed qkv [T, 3*H*dh]
     int dtype, T, H, dh, n_seqs;
     const void* qkv;
@@ -140,10 +147,9 @@ struct AttnPackedArgs {      // ragged prefill over packed qkv [T, 3*H*dh]
     void* out;               // [T, H*dh]
     // tile list for the MFMA kernel: (seq, first query row) pairs in the order prefill_tile_order gives
     const int32_t* tiles; int n_tiles;
-    int force_generic;
-    int max_len = 0;         // longest sequence of the batch (0 = unknown: T is taken)
+    int force_generic;       // 0: the faster kernel for the batch's work; > 0 the row kernel, < 0 the MFMA kernel wherever it takes the call
+    PrefillWork work;
 };
-constexpr int PREFILL_TILE_Q = 128;
 // Appends the (seq, first query row) pairs of a batch's 128-row query tiles to `tiles`: sequences longest first, the
 // tiles of one sequence together, last rows (causal: most keys) first.  The tiles of a sequence read the same keys
 // and values, and the kernel's workgroup numbering puts neighbours of this list (for one head) on one XCD at about

@@ -5,8 +5,9 @@
 //    softmax whose partial results are merged across the workgroup at the end.
 //      PACKED = false: decode / cross attention -- keys and values come from a sequence's cache extent
 //                      ([head][capacity][dh] per layer, keys then values).  HBM-bandwidth bound.
-//      PACKED = true : ragged prefill straight from the packed qkv activations, for what the MFMA kernel below does
-//                      not take (bias tables beyond its LDS copy, sequences beyond 32-bit offsets).
+//      PACKED = true : ragged prefill straight from the packed qkv activations, for batches of little work (float, and
+//                      bf16 with head size 64) and for what the MFMA kernel below does not take (bias tables beyond its
+//                      LDS copy, sequences beyond 32-bit offsets).
 //  * prefill_mfma_kernel<T, DH, CAUSAL, BIAS>: flash-style ragged prefill.  A workgroup
 //    owns 128 query rows of one (sequence, head); keys/values go through LDS in tiles of 64.
 //    S^T = K.Q^T and O^T = V^T.P^T are both computed with MFMA 16x16 tiles so that softmax statistics of a
@@ -438,7 +439,7 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
 // so a query's softmax statistics live in the four lanes that share its column, and the probabilities never leave
 // registers.  Two barriers per tile (the value tile is loaded behind the scores).  The workgroups of a CU drift
 // apart, so one wave's softmax (vector ALU) overlaps another's MFMAs on the same SIMD.
-constexpr int PF_NW = 4, PF_KT = 64, PF_THREADS = PF_NW * 64, PF_QT = PF_NW * 32;
+constexpr int PF_NW = 4, PF_KT = PREFILL_TILE_K, PF_THREADS = PF_NW * 64, PF_QT = PF_NW * 32;
 static_assert(PF_QT == PREFILL_TILE_Q, "the tile list is built for PREFILL_TILE_Q query rows per workgroup");
 constexpr int pf_tile_bytes(int row_bytes) { return PF_KT * row_bytes; }
 template <typename T, int DH> constexpr int pf_v_tiles() { return sizeof(T) == 2 && DH == 128 ? 1 : 2; }
@@ -884,6 +885,21 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     }
 }
 
+PrefillWork prefill_work(const int32_t* lens, int n_seqs, bool causal)
+{
+    PrefillWork w;
+    for (int i = 0; i < n_seqs; ++i) {
+        int64_t n = lens[i];
+        if (n > w.max_len) w.max_len = (int)n;
+        w.pairs += causal ? n * (n + 1) / 2 : n * n;
+        for (int64_t q0 = 0; q0 < n; q0 += PREFILL_TILE_Q) {
+            int64_t keys = causal && q0 + PREFILL_TILE_Q < n ? q0 + PREFILL_TILE_Q : n;
+            w.key_tiles += (keys + PREFILL_TILE_K - 1) / PREFILL_TILE_K;
+        }
+    }
+    return w;
+}
+
 void prefill_tile_order(const int32_t* lens, int n_seqs, std::vector<int32_t>& tiles)
 {
     std::vector<int> order(n_seqs);
@@ -915,24 +931,42 @@ template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedA
     return a.bias_by_dist ? launch_prefill<T, DH, false, true>(a, s) : launch_prefill<T, DH, false, false>(a, s);
 }
 
+// Which kernel a batch runs on.  The MFMA kernel works in tiles of 128 query rows x 64 keys, whole ones: a batch of short
+// sequences, or one that leaves most of the chip idle while its longest sequence's key tiles pass in turn, is served sooner by
+// the row kernel's many small workgroups.  us of either, fitted to 168 batches per type on one MI355X (1 to 64 sequences of 2
+// to 1000 tokens, ragged and not, 4 to 40 heads; within 6-11 % at the median, a quarter to a half at worst): the faster of the
+// two by these takes at most 1.01, 1.15 and 1.11 times the faster one measured; the MFMA kernel alone took up to 7.2, 22 and
+// 1.8 times (float x 64, float x 128, bf16 x 64; e.g. 64 sequences of one token, 16 heads, float x 128: 61 us, rows 4).
+// bf16 x 128 stays on the MFMA kernel, whose tiles were made for it.
+static bool prefill_mfma_pays(const AttnPackedArgs& a)
+{
+    if (a.dtype == DT_BF16 && a.dh == 128) return true;
+    struct Cost { double row_fixed, row, pair, mfma_fixed, chain, tile; };
+    static constexpr Cost F64{3.1, 0.61e-3, 16.5e-6, 3.3, 4.3, 3.7}, F128{3.3, 0.58e-3, 34.5e-6, 5.1, 8.9, 10.2}, B64{3.4, 1.06e-3, 9.6e-6, 3.2, 1.55, 1.0};
+    const Cost& c = a.dtype == DT_BF16 ? B64 : a.dh == 64 ? F64 : F128;
+    double row = c.row_fixed + a.H * (c.row * a.T + c.pair * a.work.pairs);
+    double mfma = c.mfma_fixed + c.chain * ((a.work.max_len + PREFILL_TILE_K - 1) / PREFILL_TILE_K) + c.tile * a.H * a.work.key_tiles / 256;
+    return mfma < row;
+}
+
 hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
     if ((a.dtype != DT_F32 && a.dtype != DT_BF16) || (a.dh != 64 && a.dh != 128)) return hipErrorInvalidValue;
+    const bool mfma = a.force_generic <= 0 && a.n_tiles > 0 && (a.force_generic < 0 || prefill_mfma_pays(a));
     // The key loader addresses the rows of one sequence with 32-bit byte offsets, and a head's bias table must fit
     // the kernel's LDS copy; a batch outside these limits runs on the row kernel, which is correct but far slower,
     // so say so (once).
-    const bool mfma_shape = !a.force_generic && a.n_tiles > 0;
-    const int64_t longest = a.max_len > 0 ? a.max_len : a.T, row_bytes = (int64_t)3 * a.H * a.dh * (a.dtype == DT_F32 ? 4 : 2);
+    const int64_t longest = a.work.max_len, row_bytes = (int64_t)3 * a.H * a.dh * (a.dtype == DT_F32 ? 4 : 2);
     const bool mfma_fits = longest * row_bytes < ((int64_t)1 << 32) && (!a.bias_by_dist || 2 * a.bias_radius + 1 <= 1024);
-    if (mfma_shape && !mfma_fits) {
+    if (mfma && !mfma_fits) {
         static std::once_flag warned;
         std::call_once(warned, [&]() {
             fprintf(stderr, "exe: prefill attention falls back to the row kernel (longest sequence %lld rows of %lld bytes, bias "
                             "radius %d): expect it to be much slower\n", (long long)longest, (long long)row_bytes, a.bias_radius);
         });
     }
-    if (mfma_shape && mfma_fits) {
+    if (mfma && mfma_fits) {
         if ((int64_t)a.n_tiles * a.H > 0x7fffffff) return hipErrorInvalidValue;
         if (a.dtype == DT_F32) return a.dh == 64 ? launch_prefill<float, 64>(a, s) : launch_prefill<float, 128>(a, s);
         return a.dh == 64 ? launch_prefill<bf16_t, 64>(a, s) : launch_prefill<bf16_t, 128>(a, s);

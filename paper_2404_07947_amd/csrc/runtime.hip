@@ -628,7 +628,7 @@ struct EncodeDesc {
     int n_tiles;
     int32_t* table = nullptr;   // paged pool: block table [n][table_w]
     int table_w = 0;
-    int max_len = 0;            // longest sequence of the batch
+    PrefillWork work;           // of the batch's attention
 };
 
 // One encode (prefill) layer over T packed tokens of n sequences.  parts: bit 0 = everything but the
@@ -654,7 +654,7 @@ static int encode_layer(exe_model* m, const DecLayerW& L, int layer, int n, int 
     if (parts & 2) {
         AttnPackedArgs a{c.dtype, T, c.n_heads, c.head_dim, n, m->qkv, d.tok_b, d.tok_pos, d.cu, encdec ? 0 : 1,
                          attn_scale(m), encdec ? m->bias_enc : nullptr, m->radius, m->ctx, d.tiles, d.n_tiles, 0};
-        a.max_len = d.max_len;
+        a.work = d.work;
         LAUNCH(m, EXE_K_PREFILL_ATTN, attn_bytes, attn_flops, launch_attn_packed(a, m->stream));
     }
     if (parts & 1) {
@@ -691,7 +691,8 @@ static void fill_encode_desc(exe_model* m, Stager& st, EncodeDesc& d, int n, con
 {
     bool encdec = m->c.arch == EXE_ARCH_ENC_DEC;
     int T = 0;
-    for (int L : lens) { T += L; d.max_len = std::max(d.max_len, L); }
+    for (int L : lens) T += L;
+    d.work = prefill_work(lens.data(), n, !encdec);
     int32_t* h_tok = st.take<int32_t>(T, &d.tok);
     int32_t* h_tb = st.take<int32_t>(T, &d.tok_b);
     int32_t* h_tp = st.take<int32_t>(T, &d.tok_pos);
@@ -1831,11 +1832,9 @@ extern "C" int exe_op_prefill_attention(void* hip_stream, int32_t dtype, int32_t
     int T = cu_seqlens[n_seqs];
     std::vector<int32_t> host, lens(n_seqs);
     host.resize((size_t)2 * T + n_seqs + 1);
-    int max_len = 0;
     for (int i = 0; i < n_seqs; ++i) {
         int L = cu_seqlens[i + 1] - cu_seqlens[i];
         if (L < 1) return fail(EXE_ERR_BAD_LENGTH, "empty sequence");
-        max_len = std::max(max_len, L);
         for (int p = 0; p < L; ++p) { host[cu_seqlens[i] + p] = i; host[T + cu_seqlens[i] + p] = p; }
         lens[i] = L;
     }
@@ -1849,7 +1848,7 @@ extern "C" int exe_op_prefill_attention(void* hip_stream, int32_t dtype, int32_t
     if (e == hipSuccess) {
         AttnPackedArgs a{dtype, T, H, dh, n_seqs, qkv, dev, dev + T, dev + 2 * T, causal, scale, bias_by_dist, bias_radius,
                          out, dev + 2 * T + n_seqs + 1, n_tiles, force_generic};
-        a.max_len = max_len;
+        a.work = prefill_work(lens.data(), n_seqs, causal);
         e = launch_attn_packed(a, s);
     }
     hipError_t e2 = hipStreamSynchronize(s);

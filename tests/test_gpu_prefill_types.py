@@ -16,7 +16,7 @@ F32, BF16 = wl.DTYPE_F32, wl.DTYPE_BF16
 
 @pytest.mark.parametrize("dtype,dh", [(BF16, 64), (F32, 64), (F32, 128)])
 @pytest.mark.parametrize("causal,use_bias", [(1, 0), (0, 1), (1, 1), (0, 0)])
-@pytest.mark.parametrize("generic", [0, 1])
+@pytest.mark.parametrize("generic", [-1, 0, 1])                  # the MFMA kernel, the faster for the batch, the row kernel
 @pytest.mark.parametrize("H", [3, 8])
 def test_every_row(dtype, dh, causal, use_bias, generic, H):
     td = torch.float32 if dtype == F32 else torch.bfloat16

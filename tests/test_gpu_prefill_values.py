@@ -17,7 +17,7 @@ def td(dtype):
     return torch.float32 if dtype == F32 else torch.bfloat16
 
 
-def run(dtype, dh, H, lens, qkv, scale, causal, tab=None, R=0, generic=0):
+def run(dtype, dh, H, lens, qkv, scale, causal, tab=None, R=0, generic=-1):            # -1: the MFMA kernel, whatever the size
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     out = torch.zeros((int(cu[-1]), H * dh), dtype=td(dtype), device=DEV)
     exe.exe_op_prefill_attention(dtype, cu, qkv.to(DEV), H, dh, scale, causal, None if tab is None else tab.to(DEV), R, out,
@@ -92,7 +92,8 @@ def test_scales_that_are_not_positive(dtype, dh, scale, causal, use_bias):
 
 
 @pytest.mark.parametrize("dtype,dh", [(BF16, 64), (F32, 64), (F32, 128)])
-def test_probabilities_keep_24_bits(dtype, dh):
+@pytest.mark.parametrize("generic", [-1, 1])
+def test_probabilities_keep_24_bits(dtype, dh, generic):
     """Two keys whose values nearly cancel: a feature's result is p0 * a - p1 * b with |result| down to 2^-16 of its terms, so
     a probability rounded to fewer bits shows however the result itself is stored."""
     n = 400                                              # sequences of two rows; the second row of each is compared
@@ -113,7 +114,7 @@ def test_probabilities_keep_24_bits(dtype, dh):
     qkv[:, :, 2 * dh:] = torch.from_numpy(V).float()
     qkv = qkv.reshape(2 * n, 3 * dh).to(td(dtype))
     lens = [2] * n
-    got, ref = run(dtype, dh, 1, lens, qkv, 0.125, 1)[1::2], reference(dh, 1, lens, qkv, 0.125, 1)[1::2]
+    got, ref = run(dtype, dh, 1, lens, qkv, 0.125, 1, generic=generic)[1::2], reference(dh, 1, lens, qkv, 0.125, 1)[1::2]
     p1 = 1.0 / (1.0 + ratio)
     terms = (p1 * ratio)[:, None] * V[:, 0] - p1[:, None] * V[:, 1]                  # |p0 a| + |p1 b|
     assert np.mean(np.abs(ref) / terms < 2.0 ** -11) > 0.25          # where the rounding of a bf16 result hides no 2^-18
