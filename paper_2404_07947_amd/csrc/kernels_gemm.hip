@@ -3,7 +3,8 @@
 //  * gemm_tile_kernel    MFMA 16x16x32 (bf16) or 16x16x4 (float).  Macro tiles (BM x 256 or BM x 128, 128 bytes of K
 //                        per LDS stage) filled by direct global->LDS loads into a ring of stages; software-pipelined
 //                        fragment fetch; optional split-K into float partials (bf16), finished by splitk_reduce_kernel.
-//  * gemm_large_kernel   (kernels_gemm_large.hip) bf16, tiles 256 features wide: encode, and decode batches of 100 rows and more.
+//  * gemm_large_kernel   (kernels_gemm_large.hip) bf16, tiles 256 features wide and 128 rows or more, K of 256 and more: encode,
+//                        and decode batches of 100 rows and more.
 //  * gemm_stream_kernel  (kernels_gemm_stream.hip) few rows: streams the weights, the waves of a workgroup split K.
 //  * gemm_generic_kernel float or bf16 inputs, plain FMA in float, any shape (depths and widths the others do not take).
 //
@@ -388,15 +389,15 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(int M, int N, int K, 
 }
 
 // ---------------------------------------------------------------- host-side routing
-// Tile configurations.  The first three have BN = 256 (the weight share of the LDS fill traffic is
-// BN / (BM + BN), which is what a weight-streaming decode GEMM wants large); the last three halve BN for
-// matrices with few output features, where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows run on
-// gemm_large_kernel, the others on gemm_tile_kernel.
+// Tile configurations.  Four have BN = 256 (the weight share of the LDS fill traffic is BN / (BM + BN), which is what a
+// weight-streaming decode GEMM wants large); 64x128, 128x128 and 256x128 halve BN for matrices with few output features,
+// where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows run on gemm_large_kernel if K allows, the
+// others on gemm_tile_kernel.  192x256 runs on gemm_large_kernel only.
 enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, C192x256, N_CFG };
 struct CfgInfo { int bm, bn; };
 static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}, {192, 256}};
 
-// gemm_large_kernel needs a few k-tiles per item (its loads run two ahead and its waits are counted in them)
+// the shallowest depth of gemm_large_kernel (its start and end take a few k-tiles' time)
 static bool is_large(int cfg) { return cfg == C256x256 || cfg == C128x256 || cfg == C192x256; }
 constexpr int LARGE_MIN_K = 256;
 
@@ -517,15 +518,19 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         // Beyond 1024 rows a launch has many tiles and only the large shapes are worth a look; split-K still pays where they
         // leave most of the chip idle (1500 x 1024, K 16384: 239 us in 24 tiles, 60 us in six parts), with partial sums
         // bounded, and for a model's launches only (others would have to bring a workspace that they need not have now).
-        const bool many = M > 1024 && dtype == DT_BF16, model = many || ((mode & GEMM_FEW_ROWS) && M > OP_RATE_ROWS);
+        // Shallow products (below what gemm_large_kernel takes) run on gemm_tile_kernel in every shape, those of many rows with
+        // 256 x 128 tiles where these make no more than a round, else with 256 x 256: 16384 x 512, K 128 9.5 us with the smaller
+        // and 10.9 with the larger, 8192 x 3072, K 64 16.9 and 15.8, 16384 x 3072, K 64 27.5 and 23.2.
+        const bool many = M > 1024 && dtype == DT_BF16, shallow = K < LARGE_MIN_K;
+        const bool model = !shallow && (many || ((mode & GEMM_FEW_ROWS) && M > OP_RATE_ROWS));
         const int max_splits = !many ? 16 : (mode & GEMM_FEW_ROWS) && M <= MAX_SPLIT_ROWS ? 8 : 1;
+        const int shallow_cfg = (int64_t)((M + 255) / 256) * ((N + 127) / 128) <= 256 ? C256x128 : C256x256;
         double best = 1e30;
         for (int cfg = 0; cfg < N_CFG; ++cfg) {
             if (CFG[cfg].bm >= 2 * M && CFG[cfg].bm > 64) continue;     // more than half the rows would be padding
             if (dtype == DT_F32 && cfg != C64x128) continue;
-            if (is_large(cfg) && K < LARGE_MIN_K) continue;
             if (cfg == C192x256 && !model) continue;
-            if (many && !is_large(cfg) && !(K < LARGE_MIN_K && cfg == C256x128)) continue;
+            if (many && (shallow ? cfg != shallow_cfg : !is_large(cfg))) continue;
             for (int s = 1; s <= max_splits; ++s) {
                 if (!split_ok(dtype, K, s)) continue;
                 if (many && s > 1 && (int64_t)s * M * N * 4 > MANY_ROWS_PARTIALS) break;
@@ -548,7 +553,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         return p;
     }
     const Knobs& kn = knobs();
-    if (kn.cfg >= 0 && kn.cfg < N_CFG && dtype == DT_BF16 && !(is_large(kn.cfg) && K < LARGE_MIN_K)) p.cfg = kn.cfg;
+    if (kn.cfg >= 0 && kn.cfg < N_CFG && dtype == DT_BF16 && !(kn.cfg == C192x256 && K < LARGE_MIN_K)) p.cfg = kn.cfg;
     if (kn.split > 0 && split_ok(dtype, K, kn.split)) p.splits = kn.split;
     p.spread = 1;     // never slower than issuing a k-tile's loads at once in that sweep, up to 15 % faster from M = 128 on
     if (kn.spread >= 0) p.spread = kn.spread != 0;
@@ -585,10 +590,10 @@ static int persistent_grid()
 // remaining rows (a few hundred) to a second, separately planned launch is cheaper by the cost model, else M.
 static int split_rows(int dtype, int M, int N, int K, int mode)
 {
-    if (M <= 1024 || dtype != DT_BF16 || K < LARGE_MIN_K) return M;
+    if (M <= 1024 || dtype != DT_BF16) return M;
     Plan all = make_plan(dtype, M, N, K, mode);
     if (all.route != 0) return M;
-    const bool model = mode & GEMM_FEW_ROWS;          // exe_op_gemm's launches are cut where they were (see plan_cost)
+    const bool model = (mode & GEMM_FEW_ROWS) && K >= LARGE_MIN_K;          // others are cut by the old rates (see plan_cost)
     int G = persistent_grid();
     int tn = (N + 255) / 256, tm = (M + 255) / 256, total = tm * tn;
     int rounds = total / G;
@@ -719,7 +724,9 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     } else {
         switch (p.cfg) {
             case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;
-            case C128x256: case C256x256: case C192x256: e = launch_gemm_large(a, CFG[p.cfg].bm, p.k_per_split, p.splits, persistent_grid(), s); break;
+            case C128x256: case C256x256: case C192x256:
+                if (a.K < LARGE_MIN_K) e = p.cfg == C128x256 ? launch_tile<bf16_t, 128, 256, 64, 64, 3>(a, p, s) : launch_tile<bf16_t, 256, 256, 128, 64, 2>(a, p, s);
+                else e = launch_gemm_large(a, CFG[p.cfg].bm, p.k_per_split, p.splits, persistent_grid(), s); break;
             case C64x128: e = launch_tile<bf16_t, 64, 128, 32, 64, 4>(a, p, s); break;
             case C128x128: e = launch_tile<bf16_t, 128, 128, 64, 64, 3>(a, p, s); break;
             default: e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);

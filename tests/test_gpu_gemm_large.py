@@ -18,7 +18,9 @@ TOL = {"f32": 1e-5, "resid": 1e-5, "none": 2.0 ** -8, "relu": 2.0 ** -8, "gelu":
 # tile height -> shapes: one row beyond a tile, one short of it, N % 8 == 4, more tiles than workgroups
 SHAPES = {1: [(1025, 516, 256), (1151, 1028, 320), (1100, 12296, 1024)], 6: [(1537, 5124, 256), (4000, 2052, 256)],
           2: [(1345, 8196, 256), (4099, 3076, 256), (3073, 5124, 320)]}
-CASES = [(cfg, *s) for cfg, shapes in SHAPES.items() for s in shapes]
+# K below what the large-tile kernel takes: the same tile shapes on the other tile kernel, and the narrower tile for one round
+SHALLOW = {1: [(300, 50276, 192)], 2: [(4099, 3076, 64), (8193, 6148, 192), (129, 50276, 128)], 5: [(1100, 516, 128)]}
+CASES = [(cfg, *s) for group in (SHAPES, SHALLOW) for cfg, shapes in group.items() for s in shapes]
 _ref = {}
 
 
