@@ -500,7 +500,11 @@ static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void
     double bytes = ((double)M * K + (double)N * K) * e +
                    (double)M * N * (out_mode == OUT_T ? e : (out_mode == OUT_RESID ? 8.0 : 4.0));
     int kind = M <= 256 ? EXE_K_GEMM_SKINNY : EXE_K_GEMM_TILE;   // weight streaming (HBM) vs MFMA regime
+    size_t timed = m->timer.recs.size();
     LAUNCH(m, kind, bytes, 2.0 * M * N * K, launch_gemm(g, m->stream));
+    // partial sums left for the next norm: they are what the launch writes, and the residual stream is not touched
+    if (out_mode == OUT_RESID && m->pend.splits && m->timer.recs.size() > timed)
+        m->timer.recs.back().bytes += (m->pend.splits * 4.0 - 8.0) * M * N;
     return EXE_OK;
 }
 
@@ -515,7 +519,9 @@ static int run_norm(exe_model* m, const int32_t* row_index, int rows, const void
         a.bias = m->pend.bias;
         m->pend.splits = 0;
     }
-    LAUNCH(m, EXE_K_NORM, (double)rows * m->c.d_model * (4.0 + esz_of(m)), 0.0, launch_norm(a, m->stream));
+    // reads the row, and with partial sums these as well, and writes the finished row back
+    double per = 4.0 + esz_of(m) + (a.partial ? 4.0 * (a.splits + 1) : 0.0);
+    LAUNCH(m, EXE_K_NORM, (double)rows * m->c.d_model * per, 0.0, launch_norm(a, m->stream));
     return EXE_OK;
 }
 
@@ -541,7 +547,7 @@ static int finish_resid(exe_model* m)
 {
     if (!m->pend.splits) return EXE_OK;
     GemmArgs g{m->c.dtype, m->pend.rows, m->c.d_model, 0, nullptr, nullptr, m->pend.bias, -1, 1.f, OUT_RESID, m->h, m->gemm_ws, m->gemm_ws_bytes};
-    LAUNCH(m, EXE_K_OTHER, 0.0, 0.0, launch_splitk_reduce(g, m->pend.splits, m->stream));
+    LAUNCH(m, EXE_K_OTHER, (double)g.M * g.N * 4.0 * (m->pend.splits + 2), 0.0, launch_splitk_reduce(g, m->pend.splits, m->stream));
     m->pend.splits = 0;
     return EXE_OK;
 }
