@@ -296,6 +296,14 @@ uint64_t exe_op_gemm_noalloc_max_workspace(void);
 int exe_op_gemm_stream(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
                        const void* bias, int32_t act, float alpha, int32_t out_mode, void* out, int32_t nt, int32_t ma,
                        int32_t splits, void* workspace, uint64_t workspace_bytes);
+/* A product as the model calls launch it: any kernel, split-K also beyond 1024 rows, and fewer parts than planned where the
+ * workspace (any size, NULL for none) holds no more.  pending nullable: with out_mode 1 and alpha 1, split-K partial sums are
+ * left in the workspace for exe_op_resid_norm and *pending is their number (0: out is complete).
+ * splits = 0: as the library plans it; splits >= 1 (bf16, K a multiple of 64, every part at least 256 deep): that many parts
+ * on the tile kernels, in tile configuration cfg (as exe_op_gemm_plan numbers them, -1 = the planned one), else EXE_ERR_SHAPE. */
+int exe_op_gemm_model(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
+                      const void* bias, int32_t act, float alpha, int32_t out_mode, void* out, int32_t cfg, int32_t splits,
+                      void* workspace, uint64_t workspace_bytes, int32_t* pending);
 /* How exe_op_gemm launches a shape (host function; lets a test assert that its cases cover every kernel
  * instantiation): *route 0 = MFMA tile kernel, 1 = streaming kernel (float), 2 = plain-FMA kernel; *cfg = tile configuration (0 64x256, 1 128x256,
  * 2 256x256, 3 64x128, 4 128x128, 5 256x128, 6 192x256 rows x features); *splits = split-K parts (> 1: float partials in the

@@ -27,7 +27,10 @@ struct GemmArgs {
     // OUT_RESID only: the caller's next kernel can add split-K partials to the residual stream itself.  launch_gemm then
     // leaves them in the workspace, *pending = their number (0: the result is complete), and plans with the cheaper split.
     int* pending = nullptr;
+    int force_cfg = -1, force_splits = 0;     // tile configuration and split-K parts in place of the planner's (gemm_force_ok)
 };
+// whether the tile kernels take bf16 shapes in a configuration (-1: any) and with a number of parts
+bool gemm_force_ok(int cfg, int splits, int M, int N, int K);
 enum GemmMode { GEMM_TILE_ONLY = 0, GEMM_FEW_ROWS = 1, GEMM_DEFER = 2 };       // flags, as the two members above
 constexpr int MAX_SPLIT_ROWS = 4096;      // no launch of more rows is split over K
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode);

@@ -562,6 +562,12 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
     return p;
 }
 
+bool gemm_force_ok(int cfg, int splits, int M, int N, int K)
+{
+    return cfg >= -1 && cfg < N_CFG && M >= 1 && N % 4 == 0 && K % k_tile(DT_BF16) == 0 && !(cfg == C192x256 && K < LARGE_MIN_K) &&
+           splits >= 1 && split_ok(DT_BF16, K, splits);
+}
+
 // Per-device launch state: the number of persistent workgroups of a tile GEMM (one per compute unit: every bf16
 // configuration takes more than half of a CU's LDS, so one workgroup is resident per CU; rounded down to a
 // multiple of 8 for the XCD mapping).
@@ -677,7 +683,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     if (a.pending) *a.pending = 0;
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     int mode = (a.few_rows ? GEMM_FEW_ROWS : 0) | (a.pending && a.out_mode == OUT_RESID && a.alpha == 1.f ? GEMM_DEFER : 0);
-    int M1 = split_rows(a.dtype, a.M, a.N, a.K, mode);
+    int M1 = a.force_splits ? a.M : split_rows(a.dtype, a.M, a.N, a.K, mode);
     if (M1 < a.M) {
         GemmArgs head = a, tail = a;
         head.pending = tail.pending = nullptr;
@@ -690,6 +696,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         return e != hipSuccess ? e : launch_gemm(tail, s);
     }
     Plan p = make_plan(a.dtype, a.M, a.N, a.K, mode);
+    if (a.force_splits) {
+        p.route = 0;
+        if (a.force_cfg >= 0) p.cfg = a.force_cfg;
+        p.splits = a.force_splits;
+        p.k_per_split = split_k_tiles(a.dtype, a.K, p.splits) * k_tile(a.dtype);
+        p.spread = 1;
+    }
     // the generic kernel is the only one that reads and writes float operands element by element
     if (a.dtype == DT_F32 && !(aligned16(a.A) && aligned16(a.W) && aligned16(a.out) && aligned16(a.bias))) p.route = 2;
     if (p.route == 2) {

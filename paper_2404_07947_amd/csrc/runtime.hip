@@ -1720,6 +1720,26 @@ extern "C" int exe_op_gemm_stream(void* hip_stream, int32_t dtype, int32_t M, in
     return EXE_OK;
 }
 
+extern "C" int exe_op_gemm_model(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
+                                 const void* bias, int32_t act, float alpha, int32_t out_mode, void* out, int32_t cfg,
+                                 int32_t splits, void* workspace, uint64_t workspace_bytes, int32_t* pending)
+{
+    if (M < 0 || N < 1 || K < 1 || !A || !W || !out) return fail(EXE_ERR_ARG, "bad gemm arguments");
+    if (dtype != DT_F32 && dtype != DT_BF16) return fail(EXE_ERR_ARG, "bad dtype");
+    if (out_mode < 0 || out_mode > 2) return fail(EXE_ERR_ARG, "bad out_mode");
+    if (K % 8 || N % 4) return fail(EXE_ERR_SHAPE, "K must be a multiple of 8 and N of 4");
+    if (splits < 0 || (splits == 0 && cfg != -1)) return fail(EXE_ERR_ARG, "a tile configuration needs a number of parts");
+    if (splits && (dtype != DT_BF16 || !gemm_force_ok(cfg, splits, M, N, K)))
+        return fail(EXE_ERR_SHAPE, "shape not served in configuration %d with %d parts", cfg, splits);
+    GemmArgs g{dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, (float*)workspace, workspace ? (size_t)workspace_bytes : 0};
+    g.few_rows = true;
+    g.pending = pending;
+    g.force_cfg = cfg;
+    g.force_splits = splits;
+    HIP_TRY(launch_gemm(g, (hipStream_t)hip_stream));
+    return EXE_OK;
+}
+
 // ---------------------------------------------------------------- GEMM without allocations
 // The split-K partial sums of exe_op_gemm_noalloc live in this array instead of a caller workspace.  Every GPU the
 // library runs on holds its own copy until the process ends.  In host code the array's name is only a stand-in for
