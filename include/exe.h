@@ -363,7 +363,7 @@ int exe_op_decode_attention_paged(void* hip_stream, int32_t dtype, int32_t B, co
                                   float scale, const float* bias_by_dist, int32_t bias_radius, int32_t new_kv_offset,
                                   void* out);
 /* Host-side replay of the row indexing of the paged decode-attention kernel for one sequence of `len` cached rows
- * (the same index functions the kernel calls, for the launch shape of n_waves = 4 or 16 waves): returns 0 when every
+ * (the same index functions the kernel calls, for the launch shape of n_waves = 4, 8 or 16 waves): returns 0 when every
  * row read is a cached row inside the block its table look-up names and every cached row is read exactly once, else
  * the number of violations (> 0), or a negative status for bad arguments. */
 int exe_op_paged_index_check(int32_t dtype, int32_t dh, int32_t block_size, int32_t n_waves, int32_t len);

@@ -1804,7 +1804,7 @@ extern "C" int exe_op_paged_index_check(int32_t dtype, int32_t dh, int32_t block
     int shift = 0;
     while ((1 << shift) < block_size) ++shift;
     if ((dtype != DT_F32 && dtype != DT_BF16) || (dh != 64 && dh != 128) || block_size < 8 || block_size > 4096 ||
-        (1 << shift) != block_size || (n_waves != 4 && n_waves != 16) || len < 1)
+        (1 << shift) != block_size || (n_waves != 4 && n_waves != 8 && n_waves != 16) || len < 1)
         return fail(EXE_ERR_ARG, "bad paged index check arguments");
     return paged_index_check(dtype, dh, shift, n_waves, len);
 }

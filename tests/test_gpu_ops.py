@@ -318,7 +318,7 @@ def test_paged_index_replay_on_the_host():
     and every cached row is read exactly once.  (bf16 with head size 64 reads 16 rows per step, two blocks of 8.)"""
     for dtype, dh in ((BF16, 64), (BF16, 128), (F32, 64), (F32, 128)):
         for block in (8, 16, 32, 64, 256, 4096):
-            for waves in (4, 16):
+            for waves in (4, 8, 16):
                 for L in list(range(1, 300)) + [1023, 1024, 1025, 2560, 4097]:
                     assert exe.exe_op_paged_index_check(dtype, dh, block, waves, L) == 0, (dtype, dh, block, waves, L)
 
