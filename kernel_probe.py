@@ -9,7 +9,7 @@ of known size, so that one `rocprofv3 --pmc ...` run can attribute hardware coun
 The copy (1 GiB read, 1 GiB written) gives the factor between the traffic counters and real bytes.  Prints the
 algorithmic bytes and flops of every probe, in launch order, so the counter values can be set against them.
 `--set` picks a subset: encode (the four projection GEMMs at the first encode batch's token count), prefill,
-decode_attn, decode_gemm (the four projections at 64, 153 and 256 rows), all (default).
+decode_attn, decode_gemm (the four projections at 1, 32, 64, 153 and 256 rows), all (default).
 """
 import argparse
 import os
@@ -28,17 +28,18 @@ OPT_GEMMS = ((15360, 5120, "qkv"), (5120, 5120, "out"), (20480, 5120, "ffn1"), (
 
 
 def gemm_once(M, N, K, name, out_mode):
+    """One product as the model launches it (a residual product may leave its partial sums for the norm behind it)."""
     A = torch.randn((M, K), device=DEV).to(torch.bfloat16)
     W = (torch.randn((N, K), device=DEV) * 0.02).to(torch.bfloat16)
     b = torch.randn((N,), device=DEV).to(torch.bfloat16)
     out = torch.zeros((M, N), dtype=torch.float32 if out_mode else torch.bfloat16, device=DEV)
-    ws = torch.empty(max(exe.exe_op_gemm_workspace(1, M, N, K) // 4, 1), dtype=torch.float32, device=DEV)
+    ws = torch.empty(1 << 26, dtype=torch.float32, device=DEV)
     torch.cuda.synchronize()
-    exe.exe_op_gemm(1, M, N, K, A, W, b, 0 if out_mode == 0 else -1, 1.0, out_mode, out, ws)
+    left = exe.exe_op_gemm_model(1, M, N, K, A, W, b, 0 if out_mode == 0 else -1, 1.0, out_mode, out, workspace=ws, defer=out_mode == 1)
     torch.cuda.synchronize()
-    ob = M * N * (2 if out_mode == 0 else 8)
-    print(f"gemm {name} M={M} N={N} K={K}: reads {(M * K + N * K) * 2 + (M * N * 4 if out_mode else 0)} bytes, "
-          f"writes {M * N * (2 if out_mode == 0 else 4)} bytes, {2 * M * N * K} flops (algorithmic bytes {(M * K + N * K) * 2 + ob})",
+    # algorithmic bytes as the model books them: a bf16 result, a float row read and written, or the partial sums
+    ob = M * N * (2 if out_mode == 0 else 4 * left if left else 8)
+    print(f"gemm {name} M={M} N={N} K={K}: {left} partial sums left, {2 * M * N * K} flops, algorithmic bytes {(M * K + N * K) * 2 + ob}",
           flush=True)
 
 
@@ -65,7 +66,7 @@ def main():
         for (N, K, name) in OPT_GEMMS:
             gemm_once(T, N, K, name, 1 if name in ("out", "ffn2") else 0)
     if want("decode_gemm"):
-        for M in (64, 153, 256):
+        for M in (1, 32, 64, 153, 256):
             for (N, K, name) in OPT_GEMMS:
                 gemm_once(M, N, K, name, 1 if name in ("out", "ffn2") else 0)
     if want("decode_attn"):

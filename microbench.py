@@ -7,12 +7,13 @@
       operand-tile pattern at the row strides of K = 5120, 8192 and 20480.
   python3 microbench.py decode_gemm [--rows 16,64,153,256] [--lib PATH]
       the four projections of an OPT-13B layer (QKV, out, FFN1, FFN2) at decode row counts, split-K reductions included,
-      with the weights rotating through HBM-resident copies; --lib takes a measurement variant of the library built by
-      `python -m paper_2404_07947_amd.build --variant ablateN -DEXE_GEMM_ABLATE=N` (N: 1 no MFMA, 2 no activation loads, 4 no weight loads, 32 no epilogue, sums
-      combine), whose results are meaningless and whose timing isolates a part of the kernel.
+      with the weights rotating through HBM-resident copies: as exe_op_gemm launches them (tile kernels, the plan in
+      brackets) and as a model does (the streaming kernel where it is the faster one); --lib takes a measurement variant of the
+      library built by `python -m paper_2404_07947_amd.build --variant ablateN -DEXE_GEMM_ABLATE=N` (N: 1 no MFMA, 2 no
+      activation loads, 4 no weight loads, 32 no epilogue, sums combine; the tile kernels only), whose results are
+      meaningless and whose timing isolates a part of the kernel.
   python3 microbench.py encode_gemm [--rows 16020,16384] [--lib PATH]
-      the same four projections at encode row counts; --lib e.g. a variant with the loads of a k-tile issued later
-      or earlier (`build --variant late -DEXE_GEMM_ISSUE_AT=1`).
+      the same four projections at encode row counts (the large-tile kernel); --lib as above.
   python3 microbench.py two_streams
       one decode layer's attention and projections for the whole batch on one stream, against two half-batches on
       one stream and on two streams (one a phase ahead, so that one half's attention could run beside the other
@@ -68,15 +69,15 @@ def decode_gemm(rows, iters=40, copies=6):
         b.record()
         torch.cuda.synchronize()
         return a.elapsed_time(b) / iters * 1e3
-    print("| rows | " + " | ".join(f"{n} us (plan)" for _, _, n in OPT_GEMMS) + " | layer us | weights TB/s |\n|---:|" + "---:|" * 6)
+    print("| rows | " + " | ".join(f"{n} us (plan)" for _, _, n in OPT_GEMMS) + " | layer us | weights TB/s | as a model launches them: layer us | weights TB/s |\n|---:|" + "---:|" * 8)
     for M in rows:
-        cells, layer = [], 0.0
+        cells, layer, model = [], 0.0, 0.0
         for N, K, _ in OPT_GEMMS:
             A = torch.randn((M, K), device=DEV).to(torch.bfloat16)
             Ws = [(torch.randn((N, K), device=DEV) * 0.02).to(torch.bfloat16) for _ in range(copies)]
             bias = torch.randn((N,), device=DEV).to(torch.bfloat16)
             out = torch.empty((M, N), device=DEV, dtype=torch.bfloat16)
-            ws = torch.zeros(exe.exe_op_gemm_workspace(1, M, N, K) // 4 + 16, device=DEV, dtype=torch.float32)
+            ws = torch.zeros(max(exe.exe_op_gemm_workspace(1, M, N, K) // 4, 16 * M * N) + 16, device=DEV, dtype=torch.float32)
             i = [0]
 
             def once():
@@ -84,11 +85,16 @@ def decode_gemm(rows, iters=40, copies=6):
                 exe.exe_op_gemm(1, M, N, K, A, Ws[i[0]], bias, 0, 1.0, 0, out, ws)
             t = timed(once)
             layer += t
+
+            def as_model():
+                i[0] = (i[0] + 1) % copies
+                exe.exe_op_gemm_model(1, M, N, K, A, Ws[i[0]], bias, 0, 1.0, 0, out, workspace=ws)
+            model += timed(as_model)
             p = exe.exe_op_gemm_plan(1, M, N, K)
             cells.append(f"{t:.1f} ({exe.GEMM_CFG_NAMES[p['cfg']]} /{p['splits']})")
             del A, Ws, out, ws
         w_bytes = sum(N * K * 2 for N, K, _ in OPT_GEMMS)
-        print(f"| {M} | " + " | ".join(cells) + f" | {layer:.1f} | {w_bytes / layer / 1e6:.2f} |", flush=True)
+        print(f"| {M} | " + " | ".join(cells) + f" | {layer:.1f} | {w_bytes / layer / 1e6:.2f} | {model:.1f} | {w_bytes / model / 1e6:.2f} |", flush=True)
 
 
 def encode_gemm(rows, iters=8):

@@ -58,18 +58,22 @@ def build(force: bool = False, verbose: bool = True) -> str:
 
 
 def build_variant(tag: str, defines, verbose: bool = True) -> str:
-    """Builds libexe_<tag>.so: the library with the tile GEMM compiled as a measurement variant (defines such as
-    -DEXE_GEMM_ABLATE=1 or -DEXE_GEMM_ISSUE_AT=1, see csrc/kernels_gemm.hip; an ablated variant's results are
-    meaningless, its timing isolates a part of the kernel).  The other objects are the library's own."""
+    """Builds libexe_<tag>.so: the library with the tile GEMMs compiled as a measurement variant (defines such as
+    -DEXE_GEMM_ABLATE=1, see csrc/gemm_tile.h, or -DEXE_GEMM_ISSUE_AT=1, see csrc/kernels_gemm.hip; an ablated variant's
+    results are meaningless, its timing isolates a part of the kernel).  The other objects are the library's own."""
     build(verbose=verbose)
-    obj = os.path.join(OBJ, f"kernels_gemm_{tag}.o")
-    cmd = [HIPCC, *FLAGS, *defines, "-c", os.path.join(CSRC, "kernels_gemm.hip"), "-o", obj]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in l))
-    objs = [obj if src == "kernels_gemm.hip" else os.path.join(OBJ, os.path.splitext(src)[0] + ".o") for src in SOURCES]
+    objs = []
+    for src in SOURCES:
+        obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
+        if src in ("kernels_gemm.hip", "kernels_gemm_large.hip"):
+            obj = obj[:-2] + f"_{tag}.o"
+            cmd = [HIPCC, *FLAGS, *defines, "-c", os.path.join(CSRC, src), "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            r = subprocess.run(cmd, capture_output=True, text=True)
+            if r.returncode != 0:
+                raise RuntimeError("hipcc failed:\n" + "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in l))
+        objs.append(obj)
     lib = os.path.join(HERE, f"libexe_{tag}.so")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs], check=True)
     return lib

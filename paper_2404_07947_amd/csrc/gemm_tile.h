@@ -3,6 +3,16 @@
 #pragma once
 #include "gemm_epilogue.h"
 
+// EXE_GEMM_ABLATE (a compile-time bit mask, 0 in the library proper) builds measurement variants of the two tile kernels
+// whose results are meaningless and whose timing isolates a part: bit 0 drops the MFMAs (the fragment reads from
+// LDS go with them), bit 1 drops the loads of the activation tiles, bit 2 the loads of the weight tiles, bit 5 the
+// epilogue (no output is written; a split-K reduction still runs, on whatever the workspace holds).  What
+// remains keeps its waits, barriers, epilogue and split-K reduction.  `python -m paper_2404_07947_amd.build
+// --variant ablate1 -DEXE_GEMM_ABLATE=1` builds libexe_ablate1.so beside the library.
+#ifndef EXE_GEMM_ABLATE
+#define EXE_GEMM_ABLATE 0
+#endif
+
 namespace exe {
 
 // LDS tile layout for a stage of 64 bf16 (32 float) along K: row r is 128 bytes = 8 chunks of 16 bytes; chunk c is

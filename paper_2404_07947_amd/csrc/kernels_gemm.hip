@@ -11,13 +11,6 @@
 // Both A and W are K-contiguous, so both MFMA operands are 16-byte vectors along K.  The MFMA "A" operand
 // is fed with weight rows and the "B" operand with activation rows: the accumulator then holds 4
 // consecutive output features per lane, which makes the epilogue's loads and stores 8/16-byte vectors.
-//
-// EXE_GEMM_ABLATE (a compile-time bit mask, 0 in the library proper) builds measurement variants of the tile kernel
-// whose results are meaningless and whose timing isolates a part: bit 0 drops the MFMAs (the fragment reads from
-// LDS go with them), bit 1 drops the loads of the activation tiles, bit 2 the loads of the weight tiles, bit 5 the
-// epilogue (no output is written; a split-K reduction still runs, on whatever the workspace holds).  What
-// remains keeps its waits, barriers, epilogue and split-K reduction.  `python -m paper_2404_07947_amd.build
-// --variant ablate1 -DEXE_GEMM_ABLATE=1` builds libexe_ablate1.so beside the library.
 #include <stdlib.h>
 
 #include <mutex>
@@ -27,10 +20,7 @@
 #include "gemm_tile.h"
 #include "kernels.h"
 
-#ifndef EXE_GEMM_ABLATE
-#define EXE_GEMM_ABLATE 0
-#endif
-// Sub-step of a k-tile (8 MFMAs each) at which the second of the four parts of the next stage's loads is issued;
+// gemm_tile_kernel: sub-step of a k-tile (8 MFMAs each) at which the second of the four parts of the next stage's loads is issued;
 // the third and fourth follow one sub-step apart.  0 in the library; other values build measurement variants
 // (-1 issues the second part with the first, behind the barrier).
 #ifndef EXE_GEMM_ISSUE_AT

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         int pid = v - z * total;
         int chunk = total / 8;
         if (pid < chunk * 8) pid = (pid % 8) * chunk + pid / 8;
-                constexpr int GM = 8;
+        constexpr int GM = 8;
         int group = pid / (GM * tiles_n);
         int first_m = group * GM;
         int gsz = tiles_m - first_m < GM ? tiles_m - first_m : GM;
@@ -185,12 +185,14 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
     };
 #pragma clang diagnostic pop
     auto load_a = [&](int h) {
+        if (EXE_GEMM_ABLATE & 2) return;
         unsigned dst = lds_base + ld_st * STAGE + h * SLOT_A + wave * 1024;
         const char* src = base_a + ld_kt * TROW;
         load_to_lds(src, off_a[h][0], dst);
         if (BM == 256 || (BM == 192 && grp == 0)) load_to_lds(src, off_a[h][1], dst + 8192);
     };
     auto load_w = [&](int h) {
+        if (EXE_GEMM_ABLATE & 4) return;
         unsigned dst = lds_base + ld_st * STAGE + 2 * SLOT_A + h * SLOT_W + wave * 1024;
         const char* src = base_w + ld_kt * TROW;
         load_to_lds(src, off_w[h][0], dst);
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         constexpr int J0 = decltype(half)::value * TH;
         EXE_SB;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int ks = 0; ks < ((EXE_GEMM_ABLATE & 1) ? 0 : 2); ++ks)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -295,7 +297,12 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         {
             unsigned stg = lds_base + 2 * STAGE + wave * 4096;
             int row0 = m0 + grp * (BM / 2), col0 = n0 + wn * 64;
-            if (n_split > 1)
+            if (EXE_GEMM_ABLATE & 32) {            // measurement variant: no epilogue, the accumulators are only kept alive
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j) asm volatile("" ::"v"(acc[i][j]));
+            } else if (n_split > 1)
                 epilogue_tiles<bf16_t, TM, 4, EN, EPI_PARTIAL>(acc, stg, lane, row0, col0, M, N, nullptr, 1.f, partial + (int64_t)z * M * N, nullptr);
             else if (out_mode == OUT_RESID)
                 epilogue_tiles<bf16_t, TM, 4, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
