@@ -534,7 +534,10 @@ __device__ __forceinline__ void prefill_row(const T* seq, int64_t ld, int inner,
 // take 43).
 //
 // Float: the same tiles and softmax with 16x16x4 MFMAs, four per 16-byte fragment; the second product takes one key per lane
-// group and MFMA, so P again goes from accumulator to operand without moving, and V is read 4 bytes per lane.
+// group and MFMA, so P again goes from accumulator to operand without moving, and V is read 4 bytes per lane.  A score is the
+// pairwise sum of sums of 8 features, an output of sums over 16 keys: with one chain of additions for either, the kernel erred
+// 2.3 to 3.3 times as much against 64 bits as the row kernel (1000 rows 6.5e-7 of the result, now and there 2.5e-7; 4096 rows
+// 9.4e-7, now 3.0e-7, there 3.2e-7), for 2 to 9 % less time.
 //
 // Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 43;
 // float x 64, 32 sequences of 384, 4 heads, 192 -> 75.
@@ -653,13 +656,40 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         asm volatile("" : "+v"(qx));
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
-            s_acc[0][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-            s_acc[1][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (sizeof(T) == 4) {
+                // sums of 8 features each (two MFMAs), added pairwise: part x is half x % 2 of the 16-byte chunks 4 * (x / 2) + g
+                auto sum = [&](auto self, auto first, auto count, f32x4 (&c)[2]) -> void {
+                    constexpr int X = decltype(first)::value, N = decltype(count)::value;
+                    if constexpr (N == 1) {
+                        f32x4 kf = *(const f32x4*)(sK + (kb * 16 + qi) * RB + (((X / 2 * 4 + g) ^ qx) << 4));
 #pragma unroll
-            for (int ds = 0; ds < DS; ++ds) {
-                u32x4 fk = *(const u32x4*)(sK + (kb * 16 + qi) * RB + (((ds * 4 + g) ^ qx) << 4));
-                s_acc[0][kb] = HalfUnit<T>::mma(fk, qf[0][ds], s_acc[0][kb]);
-                s_acc[1][kb] = HalfUnit<T>::mma(fk, qf[1][ds], s_acc[1][kb]);
+                        for (int qb = 0; qb < 2; ++qb) {
+                            f32x4 q = __builtin_bit_cast(f32x4, qf[qb][X / 2]);
+                            c[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[X % 2 * 2], q[X % 2 * 2], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                            c[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[X % 2 * 2 + 1], q[X % 2 * 2 + 1], c[qb], 0, 0, 0);
+                        }
+                    } else {
+                        f32x4 d[2];
+                        self(self, std::integral_constant<int, X>{}, std::integral_constant<int, N / 2>{}, c);
+                        self(self, std::integral_constant<int, X + N / 2>{}, std::integral_constant<int, N / 2>{}, d);
+                        c[0] += d[0];
+                        c[1] += d[1];
+                    }
+                };
+                f32x4 c[2];
+                sum(sum, std::integral_constant<int, 0>{}, std::integral_constant<int, 2 * DS>{}, c);
+                asm volatile("" : "+v"(c[0]), "+v"(c[1]));       // the additions stay here: moved into the softmax's branches they spill
+                s_acc[0][kb] = c[0];
+                s_acc[1][kb] = c[1];
+            } else {
+                s_acc[0][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                s_acc[1][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ds = 0; ds < DS; ++ds) {
+                    u32x4 fk = *(const u32x4*)(sK + (kb * 16 + qi) * RB + (((ds * 4 + g) ^ qx) << 4));
+                    s_acc[0][kb] = HalfUnit<T>::mma(fk, qf[0][ds], s_acc[0][kb]);
+                    s_acc[1][kb] = HalfUnit<T>::mma(fk, qf[1][ds], s_acc[1][kb]);
+                }
             }
         }
     };
@@ -752,19 +782,30 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     auto phase_pv = [&](int kt) {
         const unsigned char* tV = pf_smem + (2 + (V2 ? kt & 1 : 0)) * PF_TILE;
         if constexpr (sizeof(T) == 4) {
-            // lane group g supplies key 4*g + r of key block kb, for feature 16*dt + qi
+            // Lane group g supplies key 4*g + r of key block kb, for feature 16*dt + qi: chunk 4*dt + qi/4 of its row, at slot
+            // 4 * (dt ^ g) + (qi/4 ^ r).  A sum per key block, added pairwise.  (The offsets are recomputed per tile: held, they spill.)
+            int ga = g;
+            asm volatile("" : "+v"(ga));
+            const unsigned char* vr[4];
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb)
+            for (int r = 0; r < 4; ++r) vr[r] = tV + (4 * ga + r) * RB + (((qi >> 2) ^ r) << 4) + (qi & 3) * 4;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    int row = kb * 16 + 4 * g + r;
+            for (int dt = 0; dt < DT; ++dt) {
+                f32x4 c[2][4];
 #pragma unroll
-                    for (int dt = 0; dt < DT; ++dt) {
-                        float fv = *(const float*)(tV + row * RB + (((4 * dt + (qi >> 2)) ^ pf_swz<RB>(row)) << 4) + (qi & 3) * 4);
-                        o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[0][kb][r], o_acc[0][dt], 0, 0, 0);
-                        o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[1][kb][r], o_acc[1][dt], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) c[0][i] = c[1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float fv = *(const float*)(vr[r] + ((dt ^ ga) << 6) + kb * 16 * RB);
+                        c[0][kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[0][kb][r], c[0][kb], 0, 0, 0);
+                        c[1][kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[1][kb][r], c[1][kb], 0, 0, 0);
                     }
-                }
+                o_acc[0][dt] += (c[0][0] + c[0][1]) + (c[0][2] + c[0][3]);
+                o_acc[1][dt] += (c[1][0] + c[1][1]) + (c[1][2] + c[1][3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             return;
         }
         const unsigned char* sV = tV + v_row * RB + (v_q & 1) * 8;
@@ -935,14 +976,14 @@ template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedA
 // sequences, or one that leaves most of the chip idle while its longest sequence's key tiles pass in turn, is served sooner by
 // the row kernel's many small workgroups.  us of either, fitted to 168 batches per type on one MI355X (1 to 64 sequences of 2
 // to 1000 tokens, ragged and not, 4 to 40 heads; within 6-11 % at the median, a quarter to a half at worst): the faster of the
-// two by these takes at most 1.01, 1.15 and 1.11 times the faster one measured; the MFMA kernel alone took up to 7.2, 22 and
+// two by these takes at most 1.17, 1.19 and 1.13 times the faster one measured; the MFMA kernel alone took up to 6.9, 24 and
 // 1.8 times (float x 64, float x 128, bf16 x 64; e.g. 64 sequences of one token, 16 heads, float x 128: 61 us, rows 4).
 // bf16 x 128 stays on the MFMA kernel, whose tiles were made for it.
 static bool prefill_mfma_pays(const AttnPackedArgs& a)
 {
     if (a.dtype == DT_BF16 && a.dh == 128) return true;
     struct Cost { double row_fixed, row, pair, mfma_fixed, chain, tile; };
-    static constexpr Cost F64{3.1, 0.61e-3, 16.5e-6, 3.3, 4.3, 3.7}, F128{3.3, 0.58e-3, 34.5e-6, 5.1, 8.9, 10.2}, B64{3.4, 1.06e-3, 9.6e-6, 3.2, 1.55, 1.0};
+    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 2.9, 5.0, 3.6}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 3.2, 1.53, 1.0};
     const Cost& c = a.dtype == DT_BF16 ? B64 : a.dh == 64 ? F64 : F128;
     double row = c.row_fixed + a.H * (c.row * a.T + c.pair * a.work.pairs);
     double mfma = c.mfma_fixed + c.chain * ((a.work.max_len + PREFILL_TILE_K - 1) / PREFILL_TILE_K) + c.tile * a.H * a.work.key_tiles / 256;

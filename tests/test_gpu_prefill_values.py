@@ -121,3 +121,29 @@ def test_probabilities_keep_24_bits(dtype, dh, generic):
     # a float exponential and float sums are good to a few 2^-24 of the terms (2^-21 taken); 16-bit probabilities to 2^-18
     bound = 2.0 ** -21 * terms + (0 if dtype == F32 else 2.0 ** -8) * np.abs(ref)
     assert np.all(np.abs(got - ref) < bound), float(np.max(np.abs(got - ref) / terms))
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("n,causal,R", [(300, 1, 0), (1000, 1, 0), (1000, 0, 127)])
+def test_float_sums_are_as_good_as_the_row_kernels(dh, n, causal, R):
+    """Against 64 bits: the MFMA kernel's sums may err no more than those of the row kernel, which adds up short chains in a
+    tree (with one chain per score and one per output it erred 2.3 to 3.3 times as much)."""
+    H = 4
+    g = torch.Generator().manual_seed(n + dh)
+    qkv = torch.randn((n, 3 * H * dh), generator=g) * 1.5
+    tab = torch.randn((H, 2 * R + 1), generator=g) if R else None
+    scale = float(np.float32(1.0 / np.sqrt(dh)))
+    x, ref = qkv.double().numpy(), np.zeros((n, H * dh))
+    i, j = np.arange(n)[:, None], np.arange(n)[None, :]
+    for h in range(H):
+        q, k, v = (x[:, c * H * dh + h * dh:c * H * dh + (h + 1) * dh] for c in range(3))
+        s = q @ k.T * scale
+        if R:
+            s += tab.double().numpy()[h][np.clip(j - i, -R, R) + R]
+        if causal:
+            s = np.where(j <= i, s, -np.inf)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        ref[:, h * dh:(h + 1) * dh] = (p / p.sum(axis=1, keepdims=True)) @ v
+    err = [np.linalg.norm(run(F32, dh, H, [n], qkv, scale, causal, tab, R, generic) - ref) / np.linalg.norm(ref) for generic in (-1, 1)]
+    # measured 0.93 to 1.06; two errors of the same make over 77 000 and more outputs differ by far less than a quarter
+    assert err[0] < 1.25 * err[1], err
