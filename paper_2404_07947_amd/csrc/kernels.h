@@ -111,7 +111,7 @@ struct AttnCacheArgs {       // one query row per batch entry against that seque
     // q + b*q_stride + new_k_off + head*dh and ... + new_v_off; the kernel stores them at position len-1 of the
     // cache and attends to them straight from there (new_k_off = 0 disables)
     int new_k_off = 0, new_v_off = 0;
-    int mean_len = 0;                      // average of len over the batch (0 = unknown): picks the launch shape
+    int mean_len = 0, max_len = 0;         // average and largest len of the batch (0 = unknown): pick the launch shape
 };
 hipError_t launch_attn_cache(const AttnCacheArgs& a, hipStream_t s);
 
@@ -125,7 +125,7 @@ struct AttnPagedArgs {       // as AttnCacheArgs, with the cache of one layer he
     const float* bias_by_dist; int bias_radius;
     void* out;
     int new_k_off = 0, new_v_off = 0;      // fused append, as in AttnCacheArgs
-    int mean_len = 0;
+    int mean_len = 0, max_len = 0;
 };
 hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s);
 // host-side replay of the paged kernel's row indexing (0 = every row read lies in its block and is read once)

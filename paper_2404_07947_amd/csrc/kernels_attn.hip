@@ -324,35 +324,44 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
     }
 }
 
-// Launch shape of a decode attention launch whose sequences have mean_len rows on average (0 = unknown), 2 row blocks in
-// flight per wave: measured best of a sweep over {1,2,4,8,16} waves x {1,2,3,4,8} blocks.
-//  * 16 waves per (sequence, head), fewer where the rows would leave some without a step: 8 up to 12 steps, 4 up to 4
-//    (16 x 128 heads of 8 rows: 4 waves 6.8, 8 waves 9.0, 16 waves 14.5 us; 32 x 40 heads of 200 rows: 21.9, 21.8, 21.0).
-//  * Long streams run one workgroup per CU (dynamic LDS that nothing uses keeps a second one out): with two, twice as many
-//    streams are open in memory (256 x 40 heads of 576 rows x 128: 432 us with two, 420 with one, 8 x 96 of 1024 58.2 and
-//    56.7; short ones need the second to cover their start and end: 48 x 16 of 430 rows x 64 15.7 us with two, 17.5 with
-//    one; 32 x 40 of 576 x 128 55.0 either way).
-template <typename T, int DH> static int attn_waves(int mean_len)
+// Launch shape of a decode attention launch, 2 row blocks in flight per wave (measured best of a sweep over {1,2,3,4,8}), from the
+// mean and the largest number of cached rows per sequence (0 = unknown) and the number of workgroups, one per (sequence, head).
+//  * 16 waves, fewer where the rows would leave some without a step: 8 up to 16 steps, 4 up to 4, or to 8 where the launch has
+//    more workgroups than two per CU and their number hides latencies (256 x 40 heads of 40 rows x 128: 4 waves 42, 8 49, 16 70 us;
+//    of 100 rows: 89, 86, 102; 17 heads of 300 x 64: 13.0, 11.6, 11.6).  Just above 512 workgroups of equal rows, a second round of
+//    two per CU is nearly empty and small workgroups spread better: 13 x 40 of 256 rows 16.5, 17.1, 17.2 us.
+//  * Long streams of different lengths run one workgroup per CU (dynamic LDS that nothing uses keeps a second one out): with two,
+//    twice as many streams are open in memory.  Lengths with a standard deviation of a quarter: 1.03 to 1.1x from 256 KB of keys
+//    and values on; equal lengths: 0.9x at 256 KB, where two workgroups side by side end together, 0.96 to 1.0x at 512 KB (but 1.04 to
+//    1.07x with 4000 workgroups and more), 1.03x from 1 MB on.
+struct AttnShape { int waves; bool one_per_cu; };
+template <typename T, int DH> static AttnShape attn_shape(int mean_len, int max_len, int64_t wgs)
 {
     constexpr int step = 64 / (DH / (16 / (int)sizeof(T))) * ATTN_U;         // rows that a wave takes at a time
-    return mean_len <= 0 || mean_len > 12 * step ? 16 : mean_len > 4 * step ? 8 : 4;
+    if (mean_len <= 0) return {16, false};
+    bool equal = max_len > 0 && (int64_t)max_len * 8 <= (int64_t)mean_len * 9;
+    if (mean_len <= (wgs > 512 ? 8 : 4) * step) return {4, false};
+    if (mean_len <= 16 * step) return {8, false};
+    if (equal && wgs > 512 && wgs <= 640 && mean_len <= 80 * step) return {4, false};
+    int64_t bytes = (int64_t)mean_len * 2 * DH * (int)sizeof(T);
+    return {16, bytes >= (!equal ? ATTN_LONG_BYTES : wgs >= 2048 ? 2 * ATTN_LONG_BYTES : 4 * ATTN_LONG_BYTES)};
 }
 
 template <typename T, int DH, bool PAGED, typename... Args>
-static hipError_t launch_attn_row(int mean_len, dim3 grid, hipStream_t s, Args... args)
+static hipError_t launch_attn_row(int mean_len, int max_len, dim3 grid, hipStream_t s, Args... args)
 {
     auto k16 = attn_row_kernel<T, DH, false, 16, ATTN_U, PAGED>;
-    switch (attn_waves<T, DH>(mean_len)) {
+    AttnShape shape = attn_shape<T, DH>(mean_len, max_len, (int64_t)grid.x * grid.y);
+    switch (shape.waves) {
         case 4: attn_row_kernel<T, DH, false, 4, ATTN_U, PAGED><<<grid, 256, 0, s>>>(args...); break;
         case 8: attn_row_kernel<T, DH, false, 8, ATTN_U, PAGED><<<grid, 512, 0, s>>>(args...); break;
         default: {
-            int lds = (int64_t)mean_len * 2 * DH * (int)sizeof(T) >= ATTN_LONG_BYTES ? ATTN_LONG_LDS : 0;
             static LdsLimit limit[MAX_DEVICES];
             int dev = 0;
             if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
             hipError_t e = limit[dev].raise((const void*)k16, ATTN_LONG_LDS);
             if (e != hipSuccess) return e;
-            k16<<<grid, 1024, lds, s>>>(args...);
+            k16<<<grid, 1024, shape.one_per_cu ? ATTN_LONG_LDS : 0, s>>>(args...);
         }
     }
     return hipGetLastError();
@@ -361,7 +370,7 @@ static hipError_t launch_attn_row(int mean_len, dim3 grid, hipStream_t s, Args..
 template <typename T, int DH> static hipError_t launch_attn_cache_t(const AttnCacheArgs& a, hipStream_t s)
 {
     const int32_t* none = nullptr;
-    return launch_attn_row<T, DH, false>(a.mean_len, dim3(a.H, a.B), s, (const T*)a.q, a.q_stride, (const T*)a.pool, a.base, a.cap, a.len,
+    return launch_attn_row<T, DH, false>(a.mean_len, a.max_len, dim3(a.H, a.B), s, (const T*)a.q, a.q_stride, (const T*)a.pool, a.base, a.cap, a.len,
                                          a.qpos, none, none, a.layer, a.H, 0, a.scale, a.bias_by_dist, a.bias_radius, (T*)a.out,
                                          a.new_k_off, a.new_v_off, none, 0, 0);
 }
@@ -410,7 +419,7 @@ template <typename T, int DH> static hipError_t launch_attn_paged_t(const AttnPa
 {
     const int32_t* none = nullptr;
     const int64_t* none64 = nullptr;
-    return launch_attn_row<T, DH, true>(a.mean_len, dim3(a.H, a.B), s, (const T*)a.q, a.q_stride, (const T*)a.pool, none64, none, a.len,
+    return launch_attn_row<T, DH, true>(a.mean_len, a.max_len, dim3(a.H, a.B), s, (const T*)a.q, a.q_stride, (const T*)a.pool, none64, none, a.len,
                                         a.qpos, none, none, 0, a.H, 0, a.scale, a.bias_by_dist, a.bias_radius, (T*)a.out,
                                         a.new_k_off, a.new_v_off, a.block_table, a.max_blocks, a.block_shift);
 }

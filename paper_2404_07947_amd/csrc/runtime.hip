@@ -869,7 +869,7 @@ struct DecodeDesc {
     int32_t *tok, *pos, *len, *cap, *xcap, *xlen;
     int64_t *base, *xbase;
     double self_bytes, self_flops, x_bytes, x_flops;
-    int mean_len, mean_xlen;      // average self / cross rows per sequence
+    int mean_len, mean_xlen, max_len, max_xlen;      // average and largest self / cross rows per sequence
     int32_t* table = nullptr;     // paged pool: block table [n][table_w]
     int table_w = 0;
 };
@@ -886,6 +886,7 @@ static void fill_decode_desc(exe_model* m, Stager& st, DecodeDesc& d, const std:
     int64_t* h_base = st.take<int64_t>(n, &d.base);
     int64_t* h_xbase = st.take<int64_t>(n, &d.xbase);
     double sum_len = 0, sum_x = 0;
+    d.max_len = d.max_xlen = 0;
     for (int i = 0; i < n; ++i) {
         h_tok[i] = ds[i].token;
         h_pos[i] = ds[i].len_before;
@@ -897,6 +898,8 @@ static void fill_decode_desc(exe_model* m, Stager& st, DecodeDesc& d, const std:
         h_xbase[i] = ds[i].xbase;
         sum_len += ds[i].len_before + 1;
         sum_x += ds[i].n_in;
+        d.max_len = std::max(d.max_len, ds[i].len_before + 1);
+        d.max_xlen = std::max(d.max_xlen, ds[i].n_in);
     }
     double e = esz_of(m);
     d.mean_len = n > 0 ? (int)(sum_len / n + 0.5) : 0;
@@ -941,6 +944,7 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
         a.new_k_off = m->inner;
         a.new_v_off = 2 * m->inner;
         a.mean_len = d.mean_len;
+        a.max_len = d.max_len;
         LAUNCH(m, EXE_K_DECODE_ATTN, d.self_bytes, d.self_flops, launch_attn_paged(a, m->stream));
     } else if (parts & 2) {
         AttnCacheArgs a{c.dtype, n, c.n_heads, c.head_dim, m->qkv, 3 * m->inner, m->pool.ptr, d.base, d.cap, d.len, d.pos,
@@ -948,6 +952,7 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
         a.new_k_off = m->inner;
         a.new_v_off = 2 * m->inner;
         a.mean_len = d.mean_len;
+        a.max_len = d.max_len;
         LAUNCH(m, EXE_K_DECODE_ATTN, d.self_bytes, d.self_flops, launch_attn_cache(a, m->stream));
     }
     if (parts & 1)
@@ -960,6 +965,7 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
             AttnCacheArgs x{c.dtype, n, c.n_heads, c.head_dim, m->qkv, m->inner, m->pool.ptr, d.xbase, d.xcap, d.xlen, d.pos,
                             layer, attn_scale(m), m->bias_x, m->radius, m->ctx};
             x.mean_len = d.mean_xlen;
+            x.max_len = d.max_xlen;
             LAUNCH(m, EXE_K_CROSS_ATTN, d.x_bytes, d.x_flops, launch_attn_cache(x, m->stream));
         }
         if (parts & 1)

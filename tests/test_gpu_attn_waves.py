@@ -1,4 +1,4 @@
-"""Decode attention's launch shapes: 4, 8 or 16 waves per row by the batch's mean length, and one workgroup per CU for long streams.
+"""Decode attention's launch shapes: 4, 8 or 16 waves per row by the batch's lengths, and one workgroup per CU for long ragged ones.
 For every type and head size, extent and paged, mean lengths that pick each shape in turn: a sequence's logits are compared with
 the oracle and may not depend on the batch-mates whose lengths pick the shape."""
 import numpy as np
@@ -18,9 +18,9 @@ F32, BF16 = wl.DTYPE_F32, wl.DTYPE_BF16
 def test_logits_do_not_depend_on_the_launch_shape(dtype, dh, block):
     size = 4 if dtype == F32 else 2
     step = 2 * 1024 // (dh * size)                       # rows a wave takes at a time: two loads of 1 KB
-    # up to 4 steps: 4 waves, up to 12: 8, else 16; from 256 KB of keys and values a row on one workgroup per CU
-    means = [2 * step, 8 * step, 16 * step, (256 << 10) // (2 * dh * size) * 11 // 10]
-    assert 16 * step * 2 * dh * size < 256 << 10
+    # (few workgroups) up to 4 steps: 4 waves, up to 16: 8, else 16; from 256 KB of keys and values a row on one workgroup per CU
+    means = [2 * step, 8 * step, 24 * step, (256 << 10) // (2 * dh * size) * 11 // 10]
+    assert 24 * step * 2 * dh * size < 256 << 10
     shape = wl.tiny_shape().replace(max_pos=2048, n_heads=256 // dh, head_dim=dh, dtype=dtype)
     own, steps, mates = np.array([1, 3, 40]), 3, 9                                       # the sequences compared
     rng = np.random.default_rng(3)
