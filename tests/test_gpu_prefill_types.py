@@ -46,5 +46,5 @@ def test_every_row(dtype, dh, causal, use_bias, generic, H):
             ref = (p / p.sum(axis=1, keepdims=True)) @ v
             err = np.abs(got[cu[s]:cu[s + 1], h * dh:(h + 1) * dh] - ref).max(axis=1) / np.abs(ref).max(axis=1)
             worst = max(worst, float(err.max()))
-    # float sums throughout; in bf16 one rounding of the result (2^-9) and probabilities good to 2^-17
+    # float sums and probabilities throughout; in bf16 one rounding of the result, 2^-9
     assert worst < (1e-5 if dtype == F32 else 2.0 ** -8), worst
