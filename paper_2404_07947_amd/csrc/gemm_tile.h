@@ -2,6 +2,7 @@
 // the epilogue that turns a wave's accumulators through LDS.
 #pragma once
 #include "gemm_epilogue.h"
+#include "kernels.h"
 
 // EXE_GEMM_ABLATE (a compile-time bit mask, 0 in the library proper) builds measurement variants of the two tile kernels
 // whose results are meaningless and whose timing isolates a part: bit 0 drops the MFMAs (the fragment reads from
@@ -45,7 +46,33 @@ template <int N, int L> __device__ __forceinline__ void wait_cnt()
 // front of every one of them, which also waits for the stores of the previous group.  The buffer is private to
 // the wave and is never a destination of those loads; DS operations of one wave execute in order, and the
 // lgkmcnt(0) after the reads completes them before the next group's writes.
-enum EpiMode { EPI_PARTIAL = 0, EPI_F32, EPI_RESID, EPI_T, EPI_T_RELU, EPI_T_GELU };
+enum EpiMode { EPI_PARTIAL = 0, EPI_F32, EPI_RESID, EPI_T, EPI_T_RELU, EPI_T_GELU, EPI_T_KV };
+
+// EPI_T_KV: a lane's rows of the 32 that a wave stores next, as KvStore gives them.  What it is for: the keys and values of an
+// encode batch were written to the projection's output, read by a kernel that copied them into the cache, and written there; now
+// they are written once, and prefill attention reads them there.  A copy took 292 us a layer behind 12288 tokens of the T5-11B
+// shape's cross-attention and 12 us behind 8192 tokens of a 1024-wide model; whole encode calls: 75.9 -> 72.8 ms (T5-11B, 16
+// prompts), 2234 -> 2160 us (16 prompts, six 1024-wide layers), 781 -> 758 us (32 float prompts, two layers), 7546 -> 7406 us (one
+// prompt, 20 OPT-13B layers).
+template <int P> struct KvRows {
+    int64_t row[P];
+    int32_t step[P];
+    template <typename F> __device__ __forceinline__ void load(const KvStore& kv, int M, F m_of)
+    {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            int m = m_of(p) < M ? m_of(p) : M - 1;
+            row[p] = kv.row[m];
+            step[p] = kv.step[m];
+        }
+    }
+    // element offset of the first of the wave's features `c0` (uniform, >= first_col) in row p
+    __device__ __forceinline__ int64_t at(const KvStore& kv, int p, int c0) const
+    {
+        int c = c0 - kv.first_col;
+        return row[p] + (int64_t)(kv.head0 + (c >> kv.dh_shift)) * step[p] + (c & ((1 << kv.dh_shift) - 1));
+    }
+};
 
 template <int QW> struct LdsTurn;
 template <> struct LdsTurn<4> {
@@ -74,7 +101,7 @@ template <> struct LdsTurn<2> {
 template <typename T, int TM, int TN, int EN, int MODE>
 __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsigned stg, int lane, int row0, int col0,
                                                int M, int N, const T* __restrict__ bias, float alpha,
-                                               float* __restrict__ fout, T* __restrict__ tout)
+                                               float* __restrict__ fout, T* __restrict__ tout, const KvStore& kv = KvStore{})
 {
     static_assert(TM % 2 == 0 && TN % 2 == 0, "groups are 2 tiles high");
     constexpr int QW = EN / 8;                  // 16-byte slots a lane writes, and reads, per group
@@ -111,6 +138,7 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
             }
         }
     }
+    KvRows<QW> kr;
     f32x4 res[D][QW];
     auto load_res = [&](int g) {
         int n = g_col(g);
@@ -127,6 +155,7 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         int jp = g / NG, ig = g % NG;
+        if (MODE == EPI_T_KV && ig == 0) kr.load(kv, M, [&](int p) { return g_row(g, p); });
 #pragma unroll
         for (int x = 0; x < QW; ++x) {
             f32x4 vv = acc[ig * IW + x % IW][jp * 2 + x / IW];
@@ -151,7 +180,9 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         w[e] = (T)(MODE == EPI_T_RELU ? act_apply(r[e], 0) : MODE == EPI_T_GELU ? act_apply(r[e], 1) : r[e]);
-                    *(typename Vec4<T>::type*)(tout + o) = w;
+                    T* dst = tout + o;
+                    if (MODE == EPI_T_KV && col0 + EN * ig >= kv.first_col) dst = (T*)kv.pool + kr.at(kv, p, col0 + EN * ig) + rc * 4;
+                    *(typename Vec4<T>::type*)dst = w;
                 }
             }
         }

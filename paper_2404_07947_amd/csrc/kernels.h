@@ -8,6 +8,16 @@
 
 namespace exe {
 
+// Where a projection's key / value features go instead of `out`: straight into the cache.  Feature n >= first_col of row m is
+// element row[m] + (head0 + (n - first_col) / dh) * step[m] + (n - first_col) % dh of `pool` (the keys of all heads, then the
+// values), dh = 2^dh_shift; first_col is a multiple of 64.
+struct KvStore {
+    void* pool = nullptr;
+    const int64_t* row = nullptr;
+    const int32_t* step = nullptr;
+    int first_col = 0, dh_shift = 0, head0 = 0;
+};
+
 struct GemmArgs {
     int dtype;            // DT_F32 / DT_BF16: type of A, W, bias and (for OUT_T) out
     int M, N, K;
@@ -27,6 +37,9 @@ struct GemmArgs {
     // OUT_RESID only: the caller's next kernel can add split-K partials to the residual stream itself.  launch_gemm then
     // leaves them in the workspace, *pending = their number (0: the result is complete), and plans with the cheaper split.
     int* pending = nullptr;
+    // nullable, out_mode OUT_T without activation: stored so by the launches that can (gemm_kv_rows leading rows); the others'
+    // features all go to `out`
+    const KvStore* kv = nullptr;
     int force_cfg = -1, force_splits = 0;     // tile configuration and split-K parts in place of the planner's (gemm_force_ok)
 };
 // whether the tile kernels take bf16 shapes in a configuration (-1: any) and with a number of parts
@@ -39,6 +52,8 @@ size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode);
 // whole rounds of tiles go to a second launch)
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+// the leading rows whose key / value features launch_gemm(a) stores through a.kv
+int gemm_kv_rows(const GemmArgs& a);
 
 // The streaming kernel (kernels_gemm_stream.hip): nt * 16 output features of ma * 8 rows per workgroup, K in `splits` parts of
 // units_per_split units (128 bytes of a row each); nt = 0: a shape it does not take.  launch_gemm_stream leaves float
@@ -96,6 +111,9 @@ hipError_t launch_kv_append(int dtype, const void* src, int ld, int k_off, int v
 hipError_t launch_kv_append_paged(int dtype, const void* src, int ld, int k_off, int v_off, int T, const int32_t* tok_b,
                                   const int32_t* tok_pos, const int32_t* table, int table_w, int shift, int H, int dh,
                                   void* layer_pool, hipStream_t s);
+// row[t] and step[t] of KvStore for token t of an encode batch: base[tok_b[t]] + tok_pos[t] * dh and cap[tok_b[t]] * dh
+hipError_t launch_kv_rows(const int32_t* tok_b, const int32_t* tok_pos, const int64_t* base, const int32_t* cap, int T, int dh,
+                          int64_t* row, int32_t* step, hipStream_t s);
 hipError_t launch_argmax(const float* logits, int rows, int n, int32_t* out, hipStream_t s);
 
 struct AttnCacheArgs {       // one query row per batch entry against that sequence's cached K/V
@@ -152,6 +170,10 @@ struct AttnPackedArgs {      // ragged prefill over packed qkv [T, 3*H*dh]
     const int32_t* tiles; int n_tiles;
     int force_generic;       // 0: the faster kernel for the batch's work; > 0 the row kernel, < 0 the MFMA kernel wherever it takes the call
     PrefillWork work;
+    // nullable: keys and values come from the cache, as in AttnCacheArgs, instead of from qkv
+    const void* pool = nullptr;
+    const int64_t* base = nullptr; const int32_t* cap = nullptr;
+    int layer = 0;
 };
 // Appends the (seq, first query row) pairs of a batch's 128-row query tiles to `tiles`: sequences longest first, the
 // tiles of one sequence together, last rows (causal: most keys) first.  The tiles of a sequence read the same keys

@@ -5,7 +5,8 @@
 //    softmax whose partial results are merged across the workgroup at the end.
 //      PACKED = false: decode / cross attention -- keys and values come from a sequence's cache extent
 //                      ([head][capacity][dh] per layer, keys then values).  HBM-bandwidth bound.
-//      PACKED = true : ragged prefill straight from the packed qkv activations, for batches of little work (float, and
+//      PACKED = true : ragged prefill, queries from the packed qkv activations, keys and values from there or (base given)
+//                      from the cache, for batches of little work (float, and
 //                      bf16 with head size 64) and for what the MFMA kernel below does not take (bias tables beyond its
 //                      LDS copy, sequences beyond 32-bit offsets).
 //  * prefill_mfma_kernel<T, DH, CAUSAL, BIAS>: flash-style ragged prefill.  A workgroup
@@ -134,9 +135,15 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
         qpos = qpos_arr[r];
         nk = causal ? qpos + 1 : cu[sb + 1] - t0;
         row_stride = 3 * (int64_t)inner;
-        kp = kvbuf + (int64_t)t0 * row_stride + inner + h * DH;
-        vp = kp + inner;
-        qp = kvbuf + (int64_t)r * row_stride + h * DH;
+        qp = q + (int64_t)r * row_stride + h * DH;
+        if (base) {                          // from the cache, else from the packed activations
+            row_stride = DH;
+            kp = kvbuf + base[sb] + ((int64_t)(layer * 2) * H + h) * cap[sb] * DH;
+            vp = kp + (int64_t)H * cap[sb] * DH;
+        } else {
+            kp = q + (int64_t)t0 * row_stride + inner + h * DH;
+            vp = kp + inner;
+        }
     } else if (PAGED) {
         nk = len[r];
         qpos = qpos_arr[r];
@@ -499,13 +506,12 @@ __device__ __forceinline__ float rows_sum(float x)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// One query row by one wave, keys 0 .. nk - 1 in order, 64 at a time: a lane takes a key for the scores, and features lane,
-// lane + 64 of the result.  seq: the sequence's first row of this head's queries; sc: the scale for exp2.
+// One query row q by one wave, keys 0 .. nk - 1 in order, 64 at a time: a lane takes a key for the scores, and features lane,
+// lane + 64 of the result.  ld: elements between rows of keys and values; sc: the scale for exp2.
 template <typename T, int DH, bool BIAS>
-__device__ __forceinline__ void prefill_row(const T* seq, int64_t ld, int inner, int qr, int nk, float sc, const float* sbias, int radius,
-                                            int lane, T* out)
+__device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* values, int64_t ld, int qr, int nk, float sc,
+                                            const float* sbias, int radius, int lane, T* out)
 {
-    const T *q = seq + qr * ld, *keys = seq + inner, *values = seq + 2 * inner;
     float m = -INFINITY, l = 0.f, acc[DH / 64] = {};
     for (int j0 = 0; j0 < nk; j0 += 64) {
         int j = j0 + lane, cnt = nk - j0 < 64 ? nk - j0 : 64;
@@ -555,7 +561,9 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
                                                                   const int32_t* __restrict__ cu,
                                                                   const int32_t* __restrict__ tiles, int H,
                                                                   float scale, const float* __restrict__ bias_by_dist,
-                                                                  int radius, T* __restrict__ out)
+                                                                  int radius, T* __restrict__ out, const T* __restrict__ pool,
+                                                                  const int64_t* __restrict__ base,
+                                                                  const int32_t* __restrict__ cap, int layer)
 {
     constexpr int RB = DH * (int)sizeof(T), RPL = 1024 / RB;                   // bytes per row; rows per wave-load
     constexpr int PF_LPT = PF_KT / RPL / PF_NW;                   // direct-to-LDS loads per wave and tile
@@ -619,14 +627,20 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     // lane fills a slot of its row with the chunk that the swizzle puts there.  Written as inline assembly
     // so that the compiler does not order every later LDS read behind them.
     unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)pf_smem;
-    const char* kbase = (const char*)(seq + inner);
+    // keys and values: from the packed activations, or (base given) from the cache, where a head's rows follow each other
+    const T *keys = seq + inner, *values = seq + 2 * inner;
+    unsigned kv_row = (unsigned)ld * (unsigned)sizeof(T);
+    if (base) {
+        keys = pool + base[sb] + ((int64_t)(layer * 2) * H + h) * cap[sb] * DH;
+        values = keys + (int64_t)H * cap[sb] * DH;
+        kv_row = RB;
+    }
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
     auto load_to_lds = [&](const char* src, unsigned voff, unsigned dst) {
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(src) : "memory", "m0");
     };
 #pragma clang diagnostic pop
-    const char* vbase = (const char*)(seq + 2 * inner);
     auto load_tile = [&](const char* base, int kt, unsigned dst) {
 #pragma unroll
         for (int p = 0; p < PF_LPT; ++p) {
@@ -635,12 +649,12 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
             int key = row + lane / CPR;
             int kg = kt * PF_KT + key;
             kg = kg < n ? kg : n - 1;
-            unsigned voff = (unsigned)kg * (unsigned)(ld * (int)sizeof(T)) + (((lane & (CPR - 1)) ^ pf_swz<RB>(key)) << 4);
+            unsigned voff = (unsigned)kg * kv_row + (((lane & (CPR - 1)) ^ pf_swz<RB>(key)) << 4);
             load_to_lds(base, voff, dst + row * RB);
         }
     };
-    auto load_k = [&](int kt) { load_tile(kbase, kt, lds_base + (kt & 1) * PF_TILE); };
-    auto load_v = [&](int kt) { load_tile(vbase, kt, lds_base + (2 + (V2 ? kt & 1 : 0)) * PF_TILE); };
+    auto load_k = [&](int kt) { load_tile((const char*)keys, kt, lds_base + (kt & 1) * PF_TILE); };
+    auto load_v = [&](int kt) { load_tile((const char*)values, kt, lds_base + (2 + (V2 ? kt & 1 : 0)) * PF_TILE); };
 
     f32x4 o_acc[2][DT];
 #pragma unroll
@@ -929,7 +943,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         }
         for (; again; again &= again - 1) {
             int qr = wq0 + qb * 16 + __builtin_ctz(again);
-            prefill_row<T, DH, BIAS>(seq, ld, inner, qr, CAUSAL ? qr + 1 : n, scale * LOG2E, sbias, radius, lane,
+            prefill_row<T, DH, BIAS>(seq + qr * ld, keys, values, kv_row / (int)sizeof(T), qr, CAUSAL ? qr + 1 : n, scale * LOG2E, sbias, radius, lane,
                                      out + (int64_t)(t0 + qr) * inner + h * DH);
         }
     }
@@ -972,7 +986,7 @@ template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_p
     hipError_t e = limit[dev].raise((const void*)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<(unsigned)(a.n_tiles * a.H), PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
-                                                             BIAS ? a.bias_radius : 0, (T*)a.out);
+                                                             BIAS ? a.bias_radius : 0, (T*)a.out, (const T*)a.pool, a.base, a.cap, a.layer);
     return hipGetLastError();
 }
 template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
@@ -1023,8 +1037,8 @@ hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
     }
     dim3 grid(a.H, a.T);
 #define EXE_ROW(T, DH)                                                                                           \
-    attn_row_kernel<T, DH, true><<<grid, 256, 0, s>>>(nullptr, 0, (const T*)a.qkv, nullptr, nullptr, nullptr,    \
-                                                      a.tok_pos, a.tok_b, a.cu, 0, a.H, a.causal, a.scale,       \
+    attn_row_kernel<T, DH, true><<<grid, 256, 0, s>>>((const T*)a.qkv, 0, (const T*)a.pool, a.base, a.cap, nullptr, \
+                                                      a.tok_pos, a.tok_b, a.cu, a.layer, a.H, a.causal, a.scale, \
                                                       a.bias_by_dist, a.bias_radius, (T*)a.out, 0, 0)
     if (a.dtype == DT_F32 && a.dh == 64) EXE_ROW(float, 64);
     else if (a.dtype == DT_F32 && a.dh == 128) EXE_ROW(float, 128);

@@ -317,6 +317,24 @@ hipError_t launch_kv_append(int dtype, const void* src, int ld, int k_off, int v
     return hipGetLastError();
 }
 
+__global__ void kv_rows_kernel(const int32_t* __restrict__ tok_b, const int32_t* __restrict__ tok_pos, const int64_t* __restrict__ base,
+                               const int32_t* __restrict__ cap, int T, int dh, int64_t* __restrict__ row, int32_t* __restrict__ step)
+{
+    int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= T) return;
+    int b = tok_b[t];
+    row[t] = base[b] + (int64_t)tok_pos[t] * dh;
+    step[t] = cap[b] * dh;
+}
+
+hipError_t launch_kv_rows(const int32_t* tok_b, const int32_t* tok_pos, const int64_t* base, const int32_t* cap, int T, int dh,
+                          int64_t* row, int32_t* step, hipStream_t s)
+{
+    if (T <= 0) return hipSuccess;
+    kv_rows_kernel<<<(T + 255) / 256, 256, 0, s>>>(tok_b, tok_pos, base, cap, T, dh, row, step);
+    return hipGetLastError();
+}
+
 // Paged pool: the same rows into blocks of 2^shift positions.  `layer_pool` is the layer's slab of blocks, block b at
 // b * 2*H*2^shift*dh elements holding [K|V][head][row][dh]; table [sequences][table_w] lists each sequence's blocks.
 template <typename T>

@@ -59,7 +59,7 @@ constexpr int epilogue_cols(int BM, int BN, int WM, int WN, int ST)
 template <typename T, int BM, int BN, int WM, int WN, int ST>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
     int M, int N, int K, const T* __restrict__ A, const T* __restrict__ W, const T* __restrict__ bias, int act, float alpha, int out_mode, void* __restrict__ out, float* __restrict__ partial, int tiles_m, int tiles_n,
-    int k_per_split, int n_split, int flags, int lda, int ldw)
+    int k_per_split, int n_split, int flags, int lda, int ldw, KvStore kv)
 {
     // flags: bit 0 = spread the loads of a k-tile over the MFMAs (see below); bit 1 = the weights are read once
     // (a single row of output tiles): their loads are marked nontemporal so that they do not displace A in L2
@@ -303,6 +303,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
                 epilogue_tiles<T, TM, TN, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (out_mode == OUT_F32)
                 epilogue_tiles<T, TM, TN, EN, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+            else if (sizeof(T) == 4 && kv.pool)
+                epilogue_tiles<T, TM, TN, EN, sizeof(T) == 4 ? EPI_T_KV : EPI_T>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out, kv);
             else if (act == 0)
                 epilogue_tiles<T, TM, TN, EN, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out);
             else if (act == 1)
@@ -662,17 +664,49 @@ static hipError_t launch_tile(const GemmArgs& a, const Plan& p, hipStream_t s)
     if (knobs().nt >= 0) w_once = knobs().nt != 0;
     kern<<<grid, threads, lds, s>>>(a.M, a.N, a.K, (const T*)a.A, (const T*)a.W, (const T*)a.bias, a.act, a.alpha, a.out_mode,
                                     a.out, a.workspace, tm, tn, p.k_per_split, p.splits,
-                                    (p.spread ? 1 : 0) | (w_once ? 2 : 0), a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K);
+                                    (p.spread ? 1 : 0) | (w_once ? 2 : 0), a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K,
+                                    a.kv ? *a.kv : KvStore{});
     return hipGetLastError();
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// the generic kernel is the only one that reads and writes float operands element by element
+static bool needs_generic(const GemmArgs& a)
+{
+    return a.dtype == DT_F32 && !(aligned16(a.A) && aligned16(a.W) && aligned16(a.out) && aligned16(a.bias));
+}
+
+static int launch_mode(const GemmArgs& a)
+{
+    return (a.few_rows ? GEMM_FEW_ROWS : 0) | (a.pending && a.out_mode == OUT_RESID && a.alpha == 1.f ? GEMM_DEFER : 0);
+}
+
+// Keys and values go straight into the cache from launches of whole sums on the kernels that the rows of an encode batch run on:
+// gemm_large_kernel and the float tiles.  Few rows (the streaming kernel, the smaller bf16 tiles, split sums) leave them to a copy
+// of their own, 2-4 us.  (In the 256 x 256 shape of gemm_tile_kernel, K < 256, that epilogue would spill 75 registers.)
+static bool stores_kv(const GemmArgs& a, const Plan& p)
+{
+    return p.route == 0 && p.splits == 1 && a.out_mode == OUT_T && a.act < 0 && !needs_generic(a) &&
+           (a.dtype == DT_F32 || (is_large(p.cfg) && a.K >= LARGE_MIN_K));
+}
+
+int gemm_kv_rows(const GemmArgs& a)
+{
+    if (a.M <= 0 || a.force_splits) return 0;
+    int M1 = split_rows(a.dtype, a.M, a.N, a.K, launch_mode(a));
+    if (!stores_kv(a, make_plan(a.dtype, M1, a.N, a.K, launch_mode(a)))) return 0;
+    if (M1 == a.M) return M1;
+    GemmArgs tail = a;
+    tail.M -= M1;
+    return M1 + gemm_kv_rows(tail);
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
 {
     if (a.pending) *a.pending = 0;
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    int mode = (a.few_rows ? GEMM_FEW_ROWS : 0) | (a.pending && a.out_mode == OUT_RESID && a.alpha == 1.f ? GEMM_DEFER : 0);
+    int mode = launch_mode(a);
     int M1 = a.force_splits ? a.M : split_rows(a.dtype, a.M, a.N, a.K, mode);
     if (M1 < a.M) {
         GemmArgs head = a, tail = a;
@@ -682,6 +716,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         size_t esz = a.dtype == DT_BF16 ? 2 : 4, osz = a.out_mode == OUT_T ? esz : 4;
         tail.A = (const char*)a.A + (size_t)M1 * (a.lda ? a.lda : a.K) * esz;
         tail.out = (char*)a.out + (size_t)M1 * a.N * osz;
+        KvStore rest;
+        if (a.kv) {
+            rest = *a.kv;
+            rest.row += M1;
+            rest.step += M1;
+            tail.kv = gemm_kv_rows(a) > M1 ? &rest : nullptr;
+        }
         hipError_t e = launch_gemm(head, s);
         return e != hipSuccess ? e : launch_gemm(tail, s);
     }
@@ -693,8 +734,12 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         p.k_per_split = split_k_tiles(a.dtype, a.K, p.splits) * k_tile(a.dtype);
         p.spread = 1;
     }
-    // the generic kernel is the only one that reads and writes float operands element by element
-    if (a.dtype == DT_F32 && !(aligned16(a.A) && aligned16(a.W) && aligned16(a.out) && aligned16(a.bias))) p.route = 2;
+    if (needs_generic(a)) p.route = 2;
+    if (a.kv && (a.force_splits || !stores_kv(a, p))) {
+        GemmArgs plain = a;
+        plain.kv = nullptr;
+        return launch_gemm(plain, s);
+    }
     if (p.route == 2) {
         dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
         if (a.dtype == DT_F32)

@@ -42,7 +42,8 @@ constexpr int large_lds(int BM) { return 2 * (BM + LARGE_BN) * TROW + 8 * 4096; 
 // given at epilogue_tiles.  wide: 0 = rows are 8-byte aligned only, 1 = 16-byte stores, 3 = and nontemporal.
 template <int TM, int MODE>
 __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigned stg, int lane, int row0, int col0, int M, int N,
-                                              const bf16_t* __restrict__ bias, float alpha, bf16_t* __restrict__ out, int wide)
+                                              const bf16_t* __restrict__ bias, float alpha, bf16_t* __restrict__ out, int wide,
+                                              const KvStore& kv = KvStore{})
 {
     int lm = lane & 15, lq = lane >> 4, rr = lane >> 3, rc = lane & 7;
     f32x4 bv[4];
@@ -65,8 +66,11 @@ __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigne
         raddr[x] = stg + (x * 8 + rr) * TROW + ((rc ^ lds_swz(x * 8 + rr)) << 4);
     }
     int n = col0 + rc * 8;
+    const bool cached = MODE == EPI_T_KV && col0 >= kv.first_col;          // the wave's 64 features are of one head
+    KvRows<4> kr;
 #pragma unroll
     for (int jp = 0; jp < TM / 2; ++jp) {
+        if (MODE == EPI_T_KV && cached) kr.load(kv, M, [&](int p) { return row0 + jp * 32 + p * 8 + rr; });
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
@@ -85,6 +89,7 @@ __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigne
             int m = row0 + jp * 32 + p * 8 + rr;
             if (m >= M || n >= N) continue;
             bf16_t* o = out + (int64_t)m * N + n;
+            if (MODE == EPI_T_KV && cached) o = (bf16_t*)kv.pool + kr.at(kv, p, col0) + rc * 8;
             if (wide & 2) __builtin_nontemporal_store(v[p], (f32x4*)o);
             else if (wide) *(f32x4*)o = v[p];
             else {
@@ -113,7 +118,7 @@ __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigne
 template <int BM>
 __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias, int act, float alpha, int out_mode, void* __restrict__ out,
-    float* __restrict__ partial, int tiles_m, int tiles_n, int k_per_split, int n_split, int wide, int lda, int ldw)
+    float* __restrict__ partial, int tiles_m, int tiles_n, int k_per_split, int n_split, int wide, int lda, int ldw, KvStore kv)
 {
     constexpr int TM = BM / 32, TH = TM / 2;         // 16-row tiles of a wave, and of one of its halves
     constexpr int QA = BM / 4;                       // rows of a wave group in one activation slot
@@ -308,6 +313,8 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
                 epilogue_tiles<bf16_t, TM, 4, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (out_mode == OUT_F32)
                 epilogue_tiles<bf16_t, TM, 4, EN, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+            else if (kv.pool)
+                epilogue_rows<TM, EPI_T_KV>(acc, stg, lane, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide, kv);
             else if (act == 0)
                 epilogue_rows<TM, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
             else if (act == 1)
@@ -335,7 +342,7 @@ static hipError_t launch_large(const GemmArgs& a, int k_per_split, int splits, i
     int wide = a.N % 8 == 0 && ((uintptr_t)a.out & 15) == 0 ? (int64_t)a.M * a.N * 2 >= NT_BYTES ? 3 : 1 : 0;
     kern<<<items < grid_max ? items : grid_max, LARGE_THREADS, lds, s>>>(
         a.M, a.N, a.K, (const bf16_t*)a.A, (const bf16_t*)a.W, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out, a.workspace, tm,
-        tn, k_per_split, splits, wide, a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K);
+        tn, k_per_split, splits, wide, a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K, a.kv ? *a.kv : KvStore{});
     return hipGetLastError();
 }
 

@@ -182,6 +182,8 @@ struct exe_model {
     float* logits = nullptr;
     float* gemm_ws = nullptr;
     size_t gemm_ws_bytes = 0;
+    int64_t* kv_row = nullptr;            // per token of an encode batch, see KvStore
+    int32_t* kv_step = nullptr;
     // descriptor staging
     unsigned char *stage_h = nullptr, *stage_d = nullptr;
     size_t stage_bytes = 0;
@@ -321,7 +323,7 @@ static void free_model(exe_model* m)
     if (!m) return;
     (void)hipStreamSynchronize(m->stream);
     void* ptrs[] = {m->pool.ptr, m->h, m->a, m->qkv, m->ctx, m->u, m->a_last, m->logits, m->gemm_ws,
-                    m->stage_d, m->bias_enc, m->bias_dec, m->bias_x};
+                    m->kv_row, m->kv_step, m->stage_d, m->bias_enc, m->bias_dec, m->bias_x};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (m->stage_h) (void)hipHostFree(m->stage_h);
@@ -438,6 +440,8 @@ extern "C" int exe_model_load(const exe_config_t* cfg, const exe_tensor_t* weigh
     LOAD_TRY(hipMalloc(&m->qkv, rows * 3 * inner * e));
     LOAD_TRY(hipMalloc(&m->ctx, rows * inner * e));
     LOAD_TRY(hipMalloc(&m->u, rows * f * e));
+    LOAD_TRY(hipMalloc((void**)&m->kv_row, rows * sizeof(int64_t)));
+    LOAD_TRY(hipMalloc((void**)&m->kv_step, rows * sizeof(int32_t)));
     if (c.has_lm_head) {
         LOAD_TRY(hipMalloc(&m->a_last, (size_t)c.max_batch_seqs * d * e));
         LOAD_TRY(hipMalloc((void**)&m->logits, (size_t)c.max_batch_seqs * c.vocab * sizeof(float)));
@@ -487,10 +491,14 @@ struct Stager {
 static double esz_of(const exe_model* m) { return (double)m->esz; }
 
 static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void* W, const void* bias, int act,
-                    float alpha, int out_mode, void* out)
+                    float alpha, int out_mode, void* out, const KvStore* kv = nullptr, int* kv_rows = nullptr)
 {
     GemmArgs g{m->c.dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, m->gemm_ws, m->gemm_ws_bytes};
     g.few_rows = true;
+    if (kv) {
+        *kv_rows = gemm_kv_rows(g);
+        g.kv = *kv_rows ? kv : nullptr;
+    }
     if (out_mode == OUT_RESID) {
         g.pending = &m->pend.splits;
         m->pend.rows = M;
@@ -527,7 +535,7 @@ static int run_norm(exe_model* m, const int32_t* row_index, int rows, const void
 
 // out = epilogue(norm(h) . W^T): one launch for a few short rows, else the norm into `a` and the product
 static int run_norm_gemm(exe_model* m, const int32_t* row_index, int rows, const void* g, const void* b, float out_scale, void* a,
-                         int N, const void* W, const void* bias, int act, int out_mode, void* out)
+                         int N, const void* W, const void* bias, int act, int out_mode, void* out, const KvStore* kv = nullptr, int* kv_rows = nullptr)
 {
     const exe_config_t& c = m->c;
     NormArgs n{c.dtype, c.norm == EXE_NORM_RMSNORM, m->h, row_index, rows, c.d_model, g, b, c.norm_eps, out_scale, nullptr};
@@ -539,7 +547,7 @@ static int run_norm_gemm(exe_model* m, const int32_t* row_index, int rows, const
         return EXE_OK;
     }
     int r = run_norm(m, row_index, rows, g, b, out_scale, a);
-    return r ? r : run_gemm(m, rows, N, c.d_model, a, W, bias, act, 1.f, out_mode, out);
+    return r ? r : run_gemm(m, rows, N, c.d_model, a, W, bias, act, 1.f, out_mode, out, kv, kv_rows);
 }
 
 // completes h where no norm follows (hidden states out)
@@ -635,7 +643,31 @@ struct EncodeDesc {
     int32_t* table = nullptr;   // paged pool: block table [n][table_w]
     int table_w = 0;
     PrefillWork work;           // of the batch's attention
+    KvStore kv;                 // where the projection stores keys and values itself (pool null: it does not)
 };
+
+// Keys and values straight from an encode batch's projections (N features, the last ones keys and values) into the extents `base`,
+// `cap`, where its launches can do that.
+static int prepare_kv(exe_model* m, EncodeDesc& d, int T, int N, const void* W, const void* bias, const int64_t* base, const int32_t* cap)
+{
+    const exe_config_t& c = m->c;
+    GemmArgs g{c.dtype, T, N, c.d_model, m->a, W, bias, -1, 1.f, OUT_T, m->qkv, m->gemm_ws, m->gemm_ws_bytes};
+    g.few_rows = true;
+    if (!gemm_kv_rows(g)) return EXE_OK;
+    d.kv = KvStore{m->pool.ptr, m->kv_row, m->kv_step, N - 2 * m->inner, c.head_dim == 128 ? 7 : 6, 0};
+    HIP_TRY(launch_kv_rows(d.tok_b, d.tok_pos, base, cap, T, c.head_dim, m->kv_row, m->kv_step, m->stream));
+    return EXE_OK;
+}
+
+// appends the tokens behind the first `done` of an encode batch to the cache: keys at column k_off of m->qkv, values behind them
+static int append_rest(exe_model* m, int T, int done, int ld, int k_off, const EncodeDesc& d, const int64_t* base, const int32_t* cap, int layer)
+{
+    if (done >= T) return EXE_OK;
+    LAUNCH(m, EXE_K_OTHER, 4.0 * (T - done) * m->inner * esz_of(m), 0.0,
+           launch_kv_append(m->c.dtype, (const char*)m->qkv + (size_t)done * ld * m->esz, ld, k_off, k_off + m->inner, T - done, d.tok_b + done,
+                            d.tok_pos + done, base, cap, layer, m->c.n_heads, m->c.head_dim, m->pool.ptr, m->stream));
+    return EXE_OK;
+}
 
 // One encode (prefill) layer over T packed tokens of n sequences.  parts: bit 0 = everything but the
 // attention kernel, bit 1 = the attention kernel (the profiler times them separately).
@@ -644,23 +676,31 @@ static int encode_layer(exe_model* m, const DecLayerW& L, int layer, int n, int 
 {
     const exe_config_t& c = m->c;
     bool encdec = c.arch == EXE_ARCH_ENC_DEC;
+    const bool cached = !encdec && d.kv.pool;      // keys and values of (some) tokens are in the cache only
     int r;
     if (parts & 1) {
-        if ((r = run_norm_gemm(m, nullptr, T, L.n1_g, L.n1_b, 1.f, m->a, 3 * m->inner, L.w_qkv, L.b_qkv, -1, OUT_T, m->qkv))) return r;
+        KvStore kv = d.kv;
+        kv.head0 = layer * 2 * c.n_heads;
+        int stored = 0;
+        if ((r = run_norm_gemm(m, nullptr, T, L.n1_g, L.n1_b, 1.f, m->a, 3 * m->inner, L.w_qkv, L.b_qkv, -1, OUT_T, m->qkv,
+                               cached ? &kv : nullptr, &stored))) return r;
         if (!encdec && d.table)
             LAUNCH(m, EXE_K_OTHER, 4.0 * T * m->inner * esz_of(m), 0.0,
                    launch_kv_append_paged(c.dtype, m->qkv, 3 * m->inner, m->inner, 2 * m->inner, T, d.tok_b, d.tok_pos,
                                           d.table, d.table_w, m->blk_shift, c.n_heads, c.head_dim, layer_blocks(m, layer),
                                           m->stream));
-        else if (!encdec)
-            LAUNCH(m, EXE_K_OTHER, 4.0 * T * m->inner * esz_of(m), 0.0,
-                   launch_kv_append(c.dtype, m->qkv, 3 * m->inner, m->inner, 2 * m->inner, T, d.tok_b, d.tok_pos, d.base,
-                                    d.cap, layer, c.n_heads, c.head_dim, m->pool.ptr, m->stream));
+        else if (!encdec && (r = append_rest(m, T, stored, 3 * m->inner, m->inner, d, d.base, d.cap, layer))) return r;
     }
     if (parts & 2) {
         AttnPackedArgs a{c.dtype, T, c.n_heads, c.head_dim, n, m->qkv, d.tok_b, d.tok_pos, d.cu, encdec ? 0 : 1,
                          attn_scale(m), encdec ? m->bias_enc : nullptr, m->radius, m->ctx, d.tiles, d.n_tiles, 0};
         a.work = d.work;
+        if (cached) {
+            a.pool = m->pool.ptr;
+            a.base = d.base;
+            a.cap = d.cap;
+            a.layer = layer;
+        }
         LAUNCH(m, EXE_K_PREFILL_ATTN, attn_bytes, attn_flops, launch_attn_packed(a, m->stream));
     }
     if (parts & 1) {
@@ -827,16 +867,18 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
         else
             LAUNCH(m, EXE_K_OTHER, (double)T * c.d_model * (esz_of(m) + 4.0), 0.0,
                    launch_load_hidden(c.dtype, hidden_in, (int64_t)T * c.d_model, m->h, m->stream));
-        int r = encode_layers(m, n, T, d, lens);
-        if (r) return r;
+        int r = encdec ? prepare_kv(m, d, T, 2 * m->inner, m->dec[0].w_xkv, nullptr, d.xbase, d.xcap)
+              : d.table ? EXE_OK : prepare_kv(m, d, T, 3 * m->inner, m->dec[0].w_qkv, m->dec[0].b_qkv, d.base, d.cap);
+        if (r || (r = encode_layers(m, n, T, d, lens))) return r;
         if (encdec) {
             // encoder output (after the final norm) -> every decoder layer's cross keys/values
             if ((r = run_norm(m, nullptr, T, m->enc_fin_g, nullptr, 1.f, m->a))) return r;
             for (size_t l = 0; l < m->dec.size(); ++l) {
-                if ((r = run_gemm(m, T, 2 * m->inner, c.d_model, m->a, m->dec[l].w_xkv, nullptr, -1, 1.f, OUT_T, m->qkv))) return r;
-                LAUNCH(m, EXE_K_OTHER, 4.0 * T * m->inner * esz_of(m), 0.0,
-                       launch_kv_append(c.dtype, m->qkv, 2 * m->inner, 0, m->inner, T, d.tok_b, d.tok_pos, d.xbase, d.xcap,
-                                        (int)l, c.n_heads, c.head_dim, m->pool.ptr, m->stream));
+                KvStore kv = d.kv;
+                kv.head0 = (int)l * 2 * c.n_heads;
+                int stored = 0;
+                if ((r = run_gemm(m, T, 2 * m->inner, c.d_model, m->a, m->dec[l].w_xkv, nullptr, -1, 1.f, OUT_T, m->qkv, kv.pool ? &kv : nullptr, &stored)) ||
+                    (r = append_rest(m, T, stored, 2 * m->inner, 0, d, d.xbase, d.xcap, (int)l))) return r;
             }
             if (out_device)
                 HIP_TRY(hipMemcpyAsync(out_device, m->a, (size_t)T * c.d_model * m->esz, hipMemcpyDeviceToDevice, m->stream));
@@ -1412,6 +1454,7 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
         EventTimer t;
         HIP_TRY(t.init());
         int r;
+        if (phase == 0 && !encdec && (r = prepare_kv(m, ed, rows_n, 3 * m->inner, L->w_qkv, L->b_qkv, ed.base, ed.cap))) return r;
         for (int w = 0; w < 3; ++w)
             if ((r = layer(3))) return r;
         // pass A: whole-layer latency per repetition (launch gaps included), no per-kernel events
