@@ -26,12 +26,45 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return
 __device__ __forceinline__ float bf16lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
-__device__ __forceinline__ float wave_sum(float v)
+// Sum over groups of W lanes, in every one of them: DPP moves inside a row of 16 lanes, a few cycles each where a shuffle takes a
+// trip through the LDS pipe.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
+template <int W> __device__ __forceinline__ float row_sum(float d)
+{
+    static_assert(W == 8 || W == 16 || W == 32, "lanes per row");
+    d += dpp_move<0xB1>(d);                  // quad_perm: lane ^ 1
+    d += dpp_move<0x4E>(d);                  // quad_perm: lane ^ 2
+    d += dpp_move<0x141>(d);                 // row_half_mirror: the other four of eight
+    if (W >= 16) d += dpp_move<0x140>(d);    // row_mirror: the other eight of sixteen
+    if (W == 32) d += __shfl_xor(d, 16, WAVE);
+    return d;
+}
+// Reductions over the four 16-lane rows of a wave (the lanes that share a column of a 16x16 accumulator tile),
+// with the row-swap instructions of gfx950: v_permlane16_swap exchanges rows 1 and 3 of its first operand with
+// rows 0 and 2 of its second, v_permlane32_swap the upper half of the first with the lower half of the second.
+__device__ __forceinline__ float rows_max(float x)
+{
+    unsigned u = __float_as_uint(x);
+    auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+    auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float rows_sum(float x)
+{
+    unsigned u = __float_as_uint(x);
+    auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Over all lanes.  (Six shuffles before, each a trip through the LDS pipe: LayerNorm of bf16 2048 x 4096 10.1 -> 9.4 us, 8192 x 1024
+// 9.1 -> 8.6.)
+__device__ __forceinline__ float wave_sum(float v) { return rows_sum(row_sum<16>(v)); }
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll

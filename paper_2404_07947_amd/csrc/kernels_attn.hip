@@ -21,82 +21,15 @@
 #include <type_traits>
 #include <vector>
 
+#include "attn_row.h"
 #include "gemm_epilogue.h"
 #include "kernels.h"
 
 namespace exe {
 
-constexpr float LOG2E = 1.44269504088896340736f;
-constexpr int ATTN_BIAS_LDS = 1024;       // entries of a head's bias table that the row kernel keeps in LDS
 constexpr int ATTN_U = 2;                 // decode attention: row blocks in flight per wave
 constexpr int ATTN_LONG_BYTES = 256 << 10;
 constexpr int ATTN_LONG_LDS = 88 << 10;   // dynamic LDS that leaves room for one workgroup on a CU
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// Sum over the W lanes (8 or 16) that share a cached row, in every one of them: DPP moves inside a row of 16 lanes, a few
-// cycles each where a shuffle takes a trip through the LDS pipe.
-template <int CTRL> __device__ __forceinline__ float dpp_move(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int W> __device__ __forceinline__ float row_sum(float d)
-{
-    static_assert(W == 8 || W == 16 || W == 32, "lanes per row");
-    d += dpp_move<0xB1>(d);                  // quad_perm: lane ^ 1
-    d += dpp_move<0x4E>(d);                  // quad_perm: lane ^ 2
-    d += dpp_move<0x141>(d);                 // row_half_mirror: the other four of eight
-    if (W >= 16) d += dpp_move<0x140>(d);    // row_mirror: the other eight of sixteen
-    if (W == 32) d += __shfl_xor(d, 16, WAVE);
-    return d;
-}
-// the value of the lane `lane ^ O`
-template <int O> __device__ __forceinline__ float lane_xor(float x)
-{
-    if (O == 8) return dpp_move<0x128>(x);   // row_ror:8
-    return __shfl_xor(x, O, WAVE);
-}
-
-template <typename T, int EPL> struct Chunk;
-template <> struct Chunk<float, 4> {
-    static __device__ __forceinline__ void unpack(uint4 u, float* f)
-    {
-        f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y); f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
-    }
-};
-template <> struct Chunk<bf16_t, 8> {
-    static __device__ __forceinline__ void unpack(uint4 u, float* f)
-    {
-        f[0] = bf16lo(u.x); f[1] = bf16hi(u.x); f[2] = bf16lo(u.y); f[3] = bf16hi(u.y);
-        f[4] = bf16lo(u.z); f[5] = bf16hi(u.z); f[6] = bf16lo(u.w); f[7] = bf16hi(u.w);
-    }
-};
-
-// 16 bytes from global memory.  STREAM marks data that is read once (a sequence's cached keys and values during
-// decode): a nontemporal load keeps it from displacing other lines in L2, measured 6.3 -> 6.9 .. 7.1 TB/s.
-template <bool STREAM, typename T> __device__ __forceinline__ uint4 load_chunk(const T* p)
-{
-    if (STREAM) {
-        typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
-        v4u_t t = __builtin_nontemporal_load((const v4u_t*)p);
-        return uint4{t.x, t.y, t.z, t.w};
-    }
-    return *(const uint4*)p;
-}
-
-// Paged cache indexing, shared by the kernel and by the host-side check paged_index_check below.
-// paged_lookup_row: the row whose block look-up x of the step starting at row j names (nc rows are cached);
-// paged_lane_row: the row that the lane group rg of load u of that step reads.
-__host__ __device__ __forceinline__ int paged_lookup_row(int j, int x, int rpw, int nc)
-{
-    int row = j + x * rpw;
-    return row < nc ? row : nc - 1;
-}
-__host__ __device__ __forceinline__ int paged_lane_row(int j, int u, int rg, int rpw, int nc)
-{
-    int row = j + u * rpw + rg;
-    return row < nc ? row : nc - 1;
-}
 
 // PAGED (with PACKED = false): the cache of a sequence is a list of blocks of 2^block_shift positions instead of
 // one extent.  Block b of the pool holds [K|V][head][position in block][DH]; block_table[r * max_blocks + i] is the
@@ -113,17 +46,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
     const int32_t* __restrict__ block_table = nullptr, int max_blocks = 0, int block_shift = 0)
 {
     static_assert(!(PAGED && PACKED), "paged mode is a cache mode");
-    constexpr int EPL = 16 / sizeof(T);      // elements per 16-byte chunk
-    constexpr int LPR = DH / EPL;            // lanes that share one key/value row
-    constexpr int RPW = 64 / LPR;            // rows per wave per load
-    constexpr int NL = (PAGED && RPW * U > 8) ? U : 1;   // PAGED: table look-ups per step
-    static_assert(RPW <= 8, "the rows of one load must fit the smallest block");
-    __shared__ float s_m[NWV], s_l[NWV];
-    __shared__ __align__(16) float s_acc[NWV][DH];
-
     int h = blockIdx.x, r = blockIdx.y;
-    int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int rg = lane / LPR, cl = lane % LPR;
     int inner = H * DH;
 
     const T *kp, *vp, *qp;
@@ -159,176 +82,11 @@ __global__ __launch_bounds__(NWV * 64) void attn_row_kernel(
         vp = kp + (int64_t)H * c * DH;
         qp = q + (int64_t)r * q_stride + h * DH;
     }
-    // PAGED: keys of block b for this head start at block_k(b), its values H * block_rows * DH elements further on
-    const int block_rows = 1 << block_shift;
-    const int32_t* tbl = PAGED ? block_table + (int64_t)r * max_blocks : nullptr;
-    auto block_k = [&](int b) { return kvbuf + ((int64_t)b * 2 * H + h) * block_rows * DH; };
-    // Fused append: the newest position's key/value rows come from the projection output; one 16-lane group
-    // stores them into the cache, and every lane that meets row nk-1 reads it from the source instead of the
-    // cache, so no ordering between that store and the loads is needed.
-    const T *knew = nullptr, *vnew = nullptr;
-    if (!PACKED && new_k_off) {
-        knew = qp + new_k_off;
-        vnew = qp + new_v_off;
-        if (wave == 0 && rg == 0) {
-            const T *kd = kp, *vd = vp;
-            int row = nk - 1;
-            if (PAGED) {
-                kd = block_k(tbl[row >> block_shift]);
-                vd = kd + (int64_t)H * block_rows * DH;
-                row &= block_rows - 1;
-            }
-            *(uint4*)(const_cast<T*>(kd) + (int64_t)row * DH + cl * EPL) = *(const uint4*)(knew + cl * EPL);
-            *(uint4*)(const_cast<T*>(vd) + (int64_t)row * DH + cl * EPL) = *(const uint4*)(vnew + cl * EPL);
-        }
-    }
-
-    float qf[EPL];
-    {
-        float t[EPL];
-        Chunk<T, EPL>::unpack(*(const uint4*)(qp + cl * EPL), t);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) qf[e] = t[e] * scale * LOG2E;
-    }
-    const float* bias = bias_by_dist ? bias_by_dist + (int64_t)h * (2 * radius + 1) + radius : nullptr;
-    // The head's bias table goes to LDS first (scaled for exp2): a look-up in global memory shares the wave's
-    // in-order load counter with the K/V stream and cost 12 % of the kernel's bandwidth.
+    const T *knew = !PACKED && new_k_off ? qp + new_k_off : nullptr, *vnew = !PACKED && new_k_off ? qp + new_v_off : nullptr;
     __shared__ float s_bias[ATTN_BIAS_LDS];
-    const bool bias_lds = bias && 2 * radius + 1 <= ATTN_BIAS_LDS;
-    if (bias_lds) {
-        for (int i = threadIdx.x; i < 2 * radius + 1; i += NWV * 64) s_bias[i] = bias[i - radius] * LOG2E;
-        __syncthreads();
-    }
-    auto bias_at = [&](int rel) {
-        rel = rel < -radius ? -radius : (rel > radius ? radius : rel);
-        return bias_lds ? s_bias[rel + radius] : bias[rel] * LOG2E;
-    };
-
-    float m_run = -INFINITY, l_run = 0.f, acc[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-
-    // with a fused append the cached rows are 0 .. nk-2; the new row is folded in after the loop
-    const int nc = (!PACKED && knew) ? nk - 1 : nk;
-    // PAGED: the blocks of a step are looked up one step ahead, so that the step's loads do not wait for the table.
-    // Look-up x of the step starting at row j serves the rows of loads x, x + NL, ...; it names the block of row
-    // min(j + x * RPW, nc - 1), which is also the block of every row those loads touch: rows past the end are
-    // clamped to row nc - 1.
-    int blk[NL];
-    auto lookup = [&](int j) {
-#pragma unroll
-        for (int x = 0; x < NL; ++x) blk[x] = tbl[paged_lookup_row(j, x, RPW, nc) >> block_shift];
-    };
-    if (PAGED && wave * RPW * U < nc) lookup(wave * RPW * U);
-    const int64_t v_off = PAGED ? (int64_t)H * block_rows * DH : vp - kp;        // values behind the keys
-    for (int j0 = wave * RPW * U; j0 < nc; j0 += NWV * RPW * U) {
-        uint4 kc[U], vc[U];
-        float s[U];
-        const T* kpb[NL];                     // PAGED: keys of this head in the block of look-up x
-        int jb[NL];                           // PAGED: first row of that block
-        kpb[0] = kp;
-        jb[0] = 0;
-        if (PAGED) {
-#pragma unroll
-            for (int x = 0; x < NL; ++x) {
-                kpb[x] = block_k(blk[x]);
-                jb[x] = paged_lookup_row(j0, x, RPW, nc) & ~(block_rows - 1);
-            }
-            int jn = j0 + NWV * RPW * U;
-            if (jn < nc) lookup(jn);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            int x = NL == 1 ? 0 : u;
-            int jj = paged_lane_row(j0, u, rg, RPW, nc) - jb[x];
-            const T* kr = kpb[x] + (int64_t)jj * row_stride + cl * EPL;
-            kc[u] = load_chunk<!PACKED>(kr);
-            vc[u] = load_chunk<!PACKED>(kr + v_off);
-        }
-        float mx = m_run;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float kf[EPL];
-            Chunk<T, EPL>::unpack(kc[u], kf);
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
-            d = row_sum<LPR>(d);
-            int j = j0 + u * RPW + rg;
-            if (bias) d += bias_at(j - qpos);
-            s[u] = j < nc ? d : -INFINITY;
-            mx = fmaxf(mx, s[u]);
-        }
-        float mref = mx == -INFINITY ? 0.f : mx;
-        float alpha = fast_exp2(m_run - mref);
-        l_run *= alpha;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float p = fast_exp2(s[u] - mref);
-            l_run += p;
-            float vf[EPL];
-            Chunk<T, EPL>::unpack(vc[u], vf);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vf[e], acc[e]);
-        }
-        m_run = mx;
-    }
-
-    // the appended position (its key and value come from the projection output): folded into the state of the
-    // first row group of wave 0
-    if (!PACKED && knew && wave == 0 && rg == 0) {
-        float kf[EPL], vf[EPL];
-        Chunk<T, EPL>::unpack(*(const uint4*)(knew + cl * EPL), kf);
-        Chunk<T, EPL>::unpack(*(const uint4*)(vnew + cl * EPL), vf);
-        float d = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
-        d = row_sum<LPR>(d);
-        if (bias) d += bias_at(nk - 1 - qpos);
-        float mx = fmaxf(m_run, d);
-        float alpha = fast_exp2(m_run - mx), p = fast_exp2(d - mx);
-        l_run = l_run * alpha + p;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vf[e], acc[e] * alpha);
-        m_run = mx;
-    }
-
-    // Merge the partial states: the row groups of a wave across its lanes, then the waves through LDS.  (All NWV * RPW states
-    // through LDS, added up by DH threads, took 2-4 us of every launch.)
-    auto merge_lanes = [&](auto xo) {
-        constexpr int O = decltype(xo)::value;
-        float mo = lane_xor<O>(m_run), lo = lane_xor<O>(l_run);
-        float mx = fmaxf(m_run, mo), mref = mx == -INFINITY ? 0.f : mx;
-        float wa = fast_exp2(m_run - mref), wb = fast_exp2(mo - mref);       // 0 for a side that saw no key
-        l_run = l_run * wa + lo * wb;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = acc[e] * wa + lane_xor<O>(acc[e]) * wb;
-        m_run = mx;
-    };
-    if constexpr (LPR <= 8) merge_lanes(std::integral_constant<int, 8>{});
-    if constexpr (LPR <= 16) merge_lanes(std::integral_constant<int, 16>{});
-    if constexpr (LPR <= 32) merge_lanes(std::integral_constant<int, 32>{});
-    if (lane == 0) { s_m[wave] = m_run; s_l[wave] = l_run; }
-    if (rg == 0) {
-#pragma unroll
-        for (int e = 0; e < EPL; e += 4) *(f32x4*)&s_acc[wave][cl * EPL + e] = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < DH; c += NWV * 64) {
-        float M = s_m[0];
-#pragma unroll
-        for (int g = 1; g < NWV; ++g) M = fmaxf(M, s_m[g]);
-        float L = 0.f, o = 0.f;
-#pragma unroll
-        for (int g = 0; g < NWV; ++g) {
-            float w = fast_exp2(s_m[g] - M);      // 0 for waves that saw no key
-            L += s_l[g] * w;
-            o += s_acc[g][c] * w;
-        }
-        out[(int64_t)r * inner + h * DH + c] = from_f32<T>(o / L);
-    }
+    attn_row_body<T, DH, PACKED, NWV, U, PAGED>(qp, kp, vp, knew, vnew, row_stride, nk, qpos, h, H, scale, bias_by_dist, radius, kvbuf,
+                                                PAGED ? block_table + (int64_t)r * max_blocks : nullptr, block_shift, s_bias,
+                                                [&](int c, T o) { out[(int64_t)r * inner + h * DH + c] = o; });
 }
 
 // Launch shape of a decode attention launch, 2 row blocks in flight per wave (measured best of a sweep over {1,2,3,4,8}), from the
@@ -484,26 +242,6 @@ __device__ __forceinline__ uint2 pf_read_tr(const unsigned char* p)
 {
     pf_v4s r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) pf_v4s*)p);
     return __builtin_bit_cast(uint2, r);
-}
-
-// Reductions over the four 16-lane rows of a wave (the lanes that share a column of a 16x16 accumulator tile),
-// with the row-swap instructions of gfx950: v_permlane16_swap exchanges rows 1 and 3 of its first operand with
-// rows 0 and 2 of its second, v_permlane32_swap the upper half of the first with the lower half of the second.
-__device__ __forceinline__ float rows_max(float x)
-{
-    unsigned u = __float_as_uint(x);
-    auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    u = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
-    auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float rows_sum(float x)
-{
-    unsigned u = __float_as_uint(x);
-    auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-    auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // One query row q by one wave, keys 0 .. nk - 1 in order, 64 at a time: a lane takes a key for the scores, and features lane,
