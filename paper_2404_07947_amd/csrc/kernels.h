@@ -97,11 +97,42 @@ struct NormArgs {
     const float* partial = nullptr;
     int splits = 0, partial_rows = 0;
     const void* bias = nullptr;
+    bool last = false;           // nothing reads x after this norm
 };
 hipError_t launch_norm(const NormArgs& a, hipStream_t s);
 // A norm and the product behind it in one launch of the streaming kernel (a.A is not read), where norm_gemm_fits says so.
 bool norm_gemm_fits(const NormArgs& n, const GemmArgs& a);
 hipError_t launch_norm_gemm(const NormArgs& n, const GemmArgs& a, hipStream_t s);
+// ---- decode iterations of small models (kernels_small.hip): a layer's attention block and feed-forward block, a launch each
+constexpr int SMALL_MAX_ROWS = 32, SMALL_MAX_PARTS = 64, SMALL_SLICE = 32;     // rows; heads, or slices of the feed-forward; features of a slice
+bool small_decode_fits(int dtype, int rows, int d, int H, int dh, int f);
+struct SmallArgs {               // the residual stream in front of a block, its norm, and where the block's partial sums go
+    int dtype, rows, d, rms;
+    float eps;
+    const void *gain, *shift;    // shift: LayerNorm only
+    const float* x;              // [rows, d]
+    float* x_out;                // [rows, d], not x: the rows with the partial sums in front of the block added
+    const float* partial;        // [n_part][rows][d], of the block in front, and its bias (nullable)
+    int n_part;
+    const void* part_bias;
+    float* out;                  // [heads, or f / SMALL_SLICE][rows][d], not `partial`
+    // attention only, nullable: the rows are these embeddings, x is not read
+    const int32_t *tokens = nullptr, *pos = nullptr;
+    const void *tok_emb = nullptr, *pos_emb = nullptr;
+};
+struct SmallAttn {               // arrays as in AttnCacheArgs; self-attention appends the rows' keys and values at len - 1
+    int H, dh, cross;
+    const void *w_in, *b_in;     // [3 * H * dh, d], or (cross) [H * dh, d]; b_in nullable
+    const void* w_out;           // [d, H * dh]
+    void* pool;
+    const int64_t* base; const int32_t* cap; const int32_t* len; const int32_t* qpos;
+    int layer;
+    float scale;
+    const float* bias_by_dist; int bias_radius;
+};
+struct SmallFfn { int f; const void *w_1, *b_1; int act; const void* w_2; };     // b_1 nullable
+hipError_t launch_small_attn(const SmallArgs& a, const SmallAttn& k, hipStream_t s);
+hipError_t launch_small_ffn(const SmallArgs& a, const SmallFfn& k, hipStream_t s);
 // copies K and V rows of `src` (row stride ld, K at column k_off, V at v_off) into the cache:
 // token t belongs to batch entry tok_b[t] (t itself if nullptr) at position tok_pos[t];
 // K of (b, head, pos) lives at pool + base[b] + ((layer*2+0)*H + head)*cap[b]*dh + pos*dh, V at kv index 1.

@@ -640,8 +640,11 @@ size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode)
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s)
 {
     int64_t quads = ((int64_t)a.M * a.N) / 4;
-    splitk_reduce_kernel<bf16_t><<<(unsigned)((quads + 255) / 256), 256, 0, s>>>(
-        a.M, a.N, splits, a.workspace, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
+    unsigned grid = (unsigned)((quads + 255) / 256);
+    if (a.dtype == DT_F32)
+        splitk_reduce_kernel<float><<<grid, 256, 0, s>>>(a.M, a.N, splits, a.workspace, (const float*)a.bias, a.act, a.alpha, a.out_mode, a.out);
+    else
+        splitk_reduce_kernel<bf16_t><<<grid, 256, 0, s>>>(a.M, a.N, splits, a.workspace, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
     return hipGetLastError();
 }
 

@@ -50,12 +50,19 @@ template <typename T> struct NormIn {
     const T *gain, *shift;           // shift: LayerNorm only
     float eps, out_scale;
     int rms;
+    const float* partial;            // [n_part][partial_rows][K], added to x first, and their bias (nullable)
+    const T* part_bias;
+    int n_part, partial_rows;
 };
 constexpr int NORM_STAGES = 3;
 // Where it is taken: each workgroup repeats the norm, so the rows have to be few and short.  A launch less (2.4 us on the GPU, 2.6
 // to enqueue) against its norm: decode iterations of a 256-wide float model 1.15x, of a 512-wide encoder-decoder 1.12x;
 // 1024 wide with 4 to 16 rows 0.98-0.99x.
 constexpr int NORM_MAX_K = 512, NORM_MAX_ROWS = 16, NORM_MAX_N = 4096;
+// With partial sums to add first (a small model's last feed-forward block in front of the LM head), each workgroup reads all of them:
+// 512 KB (8 rows of 256 in 64 parts, 4 of 512) 67 and 79 us a decode iteration against 75 and 87 with a norm of its own, 1 MB 87
+// and 90, 2 MB 106 and 100.
+constexpr int64_t NORM_MAX_PART_BYTES = 1 << 20;
 constexpr int NORM_Q = NORM_MAX_K / 256;     // groups of 4 elements per lane and row
 template <typename T> constexpr int norm_lds(int MA, int K) { return stream_waves(1, MA) * NORM_STAGES * 2048 + MA * 8 * K * (int)sizeof(T); }
 
@@ -205,7 +212,33 @@ __device__ __forceinline__ void stream_body(
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 int r = wave + i * NW;
-                if (r < M) nv[i][q] = *(const f32x4*)(norm.x + (int64_t)(norm.row_index ? norm.row_index[r] : r) * K + k);
+                if (r >= M) continue;
+                int64_t at = (int64_t)(norm.row_index ? norm.row_index[r] : r) * K + k;
+                nv[i][q] = *(const f32x4*)(norm.x + at);
+                if (!norm.n_part) continue;
+                f32x4 sum = zero;
+                const float* p = norm.partial + at;
+                int64_t slice = (int64_t)norm.partial_rows * K;
+                int s = 0;
+                for (; s + 16 <= norm.n_part; s += 16) {
+                    f32x4 pv[16];
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) pv[j] = *(const f32x4*)(p + (s + j) * slice);
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) sum += pv[j];
+                }
+                for (; s + 4 <= norm.n_part; s += 4) {
+                    f32x4 p0 = *(const f32x4*)(p + s * slice), p1 = *(const f32x4*)(p + (s + 1) * slice);
+                    f32x4 p2 = *(const f32x4*)(p + (s + 2) * slice), p3 = *(const f32x4*)(p + (s + 3) * slice);
+                    sum += p0; sum += p1; sum += p2; sum += p3;
+                }
+                for (; s < norm.n_part; ++s) sum += *(const f32x4*)(p + s * slice);
+                if (norm.part_bias) {
+                    typename Vec4<T>::type pb = *(const typename Vec4<T>::type*)(norm.part_bias + k);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) sum[j] += (float)pb[j];
+                }
+                nv[i][q] += sum;
             }
             typename Vec4<T>::type gt = *(const typename Vec4<T>::type*)(norm.gain + k);
 #pragma unroll
@@ -347,7 +380,7 @@ template <typename T, int MA> static hipError_t launch_norm_stream(const NormArg
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
     hipError_t e = limit[dev].raise((const void*)kern, norm_lds<T>(MA, NORM_MAX_K));
     if (e != hipSuccess) return e;
-    NormIn<T> in{n.x, n.row_index, (const T*)n.gain, (const T*)n.shift, n.eps, n.out_scale, n.rms};
+    NormIn<T> in{n.x, n.row_index, (const T*)n.gain, (const T*)n.shift, n.eps, n.out_scale, n.rms, n.partial, (const T*)n.bias, n.partial ? n.splits : 0, n.partial_rows};
     kern<<<dim3((a.N + 15) / 16), stream_waves(1, MA) * 64, norm_lds<T>(MA, a.K), s>>>(
         a.M, a.N, a.K, (const T*)a.W, (const T*)a.bias, a.act, a.alpha, a.out_mode, a.out, in);
     return hipGetLastError();
@@ -355,9 +388,9 @@ template <typename T, int MA> static hipError_t launch_norm_stream(const NormArg
 
 bool norm_gemm_fits(const NormArgs& n, const GemmArgs& a)
 {
-    uintptr_t any = (uintptr_t)n.x | (uintptr_t)n.gain | (uintptr_t)n.shift | (uintptr_t)a.W | (uintptr_t)a.out | (uintptr_t)a.bias;
+    uintptr_t any = (uintptr_t)n.x | (uintptr_t)n.gain | (uintptr_t)n.shift | (uintptr_t)a.W | (uintptr_t)a.out | (uintptr_t)a.bias | (uintptr_t)n.partial | (uintptr_t)n.bias;
     return a.M >= 1 && a.M <= NORM_MAX_ROWS && a.K <= NORM_MAX_K && a.K % (a.dtype == DT_F32 ? 32 : 64) == 0 && a.N % 4 == 0 &&
-           a.N <= NORM_MAX_N && a.out_mode != OUT_RESID && !n.partial && n.rows == a.M && n.d == a.K && (any & 15) == 0;
+           a.N <= NORM_MAX_N && a.out_mode != OUT_RESID && (!n.partial || (n.last && (int64_t)n.splits * a.M * a.K * 4 <= NORM_MAX_PART_BYTES)) && n.rows == a.M && n.d == a.K && (any & 15) == 0;
 }
 
 hipError_t launch_norm_gemm(const NormArgs& n, const GemmArgs& a, hipStream_t s)

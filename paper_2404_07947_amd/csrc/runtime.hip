@@ -192,8 +192,11 @@ struct exe_model {
     int32_t mark_gen = 0;
     KTimer timer;
     // Split-K partial sums of the last projection into the residual stream h that still lie in gemm_ws (splits > 0): the
-    // norm that follows adds them (run_norm), finish_resid does where none follows.
-    struct Pending { int splits = 0, rows = 0; const void* bias = nullptr; } pend;
+    // norm that follows adds them (run_norm), finish_resid does where none follows.  (Of a small model's decode iteration: the
+    // last block's, in front of the rows `x`.)
+    struct Pending { int splits = 0, rows = 0; const void* bias = nullptr; const float *partial = nullptr, *x = nullptr; } pend;
+    // small models: a second buffer for the residual stream and two for the blocks' partial sums (see launch_small_attn)
+    float *small_x = nullptr, *small_part[2] = {nullptr, nullptr};
 };
 
 // ---------------------------------------------------------------- timing helpers
@@ -323,7 +326,7 @@ static void free_model(exe_model* m)
     if (!m) return;
     (void)hipStreamSynchronize(m->stream);
     void* ptrs[] = {m->pool.ptr, m->h, m->a, m->qkv, m->ctx, m->u, m->a_last, m->logits, m->gemm_ws,
-                    m->kv_row, m->kv_step, m->stage_d, m->bias_enc, m->bias_dec, m->bias_x};
+                    m->kv_row, m->kv_step, m->small_x, m->small_part[0], m->small_part[1], m->stage_d, m->bias_enc, m->bias_dec, m->bias_x};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (m->stage_h) (void)hipHostFree(m->stage_h);
@@ -460,6 +463,16 @@ extern "C" int exe_model_load(const exe_config_t* cfg, const exe_tensor_t* weigh
     m->gemm_ws_bytes = ws;
     if (ws) LOAD_TRY(hipMalloc((void**)&m->gemm_ws, ws));
 
+    if (small_decode_fits(c.dtype, 1, c.d_model, c.n_heads, c.head_dim, c.d_ff) && m->blk_rows == 0) {
+        bool aligned = true;
+        for (int k = 0; k < n_weights; ++k) aligned = aligned && ((uintptr_t)weights[k].ptr & 15) == 0;
+        size_t row = (size_t)SMALL_MAX_ROWS * c.d_model * sizeof(float);
+        if (aligned) {
+            LOAD_TRY(hipMalloc((void**)&m->small_x, row));
+            for (float*& p : m->small_part) LOAD_TRY(hipMalloc((void**)&p, row * SMALL_MAX_PARTS));
+        }
+    }
+
     // descriptor staging: token-sized int arrays (3), tile list (2 ints per 128 query rows + one per sequence),
     // and per-sequence arrays (int64 x2, int32 x6)
     size_t tiles_max = (size_t)c.max_batch_tokens / PREFILL_TILE_Q + c.max_batch_seqs + 1;
@@ -501,6 +514,8 @@ static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void
     }
     if (out_mode == OUT_RESID) {
         g.pending = &m->pend.splits;
+        m->pend.partial = m->gemm_ws;
+        m->pend.x = m->h;
         m->pend.rows = M;
         m->pend.bias = bias;
     }
@@ -516,17 +531,22 @@ static int run_gemm(exe_model* m, int M, int N, int K, const void* A, const void
     return EXE_OK;
 }
 
+static void take_pending(exe_model* m, NormArgs& a)
+{
+    if (!m->pend.splits) return;
+    a.x = const_cast<float*>(m->pend.x);
+    a.partial = m->pend.partial;
+    a.splits = m->pend.splits;
+    a.partial_rows = m->pend.rows;
+    a.bias = m->pend.bias;
+    m->pend.splits = 0;
+}
+
 static int run_norm(exe_model* m, const int32_t* row_index, int rows, const void* g, const void* b, float out_scale,
                     void* out)
 {
     NormArgs a{m->c.dtype, m->c.norm == EXE_NORM_RMSNORM, m->h, row_index, rows, m->c.d_model, g, b, m->c.norm_eps, out_scale, out};
-    if (m->pend.splits) {
-        a.partial = m->gemm_ws;
-        a.splits = m->pend.splits;
-        a.partial_rows = m->pend.rows;
-        a.bias = m->pend.bias;
-        m->pend.splits = 0;
-    }
+    take_pending(m, a);
     // reads the row, and with partial sums these as well, and writes the finished row back
     double per = 4.0 + esz_of(m) + (a.partial ? 4.0 * (a.splits + 1) : 0.0);
     LAUNCH(m, EXE_K_NORM, (double)rows * m->c.d_model * per, 0.0, launch_norm(a, m->stream));
@@ -535,14 +555,18 @@ static int run_norm(exe_model* m, const int32_t* row_index, int rows, const void
 
 // out = epilogue(norm(h) . W^T): one launch for a few short rows, else the norm into `a` and the product
 static int run_norm_gemm(exe_model* m, const int32_t* row_index, int rows, const void* g, const void* b, float out_scale, void* a,
-                         int N, const void* W, const void* bias, int act, int out_mode, void* out, const KvStore* kv = nullptr, int* kv_rows = nullptr)
+                         int N, const void* W, const void* bias, int act, int out_mode, void* out, const KvStore* kv = nullptr, int* kv_rows = nullptr, bool last = false)
 {
     const exe_config_t& c = m->c;
     NormArgs n{c.dtype, c.norm == EXE_NORM_RMSNORM, m->h, row_index, rows, c.d_model, g, b, c.norm_eps, out_scale, nullptr};
+    n.last = last;
     GemmArgs p{c.dtype, rows, N, c.d_model, nullptr, W, bias, act, 1.f, out_mode, out, nullptr, 0};
-    if (!m->pend.splits && norm_gemm_fits(n, p)) {
+    exe_model::Pending left = m->pend;
+    take_pending(m, n);
+    if (!norm_gemm_fits(n, p)) m->pend = left;
+    else {
         double e = esz_of(m);
-        LAUNCH(m, EXE_K_GEMM_SKINNY, ((double)rows + N) * c.d_model * e + (double)rows * N * (out_mode == OUT_T ? e : 4.0),
+        LAUNCH(m, EXE_K_GEMM_SKINNY, ((double)rows + N) * c.d_model * e + (double)rows * N * (out_mode == OUT_T ? e : 4.0) + 4.0 * n.splits * rows * c.d_model,
                2.0 * rows * N * c.d_model, launch_norm_gemm(n, p, m->stream));
         return EXE_OK;
     }
@@ -554,7 +578,7 @@ static int run_norm_gemm(exe_model* m, const int32_t* row_index, int rows, const
 static int finish_resid(exe_model* m)
 {
     if (!m->pend.splits) return EXE_OK;
-    GemmArgs g{m->c.dtype, m->pend.rows, m->c.d_model, 0, nullptr, nullptr, m->pend.bias, -1, 1.f, OUT_RESID, m->h, m->gemm_ws, m->gemm_ws_bytes};
+    GemmArgs g{m->c.dtype, m->pend.rows, m->c.d_model, 0, nullptr, nullptr, m->pend.bias, -1, 1.f, OUT_RESID, m->h, const_cast<float*>(m->pend.partial), 0};
     LAUNCH(m, EXE_K_OTHER, (double)g.M * g.N * 4.0 * (m->pend.splits + 2), 0.0, launch_splitk_reduce(g, m->pend.splits, m->stream));
     m->pend.splits = 0;
     return EXE_OK;
@@ -579,7 +603,8 @@ static int head_launches(exe_model* m, const int32_t* row_index_dev, int n, floa
     const exe_config_t& c = m->c;
     int r;
     float out_scale = c.arch == EXE_ARCH_ENC_DEC ? 1.f / sqrtf((float)c.d_model) : 1.f;
-    if ((r = run_norm_gemm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last, c.vocab, m->tok_emb, nullptr, -1, OUT_F32, logits))) return r;
+    if ((r = run_norm_gemm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last, c.vocab, m->tok_emb, nullptr, -1, OUT_F32, logits,
+                           nullptr, nullptr, true))) return r;
     if (tokens) LAUNCH(m, EXE_K_OTHER, (double)n * c.vocab * 4.0, 0.0, launch_argmax(logits, n, c.vocab, m->h_next, m->stream));
     return EXE_OK;
 }
@@ -1018,6 +1043,60 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
     return EXE_OK;
 }
 
+// All layers of a decode iteration of n rows as two (encoder-decoder: three) launches each, from the embedding or m->h on; leaves
+// the last block's partial sums pending.
+static int decode_layers_small(exe_model* m, int n, const DecodeDesc& d)
+{
+    const exe_config_t& c = m->c;
+    const bool encdec = c.arch == EXE_ARCH_ENC_DEC;
+    const double e = esz_of(m), D = c.d_model, F = c.d_ff;
+    float *x = m->h, *x_next = m->small_x, *part = m->small_part[0], *part_next = m->small_part[1];
+    SmallArgs a{c.dtype, n, c.d_model, c.norm == EXE_NORM_RMSNORM, c.norm_eps, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr};
+    if (c.has_embed) {
+        a.tokens = d.tok;
+        a.pos = d.pos;
+        a.tok_emb = m->tok_emb;
+        a.pos_emb = m->pos_emb;
+    }
+    auto begin = [&](const void* gain, const void* shift) {
+        a.gain = gain;
+        a.shift = shift;
+        a.x = x;
+        a.x_out = x_next;
+        a.partial = part;
+        a.out = part_next;
+    };
+    auto end = [&](int parts, const void* bias) {
+        a.n_part = parts;
+        a.part_bias = bias;
+        a.tokens = nullptr;
+        std::swap(x, x_next);
+        std::swap(part, part_next);
+    };
+    auto attention = [&](const DecLayerW& L, int layer, bool cross) -> int {
+        SmallAttn k{c.n_heads, c.head_dim, cross, cross ? L.w_xq : L.w_qkv, cross ? nullptr : L.b_qkv, cross ? L.w_xo : L.w_o, m->pool.ptr,
+                    cross ? d.xbase : d.base, cross ? d.xcap : d.cap, cross ? d.xlen : d.len, d.pos, layer, attn_scale(m),
+                    cross ? m->bias_x : encdec ? m->bias_dec : nullptr, m->radius};
+        begin(cross ? L.nx_g : L.n1_g, cross ? nullptr : L.n1_b);
+        double w = (cross ? 2.0 : 4.0) * m->inner * D, rows = n * D * 4.0 * (2 + a.n_part + c.n_heads);
+        LAUNCH(m, cross ? EXE_K_CROSS_ATTN : EXE_K_DECODE_ATTN, (cross ? d.x_bytes : d.self_bytes) + w * e + rows,
+               (cross ? d.x_flops : d.self_flops) + 2.0 * n * w, launch_small_attn(a, k, m->stream));
+        end(c.n_heads, cross ? nullptr : L.b_o);
+        return EXE_OK;
+    };
+    for (size_t l = 0; l < m->dec.size(); ++l) {
+        const DecLayerW& L = m->dec[l];
+        int r = attention(L, (int)l, false);
+        if (r || (encdec && (r = attention(L, (int)l, true)))) return r;
+        begin(L.n2_g, L.n2_b);
+        SmallFfn k{c.d_ff, L.w_1, L.b_1, c.act, L.w_2};
+        LAUNCH(m, EXE_K_GEMM_SKINNY, 2.0 * D * F * e + n * D * 4.0 * (2 + a.n_part + c.d_ff / SMALL_SLICE), 4.0 * n * D * F, launch_small_ffn(a, k, m->stream));
+        end(c.d_ff / SMALL_SLICE, L.b_2);
+    }
+    m->pend = exe_model::Pending{a.n_part, n, a.part_bias, part, x};
+    return EXE_OK;
+}
+
 extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids, const int32_t* tokens_in,
                                const int32_t* kv_lengths, const void* hidden_in, int32_t* next_tokens, void* out_device)
 {
@@ -1063,9 +1142,14 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
     m->pend.splits = 0;                    // h is about to be written anew
     HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
     int r;
-    if ((r = decode_input(m, dd, n, hidden_in))) return r;
-    for (size_t l = 0; l < m->dec.size(); ++l)
-        if ((r = decode_layer(m, m->dec[l], (int)l, n, dd, 3))) return r;
+    const bool small = m->small_x && small_decode_fits(c.dtype, n, c.d_model, c.n_heads, c.head_dim, c.d_ff);
+    if (!(small && c.has_embed) && (r = decode_input(m, dd, n, hidden_in))) return r;
+    if (small) {
+        if ((r = decode_layers_small(m, n, dd))) return r;
+    } else {
+        for (size_t l = 0; l < m->dec.size(); ++l)
+            if ((r = decode_layer(m, m->dec[l], (int)l, n, dd, 3))) return r;
+    }
     double e = esz_of(m);
     if (c.has_lm_head) {
         if ((r = run_head(m, nullptr, n, next_tokens, out_device))) return r;
