@@ -119,6 +119,10 @@ struct SmallArgs {               // the residual stream in front of a block, its
     // attention only, nullable: the rows are these embeddings, x is not read
     const int32_t *tokens = nullptr, *pos = nullptr;
     const void *tok_emb = nullptr, *pos_emb = nullptr;
+    // attention only, nullable: stage_bytes (as launch_stage takes them) that this launch copies for the launches behind it
+    const void* stage_from = nullptr;
+    void* stage_to = nullptr;
+    size_t stage_bytes = 0;
 };
 struct SmallAttn {               // arrays as in AttnCacheArgs; self-attention appends the rows' keys and values at len - 1
     int H, dh, cross;

@@ -40,6 +40,9 @@ template <typename T> struct SmallRow {
     const T *gain, *shift;               // of the block's norm; shift: LayerNorm only
     float eps;
     int rms;
+    const uint4* stage_from;             // what the first workgroup of the attention block copies for later launches
+    uint4* stage_to;
+    int stage_n;
 };
 
 constexpr int SA_WAVES = 16, SA_THREADS = SA_WAVES * 64, ATTN_FIRST = 2;     // waves, threads, row blocks in flight per wave
@@ -67,6 +70,8 @@ __global__ __launch_bounds__(SA_THREADS) void small_attn_kernel(SmallRow<T> in, 
     int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int rg = lane >> 4, cl = lane & 15;
     int chunks = d / (16 * EPL);
+    if (h == 0 && r == 0)
+        for (int i = tid; i < in.stage_n; i += SA_THREADS) in.stage_to[i] = in.stage_from[i];
 
     // The partial sums in front go out first, spread over all threads: group tid / d of them takes parts tid / d, + groups, ..
     constexpr int PB = 8;                                     // loads of a thread in flight
@@ -420,7 +425,8 @@ bool small_decode_fits(int dtype, int rows, int d, int H, int dh, int f)
 template <typename T> static SmallRow<T> small_row(const SmallArgs& a)
 {
     return SmallRow<T>{a.x, a.tokens, a.pos, (const T*)a.tok_emb, (const T*)a.pos_emb, a.partial, (const T*)a.part_bias, a.n_part, a.x_out,
-                       (const T*)a.gain, (const T*)a.shift, a.eps, a.rms};
+                       (const T*)a.gain, (const T*)a.shift, a.eps, a.rms, (const uint4*)a.stage_from, (uint4*)a.stage_to,
+                       (int)((a.stage_bytes + 15) / 16)};
 }
 
 template <typename T, int DH> static hipError_t small_attn(const SmallArgs& a, const SmallAttn& k, hipStream_t s)

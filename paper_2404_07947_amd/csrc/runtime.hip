@@ -1044,19 +1044,25 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
 }
 
 // All layers of a decode iteration of n rows as two (encoder-decoder: three) launches each, from the embedding or m->h on; leaves
-// the last block's partial sums pending.
-static int decode_layers_small(exe_model* m, int n, const DecodeDesc& d)
+// the last block's partial sums pending.  staged: bytes of descriptors that are in pinned memory only (with an embedding).  The first
+// launch then reads them there and copies them for the others: a read across the bus, about a microsecond, in place of a
+// launch of its own: two float layers of 256, 4 rows 65.4 -> 63.5 us a call, T5-style layers, 12 rows 88.7 -> 84.8.
+static int decode_layers_small(exe_model* m, int n, const DecodeDesc& d, size_t staged)
 {
     const exe_config_t& c = m->c;
     const bool encdec = c.arch == EXE_ARCH_ENC_DEC;
     const double e = esz_of(m), D = c.d_model, F = c.d_ff;
     float *x = m->h, *x_next = m->small_x, *part = m->small_part[0], *part_next = m->small_part[1];
     SmallArgs a{c.dtype, n, c.d_model, c.norm == EXE_NORM_RMSNORM, c.norm_eps, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr};
+    auto pinned = [&](auto* p) { return staged ? (decltype(p))(m->stage_h + ((unsigned char*)p - m->stage_d)) : p; };
     if (c.has_embed) {
-        a.tokens = d.tok;
-        a.pos = d.pos;
+        a.tokens = pinned(d.tok);
+        a.pos = pinned(d.pos);
         a.tok_emb = m->tok_emb;
         a.pos_emb = m->pos_emb;
+        a.stage_from = m->stage_h;
+        a.stage_to = m->stage_d;
+        a.stage_bytes = staged;
     }
     auto begin = [&](const void* gain, const void* shift) {
         a.gain = gain;
@@ -1070,12 +1076,13 @@ static int decode_layers_small(exe_model* m, int n, const DecodeDesc& d)
         a.n_part = parts;
         a.part_bias = bias;
         a.tokens = nullptr;
+        a.stage_bytes = staged = 0;
         std::swap(x, x_next);
         std::swap(part, part_next);
     };
     auto attention = [&](const DecLayerW& L, int layer, bool cross) -> int {
         SmallAttn k{c.n_heads, c.head_dim, cross, cross ? L.w_xq : L.w_qkv, cross ? nullptr : L.b_qkv, cross ? L.w_xo : L.w_o, m->pool.ptr,
-                    cross ? d.xbase : d.base, cross ? d.xcap : d.cap, cross ? d.xlen : d.len, d.pos, layer, attn_scale(m),
+                    pinned(cross ? d.xbase : d.base), pinned(cross ? d.xcap : d.cap), pinned(cross ? d.xlen : d.len), pinned(d.pos), layer, attn_scale(m),
                     cross ? m->bias_x : encdec ? m->bias_dec : nullptr, m->radius};
         begin(cross ? L.nx_g : L.n1_g, cross ? nullptr : L.n1_b);
         double w = (cross ? 2.0 : 4.0) * m->inner * D, rows = n * D * 4.0 * (2 + a.n_part + c.n_heads);
@@ -1140,12 +1147,14 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
         if (st.off > m->stage_bytes) return fail(EXE_ERR_ARG, "descriptor staging overflow");
     }
     m->pend.splits = 0;                    // h is about to be written anew
-    HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
     int r;
     const bool small = m->small_x && small_decode_fits(c.dtype, n, c.d_model, c.n_heads, c.head_dim, c.d_ff);
-    if (!(small && c.has_embed) && (r = decode_input(m, dd, n, hidden_in))) return r;
+    if (!(small && c.has_embed)) {
+        HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
+        if ((r = decode_input(m, dd, n, hidden_in))) return r;
+    }
     if (small) {
-        if ((r = decode_layers_small(m, n, dd))) return r;
+        if ((r = decode_layers_small(m, n, dd, c.has_embed ? st.off : 0))) return r;
     } else {
         for (size_t l = 0; l < m->dec.size(); ++l)
             if ((r = decode_layer(m, m->dec[l], (int)l, n, dd, 3))) return r;
