@@ -72,6 +72,41 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// Largest value and its index, the lowest of equal ones; a NaN is never taken.
+__device__ __forceinline__ void argmax_take(float& best, int& idx, float ov, int oi)
+{
+    if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
+}
+template <int CTRL> __device__ __forceinline__ int dpp_move_int(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true); }
+// over 16 lanes, then over the wave, in every lane (moves as in row_sum and rows_sum).  With shuffles, and one thread going through
+// the waves' candidates, 4 rows of 2048 in a decode iteration took 3.7 us, now 2.5.
+__device__ __forceinline__ void argmax_row16(float& best, int& idx)
+{
+    argmax_take(best, idx, dpp_move<0xB1>(best), dpp_move_int<0xB1>(idx));
+    argmax_take(best, idx, dpp_move<0x4E>(best), dpp_move_int<0x4E>(idx));
+    argmax_take(best, idx, dpp_move<0x141>(best), dpp_move_int<0x141>(idx));
+    argmax_take(best, idx, dpp_move<0x140>(best), dpp_move_int<0x140>(idx));
+}
+// over the four lanes l, l + 16, ..
+__device__ __forceinline__ void argmax_column(float& best, int& idx)
+{
+    auto bv = __builtin_amdgcn_permlane16_swap(__float_as_uint(best), __float_as_uint(best), false, false);
+    auto bi = __builtin_amdgcn_permlane16_swap((unsigned)idx, (unsigned)idx, false, false);
+    best = __uint_as_float(bv[0]);
+    idx = (int)bi[0];
+    argmax_take(best, idx, __uint_as_float(bv[1]), (int)bi[1]);
+    bv = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
+    bi = __builtin_amdgcn_permlane32_swap((unsigned)idx, (unsigned)idx, false, false);
+    best = __uint_as_float(bv[0]);
+    idx = (int)bi[0];
+    argmax_take(best, idx, __uint_as_float(bv[1]), (int)bi[1]);
+}
+__device__ __forceinline__ void argmax_rows(float& best, int& idx)
+{
+    argmax_row16(best, idx);
+    argmax_column(best, idx);
+}
+
 // GELU, erf form: x * Phi(x), with Phi(-t) = 2^-(1 + t * R(t)) for t >= 0.  R is a polynomial of degree 11, fitted to
 // (-log2(Phi(-t)) - 1) / t on [0, 9] by weighted least squares (weights iterated towards equal error, relative error of Phi
 // within 4e-8 for t < 2.5 and falling with Phi beyond); its leading coefficient is positive, so Phi vanishes beyond.

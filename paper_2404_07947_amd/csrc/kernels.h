@@ -85,6 +85,8 @@ hipError_t launch_embed(int dtype, const int32_t* tokens, const int32_t* pos, in
                         const void* pos_emb, float* h, hipStream_t s);
 hipError_t launch_load_hidden(int dtype, const void* x, int64_t n, float* h, hipStream_t s);
 hipError_t launch_store_hidden(int dtype, const float* h, int64_t n, void* out, hipStream_t s);
+// The largest of 16 neighbouring features of a row and its index, [feature / 16][16 rows]; index 0x7fffffff: all NaN.
+struct TopLogit { float value; int32_t index; };
 struct NormArgs {
     int dtype, rms;
     float* x;                    // residual rows; written only with `partial`
@@ -98,6 +100,7 @@ struct NormArgs {
     int splits = 0, partial_rows = 0;
     const void* bias = nullptr;
     bool last = false;           // nothing reads x after this norm
+    TopLogit* top = nullptr;     // launch_norm_gemm only (float outputs, no bias, alpha 1), may be pinned: see TopLogit
 };
 hipError_t launch_norm(const NormArgs& a, hipStream_t s);
 // A norm and the product behind it in one launch of the streaming kernel (a.A is not read), where norm_gemm_fits says so.

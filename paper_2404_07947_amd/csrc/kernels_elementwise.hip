@@ -376,35 +376,6 @@ hipError_t launch_kv_append_paged(int dtype, const void* src, int ld, int k_off,
 }
 
 // ---------------------------------------------------------------- greedy argmax
-__device__ __forceinline__ void argmax_take(float& best, int& idx, float ov, int oi)
-{
-    if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
-}
-template <int CTRL> __device__ __forceinline__ int dpp_move_int(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true); }
-// over 16 lanes, then over the wave, in every lane (moves as in row_sum and rows_sum).  With shuffles, and one thread going through
-// the waves' candidates, 4 rows of 2048 in a decode iteration took 3.7 us, now 2.5.
-__device__ __forceinline__ void argmax_row16(float& best, int& idx)
-{
-    argmax_take(best, idx, dpp_move<0xB1>(best), dpp_move_int<0xB1>(idx));
-    argmax_take(best, idx, dpp_move<0x4E>(best), dpp_move_int<0x4E>(idx));
-    argmax_take(best, idx, dpp_move<0x141>(best), dpp_move_int<0x141>(idx));
-    argmax_take(best, idx, dpp_move<0x140>(best), dpp_move_int<0x140>(idx));
-}
-__device__ __forceinline__ void argmax_rows(float& best, int& idx)
-{
-    argmax_row16(best, idx);
-    auto bv = __builtin_amdgcn_permlane16_swap(__float_as_uint(best), __float_as_uint(best), false, false);
-    auto bi = __builtin_amdgcn_permlane16_swap((unsigned)idx, (unsigned)idx, false, false);
-    best = __uint_as_float(bv[0]);
-    idx = (int)bi[0];
-    argmax_take(best, idx, __uint_as_float(bv[1]), (int)bi[1]);
-    bv = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
-    bi = __builtin_amdgcn_permlane32_swap((unsigned)idx, (unsigned)idx, false, false);
-    best = __uint_as_float(bv[0]);
-    idx = (int)bi[0];
-    argmax_take(best, idx, __uint_as_float(bv[1]), (int)bi[1]);
-}
-
 // One workgroup per row; ties resolve to the lowest index at every level of the reduction.  D loads in flight per thread: one at
 // a time, a row of 50 272 logits took 20 us (with four 7).  `out` may be pinned host memory.
 template <int V, unsigned D> __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int n, int32_t* __restrict__ out)

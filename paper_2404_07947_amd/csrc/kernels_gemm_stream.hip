@@ -53,6 +53,7 @@ template <typename T> struct NormIn {
     const float* partial;            // [n_part][partial_rows][K], added to x first, and their bias (nullable)
     const T* part_bias;
     int n_part, partial_rows;
+    TopLogit* top;                   // nullable
 };
 constexpr int NORM_STAGES = 3;
 // Where it is taken: each workgroup repeats the norm, so the rows have to be few and short.  A launch less (2.4 us on the GPU, 2.6
@@ -283,6 +284,15 @@ __device__ __forceinline__ void stream_body(
 #pragma unroll
         for (int w = 1; w < NW; ++w) v += red[(w * NT * MT + x) * 64 + lane];
         int m = m0 + (x % MT) * 16 + fr, n = n0 + (x / MT) * 16 + 4 * g;
+        if (NORM && norm.top) {                      // uniform
+            float best = -INFINITY;
+            int idx = 0x7fffffff;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (n + j < N) argmax_take(best, idx, v[j], n + j);
+            argmax_column(best, idx);
+            if (g == 0 && m < M) norm.top[blockIdx.x * 16 + fr] = TopLogit{best, idx};
+        }
         if (m >= M || n >= N || (MA == 1 && fr >= 8)) continue;
         if (n_split > 1) *(f32x4*)(partial + ((int64_t)z * M + m) * N + n) = v;
         else epilogue_store4<T>(v, m, n, N, bias, act, alpha, out_mode, out);
@@ -380,7 +390,7 @@ template <typename T, int MA> static hipError_t launch_norm_stream(const NormArg
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
     hipError_t e = limit[dev].raise((const void*)kern, norm_lds<T>(MA, NORM_MAX_K));
     if (e != hipSuccess) return e;
-    NormIn<T> in{n.x, n.row_index, (const T*)n.gain, (const T*)n.shift, n.eps, n.out_scale, n.rms, n.partial, (const T*)n.bias, n.partial ? n.splits : 0, n.partial_rows};
+    NormIn<T> in{n.x, n.row_index, (const T*)n.gain, (const T*)n.shift, n.eps, n.out_scale, n.rms, n.partial, (const T*)n.bias, n.partial ? n.splits : 0, n.partial_rows, n.top};
     kern<<<dim3((a.N + 15) / 16), stream_waves(1, MA) * 64, norm_lds<T>(MA, a.K), s>>>(
         a.M, a.N, a.K, (const T*)a.W, (const T*)a.bias, a.act, a.alpha, a.out_mode, a.out, in);
     return hipGetLastError();

@@ -1,0 +1,51 @@
+"""The tokens of a small model's calls against the logits they return: vocabularies at the edges of the LM head's 16 features a
+workgroup, rows at the edges of its 8 and 16 a workgroup and of the limits beyond which a kernel of its own picks them, equal logits (the lowest index), rows of NaN and of infinities."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2404_07947_amd as exe
+import workload as wl
+from gpu_util import DEV, kv_bytes_per_token
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("vocab,dtype", [(16, wl.DTYPE_F32), (260, wl.DTYPE_BF16), (1028, wl.DTYPE_F32), (2048, wl.DTYPE_BF16), (4096, wl.DTYPE_F32)])
+@pytest.mark.parametrize("kind", ["plain", "ties", "nan", "all_nan", "inf"])
+def test_tokens_are_the_argmax_of_the_logits(n, vocab, dtype, kind):
+    shape = wl.tiny_shape().replace(n_layers=1, vocab=vocab, max_pos=64, dtype=dtype)
+    w = [t.to(DEV) for t in wl.make_weights(shape, 3)]
+    emb = next(t for t in w if tuple(t.shape) == (vocab, shape.d_model))
+    rng = np.random.default_rng(n)
+    used = 4                                               # the tokens that are fed; the others' rows are free to change
+    if kind == "ties":
+        emb[used:] = emb[used:used + 3].repeat(-(-vocab // 3), 1)[:vocab - used] * 40
+    elif kind == "nan":
+        emb[torch.from_numpy(rng.permutation(np.arange(used, vocab))[:vocab // 2])] = float("nan")
+    elif kind == "all_nan":
+        emb[used:] = float("nan")
+        emb[:used, 0] = float("nan")                       # and with them the rows themselves
+    elif kind == "inf":
+        emb[used:, 0] = torch.from_numpy(rng.choice([np.inf, -np.inf], size=vocab - used)).to(emb)
+    cfg = exe.config_from_shape(shape, kv_pool_bytes=4096 * kv_bytes_per_token(shape), max_seqs=64, max_batch_tokens=512, max_batch_seqs=64)
+    m = exe.Model(cfg, w)
+    lens = rng.integers(1, 8, size=n).astype(np.int32)
+    out = torch.zeros((n, vocab), dtype=torch.float32, device=DEV)
+    print(f"head tokens n={n} vocab={vocab} {kind}", flush=True)
+
+    def check(tokens):
+        logits = out.cpu().numpy()
+        low = np.where(np.isnan(logits), -np.inf, logits)
+        want = np.where(np.isnan(logits).all(axis=1), 0, low.argmax(axis=1))
+        for r in np.nonzero(np.isneginf(low.max(axis=1)) & ~np.isnan(logits).all(axis=1))[0]:
+            want[r] = np.nonzero(~np.isnan(logits[r]))[0][0]
+        assert np.array_equal(tokens, want)
+        if kind == "ties":                                 # they are met: the largest logit is there more than once, or of a fed token
+            assert n < 8 or max((logits == logits.max(axis=1, keepdims=True)).sum(axis=1)) > 1
+
+    check(m.encode(np.arange(n), lens, rng.integers(0, used, size=int(lens.sum())).astype(np.int32), reserve_lengths=lens + 3, out_device=out))
+    for t in range(2):
+        check(m.decode_step(np.arange(n), rng.integers(0, used, size=n).astype(np.int32), lens + t + 1, out_device=out))
+    m.close()
