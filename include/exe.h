@@ -311,6 +311,11 @@ int exe_op_gemm_model(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int
  * beyond whole rounds of 256 x 256 tiles go to a second, separately planned launch: ask again with M - *rows_first). */
 int exe_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t* route, int32_t* cfg, int32_t* splits,
                      int32_t* rows_first);
+/* How the model calls launch a projection whose last features are keys and values (host function): *n_launches in the order
+ * of their rows, of the first `cap` of them rows[i] and stores[i] = 1 if such a launch can store keys and values in the cache
+ * itself; *kv_rows = the leading rows that an encode call counts on being stored so (it copies the others' keys and values). */
+int exe_op_gemm_kv_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t cap, int32_t* rows, int32_t* stores,
+                        int32_t* n_launches, int32_t* kv_rows);
 /* exe_op_gemm for bf16 operands whose rows are lda / ldw elements apart (>= K, multiples of 8; K a multiple of 64;
  * shapes the MFMA tile kernel serves only).  Row strides that are not a multiple of 4 KiB spread a tile's rows
  * over more memory channels. */

@@ -694,41 +694,79 @@ static bool stores_kv(const GemmArgs& a, const Plan& p)
            (a.dtype == DT_F32 || (is_large(p.cfg) && a.K >= LARGE_MIN_K));
 }
 
+// The launches of a product in the order of their rows, f(first row, rows): one, or where whole rounds of tiles go first (split_rows)
+// those rows' own launches and then the others'.  What is launched and what is said about it beforehand both come from here:
+// either part may be cut again.
+template <typename F> static void each_launch(int dtype, int row, int M, int N, int K, int mode, F&& f)
+{
+    int M1 = split_rows(dtype, M, N, K, mode);
+    if (M1 == M) {
+        f(row, M);
+        return;
+    }
+    each_launch(dtype, row, M1, N, K, mode & ~GEMM_DEFER, f);
+    each_launch(dtype, row + M1, M - M1, N, K, mode & ~GEMM_DEFER, f);
+}
+
 int gemm_kv_rows(const GemmArgs& a)
 {
     if (a.M <= 0 || a.force_splits) return 0;
-    int M1 = split_rows(a.dtype, a.M, a.N, a.K, launch_mode(a));
-    if (!stores_kv(a, make_plan(a.dtype, M1, a.N, a.K, launch_mode(a)))) return 0;
-    if (M1 == a.M) return M1;
-    GemmArgs tail = a;
-    tail.M -= M1;
-    return M1 + gemm_kv_rows(tail);
+    int stored = 0;
+    each_launch(a.dtype, 0, a.M, a.N, a.K, launch_mode(a), [&](int row, int rows) {
+        if (stored == row && stores_kv(a, make_plan(a.dtype, rows, a.N, a.K, launch_mode(a)))) stored += rows;
+    });
+    return stored;
 }
+
+int gemm_launches(const GemmArgs& a, int cap, int32_t* rows, int32_t* stores)
+{
+    int n = 0;
+    each_launch(a.dtype, 0, a.M, a.N, a.K, launch_mode(a), [&](int, int M) {
+        if (n < cap) {
+            rows[n] = M;
+            stores[n] = stores_kv(a, make_plan(a.dtype, M, a.N, a.K, launch_mode(a)));
+        }
+        ++n;
+    });
+    return n;
+}
+
+static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s);
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
 {
     if (a.pending) *a.pending = 0;
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    int mode = launch_mode(a);
-    int M1 = a.force_splits ? a.M : split_rows(a.dtype, a.M, a.N, a.K, mode);
-    if (M1 < a.M) {
-        GemmArgs head = a, tail = a;
-        head.pending = tail.pending = nullptr;
-        head.M = M1;
-        tail.M = a.M - M1;
-        size_t esz = a.dtype == DT_BF16 ? 2 : 4, osz = a.out_mode == OUT_T ? esz : 4;
-        tail.A = (const char*)a.A + (size_t)M1 * (a.lda ? a.lda : a.K) * esz;
-        tail.out = (char*)a.out + (size_t)M1 * a.N * osz;
-        KvStore rest;
-        if (a.kv) {
-            rest = *a.kv;
-            rest.row += M1;
-            rest.step += M1;
-            tail.kv = gemm_kv_rows(a) > M1 ? &rest : nullptr;
+    const int mode = launch_mode(a);
+    if (a.force_splits) return launch_rows(a, mode, s);
+    const size_t esz = a.dtype == DT_BF16 ? 2 : 4, osz = a.out_mode == OUT_T ? esz : 4;
+    hipError_t e = hipSuccess;
+    int stored = 0;                          // leading rows whose keys and values are in the cache: see gemm_kv_rows
+    each_launch(a.dtype, 0, a.M, a.N, a.K, mode, [&](int row, int rows) {
+        if (e != hipSuccess) return;
+        GemmArgs part = a;
+        const bool whole = rows == a.M;
+        if (!whole) part.pending = nullptr;
+        part.M = rows;
+        part.A = (const char*)a.A + (size_t)row * (a.lda ? a.lda : a.K) * esz;
+        part.out = (char*)a.out + (size_t)row * a.N * osz;
+        KvStore kv;
+        part.kv = nullptr;
+        if (a.kv && stored == row && stores_kv(a, make_plan(a.dtype, rows, a.N, a.K, mode))) {
+            kv = *a.kv;
+            kv.row += row;
+            kv.step += row;
+            part.kv = &kv;
+            stored += rows;
         }
-        hipError_t e = launch_gemm(head, s);
-        return e != hipSuccess ? e : launch_gemm(tail, s);
-    }
+        e = launch_rows(part, whole ? mode : mode & ~GEMM_DEFER, s);
+    });
+    return e;
+}
+
+// one launch (and, of split sums, their reduction)
+static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s)
+{
     Plan p = make_plan(a.dtype, a.M, a.N, a.K, mode);
     if (a.force_splits) {
         p.route = 0;
@@ -738,11 +776,6 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         p.spread = 1;
     }
     if (needs_generic(a)) p.route = 2;
-    if (a.kv && (a.force_splits || !stores_kv(a, p))) {
-        GemmArgs plain = a;
-        plain.kv = nullptr;
-        return launch_gemm(plain, s);
-    }
     if (p.route == 2) {
         dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
         if (a.dtype == DT_F32)

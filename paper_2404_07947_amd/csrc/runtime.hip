@@ -1975,6 +1975,18 @@ extern "C" int exe_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, 
     return EXE_OK;
 }
 
+extern "C" int exe_op_gemm_kv_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t cap, int32_t* rows, int32_t* stores,
+                                   int32_t* n_launches, int32_t* kv_rows)
+{
+    if (M < 1 || N < 1 || K < 1 || cap < 0 || (cap > 0 && (!rows || !stores)) || !n_launches || !kv_rows)
+        return fail(EXE_ERR_ARG, "bad gemm plan arguments");
+    GemmArgs g{dtype, M, N, K, nullptr, nullptr, nullptr, -1, 1.f, OUT_T, nullptr, nullptr, 0};
+    g.few_rows = true;
+    *n_launches = gemm_launches(g, cap, rows, stores);
+    *kv_rows = gemm_kv_rows(g);
+    return EXE_OK;
+}
+
 extern "C" int exe_op_paged_index_check(int32_t dtype, int32_t dh, int32_t block_size, int32_t n_waves, int32_t len)
 {
     int shift = 0;

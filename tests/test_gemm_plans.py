@@ -42,3 +42,30 @@ def test_float_rows_beyond_32_bit_offsets_take_the_kernel_with_64_bit_ones(M, N)
 @pytest.mark.parametrize("dtype,K", [(F32, 1 << 24), (BF16, 1 << 25)])
 def test_the_streaming_gemm_refuses_80_such_rows(dtype, K):
     assert exe.lib().exe_op_gemm_stream(None, dtype, 8, 128, K, 64, 64, None, -1, 1.0, 2, 64, 5, 1, 1, None, 0) == -2
+
+
+# (features, depth) of the projections whose last features are keys and values: OPT-13B, the GPT-3-175B width, T5-11B's encoder and its
+# cross keys and values, 1024 wide, 256 wide, and widths between
+KV_SHAPES = [(15360, 5120), (36864, 12288), (49152, 1024), (32768, 1024), (3072, 1024), (768, 256)] + [(3 * d, d) for d in (5888, 8960, 11776, 13824)]
+
+
+@pytest.mark.parametrize("N,K", KV_SHAPES)
+@pytest.mark.parametrize("dtype", [BF16, F32])
+def test_rows_counted_on_are_the_rows_stored(dtype, N, K):
+    """A product of many rows is cut into launches, each part again where that pays; an encode call copies the keys and values behind
+    those that it counts on.  Every token count to 20 000: the leading rows whose launches store are what it counts on, and a launch
+    is not cut once more when it is made."""
+    for M in range(1, 20001 if dtype == BF16 else 3001):
+        launches, counted = exe.exe_op_gemm_kv_plan(dtype, M, N, K)
+        assert sum(r for r, _ in launches) == M
+        lead = next((i for i, (_, stores) in enumerate(launches) if not stores), len(launches))
+        assert counted == sum(r for r, _ in launches[:lead]), (M, launches)
+        for r, stores in launches if len(launches) > 1 else ():
+            assert exe.exe_op_gemm_kv_plan(dtype, r, N, K)[0] == [(r, stores)], (M, launches)
+
+
+def test_launches_cut_twice():
+    """The counts that test_gpu_kv_store.py runs: in the middle of three launches 256 rows that do not store."""
+    assert exe.exe_op_gemm_kv_plan(BF16, 2049, 36864, 12288) == ([(1792, 1), (256, 0), (1, 0)], 1792)
+    assert exe.exe_op_gemm_kv_plan(BF16, 2298, 36864, 12288) == ([(1792, 1), (256, 0), (250, 0)], 1792)
+    assert exe.exe_op_gemm_kv_plan(BF16, 16385, 17664, 5888) == ([(16128, 1), (256, 0), (1, 0)], 16128)

@@ -66,3 +66,25 @@ def test_cross_keys_and_values(dtype, lens):
             tol = 2.0 ** -16 + (2.0 ** -8 if dtype == wl.DTYPE_BF16 else 0.0)
             assert float((kv[l] - ref).abs().max() / ref.abs().max()) < tol, (i, l)
         t0 += L
+
+
+# rows and heads of 128 at which the QKV product is three launches and the second, of 256 rows, does not store (asserted in
+# test_gemm_plans.py): counts at the GPT-3-175B width, and a long batch of a narrower one
+@pytest.mark.parametrize("rows,heads", [(2049, 96), (2298, 96), (16385, 46)])
+def test_a_launch_cut_twice(rows, heads):
+    d = heads * 128
+    shape = wl.gpt3_175b_share_shape(1).replace(d_model=d, n_heads=heads, d_ff=512)
+    print(f"kv store rows={rows} heads={heads}", flush=True)
+    w = wl.make_weights(shape, 5, device=DEV)
+    lens = np.array([700, 333, 1, rows - 1034], dtype=np.int32)
+    x = torch.randn((rows, d), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV).bfloat16()
+    got = []
+    for block in (0, 16):
+        m = model_of(shape, w, rows, 4, block)
+        out = torch.zeros((rows, d), dtype=torch.bfloat16, device=DEV)
+        m.encode(np.arange(4), lens, None, hidden_in=x, want_tokens=False, out_device=out)
+        got.append(([m.seq_export(i)[0] for i in range(4)], out.cpu()))
+        m.close()
+    for i in range(4):
+        assert np.array_equal(got[0][0][i], got[1][0][i]), i
+    assert torch.equal(got[0][1], got[1][1])
