@@ -316,6 +316,10 @@ int exe_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t* ro
  * itself; *kv_rows = the leading rows that an encode call counts on being stored so (it copies the others' keys and values). */
 int exe_op_gemm_kv_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t cap, int32_t* rows, int32_t* stores,
                         int32_t* n_launches, int32_t* kv_rows);
+/* The element of the cache at which such a launch stores the first of the dh features of a position, for (layer, K or V, head)
+ * number `head` of an extent of capacity `cap` that starts at element `base`: base + (head * cap + pos) * dh (host function;
+ * the kernels' own arithmetic). */
+int64_t exe_op_kv_store_index(int64_t base, int32_t cap, int32_t head, int32_t pos, int32_t dh);
 /* exe_op_gemm for bf16 operands whose rows are lda / ldw elements apart (>= K, multiples of 8; K a multiple of 64;
  * shapes the MFMA tile kernel serves only).  Row strides that are not a multiple of 4 KiB spread a tile's rows
  * over more memory channels. */

@@ -13,7 +13,7 @@ _lib = None
 DECLARED_SYMBOLS = [
     "exe_expected_weights", "exe_model_load", "exe_model_free", "exe_encode", "exe_decode_step",
     "exe_seq_release", "exe_seq_length", "exe_kv_stats", "exe_seq_export_bytes", "exe_seq_export", "exe_seq_import", "exe_seq_reserve", "exe_kv_compact", "exe_profile", "exe_run_rra", "exe_kernel_timing",
-    "exe_kernel_times", "exe_op_gemm", "exe_op_gemm_workspace", "exe_op_gemm_plan", "exe_op_gemm_kv_plan", "exe_op_gemm_stream", "exe_op_gemm_model", "exe_op_gemm_ld", "exe_op_gemm_noalloc", "exe_op_gemm_noalloc_max_workspace", "exe_op_paged_index_check", "exe_op_norm", "exe_op_resid_norm", "exe_op_prefill_attention", "exe_op_prefill_tiles",
+    "exe_kernel_times", "exe_op_gemm", "exe_op_gemm_workspace", "exe_op_gemm_plan", "exe_op_gemm_kv_plan", "exe_op_kv_store_index", "exe_op_gemm_stream", "exe_op_gemm_model", "exe_op_gemm_ld", "exe_op_gemm_noalloc", "exe_op_gemm_noalloc_max_workspace", "exe_op_paged_index_check", "exe_op_norm", "exe_op_resid_norm", "exe_op_prefill_attention", "exe_op_prefill_tiles",
     "exe_op_decode_attention", "exe_op_decode_attention_paged", "exe_probe_peaks", "exe_probe_ingest", "exe_op_argmax", "exe_rel_bucket", "exe_last_error", "exe_version",
     # exe_sched.h (host only)
     "exe_sim_completion", "exe_sim_step_ms", "exe_sim_rra", "exe_sim_waa", "exe_sched_search", "exe_sched_rra",
@@ -138,6 +138,7 @@ def lib():
     L.exe_op_gemm_workspace.restype = C.c_uint64
     L.exe_op_gemm_plan.argtypes = [i32, i32, i32, i32, ip, ip, ip, ip]
     L.exe_op_gemm_kv_plan.argtypes = [i32, i32, i32, i32, i32, ip, ip, ip, ip]
+    L.exe_op_kv_store_index.argtypes, L.exe_op_kv_store_index.restype = [C.c_int64, i32, i32, i32, i32], C.c_int64
     L.exe_op_gemm_ld.argtypes = [vp, i32, i32, i32, i32, vp, i32, vp, i32, vp, i32, C.c_float, i32, vp, vp, C.c_uint64]
     L.exe_op_gemm_stream.argtypes = [vp, i32, i32, i32, i32, vp, vp, vp, i32, C.c_float, i32, vp, i32, i32, i32, vp, C.c_uint64]
     L.exe_op_gemm_model.argtypes = [vp, i32, i32, i32, i32, vp, vp, vp, i32, C.c_float, i32, vp, i32, i32, vp, C.c_uint64, ip]
@@ -354,6 +355,13 @@ def exe_op_gemm_kv_plan(dtype: int, M: int, N: int, K: int):
     _check(lib().exe_op_gemm_kv_plan(dtype, M, N, K, 64, rows, stores, C.byref(n), C.byref(kv)))
     assert n.value <= 64
     return list(zip(rows[:n.value], stores[:n.value])), kv.value
+
+
+def exe_op_kv_store_index(base: int, cap: int, head: int, pos: int, dh: int) -> int:
+    i = int(lib().exe_op_kv_store_index(base, cap, head, pos, dh))
+    if i < 0:
+        _check(i)
+    return i
 
 
 def exe_op_gemm_ld(dtype, M, N, K, A, lda, W, ldw, bias, act, alpha, out_mode, out, workspace=None, stream=None):

@@ -56,21 +56,21 @@ enum EpiMode { EPI_PARTIAL = 0, EPI_F32, EPI_RESID, EPI_T, EPI_T_RELU, EPI_T_GEL
 // prompt, 20 OPT-13B layers).
 template <int P> struct KvRows {
     int64_t row[P];
-    int32_t step[P];
+    int32_t cap[P];
     template <typename F> __device__ __forceinline__ void load(const KvStore& kv, int M, F m_of)
     {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             int m = m_of(p) < M ? m_of(p) : M - 1;
             row[p] = kv.row[m];
-            step[p] = kv.step[m];
+            cap[p] = kv.cap[m];
         }
     }
     // element offset of the first of the wave's features `c0` (uniform, >= first_col) in row p
     __device__ __forceinline__ int64_t at(const KvStore& kv, int p, int c0) const
     {
         int c = c0 - kv.first_col;
-        return row[p] + (int64_t)(kv.head0 + (c >> kv.dh_shift)) * step[p] + (c & ((1 << kv.dh_shift) - 1));
+        return kv_at(row[p], cap[p], kv.head0 + (c >> kv.dh_shift), kv.dh_shift) + (c & ((1 << kv.dh_shift) - 1));
     }
 };
 

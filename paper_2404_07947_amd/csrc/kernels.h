@@ -9,14 +9,17 @@
 namespace exe {
 
 // Where a projection's key / value features go instead of `out`: straight into the cache.  Feature n >= first_col of row m is
-// element row[m] + (head0 + (n - first_col) / dh) * step[m] + (n - first_col) % dh of `pool` (the keys of all heads, then the
-// values), dh = 2^dh_shift; first_col is a multiple of 64.
+// element kv_at(row[m], cap[m], head0 + (n - first_col) / dh, dh_shift) + (n - first_col) % dh of `pool` (the keys of all heads, then
+// the values), dh = 2^dh_shift; first_col is a multiple of 64.
 struct KvStore {
     void* pool = nullptr;
     const int64_t* row = nullptr;
-    const int32_t* step = nullptr;
+    const int32_t* cap = nullptr;
     int first_col = 0, dh_shift = 0, head0 = 0;
 };
+// row: the first element of the position in the extent's first head; cap * dh, the elements of a head, need not fit 32 bits
+__host__ __device__ __forceinline__ int64_t kv_row_of(int64_t base, int pos, int dh) { return base + (int64_t)pos * dh; }
+__host__ __device__ __forceinline__ int64_t kv_at(int64_t row, int cap, int head, int dh_shift) { return row + ((int64_t)head * cap << dh_shift); }
 
 struct GemmArgs {
     int dtype;            // DT_F32 / DT_BF16: type of A, W, bias and (for OUT_T) out
@@ -152,9 +155,9 @@ hipError_t launch_kv_append(int dtype, const void* src, int ld, int k_off, int v
 hipError_t launch_kv_append_paged(int dtype, const void* src, int ld, int k_off, int v_off, int T, const int32_t* tok_b,
                                   const int32_t* tok_pos, const int32_t* table, int table_w, int shift, int H, int dh,
                                   void* layer_pool, hipStream_t s);
-// row[t] and step[t] of KvStore for token t of an encode batch: base[tok_b[t]] + tok_pos[t] * dh and cap[tok_b[t]] * dh
+// row[t] and row_cap[t] of KvStore for token t of an encode batch, whose sequence tok_b[t] has the extent base, cap
 hipError_t launch_kv_rows(const int32_t* tok_b, const int32_t* tok_pos, const int64_t* base, const int32_t* cap, int T, int dh,
-                          int64_t* row, int32_t* step, hipStream_t s);
+                          int64_t* row, int32_t* row_cap, hipStream_t s);
 hipError_t launch_argmax(const float* logits, int rows, int n, int32_t* out, hipStream_t s);
 
 struct AttnCacheArgs {       // one query row per batch entry against that sequence's cached K/V

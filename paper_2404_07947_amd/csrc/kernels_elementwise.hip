@@ -318,20 +318,20 @@ hipError_t launch_kv_append(int dtype, const void* src, int ld, int k_off, int v
 }
 
 __global__ void kv_rows_kernel(const int32_t* __restrict__ tok_b, const int32_t* __restrict__ tok_pos, const int64_t* __restrict__ base,
-                               const int32_t* __restrict__ cap, int T, int dh, int64_t* __restrict__ row, int32_t* __restrict__ step)
+                               const int32_t* __restrict__ cap, int T, int dh, int64_t* __restrict__ row, int32_t* __restrict__ row_cap)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
     int b = tok_b[t];
-    row[t] = base[b] + (int64_t)tok_pos[t] * dh;
-    step[t] = cap[b] * dh;
+    row[t] = kv_row_of(base[b], tok_pos[t], dh);
+    row_cap[t] = cap[b];
 }
 
 hipError_t launch_kv_rows(const int32_t* tok_b, const int32_t* tok_pos, const int64_t* base, const int32_t* cap, int T, int dh,
-                          int64_t* row, int32_t* step, hipStream_t s)
+                          int64_t* row, int32_t* row_cap, hipStream_t s)
 {
     if (T <= 0) return hipSuccess;
-    kv_rows_kernel<<<(T + 255) / 256, 256, 0, s>>>(tok_b, tok_pos, base, cap, T, dh, row, step);
+    kv_rows_kernel<<<(T + 255) / 256, 256, 0, s>>>(tok_b, tok_pos, base, cap, T, dh, row, row_cap);
     return hipGetLastError();
 }
 

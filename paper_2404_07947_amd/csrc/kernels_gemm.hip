@@ -755,7 +755,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         if (a.kv && stored == row && stores_kv(a, make_plan(a.dtype, rows, a.N, a.K, mode))) {
             kv = *a.kv;
             kv.row += row;
-            kv.step += row;
+            kv.cap += row;
             part.kv = &kv;
             stored += rows;
         }

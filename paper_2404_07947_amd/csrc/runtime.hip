@@ -183,9 +183,9 @@ struct exe_model {
     float* logits = nullptr;
     float* gemm_ws = nullptr;
     size_t gemm_ws_bytes = 0;
-    void* aux = nullptr;                  // holds kv_row, kv_step, small_x and small_part
+    void* aux = nullptr;                  // holds kv_row, kv_cap, small_x and small_part
     int64_t* kv_row = nullptr;            // per token of an encode batch, see KvStore
-    int32_t* kv_step = nullptr;
+    int32_t* kv_cap = nullptr;
     // descriptor staging
     unsigned char *stage_h = nullptr, *stage_d = nullptr;
     size_t stage_bytes = 0;
@@ -481,7 +481,7 @@ extern "C" int exe_model_load(const exe_config_t* cfg, const exe_tensor_t* weigh
         m->small_part[1] = m->small_part[0] + small_row * small_parts;
     }
     m->kv_row = (int64_t*)((float*)m->aux + small_floats);
-    m->kv_step = (int32_t*)(m->kv_row + rows);
+    m->kv_cap = (int32_t*)(m->kv_row + rows);
 
     // descriptor staging: token-sized int arrays (3), tile list (2 ints per 128 query rows + one per sequence),
     // and per-sequence arrays (int64 x2, int32 x6)
@@ -713,8 +713,8 @@ static int prepare_kv(exe_model* m, EncodeDesc& d, int T, int N, const void* W, 
     GemmArgs g{c.dtype, T, N, c.d_model, m->a, W, bias, -1, 1.f, OUT_T, m->qkv, m->gemm_ws, m->gemm_ws_bytes};
     g.few_rows = true;
     if (!gemm_kv_rows(g)) return EXE_OK;
-    d.kv = KvStore{m->pool.ptr, m->kv_row, m->kv_step, N - 2 * m->inner, c.head_dim == 128 ? 7 : 6, 0};
-    HIP_TRY(launch_kv_rows(d.tok_b, d.tok_pos, base, cap, T, c.head_dim, m->kv_row, m->kv_step, m->stream));
+    d.kv = KvStore{m->pool.ptr, m->kv_row, m->kv_cap, N - 2 * m->inner, c.head_dim == 128 ? 7 : 6, 0};
+    HIP_TRY(launch_kv_rows(d.tok_b, d.tok_pos, base, cap, T, c.head_dim, m->kv_row, m->kv_cap, m->stream));
     return EXE_OK;
 }
 
@@ -1985,6 +1985,12 @@ extern "C" int exe_op_gemm_kv_plan(int32_t dtype, int32_t M, int32_t N, int32_t 
     *n_launches = gemm_launches(g, cap, rows, stores);
     *kv_rows = gemm_kv_rows(g);
     return EXE_OK;
+}
+
+extern "C" int64_t exe_op_kv_store_index(int64_t base, int32_t cap, int32_t head, int32_t pos, int32_t dh)
+{
+    if ((dh != 64 && dh != 128) || cap < 1 || head < 0 || pos < 0 || pos >= cap) return fail(EXE_ERR_ARG, "bad K/V index arguments");
+    return kv_at(kv_row_of(base, pos, dh), cap, head, dh == 128 ? 7 : 6);
 }
 
 extern "C" int exe_op_paged_index_check(int32_t dtype, int32_t dh, int32_t block_size, int32_t n_waves, int32_t len)

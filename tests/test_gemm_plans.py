@@ -69,3 +69,13 @@ def test_launches_cut_twice():
     assert exe.exe_op_gemm_kv_plan(BF16, 2049, 36864, 12288) == ([(1792, 1), (256, 0), (1, 0)], 1792)
     assert exe.exe_op_gemm_kv_plan(BF16, 2298, 36864, 12288) == ([(1792, 1), (256, 0), (250, 0)], 1792)
     assert exe.exe_op_gemm_kv_plan(BF16, 16385, 17664, 5888) == ([(16128, 1), (256, 0), (1, 0)], 16128)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_elements_of_a_head_beyond_32_bits(dh):
+    """Extents are as long as the pool: 2^31 elements a head and more."""
+    for cap in (8, 1 << 20, (1 << 31) // dh - 8, (1 << 31) // dh, (1 << 32) // dh + 8, (1 << 31) - 8):
+        for head in (0, 1, 7, 2 * 96 * 40 - 1):
+            for pos in (0, 1, cap - 1):
+                for base in (0, 1 << 33):
+                    assert exe.exe_op_kv_store_index(base, cap, head, pos, dh) == base + (head * cap + pos) * dh
