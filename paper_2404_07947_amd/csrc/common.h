@@ -62,9 +62,21 @@ __device__ __forceinline__ float rows_sum(float x)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// Over all lanes.  (Six shuffles before, each a trip through the LDS pipe: LayerNorm of bf16 2048 x 4096 10.1 -> 9.4 us, 8192 x 1024
-// 9.1 -> 8.6.)
-__device__ __forceinline__ float wave_sum(float v) { return rows_sum(row_sum<16>(v)); }
+// Over all lanes, added in the order of a butterfly from lane ^ 32 down to lane ^ 1 (a norm's bits, and what follows from them in a
+// 16-bit model, depend on it).  Six shuffles, each a trip through the LDS pipe, took longer: LayerNorm of bf16 2048 x 4096 10.2 us, now
+// 9.5, 8192 x 1024 9.0 and 8.6.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    v += dpp_move<0x128>(v);                 // row_ror:8: lane ^ 8
+    v += dpp_move<0x124>(v);                 // row_ror:4: as lane ^ 4, since lanes eight apart hold the same by now
+    v += dpp_move<0x4E>(v);                  // quad_perm: lane ^ 2
+    v += dpp_move<0xB1>(v);                  // quad_perm: lane ^ 1
+    return v;
+}
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll

@@ -68,3 +68,18 @@ def test_resid_norm(dtype, rms, splits, d):
         assert np.array_equal(got[rest], x.numpy()[rest])
         ref = reference(rms, full[pick].astype(np.float32), g, b, 1e-6, 1.0)
         assert relerr(out.float().cpu().numpy(), ref) < (1e-5 if dtype == F32 else 2.0 ** -8)
+
+
+def test_order_of_a_wave_s_sum():
+    """A wave adds up from lane ^ 32 down to lane ^ 1 (bits of 16-bit models follow from it): opposite values half a row of 256 apart
+    cancel before anything is lost beside them.  2^27 has a last place of 16, the other lanes sum to 3 to 9 each: an order that adds a
+    neighbour first shifts the mean, and with it the small elements, by several per cent."""
+    x = torch.rand((1, 256), generator=torch.Generator().manual_seed(3)) * 1.5 + 0.75
+    x[0, :4], x[0, 128:132] = torch.tensor([2.0 ** 27, 0, 0, 0]), torch.tensor([-2.0 ** 27, 0, 0, 0])
+    g, b = torch.ones(256), torch.zeros(256)
+    out = torch.zeros((1, 256), device=DEV)
+    exe.exe_op_norm(F32, 0, x.to(DEV), None, 1, 256, g.to(DEV), b.to(DEV), 1e-5, 1.0, out)
+    small = np.r_[4:128, 132:256]
+    ref = reference(0, x.numpy(), g, b, 1e-5, 1.0)[0, small]
+    # float sum of 62 lanes, difference from the mean and two products: 2^-24 each of values below 2.25, relative to differences of 0.75
+    assert relerr(out.cpu().numpy()[0, small], ref) < 80 * 2.0 ** -24
