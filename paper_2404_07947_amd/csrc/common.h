@@ -119,31 +119,34 @@ __device__ __forceinline__ void argmax_rows(float& best, int& idx)
     argmax_column(best, idx);
 }
 
-// GELU, erf form: x * Phi(x), with Phi(-t) = 2^-(1 + t * R(t)) for t >= 0.  R is a polynomial of degree 11, fitted to
-// (-log2(Phi(-t)) - 1) / t on [0, 9] by weighted least squares (weights iterated towards equal error, relative error of Phi
-// within 4e-8 for t < 2.5 and falling with Phi beyond); its leading coefficient is positive, so Phi vanishes beyond.
-// What bounds it: the vector ALU of an epilogue.  0.5 * x * (1 + erff(x / sqrt 2)) took about 50 instructions, both of erff's
-// branches in most waves, this takes 20: bf16 8192 x 4096, K 1024 83.4 -> 72.9 us (60.6 without an activation), 8192 x 49152, K 12288
-// 6528 -> 6394, float 12288 x 1024, K 256 66.8 -> 63.3.
-// Error against 64 bits over normally distributed x 3.4e-8 of the result (2-norm; the erff form, with an erf rounded once, 3.8e-8),
-// and for negative x, where 1 + erf cancels, smaller throughout (x in [-3, -2]: 7e-7 relative, there 1e-5).
+// GELU, erf form: x * Phi(x), by Phi(-t) = 2^-(t * R(t)) / 2 for t = |x|: max(x, 0) - t / 2 * 2^-(t * R(t)), whose last step rounds once.
+// R is of degree 11, a weighted least-squares fit on [0, 9] (weights iterated towards equal error; each coefficient rounded to
+// float, the ones above it fitted again), its leading coefficient positive, so that Phi vanishes beyond.  With the coefficients as
+// they stand, in 64 bits: relative error of Phi(-t) 1.9e-9 for t below 3, then growing (4e-9 to 4, 5e-8 to 5, 3e-5 to 7, 5e-2 to
+// 9) while the absolute error falls (9e-10 below 1, 2e-11 to 3, 1e-13 to 5, 1e-14 to 7, 3e-17 to 9).
+// What bounds it: the vector ALU of an epilogue, here 21 instructions (the power counted four times).  0.5 * x * (1 + erff(x / sqrt 2)),
+// with both of erff's branches in waves of wide inputs, took longer: bf16 8192 x 4096, K 1024 76.2 us, now 69.8 (53.6 without an
+// activation), 8192 x 49152, K 12288 6350 and 6243; of narrow ones one branch is met, float 12288 x 1024, K 256 at a deviation of
+// 0.32 63.4 and 64.7.
+// Error against 64 bits, 2-norm relative, and of 0.5 * x * (1 + erf) in float with an erf rounded once: x normal with deviation
+// 0.1 3.1e-8 and 3.8e-8, 0.32 3.1e-8 and 4.0e-8, 1 2.7e-8 and 3.7e-8, 2.2 2.5e-8 and 3.4e-8; and no larger in any stretch of x.
 __device__ __forceinline__ float gelu(float x)
 {
-    float t = fabsf(x);
-    float r = 1.1646179e-10f;
-    r = fmaf(r, t, -6.0699383e-09f);
-    r = fmaf(r, t, 1.4037859e-07f);
-    r = fmaf(r, t, -1.8968133e-06f);
-    r = fmaf(r, t, 1.6492046e-05f);
-    r = fmaf(r, t, -9.3861607e-05f);
-    r = fmaf(r, t, 3.1115115e-04f);
-    r = fmaf(r, t, -2.8213937e-05f);
-    r = fmaf(r, t, -6.9429772e-03f);
-    r = fmaf(r, t, 5.2453075e-02f);
-    r = fmaf(r, t, 4.5921367e-01f);
-    r = fmaf(r, t, 1.1511053e+00f);
-    float e = __builtin_amdgcn_exp2f(-fmaf(r, t, 1.f));      // Phi(-t)
-    return x * (x < 0.f ? e : 1.f - e);
+    float t = fabsf(fminf(x, 3.4028235e+38f));               // finite for +inf, whose result is +inf; -inf gives NaN, as -inf * 0 does
+    float r = 2.61296429e-10f;
+    r = fmaf(r, t, -1.1455894e-08f);
+    r = fmaf(r, t, 2.27268643e-07f);
+    r = fmaf(r, t, -2.69496695e-06f);
+    r = fmaf(r, t, 2.10983981e-05f);
+    r = fmaf(r, t, -1.11249807e-04f);
+    r = fmaf(r, t, 3.54487536e-04f);
+    r = fmaf(r, t, -9.85201768e-05f);
+    r = fmaf(r, t, -6.87161693e-03f);
+    r = fmaf(r, t, 5.24111241e-02f);
+    r = fmaf(r, t, 4.59225982e-01f);
+    r = fmaf(r, t, 1.15110397f);
+    float p = __builtin_amdgcn_exp2f(-(r * t));              // 2 Phi(-t)
+    return fmaf(-0.5f * t, p, x < 0.f ? -0.f : x);
 }
 
 __device__ __forceinline__ float act_apply(float x, int act)
