@@ -705,16 +705,20 @@ struct EncodeDesc {
     KvStore kv;                 // where the projection stores keys and values itself (pool null: it does not)
 };
 
-// Keys and values straight from an encode batch's projections (N features, the last ones keys and values) into the extents `base`,
-// `cap`, where its launches can do that.
-static int prepare_kv(exe_model* m, EncodeDesc& d, int T, int N, const void* W, const void* bias, const int64_t* base, const int32_t* cap)
+// Keys and values straight from an encode batch's projections (every layer's QKV; encoder-decoder: every decoder layer's cross keys
+// and values) into the batch's extents, where their launches can do that.
+static int prepare_kv(exe_model* m, EncodeDesc& d, int T)
 {
     const exe_config_t& c = m->c;
-    GemmArgs g{c.dtype, T, N, c.d_model, m->a, W, bias, -1, 1.f, OUT_T, m->qkv, m->gemm_ws, m->gemm_ws_bytes};
+    if (paged(m)) return EXE_OK;
+    const bool cross = c.arch == EXE_ARCH_ENC_DEC;
+    const int N = (cross ? 2 : 3) * m->inner;
+    GemmArgs g{c.dtype, T, N, c.d_model, m->a, cross ? m->dec[0].w_xkv : m->dec[0].w_qkv, cross ? nullptr : m->dec[0].b_qkv, -1, 1.f, OUT_T,
+               m->qkv, m->gemm_ws, m->gemm_ws_bytes};
     g.few_rows = true;
     if (!gemm_kv_rows(g)) return EXE_OK;
     d.kv = KvStore{m->pool.ptr, m->kv_row, m->kv_cap, N - 2 * m->inner, c.head_dim == 128 ? 7 : 6, 0};
-    HIP_TRY(launch_kv_rows(d.tok_b, d.tok_pos, base, cap, T, c.head_dim, m->kv_row, m->kv_cap, m->stream));
+    HIP_TRY(launch_kv_rows(d.tok_b, d.tok_pos, cross ? d.xbase : d.base, cross ? d.xcap : d.cap, T, c.head_dim, m->kv_row, m->kv_cap, m->stream));
     return EXE_OK;
 }
 
@@ -726,6 +730,16 @@ static int append_rest(exe_model* m, int T, int done, int ld, int k_off, const E
            launch_kv_append(m->c.dtype, (const char*)m->qkv + (size_t)done * ld * m->esz, ld, k_off, k_off + m->inner, T - done, d.tok_b + done,
                             d.tok_pos + done, base, cap, layer, m->c.n_heads, m->c.head_dim, m->pool.ptr, m->stream));
     return EXE_OK;
+}
+
+// a decoder layer's cross keys and values from the encoder output in m->a
+static int cross_kv(exe_model* m, int T, const EncodeDesc& d, int layer)
+{
+    KvStore kv = d.kv;
+    kv.head0 = layer * 2 * m->c.n_heads;
+    int stored = 0;
+    int r = run_gemm(m, T, 2 * m->inner, m->c.d_model, m->a, m->dec[layer].w_xkv, nullptr, -1, 1.f, OUT_T, m->qkv, kv.pool ? &kv : nullptr, &stored);
+    return r ? r : append_rest(m, T, stored, 2 * m->inner, 0, d, d.xbase, d.xcap, layer);
 }
 
 // One encode (prefill) layer over T packed tokens of n sequences.  parts: bit 0 = everything but the
@@ -926,19 +940,13 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
         else
             LAUNCH(m, EXE_K_OTHER, (double)T * c.d_model * (esz_of(m) + 4.0), 0.0,
                    launch_load_hidden(c.dtype, hidden_in, (int64_t)T * c.d_model, m->h, m->stream));
-        int r = encdec ? prepare_kv(m, d, T, 2 * m->inner, m->dec[0].w_xkv, nullptr, d.xbase, d.xcap)
-              : d.table ? EXE_OK : prepare_kv(m, d, T, 3 * m->inner, m->dec[0].w_qkv, m->dec[0].b_qkv, d.base, d.cap);
+        int r = prepare_kv(m, d, T);
         if (r || (r = encode_layers(m, n, T, d, lens))) return r;
         if (encdec) {
             // encoder output (after the final norm) -> every decoder layer's cross keys/values
             if ((r = run_norm(m, nullptr, T, m->enc_fin_g, nullptr, 1.f, m->a))) return r;
-            for (size_t l = 0; l < m->dec.size(); ++l) {
-                KvStore kv = d.kv;
-                kv.head0 = (int)l * 2 * c.n_heads;
-                int stored = 0;
-                if ((r = run_gemm(m, T, 2 * m->inner, c.d_model, m->a, m->dec[l].w_xkv, nullptr, -1, 1.f, OUT_T, m->qkv, kv.pool ? &kv : nullptr, &stored)) ||
-                    (r = append_rest(m, T, stored, 2 * m->inner, 0, d, d.xbase, d.xcap, (int)l))) return r;
-            }
+            for (size_t l = 0; l < m->dec.size(); ++l)
+                if ((r = cross_kv(m, T, d, (int)l))) return r;
             if (out_device)
                 HIP_TRY(hipMemcpyAsync(out_device, m->a, (size_t)T * c.d_model * m->esz, hipMemcpyDeviceToDevice, m->stream));
             HIP_TRY(hipStreamSynchronize(m->stream));
@@ -1581,7 +1589,7 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
         EventTimer t;
         HIP_TRY(t.init());
         int r;
-        if (phase == 0 && !encdec && (r = prepare_kv(m, ed, rows_n, 3 * m->inner, L->w_qkv, L->b_qkv, ed.base, ed.cap))) return r;
+        if (phase == 0 && (r = prepare_kv(m, ed, rows_n))) return r;
         for (int w = 0; w < 3; ++w)
             if ((r = layer(3))) return r;
         // pass A: whole-layer latency per repetition (launch gaps included), no per-kernel events
@@ -1619,10 +1627,7 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
             HIP_TRY(hipEventRecord(t.a, m->stream));
             for (int i = 0; i < n_steps; ++i) {
                 if ((r = run_norm(m, nullptr, rows_n, m->enc_fin_g, nullptr, 1.f, m->a))) return r;
-                if ((r = run_gemm(m, rows_n, 2 * m->inner, c.d_model, m->a, m->dec[0].w_xkv, nullptr, -1, 1.f, OUT_T, m->qkv))) return r;
-                LAUNCH(m, EXE_K_OTHER, 0.0, 0.0,
-                       launch_kv_append(c.dtype, m->qkv, 2 * m->inner, 0, m->inner, rows_n, ed.tok_b, ed.tok_pos, ed.xbase,
-                                        ed.xcap, 0, c.n_heads, c.head_dim, m->pool.ptr, m->stream));
+                if ((r = cross_kv(m, rows_n, ed, 0))) return r;
             }
             HIP_TRY(hipEventRecord(t.b, m->stream));
             HIP_TRY(hipEventSynchronize(t.b));

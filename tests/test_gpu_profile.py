@@ -66,3 +66,18 @@ def test_profile_table_encoder_decoder():
     assert enc[0]["head_ms"] > 0 and enc[0]["attn_ms_per_layer"] > 0
     assert m.kv_stats()["used_bytes"] == 0
     m.close()
+
+
+@pytest.mark.parametrize("length,copied", [(2048, 0), (4, 1)])
+def test_cross_keys_and_values_are_timed_as_an_encode_call_stores_them(length, copied):
+    """2 x 2048 tokens: the projections store them; 8: a copy of their own does.  With kernel timing on, what is timed last (final norm and
+    cross keys and values) stays booked."""
+    m = make_model(wl.small_t5_shape(wl.DTYPE_BF16).replace(head_dim=128, n_heads=4, d_model=512, d_ff=1024), pool_tokens=16 * 4096)
+    m.kernel_timing(True)
+    m.profile(0, [2], [length], n_steps=3)
+    k = {r["kind"]: r["launches"] for r in m.kernel_times()}
+    assert k["norm"] == 3 and k["gemm_tile"] + k["gemm_skinny"] == 3 and k["other"] == 3 * copied
+    m.kernel_timing(True)
+    m.encode([0, 1], [length] * 2, np.zeros(2 * length, np.int32), want_tokens=False)
+    assert {r["kind"]: r["launches"] for r in m.kernel_times()}["other"] == 1 + 2 * copied          # the embedding; two decoder layers
+    m.close()
