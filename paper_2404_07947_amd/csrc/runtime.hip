@@ -1085,65 +1085,105 @@ static int decode_layer(exe_model* m, const DecLayerW& L, int layer, int n, cons
     return EXE_OK;
 }
 
-// All layers of a decode iteration of n rows as two (encoder-decoder: three) launches each, from the embedding or m->h on; leaves
-// the last block's partial sums pending.  staged: bytes of descriptors that are in pinned memory only (with an embedding).  The first
-// launch then reads them there and copies them for the others: a read across the bus, about a microsecond, in place of a
-// launch of its own: two float layers of 256, 4 rows 65.4 -> 63.5 us a call, T5-style layers, 12 rows 88.7 -> 84.8.
-static int decode_layers_small(exe_model* m, int n, const DecodeDesc& d, size_t staged)
+// Layers of a small model's decode iteration of n rows, two (encoder-decoder: three) launches each, from the embedding or m->h on.
+// The residual stream and the blocks' partial sums go back and forth between two buffers each.  staged: bytes of descriptors that are
+// in pinned memory only, and the rows are their embeddings.  The first launch then reads them there and copies them for the
+// others: a read across the bus, about a microsecond, in place of a launch of its own: two float layers of 256, 4 rows 65.4 -> 63.5 us
+// a call, T5-style layers, 12 rows 88.7 -> 84.8.
+struct SmallChain {
+    exe_model* m;
+    int n;
+    const DecodeDesc* d;
+    size_t staged;
+    float *x, *x_next, *part, *part_next;
+    SmallArgs a;
+};
+
+template <typename P> static P* small_pinned(const SmallChain& s, P* p)
+{
+    return s.staged ? (P*)(s.m->stage_h + ((unsigned char*)p - s.m->stage_d)) : p;
+}
+
+static SmallChain small_begin(exe_model* m, int n, const DecodeDesc& d, size_t staged)
 {
     const exe_config_t& c = m->c;
-    const bool encdec = c.arch == EXE_ARCH_ENC_DEC;
-    const double e = esz_of(m), D = c.d_model, F = c.d_ff;
-    float *x = m->h, *x_next = m->small_x, *part = m->small_part[0], *part_next = m->small_part[1];
-    SmallArgs a{c.dtype, n, c.d_model, c.norm == EXE_NORM_RMSNORM, c.norm_eps, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr};
-    auto pinned = [&](auto* p) { return staged ? (decltype(p))(m->stage_h + ((unsigned char*)p - m->stage_d)) : p; };
-    if (c.has_embed) {
-        a.tokens = pinned(d.tok);
-        a.pos = pinned(d.pos);
-        a.tok_emb = m->tok_emb;
-        a.pos_emb = m->pos_emb;
-        a.stage_from = m->stage_h;
-        a.stage_to = m->stage_d;
-        a.stage_bytes = staged;
+    SmallChain s{m, n, &d, staged, m->h, m->small_x, m->small_part[0], m->small_part[1],
+                 SmallArgs{c.dtype, n, c.d_model, c.norm == EXE_NORM_RMSNORM, c.norm_eps, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr}};
+    if (staged) {
+        s.a.tokens = small_pinned(s, d.tok);
+        s.a.pos = small_pinned(s, d.pos);
+        s.a.tok_emb = m->tok_emb;
+        s.a.pos_emb = m->pos_emb;
+        s.a.stage_from = m->stage_h;
+        s.a.stage_to = m->stage_d;
+        s.a.stage_bytes = staged;
     }
-    auto begin = [&](const void* gain, const void* shift) {
-        a.gain = gain;
-        a.shift = shift;
-        a.x = x;
-        a.x_out = x_next;
-        a.partial = part;
-        a.out = part_next;
-    };
-    auto end = [&](int parts, const void* bias) {
-        a.n_part = parts;
-        a.part_bias = bias;
-        a.tokens = nullptr;
-        a.stage_bytes = staged = 0;
-        std::swap(x, x_next);
-        std::swap(part, part_next);
-    };
-    auto attention = [&](const DecLayerW& L, int layer, bool cross) -> int {
-        SmallAttn k{c.n_heads, c.head_dim, cross, cross ? L.w_xq : L.w_qkv, cross ? nullptr : L.b_qkv, cross ? L.w_xo : L.w_o, m->pool.ptr,
-                    pinned(cross ? d.xbase : d.base), pinned(cross ? d.xcap : d.cap), pinned(cross ? d.xlen : d.len), pinned(d.pos), layer, attn_scale(m),
-                    cross ? m->bias_x : encdec ? m->bias_dec : nullptr, m->radius};
-        begin(cross ? L.nx_g : L.n1_g, cross ? nullptr : L.n1_b);
-        double w = (cross ? 2.0 : 4.0) * m->inner * D, rows = n * D * 4.0 * (2 + a.n_part + c.n_heads);
-        LAUNCH(m, cross ? EXE_K_CROSS_ATTN : EXE_K_DECODE_ATTN, (cross ? d.x_bytes : d.self_bytes) + w * e + rows,
-               (cross ? d.x_flops : d.self_flops) + 2.0 * n * w, launch_small_attn(a, k, m->stream));
-        end(c.n_heads, cross ? nullptr : L.b_o);
-        return EXE_OK;
-    };
-    for (size_t l = 0; l < m->dec.size(); ++l) {
-        const DecLayerW& L = m->dec[l];
-        int r = attention(L, (int)l, false);
-        if (r || (encdec && (r = attention(L, (int)l, true)))) return r;
-        begin(L.n2_g, L.n2_b);
-        SmallFfn k{c.d_ff, L.w_1, L.b_1, c.act, L.w_2};
-        LAUNCH(m, EXE_K_GEMM_SKINNY, 2.0 * D * F * e + n * D * 4.0 * (2 + a.n_part + c.d_ff / SMALL_SLICE), 4.0 * n * D * F, launch_small_ffn(a, k, m->stream));
-        end(c.d_ff / SMALL_SLICE, L.b_2);
-    }
-    m->pend = exe_model::Pending{a.n_part, n, a.part_bias, part, x};
+    return s;
+}
+
+static void small_block(SmallChain& s, const void* gain, const void* shift)
+{
+    s.a.gain = gain;
+    s.a.shift = shift;
+    s.a.x = s.x;
+    s.a.x_out = s.x_next;
+    s.a.partial = s.part;
+    s.a.out = s.part_next;
+}
+
+static void small_block_done(SmallChain& s, int parts, const void* bias)
+{
+    s.a.n_part = parts;
+    s.a.part_bias = bias;
+    s.a.tokens = nullptr;
+    s.a.stage_bytes = s.staged = 0;
+    std::swap(s.x, s.x_next);
+    std::swap(s.part, s.part_next);
+}
+
+static int small_attention(SmallChain& s, const DecLayerW& L, int layer, bool cross)
+{
+    exe_model* m = s.m;
+    const exe_config_t& c = m->c;
+    const DecodeDesc& d = *s.d;
+    SmallAttn k{c.n_heads, c.head_dim, cross, cross ? L.w_xq : L.w_qkv, cross ? nullptr : L.b_qkv, cross ? L.w_xo : L.w_o, m->pool.ptr,
+                small_pinned(s, cross ? d.xbase : d.base), small_pinned(s, cross ? d.xcap : d.cap), small_pinned(s, cross ? d.xlen : d.len),
+                small_pinned(s, d.pos), layer, attn_scale(m), cross ? m->bias_x : c.arch == EXE_ARCH_ENC_DEC ? m->bias_dec : nullptr, m->radius};
+    small_block(s, cross ? L.nx_g : L.n1_g, cross ? nullptr : L.n1_b);
+    double D = c.d_model, w = (cross ? 2.0 : 4.0) * m->inner * D, rows = s.n * D * 4.0 * (2 + s.a.n_part + c.n_heads);
+    LAUNCH(m, cross ? EXE_K_CROSS_ATTN : EXE_K_DECODE_ATTN, (cross ? d.x_bytes : d.self_bytes) + w * esz_of(m) + rows,
+           (cross ? d.x_flops : d.self_flops) + 2.0 * s.n * w, launch_small_attn(s.a, k, m->stream));
+    small_block_done(s, c.n_heads, cross ? nullptr : L.b_o);
     return EXE_OK;
+}
+
+// parts: bit 0 = the feed-forward block, bit 1 = the attention blocks
+static int small_layer(SmallChain& s, const DecLayerW& L, int layer, int parts)
+{
+    exe_model* m = s.m;
+    const exe_config_t& c = m->c;
+    int r;
+    if (parts & 2)
+        if ((r = small_attention(s, L, layer, false)) || (c.arch == EXE_ARCH_ENC_DEC && (r = small_attention(s, L, layer, true)))) return r;
+    if (parts & 1) {
+        small_block(s, L.n2_g, L.n2_b);
+        SmallFfn k{c.d_ff, L.w_1, L.b_1, c.act, L.w_2};
+        double D = c.d_model, F = c.d_ff;
+        LAUNCH(m, EXE_K_GEMM_SKINNY, 2.0 * D * F * esz_of(m) + s.n * D * 4.0 * (2 + s.a.n_part + c.d_ff / SMALL_SLICE), 4.0 * s.n * D * F,
+               launch_small_ffn(s.a, k, m->stream));
+        small_block_done(s, c.d_ff / SMALL_SLICE, L.b_2);
+    }
+    return EXE_OK;
+}
+
+// leaves the last block's partial sums to what follows (run_norm, run_norm_gemm, finish_resid)
+static void small_end(const SmallChain& s) { s.m->pend = exe_model::Pending{s.a.n_part, s.n, s.a.part_bias, s.part, s.x}; }
+
+// whether a decode iteration of n rows runs so
+static bool small_decode(const exe_model* m, int n)
+{
+    const exe_config_t& c = m->c;
+    return m->small_x && small_decode_fits(c.dtype, n, c.d_model, c.n_heads, c.head_dim, c.d_ff);
 }
 
 extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids, const int32_t* tokens_in,
@@ -1190,13 +1230,16 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
     }
     m->pend.splits = 0;                    // h is about to be written anew
     int r;
-    const bool small = m->small_x && small_decode_fits(c.dtype, n, c.d_model, c.n_heads, c.head_dim, c.d_ff);
+    const bool small = small_decode(m, n);
     if (!(small && c.has_embed)) {
         HIP_TRY(launch_stage(m->stage_h, m->stage_d, st.off, m->stream));
         if ((r = decode_input(m, dd, n, hidden_in))) return r;
     }
     if (small) {
-        if ((r = decode_layers_small(m, n, dd, c.has_embed ? st.off : 0))) return r;
+        SmallChain chain = small_begin(m, n, dd, c.has_embed ? st.off : 0);
+        for (size_t l = 0; l < m->dec.size(); ++l)
+            if ((r = small_layer(chain, m->dec[l], (int)l, 3))) return r;
+        small_end(chain);
     } else {
         for (size_t l = 0; l < m->dec.size(); ++l)
             if ((r = decode_layer(m, m->dec[l], (int)l, n, dd, 3))) return r;
@@ -1580,7 +1623,12 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
         rows_n = n;
         L = &m->dec[0];
     }
+    // a small model's decode layer takes the partial sums of the one before with it, as in an iteration of many layers
+    const bool small = phase == 1 && small_decode(m, n);
+    SmallChain chain{};
+    if (small) chain = small_begin(m, n, dd, 0);
     auto layer = [&](int parts) -> int {
+        if (small) return small_layer(chain, *L, 0, parts);
         return phase == 0 ? encode_layer(m, *L, 0, n, rows_n, ed, ab, af, parts) : decode_layer(m, *L, 0, n, dd, parts);
     };
     auto body = [&]() -> int {
@@ -1635,9 +1683,15 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
             HIP_TRY(hipEventElapsedTime(&ms, t.a, t.b));
             head = ms / n_steps * c.n_dec_layers;
         } else if (c.has_lm_head) {
+            if (small && (r = layer(1))) return r;         // the partial sums in front of the head are a feed-forward's
+            auto head_once = [&]() -> int {
+                if (small) small_end(chain);
+                return head_launches(m, phase == 0 ? ed.last : nullptr, n, m->logits, true);
+            };
+            if ((r = head_once())) return r;               // its kernels may not have run yet
             HIP_TRY(hipEventRecord(t.a, m->stream));
             for (int i = 0; i < n_steps; ++i)
-                if ((r = head_launches(m, phase == 0 ? ed.last : nullptr, n, m->logits, true))) return r;
+                if ((r = head_once())) return r;
             HIP_TRY(hipEventRecord(t.b, m->stream));
             HIP_TRY(hipEventSynchronize(t.b));
             float ms = 0.f;
