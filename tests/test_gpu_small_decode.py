@@ -18,7 +18,8 @@ def decoder_only(dtype, d, H, dh, f, layers, hidden):
     return s.replace(has_embed=0, has_lm_head=0, vocab=0, pos=wl.POS_NONE, max_pos=0) if hidden else s
 
 
-# (rows at and beyond the blocks' 16 and the limit of 32), widths from one chunk of 256 bytes to four, one slice of 64 to 32
+# (rows at and beyond the blocks' 16 and the limit of 32), widths from one chunk of 256 bytes to four, one slice of 64 to 32.  Beyond
+# 12 rows the two last shapes in bf16, 512 wide with 512 features of all heads, run as launches of their own: see the work limit below.
 @pytest.mark.parametrize("n", [1, 2, 16, 17, 32, 33])
 @pytest.mark.parametrize("dtype,d,H,dh,f,layers,hidden", [
     (F32, 64, 1, 64, 64, 1, 0), (F32, 192, 3, 64, 2048, 2, 0), (F32, 256, 2, 128, 320, 3, 0), (F32, 256, 4, 64, 1024, 2, 1),
@@ -77,3 +78,28 @@ def test_encoder_decoder(n, dtype, d, H, dh, f, layers, cross_bias):
         ref.append(np.stack([o.decode(i, int(fed[i]))[1] for i in range(n)]))
     m.close()
     assert row_relerr(np.stack(got), np.stack(ref)) < TOL[dtype]
+
+
+# the limit of rows x heads x head size x width, 3 * 2^20, at 12 rows of 512 x 512 (and in float of 256 x 1024), and wide bf16 rows
+# below it at more than 16 rows
+EDGES = [(n, *k) for n in (12, 13) for k in ((BF16, 512, 4, 128), (BF16, 512, 8, 64), (F32, 256, 16, 64))]
+EDGES += [(n, BF16, 512, H, 64) for n in (17, 32) for H in (1, 2, 3)] + [(17, BF16, 512, 5, 64), (18, BF16, 512, 5, 64), (19, BF16, 512, 5, 64), (20, BF16, 512, 5, 64), (17, BF16, 512, 2, 128)]
+
+
+@pytest.mark.parametrize("n,dtype,d,H,dh", EDGES)
+def test_at_the_work_limit(n, dtype, d, H, dh):
+    test_decoder_only(n, dtype, d, H, dh, 1024, 2, 0)
+
+
+@pytest.mark.parametrize("n,dtype,d,H,dh", EDGES + [(n, F32, 256, 4, 64) for n in (1, 32, 33)])
+def test_which_launches_an_iteration_makes(n, dtype, d, H, dh):
+    """A launch for the attention block and one for the feed-forward of each layer within the limits, else four products a layer."""
+    layers = 2
+    m, _, _ = make_pair(decoder_only(dtype, d, H, dh, 1024, layers, 0), 5, pool_tokens=8192)
+    m.encode(np.arange(n), np.full(n, 3), np.zeros(3 * n, np.int32), reserve_lengths=np.full(n, 8))
+    m.kernel_timing(True)
+    m.decode_step(np.arange(n), np.zeros(n, np.int32), np.full(n, 4))
+    k = {r["kind"]: r["launches"] for r in m.kernel_times()}
+    m.close()
+    fused = n <= 32 and n * H * dh * d <= 3 << 20
+    assert k["decode_attn"] == layers and k["gemm_skinny"] == (1 if fused else 4) * layers + 1
