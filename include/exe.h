@@ -251,7 +251,11 @@ int exe_run_rra(exe_model_t* m, const exe_rra_config_t* cfg, int32_t n_requests,
  * Enabling it serialises nothing but adds two event records per launch.
  */
 /* EXE_K_GEMM_TILE: GEMM launches with more than 256 rows (MFMA-bound); EXE_K_GEMM_SKINNY: at most 256 rows
- * (the weights are streamed once: HBM-bound). */
+ * (the weights are streamed once: HBM-bound).  Launches that take several of these together are booked whole under one class:
+ * a projection with the norm in front of it (few short rows) as the GEMM; decode iterations of small models (extents, no paged
+ * pool) per layer as EXE_K_DECODE_ATTN (norm, q, k, v, self-attention, out-projection), EXE_K_CROSS_ATTN (the same of
+ * cross-attention) and EXE_K_GEMM_SKINNY (norm and feed-forward).  Bytes are algorithmic: weights count once a launch, however
+ * many workgroups read them. */
 enum { EXE_K_GEMM_TILE = 0, EXE_K_GEMM_SKINNY = 1, EXE_K_PREFILL_ATTN = 2, EXE_K_DECODE_ATTN = 3,
        EXE_K_CROSS_ATTN = 4, EXE_K_NORM = 5, EXE_K_OTHER = 6, EXE_K_COUNT = 7 };
 typedef struct exe_kernel_time {

@@ -30,7 +30,7 @@ def test_gelu_values(dtype, rows, k):
     ref = x * ndtr(x)
     err = np.abs(got - ref)
     # Float, x in (-3, 0): the exponent t * R(t) is below 16 (8.6 at 3): its rounding and that of R in front of it move its power by
-    # (2^-21 + 3 * 2^-23) * ln 2 at most, power and product add 2^-23 and 2^-24: 0.7 * 2^-20.  For positive x all of it enters
+    # (2^-21 + 3 * 2^-23) * ln 2 at most, power and product add 2^-23 and 2^-24: 0.8 * 2^-20.  For positive x all of it enters
     # relative to Phi >= 1/2, with exponents below 1 where the two are of a size.
     # bf16: the rounding of the result on top, half a unit of 8 significant bits: 2^-8 of the value at most.
     rnd = 0.0 if dtype == wl.DTYPE_F32 else 2.0 ** -8
