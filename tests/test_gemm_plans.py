@@ -64,8 +64,12 @@ def test_rows_counted_on_are_the_rows_stored(dtype, N, K):
             assert exe.exe_op_gemm_kv_plan(dtype, r, N, K)[0] == [(r, stores)], (M, launches)
 
 
-def test_launches_cut_twice():
-    """The counts that test_gpu_kv_store.py runs: in the middle of three launches 256 rows that do not store."""
+def test_launches_that_the_cache_tests_run():
+    """The counts that test_gpu_kv_store.py runs: in the middle of three launches 256 rows that do not store; two launches, the second
+    of a row; float launches that store, from 2049 rows on."""
+    assert exe.exe_op_gemm_kv_plan(BF16, 5377, 3072, 512) == ([(5376, 1), (1, 0)], 5376)
+    assert exe.exe_op_gemm_kv_plan(BF16, 10753, 1536, 512) == ([(10752, 1), (1, 0)], 10752)
+    assert exe.exe_op_gemm_kv_plan(F32, 2101, 512, 256) == ([(2101, 1)], 2101)
     assert exe.exe_op_gemm_kv_plan(BF16, 2049, 36864, 12288) == ([(1792, 1), (256, 0), (1, 0)], 1792)
     assert exe.exe_op_gemm_kv_plan(BF16, 2298, 36864, 12288) == ([(1792, 1), (256, 0), (250, 0)], 1792)
     assert exe.exe_op_gemm_kv_plan(BF16, 16385, 17664, 5888) == ([(16128, 1), (256, 0), (1, 0)], 16128)

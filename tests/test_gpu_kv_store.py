@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 def shape_of(dtype, dh, layers=2):
-    # 8 heads: 3 * 8 * dh features, odd multiples of the tiles' 256 for dh = 64 ... 1536 and 3072
+    # 8 heads: 3 * 8 * dh features, 1536 and 3072: keys begin at the border of a tile of 256, values too
     return wl.tiny_shape().replace(n_layers=layers, d_model=512, n_heads=8, head_dim=dh, d_ff=512, vocab=512, max_pos=1024, dtype=dtype)
 
 
@@ -22,8 +22,10 @@ def model_of(shape, w, tokens, seqs, block=0):
     return exe.Model(cfg, w)
 
 
-# rows: below what the tiles take, one past a tile, several rounds of tiles with a remainder (bf16 launches are cut beyond 1024 rows)
-@pytest.mark.parametrize("lens", [[3, 40], [257], [700, 333, 1, 90], [1000] * 9 + [129, 64, 1]], ids=["few", "one", "ragged", "many"])
+# rows: below what the tiles take, one past a tile, several rounds of tiles with a remainder; in bf16 cut into two launches of which
+# the second, of a row, does not store (5377 rows of 3072 features, 10753 of 1536)
+@pytest.mark.parametrize("lens", [[3, 40], [257], [700, 333, 1, 90], [1000] * 9 + [129, 64, 1], [1000] * 5 + [375, 2], [1000] * 10 + [750, 3]],
+                         ids=["few", "one", "ragged", "many", "cut", "cut_narrow"])
 @pytest.mark.parametrize("dtype,dh", [(wl.DTYPE_F32, 64), (wl.DTYPE_F32, 128), (wl.DTYPE_BF16, 64), (wl.DTYPE_BF16, 128)])
 def test_cache_bits_and_logits(dtype, dh, lens):
     shape = shape_of(dtype, dh)
@@ -44,7 +46,7 @@ def test_cache_bits_and_logits(dtype, dh, lens):
 
 
 @pytest.mark.parametrize("dtype", [wl.DTYPE_F32, wl.DTYPE_BF16])
-@pytest.mark.parametrize("lens", [[20, 9], [1200, 77, 1, 300]], ids=["few", "many"])
+@pytest.mark.parametrize("lens", [[20, 9], [1200, 77, 1, 300], [1200, 77, 1, 823]], ids=["few", "many", "float_tiles"])
 def test_cross_keys_and_values(dtype, lens):
     """Cross-attention keys and values are the projection of the returned encoder output, rounded once."""
     shape = wl.small_t5_shape(dtype)
