@@ -192,9 +192,10 @@ int exe_kv_stats(exe_model_t* m, uint64_t* pool_bytes, uint64_t* used_bytes, uin
  * One row per (batch, length) pair, batch-major.  A single layer (layer 0's weights) runs n_steps timed
  * repetitions after 3 warm-up ones; only that layer's K/V is allocated (from the model's pool, which must
  * hold no live sequence; it is returned afterwards).  attn_ms_per_layer is the attention kernels' own time
- * (HIP events around each launch; where a launch takes the attention block as a whole, as in decode iterations of small
- * models, that launch: its norm and projections too); rest_ms_per_layer is the whole layer's latency (events around the layer,
- * launch gaps included) minus it; std_ms is the standard deviation of the whole-layer latency; head_ms is the
+ * (HIP events around each launch); rest_ms_per_layer is the whole layer's latency (events around the layer,
+ * launch gaps included) minus it (decode iterations of small models, whose launches take the attention block with its norm and
+ * projections, or the feed-forward, as a whole: the layer's latency in the ratio of those launches' own times);
+ * std_ms is the standard deviation of the whole-layer latency; head_ms is the
  * final norm + LM head + argmax (encoder-decoder encode: final norm + every decoder layer's cross K/V
  * projection); full_step_ms = layers * (attn + rest) + head_ms is an extrapolation to the full depth.
  */

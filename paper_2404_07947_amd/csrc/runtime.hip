@@ -1551,10 +1551,14 @@ struct EventTimer {
     hipError_t init() { hipError_t e = hipEventCreate(&a); return e != hipSuccess ? e : hipEventCreate(&b); }
 };
 
-static double attn_ms_of(exe_model* m)
+// time of the attention launches since the last reset; all (nullable): of all launches
+static double attn_ms_of(exe_model* m, double* all = nullptr)
 {
     exe_kernel_time_t rows[EXE_K_COUNT];
+    if (all) *all = 0.0;
     if (exe_kernel_times(m, rows)) return 0.0;
+    for (const exe_kernel_time_t& r : rows)
+        if (all) *all += r.ms;
     return rows[EXE_K_PREFILL_ATTN].ms + rows[EXE_K_DECODE_ATTN].ms + rows[EXE_K_CROSS_ATTN].ms;
 }
 
@@ -1654,20 +1658,29 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
             HIP_TRY(hipEventElapsedTime(&ms, t.a, t.b));
             layer_ms[i] = ms;
         }
-        // pass B: the attention kernels alone, from events around each launch
-        bool was_on = m->timer.on;
-        exe_kernel_timing(m, 1);
-        double attn = 0;
-        for (int i = 0; i < n_steps; ++i) {
-            if ((r = layer(2))) { exe_kernel_timing(m, was_on); return r; }
-            attn += attn_ms_of(m);
-        }
-        exe_kernel_timing(m, was_on);
-        attn /= n_steps;
         double mean = 0, var = 0;
         for (double x : layer_ms) mean += x;
         mean /= n_steps;
         for (double x : layer_ms) var += (x - mean) * (x - mean);
+        // pass B: the attention kernels alone, from events around each launch.  Of a small model's few short launches the feed-forward
+        // would be what is left between two sums of such times, each a microsecond or two off: there the layer's latency is shared
+        // out by the launches' own times (the median share: the host may be held up between an event and its launch).
+        bool was_on = m->timer.on;
+        exe_kernel_timing(m, 1);
+        double attn = 0;
+        std::vector<double> share;
+        for (int i = 0; i < n_steps; ++i) {
+            if ((r = layer(small ? 3 : 2))) { exe_kernel_timing(m, was_on); return r; }
+            double all, ms = attn_ms_of(m, &all);
+            attn += ms;
+            share.push_back(all > 0.0 ? ms / all : 0.0);
+        }
+        exe_kernel_timing(m, was_on);
+        attn /= n_steps;
+        if (small) {
+            std::nth_element(share.begin(), share.begin() + n_steps / 2, share.end());
+            attn = mean * share[n_steps / 2];
+        }
         row->attn_ms_per_layer = (float)attn;
         row->rest_ms_per_layer = (float)std::max(0.0, mean - attn);
         row->std_ms = (float)std::sqrt(var / n_steps);
@@ -1686,7 +1699,6 @@ static int profile_row(exe_model* m, int phase, const std::vector<int>& lens, in
             HIP_TRY(hipEventElapsedTime(&ms, t.a, t.b));
             head = ms / n_steps * c.n_dec_layers;
         } else if (c.has_lm_head) {
-            if (small && (r = layer(1))) return r;         // the partial sums in front of the head are a feed-forward's
             auto head_once = [&]() -> int {
                 if (small) small_end(chain);
                 return head_launches(m, phase == 0 ? ed.last : nullptr, n, m->logits, true);
