@@ -738,7 +738,11 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     if (a.pending) *a.pending = 0;
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     const int mode = launch_mode(a);
-    if (a.force_splits) return launch_rows(a, mode, s);
+    if (a.force_splits) {
+        GemmArgs plain = a;
+        plain.kv = nullptr;
+        return launch_rows(plain, mode, s);
+    }
     const size_t esz = a.dtype == DT_BF16 ? 2 : 4, osz = a.out_mode == OUT_T ? esz : 4;
     hipError_t e = hipSuccess;
     int stored = 0;                          // leading rows whose keys and values are in the cache: see gemm_kv_rows
