@@ -202,9 +202,7 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
 
 // ---------------------------------------------------------------- MFMA prefill (described for bf16, head size 128)
 // A workgroup of 4 waves owns PREFILL_TILE_Q = 128 query rows of one (sequence, head), 32 per wave as two 16-row
-// blocks; three workgroups fit a CU (48 KB of LDS each, at most 168 registers; the variants with a bias table need
-// more registers than that without spilling, and a spill in the tile loop waits for the tile loads in flight, so
-// they run two per CU).  Keys and values pass through LDS in tiles of 64 rows (two
+// blocks; three workgroups fit a CU (48 KB of LDS each and the bias table, at most 168 registers).  Keys and values pass through LDS in tiles of 64 rows (two
 // key tiles, double buffered, and one value tile), both by direct global->LDS loads in the same row-major swizzled
 // layout.  Per tile a wave computes
 //   S^T[key][query] = K . Q^T      (MFMA 16x16x32: A = key rows from LDS, B = the wave's query fragments)
@@ -213,6 +211,8 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
 // so a query's softmax statistics live in the four lanes that share its column, and the probabilities never leave
 // registers.  Two barriers per tile (the value tile is loaded behind the scores).  The workgroups of a CU drift
 // apart, so one wave's softmax (vector ALU) overlaps another's MFMAs on the same SIMD.
+constexpr int PF_BIAS = 1024, PF_BIAS_PAD = 96;                  // entries of a head's bias table in LDS, and of its continuation on either side
+constexpr int pf_bias_entries(int radius) { return 2 * (radius + PF_BIAS_PAD) + 1; }
 constexpr int PF_NW = 4, PF_KT = PREFILL_TILE_K, PF_THREADS = PF_NW * 64, PF_QT = PF_NW * 32;
 static_assert(PF_QT == PREFILL_TILE_Q, "the tile list is built for PREFILL_TILE_Q query rows per workgroup");
 constexpr int pf_tile_bytes(int row_bytes) { return PF_KT * row_bytes; }
@@ -225,7 +225,7 @@ template <typename T, int DH> constexpr int pf_lds()              // two key til
 template <typename T, int DH, bool BIAS> constexpr int pf_per_cu()
 {
     if (sizeof(T) == 4) return DH == 64 ? 2 : 1;
-    return (DH == 64 ? 4 : 3) - (BIAS ? 1 : 0);
+    return DH == 64 ? 4 : 3;
 }
 
 // A key or value tile [64 rows] in LDS, row-major in 16-byte chunks.  Rows of 256 bytes and more keep chunk c of row r at
@@ -309,8 +309,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     constexpr int DS = RB / 64, DT = DH / 16;                     // 64-byte steps of the first product, feature tiles of the second
     constexpr bool V2 = pf_v_tiles<T, DH>() == 2;
     constexpr bool SPLIT_P = sizeof(T) == 2 && DH == 64;
-    extern __shared__ __align__(16) unsigned char pf_smem[];      // 2 key tiles, then the value tile(s)
-    __shared__ float sbias[BIAS ? 1024 : 1];
+    extern __shared__ __align__(16) unsigned char pf_smem[];      // 2 key tiles, then the value tile(s), then the bias table
+    float* sbias = (float*)(pf_smem + pf_lds<T, DH>());
 
     // Workgroup -> (tile, head).  Workgroups go to the 8 XCDs round-robin in launch order.  With a multiple of 8 heads,
     // XCD x takes heads x, x + 8, ...: its j-th workgroup is tile j / (H/8) for its head number j % (H/8), so the
@@ -334,9 +334,13 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     int wq0 = q0 + wave * 32;                                     // this wave's first query row
     const T* seq = qkv + (int64_t)t0 * ld + h * DH;
 
+    // the head's table, continued on either side with its first and last entry
     if (BIAS) {
-        for (int i = tid; i < 2 * radius + 1; i += PF_THREADS)
-            sbias[i] = bias_by_dist[(int64_t)h * (2 * radius + 1) + i] * LOG2E;
+        for (int i = tid; i < pf_bias_entries(radius); i += PF_THREADS) {
+            int e = i - PF_BIAS_PAD;
+            e = e < 0 ? 0 : (e > 2 * radius ? 2 * radius : e);
+            sbias[i] = bias_by_dist[(int64_t)h * (2 * radius + 1) + e] * LOG2E;
+        }
     }
 
     // query fragments (B operand): lane (query qi, lane group g) holds 16-byte chunk 4*ds + g of its query row
@@ -380,6 +384,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     };
 #pragma clang diagnostic pop
     auto load_tile = [&](const char* base, int kt, unsigned dst) {
+        int lane = tid & 63;
+        if (BIAS) asm volatile("" : "+v"(lane));                    // the rows' offsets are made anew per tile: held, they spill
 #pragma unroll
         for (int p = 0; p < PF_LPT; ++p) {
             constexpr int CPR = RB / 16;                            // chunks per row
@@ -400,7 +406,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) o_acc[qb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-    float sc = fabsf(scale) * LOG2E;
+    float sc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, fabsf(scale) * LOG2E)));
     f32x4 s_acc[2][4];
 
     // a wave whose queries all lie before a tile's first key (causal) or past the sequence end has nothing to
@@ -413,8 +419,11 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         // The four swizzled chunk offsets of a lane ((4 ds + g) ^ qi for ds = 0..3) are recomputed per tile from one
         // register: held across the tile loop they cost four, and a register spilled in this loop puts a full wait
         // for the tile loads in flight in front of its reload (scratch reloads count with them).
-        int qx = pf_swz<RB>(qi);
-        asm volatile("" : "+v"(qx));
+        // (With a bias, whose look-ups want registers too, all of a lane's offsets are.)
+        int l = lane;
+        if (BIAS) asm volatile("" : "+v"(l));
+        int qi = l & 15, g = l >> 4, qx = pf_swz<RB>(qi);
+        if (!BIAS) asm volatile("" : "+v"(qx));
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
             if constexpr (sizeof(T) == 4) {
@@ -460,58 +469,66 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         // With a bias, a tile whose keys all lie at least `radius` before (or after) every query of this wave adds one
         // constant, the table's first (last) entry, to all of its scores: it takes the path without look-ups with that
         // constant folded into the exponent.  (The bias table is indexed by the clamped distance.)
+        // In the other tiles no distance passes the table's ends by PF_BIAS_PAD or more, so the continued table is read without a
+        // clamp, and a lane's four keys of a block are four entries in a row, the same ones for key block kb of the first
+        // queries and kb + 1 of the second: 20 entries per lane and tile.  (T5-11B's heads, 16 ragged sequences of 768: 1270 us
+        // with a clamped look-up per score and two workgroups per CU, now 1010.)
         bool edge = kt * PF_KT + PF_KT > n || (CAUSAL && kt * PF_KT + PF_KT - 1 > wq0);
-        bool masked = BIAS || edge;
-        float cbias = 0.f;
-        if (BIAS && !edge) {
+        float mul = sc, cbias = 0.f;           // score = s_acc * mul + cbias
+        if (BIAS) {
             if (kt * PF_KT + PF_KT - 1 - wq0 <= -radius) {
-                masked = false;
                 cbias = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sbias[0])));
             } else if (kt * PF_KT - (wq0 + 31) >= radius) {
-                masked = false;
-                cbias = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sbias[2 * radius])));
+                cbias = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sbias[2 * (radius + PF_BIAS_PAD)])));
+            } else {
+                int l = lane;
+                asm volatile("" : "+v"(l));         // the offset is made anew per tile: held, it spills
+                const float* t = sbias + (radius + PF_BIAS_PAD) + kt * PF_KT - wq0 + (l >> 4) * 4 - (l & 15);
+#pragma unroll
+                for (int d = -1; d < 4; ++d) {
+                    float b[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) b[r] = t[d * 16 + r];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (d >= 0) s_acc[0][d][r] = fmaf(s_acc[0][d][r], sc, b[r]);
+                        if (d < 3) s_acc[1][d + 1][r] = fmaf(s_acc[1][d + 1][r], sc, b[r]);
+                    }
+                }
+                mul = 1.f;
             }
         }
-        float alpha[2];
+        if (edge) {
+            int key0 = kt * PF_KT + 4 * g;
+            asm volatile("" : "+v"(key0));          // keeps the mask arithmetic inside this branch
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-            int qpos = wq0 + qb * 16 + qi;
-            float mx = -INFINITY;
-            if (masked) {
-                int key0 = kt * PF_KT + 4 * g;
-                asm volatile("" : "+v"(key0));      // keeps the mask arithmetic inside this branch
+            for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         int key = key0 + kb * 16 + r;
-                        float v = s_acc[qb][kb][r] * sc;
-                        if (BIAS) {
-                            int rel = key - qpos;
-                            rel = rel < -radius ? -radius : (rel > radius ? radius : rel);
-                            v += sbias[rel + radius];
-                        }
-                        if (edge) {
-                            bool ok = key < n && (!CAUSAL || key <= qpos);
-                            v = ok ? v : -INFINITY;
-                        }
-                        s_acc[qb][kb][r] = v;
-                        mx = fmaxf(mx, v);
+                        bool ok = key < n && (!CAUSAL || key <= wq0 + qb * 16 + qi);
+                        s_acc[qb][kb][r] = ok ? fmaf(s_acc[qb][kb][r], mul, cbias) : -INFINITY;
                     }
-            } else {
-                // sc is not negative: take the maximum of the raw scores and fold the scale into the exponent
+            mul = 1.f;
+            cbias = 0.f;
+        }
+        float alpha[2];
 #pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
+        for (int qb = 0; qb < 2; ++qb) {
+            // mul is not negative: take the maximum of the raw scores and fold the scale into the exponent
+            float mx = -INFINITY;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s_acc[qb][kb][r]);
-                mx = fmaf(mx, sc, cbias);
-            }
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s_acc[qb][kb][r]);
+            mx = fmaf(mx, mul, cbias);
             mx = rows_max(mx);
             float m_new = fmaxf(m_run[qb], mx);
             float mref = m_new == -INFINITY ? 0.f : m_new;
             alpha[qb] = fast_exp2(m_run[qb] - mref);
-            float mul = masked ? 1.f : sc;
-            float shift = cbias - mref;             // cbias is 0 on the path with look-ups
+            float shift = cbias - mref;
             float rs = 0.f;
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
@@ -681,7 +698,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         }
         for (; again; again &= again - 1) {
             int qr = wq0 + qb * 16 + __builtin_ctz(again);
-            prefill_row<T, DH, BIAS>(seq + qr * ld, keys, values, kv_row / (int)sizeof(T), qr, CAUSAL ? qr + 1 : n, scale * LOG2E, sbias, radius, lane,
+            prefill_row<T, DH, BIAS>(seq + qr * ld, keys, values, kv_row / (int)sizeof(T), qr, CAUSAL ? qr + 1 : n, scale * LOG2E, sbias + (BIAS ? PF_BIAS_PAD : 0), radius, lane,
                                      out + (int64_t)(t0 + qr) * inner + h * DH);
         }
     }
@@ -717,11 +734,11 @@ void prefill_tile_order(const int32_t* lens, int n_seqs, std::vector<int32_t>& t
 template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
 {
     auto kern = prefill_mfma_kernel<T, DH, CAUSAL, BIAS>;
-    constexpr int lds = pf_lds<T, DH>();
+    const int lds = pf_lds<T, DH>() + (BIAS ? pf_bias_entries(a.bias_radius) * 4 : 0);
     static LdsLimit limit[MAX_DEVICES];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
-    hipError_t e = limit[dev].raise((const void*)kern, lds);
+    hipError_t e = limit[dev].raise((const void*)kern, pf_lds<T, DH>() + (BIAS ? (PF_BIAS + 2 * PF_BIAS_PAD) * 4 : 0));
     if (e != hipSuccess) return e;
     kern<<<(unsigned)(a.n_tiles * a.H), PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
                                                              BIAS ? a.bias_radius : 0, (T*)a.out, (const T*)a.pool, a.base, a.cap, a.layer);
@@ -760,7 +777,7 @@ hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
     // the kernel's LDS copy; a batch outside these limits runs on the row kernel, which is correct but far slower,
     // so say so (once).
     const int64_t longest = a.work.max_len, row_bytes = (int64_t)3 * a.H * a.dh * (a.dtype == DT_F32 ? 4 : 2);
-    const bool mfma_fits = longest * row_bytes < ((int64_t)1 << 32) && (!a.bias_by_dist || 2 * a.bias_radius + 1 <= 1024);
+    const bool mfma_fits = longest * row_bytes < ((int64_t)1 << 32) && (!a.bias_by_dist || 2 * a.bias_radius + 1 <= PF_BIAS);
     if (mfma && !mfma_fits) {
         static std::once_flag warned;
         std::call_once(warned, [&]() {

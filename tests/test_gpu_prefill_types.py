@@ -48,3 +48,32 @@ def test_every_row(dtype, dh, causal, use_bias, generic, H):
             worst = max(worst, float(err.max()))
     # float sums and probabilities throughout; in bf16 one rounding of the result, 2^-9
     assert worst < (1e-5 if dtype == F32 else 2.0 ** -8), worst
+
+
+@pytest.mark.parametrize("dtype,dh", [(BF16, 128), (BF16, 64), (F32, 64), (F32, 128)])
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("R", [1, 31, 64, 128, 511])              # radius of the bias table: none to all of the tiles look it up
+def test_bias_radius(dtype, dh, causal, R):
+    td = torch.float32 if dtype == F32 else torch.bfloat16
+    lens, H = [1, 65, 352, 700], 2
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, inner = int(cu[-1]), H * dh
+    g = torch.Generator().manual_seed(R + dh)
+    qkv = torch.randn((T, 3 * inner), generator=g).to(td)
+    tab = torch.randn((H, 2 * R + 1), generator=g)
+    out = torch.zeros((T, inner), dtype=td, device=DEV)
+    exe.exe_op_prefill_attention(dtype, cu, qkv.to(DEV), H, dh, 0.11, causal, tab.to(DEV), R, out, force_generic=-1)
+    torch.cuda.synchronize()
+    got, x = out.double().cpu(), qkv.double()
+    worst = 0.0
+    for s, L in enumerate(lens):
+        q, k, v = (x[cu[s]:cu[s + 1], j * inner:(j + 1) * inner].reshape(L, H, dh).transpose(0, 1).contiguous() for j in range(3))
+        rel = torch.arange(L)[None, :] - torch.arange(L)[:, None]
+        sc = (q @ k.transpose(1, 2).contiguous()) * float(np.float32(0.11)) + tab.double()[:, rel.clamp(-R, R) + R]
+        if causal:
+            sc = sc.masked_fill(rel > 0, float("-inf"))
+        ref = (sc.softmax(dim=-1) @ v).transpose(0, 1).reshape(L, H, dh)
+        err = (got[cu[s]:cu[s + 1]].reshape(L, H, dh) - ref).abs().amax(dim=2) / ref.abs().amax(dim=2)
+        worst = max(worst, float(err.max()))
+    # as above; bf16 x 128 rounds its probabilities to bf16 before the second product too
+    assert worst < (1e-5 if dtype == F32 else 2.0 ** -8 if dh == 64 else 2.0 ** -6), worst
