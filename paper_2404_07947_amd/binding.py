@@ -9,6 +9,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _lib = None
+_call = None                                     # csrc/call.c
 
 DECLARED_SYMBOLS = [
     "exe_expected_weights", "exe_model_load", "exe_model_free", "exe_encode", "exe_decode_step",
@@ -107,13 +108,16 @@ def lib_path() -> str:
 
 def lib():
     """Loads libexe.so.  There is no fallback: a missing library is an error."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     p = lib_path()
-    if not os.path.exists(p):
-        raise ImportError(f"{p} is not built; run `python -m paper_2404_07947_amd.build` (needs hipcc)")
+    for f in (p, os.path.join(_HERE, "_call.so")):
+        if not os.path.exists(f):
+            raise ImportError(f"{f} is not built; run `python -m paper_2404_07947_amd.build` (needs hipcc)")
+    from . import _call
     L = C.CDLL(p)
+    L.at = {f: C.cast(getattr(L, "exe_" + f), C.c_void_p).value for f in ("encode", "decode_step", "seq_release")}
     vp, i32, ip = C.c_void_p, C.c_int32, C.POINTER(C.c_int32)
     L.exe_expected_weights.argtypes = [C.POINTER(Config)]
     L.exe_model_load.argtypes = [C.POINTER(Config), C.POINTER(Tensor), i32, vp, C.POINTER(vp)]
@@ -231,6 +235,9 @@ class Model:
         _check(L.exe_model_load(C.byref(cfg), arr, len(self._weights), _stream_ptr(stream), C.byref(h)))
         self._h = h
 
+    def _handle(self) -> Optional[int]:
+        return self._h.value if self._h else None
+
     @staticmethod
     def expected_weights(cfg: Config) -> int:
         return _check(lib().exe_expected_weights(C.byref(cfg)))
@@ -251,21 +258,19 @@ class Model:
         ids, lens = _i32(seq_ids), _i32(input_lengths)
         toks, res = _i32(tokens_packed), _i32(reserve_lengths)
         nxt = np.zeros(len(ids), dtype=np.int32) if want_tokens else None
-        _check(lib().exe_encode(self._h, len(ids), _ip(ids), _ip(lens), _ip(toks), _ip(res), _dev(hidden_in),
-                                _ip(nxt), _dev(out_device)))
+        _check(_call.encode(lib().at["encode"], self._handle(), ids, lens, toks, res, _dev(hidden_in), nxt, _dev(out_device)))
         return nxt
 
     def decode_step(self, seq_ids, tokens_in, kv_lengths, hidden_in=None, want_tokens: bool = True,
                     out_device=None) -> Optional[np.ndarray]:
         ids, toks, kvl = _i32(seq_ids), _i32(tokens_in), _i32(kv_lengths)
         nxt = np.zeros(len(ids), dtype=np.int32) if want_tokens else None
-        _check(lib().exe_decode_step(self._h, len(ids), _ip(ids), _ip(toks), _ip(kvl), _dev(hidden_in), _ip(nxt),
-                                     _dev(out_device)))
+        _check(_call.decode_step(lib().at["decode_step"], self._handle(), ids, toks, kvl, _dev(hidden_in), nxt, _dev(out_device)))
         return nxt
 
     def seq_release(self, seq_ids) -> None:
         ids = _i32(seq_ids)
-        _check(lib().exe_seq_release(self._h, len(ids), _ip(ids)))
+        _check(_call.seq_release(lib().at["seq_release"], self._handle(), ids))
 
     def seq_length(self, seq_id: int) -> int:
         return _check(lib().exe_seq_length(self._h, int(seq_id)))

@@ -4,12 +4,15 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libexe.so")
+CALL = os.path.join(HERE, "_call.so")              # csrc/call.c: host code against Python's headers
+CC = os.environ.get("CC", "gcc")
 SOURCES = ["kernels_elementwise.hip", "kernels_gemm.hip", "kernels_gemm_large.hip", "kernels_gemm_stream.hip", "kernels_attn.hip", "kernels_small.hip", "runtime.hip", "probe.hip", "sched.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Kernel arguments preloaded into scalar registers instead of fetched by each wave's first instructions: decode iterations of
@@ -54,6 +57,13 @@ def build(force: bool = False, verbose: bool = True) -> str:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
         os.replace(LIB + ".tmp", LIB)
+    src = os.path.join(CSRC, "call.c")
+    if force or not os.path.exists(CALL) or os.path.getmtime(src) > os.path.getmtime(CALL):
+        cmd = [CC, "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], src, "-o", CALL + ".tmp"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+        os.replace(CALL + ".tmp", CALL)
     return LIB
 
 
