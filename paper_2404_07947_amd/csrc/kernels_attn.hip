@@ -202,30 +202,29 @@ hipError_t launch_attn_paged(const AttnPagedArgs& a, hipStream_t s)
 
 // ---------------------------------------------------------------- MFMA prefill (described for bf16, head size 128)
 // A workgroup of 4 waves owns PREFILL_TILE_Q = 128 query rows of one (sequence, head), 32 per wave as two 16-row
-// blocks; three workgroups fit a CU (48 KB of LDS each and the bias table, at most 168 registers).  Keys and values pass through LDS in tiles of 64 rows (two
-// key tiles, double buffered, and one value tile), both by direct global->LDS loads in the same row-major swizzled
-// layout.  Per tile a wave computes
+// blocks (QB = 1: 64 rows, one block per wave); three workgroups fit a CU (48 KB of LDS each and the bias table, at most 168
+// registers).  Keys and values pass through LDS in tiles of 64 rows (two key tiles, double buffered, and one value tile, or V2:
+// two), both by direct global->LDS loads in the same row-major swizzled layout.  Per tile a wave computes
 //   S^T[key][query] = K . Q^T      (MFMA 16x16x32: A = key rows from LDS, B = the wave's query fragments)
 //   O^T[d][query]  += V^T . P^T    (A = values through the transposing LDS read, B = P straight from the
 //                                   accumulators of S^T)
 // so a query's softmax statistics live in the four lanes that share its column, and the probabilities never leave
-// registers.  Two barriers per tile (the value tile is loaded behind the scores).  The workgroups of a CU drift
+// registers.  Two barriers per tile (the value tile is loaded behind the scores; V2: one).  The workgroups of a CU drift
 // apart, so one wave's softmax (vector ALU) overlaps another's MFMAs on the same SIMD.
 constexpr int PF_BIAS = 1024, PF_BIAS_PAD = 96;                  // entries of a head's bias table in LDS, and of its continuation on either side
 constexpr int pf_bias_entries(int radius) { return 2 * (radius + PF_BIAS_PAD) + 1; }
 constexpr int PF_NW = 4, PF_KT = PREFILL_TILE_K, PF_THREADS = PF_NW * 64, PF_QT = PF_NW * 32;
 static_assert(PF_QT == PREFILL_TILE_Q, "the tile list is built for PREFILL_TILE_Q query rows per workgroup");
 constexpr int pf_tile_bytes(int row_bytes) { return PF_KT * row_bytes; }
-template <typename T, int DH> constexpr int pf_v_tiles() { return sizeof(T) == 2 && DH == 128 ? 1 : 2; }
-template <typename T, int DH> constexpr int pf_lds()              // two key tiles, then the value tile(s)
+template <typename T, int DH, bool V2> constexpr int pf_lds()     // two key tiles, then the value tile(s)
 {
-    return (2 + pf_v_tiles<T, DH>()) * pf_tile_bytes(DH * (int)sizeof(T));
+    return (V2 ? 4 : 3) * pf_tile_bytes(DH * (int)sizeof(T));
 }
 // workgroups per CU that the registers must leave room for (LDS does)
-template <typename T, int DH, bool BIAS> constexpr int pf_per_cu()
+template <typename T, int DH, bool V2> constexpr int pf_per_cu()
 {
-    if (sizeof(T) == 4) return DH == 64 ? 2 : 1;
-    return DH == 64 ? 4 : 3;
+    if (sizeof(T) == 4) return DH == 128 ? 1 : V2 ? 2 : 3;
+    return DH == 64 ? 5 : V2 ? 2 : 3;
 }
 
 // A key or value tile [64 rows] in LDS, row-major in 16-byte chunks.  Rows of 256 bytes and more keep chunk c of row r at
@@ -280,8 +279,7 @@ __device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* 
     for (int f = 0; f < DH / 64; ++f) out[lane + f * 64] = from_f32<T>(acc[f] / l);
 }
 
-// Head size 64: half the bytes per tile, so the value tiles are double buffered too and one barrier per tile is enough.
-// Its probabilities enter the second product as the sum of three bf16 values, their first, second and third 8 bits, so no bit
+// Head size 64: half the bytes per tile, so the value tiles are double buffered too.  Its probabilities enter the second product as the sum of three bf16 values, their first, second and third 8 bits, so no bit
 // of the float is lost: the row kernel, which served this head size before, multiplies floats too.  The two further sets of
 // MFMAs hide behind the exponentials for the most part (one set more and a rounded rest, 2^-17 relative: 40 us where three
 // take 43).
@@ -292,10 +290,10 @@ __device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* 
 // 2.3 to 3.3 times as much against 64 bits as the row kernel (1000 rows 6.5e-7 of the result, now and there 2.5e-7; 4096 rows
 // 9.4e-7, now 3.0e-7, there 3.2e-7), for 2 to 9 % less time.
 //
-// Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 43;
-// float x 64, 32 sequences of 384, 4 heads, 192 -> 75.
-template <typename T, int DH, bool CAUSAL, bool BIAS>
-__global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefill_mfma_kernel(const T* __restrict__ qkv,
+// Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 34;
+// float x 64, 32 sequences of 384, 4 heads, 192 -> 56.
+template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB>
+__global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_mfma_kernel(const T* __restrict__ qkv,
                                                                   const int32_t* __restrict__ cu,
                                                                   const int32_t* __restrict__ tiles, int H,
                                                                   float scale, const float* __restrict__ bias_by_dist,
@@ -307,10 +305,9 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     constexpr int PF_LPT = PF_KT / RPL / PF_NW;                   // direct-to-LDS loads per wave and tile
     constexpr int PF_TILE = pf_tile_bytes(RB);
     constexpr int DS = RB / 64, DT = DH / 16;                     // 64-byte steps of the first product, feature tiles of the second
-    constexpr bool V2 = pf_v_tiles<T, DH>() == 2;
     constexpr bool SPLIT_P = sizeof(T) == 2 && DH == 64;
     extern __shared__ __align__(16) unsigned char pf_smem[];      // 2 key tiles, then the value tile(s), then the bias table
-    float* sbias = (float*)(pf_smem + pf_lds<T, DH>());
+    float* sbias = (float*)(pf_smem + pf_lds<T, DH, V2>());
 
     // Workgroup -> (tile, head).  Workgroups go to the 8 XCDs round-robin in launch order.  With a multiple of 8 heads,
     // XCD x takes heads x, x + 8, ...: its j-th workgroup is tile j / (H/8) for its head number j % (H/8), so the
@@ -325,13 +322,15 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         tile = blockIdx.x / H;
         h = blockIdx.x - tile * H;
     }
-    int sb = tiles[tile * 2], q0 = tiles[tile * 2 + 1];
+    constexpr int QT = PF_NW * 16 * QB, PIECES = PF_QT / QT;      // the list's tiles are cut into pieces
+    int sb = tiles[tile / PIECES * 2], q0 = tiles[tile / PIECES * 2 + 1] + (PIECES - 1 - tile % PIECES) * QT;
     int t0 = cu[sb], n = cu[sb + 1] - t0;
+    if (q0 >= n) return;
     int inner = H * DH;
     int64_t ld = 3 * (int64_t)inner;
     int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int qi = lane & 15, g = lane >> 4;
-    int wq0 = q0 + wave * 32;                                     // this wave's first query row
+    int wq0 = q0 + wave * (16 * QB);                                     // this wave's first query row
     const T* seq = qkv + (int64_t)t0 * ld + h * DH;
 
     // the head's table, continued on either side with its first and last entry
@@ -344,9 +343,9 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     }
 
     // query fragments (B operand): lane (query qi, lane group g) holds 16-byte chunk 4*ds + g of its query row
-    u32x4 qf[2][DS];
+    u32x4 qf[QB][DS];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
         int qr = wq0 + qb * 16 + qi;
         qr = qr < n ? qr : n - 1;
         const u32x4* qp = (const u32x4*)(seq + (int64_t)qr * ld) + g;
@@ -357,12 +356,12 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     // the queries
     if (scale < 0.f) {
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
             for (int ds = 0; ds < DS; ++ds) qf[qb][ds] ^= sizeof(T) == 4 ? 0x80000000u : 0x80008000u;
     }
     int kend = n;
-    if (CAUSAL) kend = q0 + PF_QT < n ? q0 + PF_QT : n;
+    if (CAUSAL) kend = q0 + QT < n ? q0 + QT : n;
     int n_tiles = (kend + PF_KT - 1) / PF_KT;
 
     // ---- loaders.  Per tile of keys and of values a wave issues PF_LPT 1 KB direct-to-LDS loads of RPL rows each; a
@@ -400,18 +399,23 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
     auto load_k = [&](int kt) { load_tile((const char*)keys, kt, lds_base + (kt & 1) * PF_TILE); };
     auto load_v = [&](int kt) { load_tile((const char*)values, kt, lds_base + (2 + (V2 ? kt & 1 : 0)) * PF_TILE); };
 
-    f32x4 o_acc[2][DT];
+    f32x4 o_acc[QB][DT];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) o_acc[qb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+    float m_run[QB], l_run[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        m_run[qb] = -INFINITY;
+        l_run[qb] = 0.f;
+    }
     float sc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, fabsf(scale) * LOG2E)));
-    f32x4 s_acc[2][4];
+    f32x4 s_acc[QB][4];
 
     // a wave whose queries all lie before a tile's first key (causal) or past the sequence end has nothing to
     // compute for that tile; it still moves its share of the tiles
-    auto active = [&](int kt) { return wq0 < n && (!CAUSAL || kt * PF_KT <= wq0 + 31); };
+    auto active = [&](int kt) { return wq0 < n && (!CAUSAL || kt * PF_KT <= wq0 + 16 * QB - 1); };
 
     // ---- the three phases of a tile
     auto phase_s = [&](int kt) {
@@ -428,37 +432,39 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         for (int kb = 0; kb < 4; ++kb) {
             if constexpr (sizeof(T) == 4) {
                 // sums of 8 features each (two MFMAs), added pairwise: part x is half x % 2 of the 16-byte chunks 4 * (x / 2) + g
-                auto sum = [&](auto self, auto first, auto count, f32x4 (&c)[2]) -> void {
+                auto sum = [&](auto self, auto first, auto count, f32x4 (&c)[QB]) -> void {
                     constexpr int X = decltype(first)::value, N = decltype(count)::value;
                     if constexpr (N == 1) {
                         f32x4 kf = *(const f32x4*)(sK + (kb * 16 + qi) * RB + (((X / 2 * 4 + g) ^ qx) << 4));
 #pragma unroll
-                        for (int qb = 0; qb < 2; ++qb) {
+                        for (int qb = 0; qb < QB; ++qb) {
                             f32x4 q = __builtin_bit_cast(f32x4, qf[qb][X / 2]);
                             c[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[X % 2 * 2], q[X % 2 * 2], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                             c[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[X % 2 * 2 + 1], q[X % 2 * 2 + 1], c[qb], 0, 0, 0);
                         }
                     } else {
-                        f32x4 d[2];
+                        f32x4 d[QB];
                         self(self, std::integral_constant<int, X>{}, std::integral_constant<int, N / 2>{}, c);
                         self(self, std::integral_constant<int, X + N / 2>{}, std::integral_constant<int, N / 2>{}, d);
-                        c[0] += d[0];
-                        c[1] += d[1];
+#pragma unroll
+                        for (int qb = 0; qb < QB; ++qb) c[qb] += d[qb];
                     }
                 };
-                f32x4 c[2];
+                f32x4 c[QB];
                 sum(sum, std::integral_constant<int, 0>{}, std::integral_constant<int, 2 * DS>{}, c);
-                asm volatile("" : "+v"(c[0]), "+v"(c[1]));       // the additions stay here: moved into the softmax's branches they spill
-                s_acc[0][kb] = c[0];
-                s_acc[1][kb] = c[1];
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    asm volatile("" : "+v"(c[qb]));               // the additions stay here: moved into the softmax's branches they spill
+                    s_acc[qb][kb] = c[qb];
+                }
             } else {
-                s_acc[0][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-                s_acc[1][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) s_acc[qb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int ds = 0; ds < DS; ++ds) {
                     u32x4 fk = *(const u32x4*)(sK + (kb * 16 + qi) * RB + (((ds * 4 + g) ^ qx) << 4));
-                    s_acc[0][kb] = HalfUnit<T>::mma(fk, qf[0][ds], s_acc[0][kb]);
-                    s_acc[1][kb] = HalfUnit<T>::mma(fk, qf[1][ds], s_acc[1][kb]);
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) s_acc[qb][kb] = HalfUnit<T>::mma(fk, qf[qb][ds], s_acc[qb][kb]);
                 }
             }
         }
@@ -478,21 +484,21 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         if (BIAS) {
             if (kt * PF_KT + PF_KT - 1 - wq0 <= -radius) {
                 cbias = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sbias[0])));
-            } else if (kt * PF_KT - (wq0 + 31) >= radius) {
+            } else if (kt * PF_KT - (wq0 + 16 * QB - 1) >= radius) {
                 cbias = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sbias[2 * (radius + PF_BIAS_PAD)])));
             } else {
                 int l = lane;
                 asm volatile("" : "+v"(l));         // the offset is made anew per tile: held, it spills
                 const float* t = sbias + (radius + PF_BIAS_PAD) + kt * PF_KT - wq0 + (l >> 4) * 4 - (l & 15);
 #pragma unroll
-                for (int d = -1; d < 4; ++d) {
+                for (int d = 1 - QB; d < 4; ++d) {
                     float b[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) b[r] = t[d * 16 + r];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         if (d >= 0) s_acc[0][d][r] = fmaf(s_acc[0][d][r], sc, b[r]);
-                        if (d < 3) s_acc[1][d + 1][r] = fmaf(s_acc[1][d + 1][r], sc, b[r]);
+                        if (QB > 1 && d < 3) s_acc[QB - 1][d + 1][r] = fmaf(s_acc[QB - 1][d + 1][r], sc, b[r]);
                     }
                 }
                 mul = 1.f;
@@ -502,7 +508,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
             int key0 = kt * PF_KT + 4 * g;
             asm volatile("" : "+v"(key0));          // keeps the mask arithmetic inside this branch
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+            for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -514,9 +520,9 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
             mul = 1.f;
             cbias = 0.f;
         }
-        float alpha[2];
+        float alpha[QB];
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < QB; ++qb) {
             // mul is not negative: take the maximum of the raw scores and fold the scale into the exponent
             float mx = -INFINITY;
 #pragma unroll
@@ -543,9 +549,9 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
             m_run[qb] = m_new;
         }
         // the running maximum of a query stops moving after the first tiles: rescale only when some lane needs it
-        if (__builtin_amdgcn_ballot_w64(alpha[0] != 1.f || alpha[1] != 1.f) != 0) {
+        if (__builtin_amdgcn_ballot_w64(alpha[0] != 1.f || alpha[QB - 1] != 1.f) != 0) {
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+            for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -569,19 +575,21 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
             for (int r = 0; r < 4; ++r) vr[r] = tV + (4 * ga + r) * RB + (((qi >> 2) ^ r) << 4) + (qi & 3) * 4;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                f32x4 c[2][4];
+                f32x4 c[QB][4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) c[0][i] = c[1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) c[qb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         float fv = *(const float*)(vr[r] + ((dt ^ ga) << 6) + kb * 16 * RB);
-                        c[0][kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[0][kb][r], c[0][kb], 0, 0, 0);
-                        c[1][kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[1][kb][r], c[1][kb], 0, 0, 0);
+#pragma unroll
+                        for (int qb = 0; qb < QB; ++qb) c[qb][kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv, s_acc[qb][kb][r], c[qb][kb], 0, 0, 0);
                     }
-                o_acc[0][dt] += (c[0][0] + c[0][1]) + (c[0][2] + c[0][3]);
-                o_acc[1][dt] += (c[1][0] + c[1][1]) + (c[1][2] + c[1][3]);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) o_acc[qb][dt] += (c[qb][0] + c[qb][1]) + (c[qb][2] + c[qb][3]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             return;
@@ -591,9 +599,9 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
         for (int ks = 0; ks < 2; ++ks) {
             // p, or (SPLIT_P) its first, second and third 8 bits: p = pf[0] + pf[1] + pf[2]
             constexpr int NP = SPLIT_P ? 3 : 1;
-            bf16x8 pf[NP][2];
+            bf16x8 pf[NP][QB];
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
+            for (int qb = 0; qb < QB; ++qb) {
                 if constexpr (!SPLIT_P) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) pf[0][qb][e] = (bf16_t)s_acc[qb][2 * ks + (e >> 2)][e & 3];
@@ -623,8 +631,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
                 bf16x8 fv = __builtin_bit_cast(bf16x8, both);
 #pragma unroll
                 for (int i = 0; i < NP; ++i) {
-                    o_acc[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[i][0], o_acc[0][dt], 0, 0, 0);
-                    o_acc[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[i][1], o_acc[1][dt], 0, 0, 0);
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) o_acc[qb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv, pf[i][qb], o_acc[qb][dt], 0, 0, 0);
                 }
             }
         }
@@ -673,7 +681,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, BIAS>())) void prefil
 
     // lane (qi, g) holds features 16*dt + 4*g .. +3 of its query
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < QB; ++qb) {
         int qpos = wq0 + qb * 16 + qi;
         float inv = 1.f / l_run[qb];
         float most = o_acc[qb][0][0];                              // NaN if one of them is
@@ -731,18 +739,50 @@ void prefill_tile_order(const int32_t* lens, int n_seqs, std::vector<int32_t>& t
         }
 }
 
-template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
+template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
 {
-    auto kern = prefill_mfma_kernel<T, DH, CAUSAL, BIAS>;
-    const int lds = pf_lds<T, DH>() + (BIAS ? pf_bias_entries(a.bias_radius) * 4 : 0);
+    auto kern = prefill_mfma_kernel<T, DH, CAUSAL, BIAS, V2, QB>;
+    const int lds = pf_lds<T, DH, V2>() + (BIAS ? pf_bias_entries(a.bias_radius) * 4 : 0);
+    const int64_t wgs = (int64_t)a.n_tiles * (2 / QB) * a.H;
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
     static LdsLimit limit[MAX_DEVICES];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
-    hipError_t e = limit[dev].raise((const void*)kern, pf_lds<T, DH>() + (BIAS ? (PF_BIAS + 2 * PF_BIAS_PAD) * 4 : 0));
+    hipError_t e = limit[dev].raise((const void*)kern, pf_lds<T, DH, V2>() + (BIAS ? (PF_BIAS + 2 * PF_BIAS_PAD) * 4 : 0));
     if (e != hipSuccess) return e;
-    kern<<<(unsigned)(a.n_tiles * a.H), PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
-                                                             BIAS ? a.bias_radius : 0, (T*)a.out, (const T*)a.pool, a.base, a.cap, a.layer);
+    kern<<<(unsigned)wgs, PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
+                                                BIAS ? a.bias_radius : 0, (T*)a.out, (const T*)a.pool, a.base, a.cap, a.layer);
     return hipGetLastError();
+}
+
+// The form of the MFMA kernel: query blocks per wave (QB; the other half of a listed tile goes to a workgroup of its own at QB 1)
+// and value buffers (V2), by how many workgroups of whole tiles there are.  One or two buffers do not change a row's result, nor do
+// the blocks.  us of a launch on one MI355X (by events, which add about 3):
+//   QB 2 with one value buffer / with two / QB 1 with two
+//   bf16 x 128, causal  160 workgroups (1 x 512, 40 heads) 24.9 / 19.7 / 17.5    320 36.8 / 31.0 / 26.2    600 36.8 / 28.7 / 33.2
+//                       1280 82 / 80 / 92    1536 (96 heads) 96.4 / 96.5 / 117    5800 205 / 212 / 258: the third workgroup on a CU
+//   not causal, T5's bias  128 12.6 / 12.0 / 10.1    384 23.7 / 23.6 / 25.5    768 60.6 / 71.2 / 81.3    13696 977 / 1137 / 1423
+//   QB 2 with two / QB 1 with two (/ with one)
+//   bf16 x 64   64 18.3 / 12.1    592 27.3 / 22.8    2672 62.4 / 57.6: half the registers, so five workgroups on a CU in place of four
+//   float x 64  148 60.0 / 40.8 / 41.6    292 73.2 / 45.0 / 51.7    452 81.0 / 63.4 / 58.6    804 122 / 106 / 100: MFMA-bound, so
+//               what counts is how evenly the CUs are loaded; one buffer and a third workgroup from three pieces per CU on
+template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
+{
+    const int64_t wgs = (int64_t)a.n_tiles * a.H;
+    if constexpr (DH == 64) {
+        if constexpr (sizeof(T) == 4) {
+            if (2 * wgs > 768) return launch_prefill<T, DH, CAUSAL, BIAS, false, 1>(a, s);
+        }
+        return launch_prefill<T, DH, CAUSAL, BIAS, true, 1>(a, s);
+    } else if constexpr (sizeof(T) == 4) {
+        return launch_prefill<T, DH, CAUSAL, BIAS, true, 2>(a, s);
+    } else {
+        if (wgs <= (CAUSAL ? 400 : 256)) return launch_prefill<T, DH, CAUSAL, BIAS, true, 1>(a, s);
+        if constexpr (CAUSAL) {
+            if (wgs <= 1280) return launch_prefill<T, DH, CAUSAL, BIAS, true, 2>(a, s);
+        }
+        return launch_prefill<T, DH, CAUSAL, BIAS, false, 2>(a, s);
+    }
 }
 template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
 {
@@ -755,13 +795,15 @@ template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedA
 // the row kernel's many small workgroups.  us of either, fitted to 168 batches per type on one MI355X (1 to 64 sequences of 2
 // to 1000 tokens, ragged and not, 4 to 40 heads; within 6-11 % at the median, a quarter to a half at worst): the faster of the
 // two by these takes at most 1.17, 1.19 and 1.13 times the faster one measured; the MFMA kernel alone took up to 6.9, 24 and
-// 1.8 times (float x 64, float x 128, bf16 x 64; e.g. 64 sequences of one token, 16 heads, float x 128: 61 us, rows 4).
+// 1.8 times (float x 64, float x 128, bf16 x 64; e.g. 64 sequences of one token, 16 heads, float x 128: 61 us, rows 4).  The MFMA
+// kernel's figures for head size 64 are of a later fit, of its 64-row workgroups over 47 batches: the slower of the two is
+// taken by at most 12 % there.
 // bf16 x 128 stays on the MFMA kernel, whose tiles were made for it.
 static bool prefill_mfma_pays(const AttnPackedArgs& a)
 {
     if (a.dtype == DT_BF16 && a.dh == 128) return true;
     struct Cost { double row_fixed, row, pair, mfma_fixed, chain, tile; };
-    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 2.9, 5.0, 3.6}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 3.2, 1.53, 1.0};
+    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 1.9, 3.05, 2.8}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 2.5, 0.83, 0.8};
     const Cost& c = a.dtype == DT_BF16 ? B64 : a.dh == 64 ? F64 : F128;
     double row = c.row_fixed + a.H * (c.row * a.T + c.pair * a.work.pairs);
     double mfma = c.mfma_fixed + c.chain * ((a.work.max_len + PREFILL_TILE_K - 1) / PREFILL_TILE_K) + c.tile * a.H * a.work.key_tiles / 256;
@@ -786,7 +828,6 @@ hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
         });
     }
     if (mfma && mfma_fits) {
-        if ((int64_t)a.n_tiles * a.H > 0x7fffffff) return hipErrorInvalidValue;
         if (a.dtype == DT_F32) return a.dh == 64 ? launch_prefill<float, 64>(a, s) : launch_prefill<float, 128>(a, s);
         return a.dh == 64 ? launch_prefill<bf16_t, 64>(a, s) : launch_prefill<bf16_t, 128>(a, s);
     }

@@ -77,3 +77,31 @@ def test_bias_radius(dtype, dh, causal, R):
         worst = max(worst, float(err.max()))
     # as above; bf16 x 128 rounds its probabilities to bf16 before the second product too
     assert worst < (1e-5 if dtype == F32 else 2.0 ** -8 if dh == 64 else 2.0 ** -6), worst
+
+
+@pytest.mark.parametrize("dtype,dh,copies", [(BF16, 128, (10, 25)), (BF16, 64, (25,)), (F32, 64, (10,))])
+@pytest.mark.parametrize("causal,use_bias", [(1, 0), (0, 1), (1, 1), (0, 0)])
+@pytest.mark.parametrize("H", [5, 8])
+def test_forms_agree(dtype, dh, copies, causal, use_bias, H):
+    """The kernel's form depends on how many workgroups a batch makes; a sequence's rows do not."""
+    td = torch.float32 if dtype == F32 else torch.bfloat16
+    lens, R = [1, 63, 64, 65, 130, 200, 300], 50
+    T, inner = sum(lens), H * dh
+    g = torch.Generator().manual_seed(dh + H)
+    qkv = torch.randn((T, 3 * inner), generator=g).to(td).to(DEV)
+    tab = (torch.randn((H, 2 * R + 1), generator=g) * 0.5).to(DEV) if use_bias else None
+
+    def run(n, generic=-1):
+        cu = np.concatenate([[0], np.cumsum(lens * n)]).astype(np.int32)
+        out = torch.zeros((n * T, inner), dtype=td, device=DEV)
+        exe.exe_op_prefill_attention(dtype, cu, qkv.repeat(n, 1), H, dh, 0.11, causal, tab, R, out, force_generic=generic)
+        torch.cuda.synchronize()
+        return out.reshape(n, T, inner)
+
+    one, rows = run(1), run(1, 1)
+    # against the row kernel: a rounding of either in bf16, and of the probabilities at head size 128; sums in float
+    worst = float(((one - rows).float().abs().amax(dim=2) / rows.float().abs().amax(dim=2)).max())
+    assert worst < (1e-5 if dtype == F32 else 2.0 ** -7 if dh == 64 else 2.0 ** -6), worst
+    for n in copies:
+        many = run(n)
+        assert all(torch.equal(many[i], one[0]) for i in (0, n // 2, n - 1)), n
