@@ -13,7 +13,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libexe.so")
 CALL = os.path.join(HERE, "_call.so")              # csrc/call.c: host code against Python's headers
 CC = os.environ.get("CC", "gcc")
-SOURCES = ["kernels_elementwise.hip", "kernels_gemm.hip", "kernels_gemm_large.hip", "kernels_gemm_stream.hip", "kernels_attn.hip", "kernels_small.hip", "runtime.hip", "probe.hip", "sched.cpp"]
+SOURCES = ["kernels_elementwise.hip", "kernels_gemm.hip", "kernels_gemm_large.hip", "kernels_gemm_stream.hip", "kernels_gemm_f32.hip", "kernels_attn.hip", "kernels_small.hip", "runtime.hip", "probe.hip", "sched.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Kernel arguments preloaded into scalar registers instead of fetched by each wave's first instructions: decode iterations of
 # small models run 1-3 % faster (0.3 us of a 4-6 us launch).

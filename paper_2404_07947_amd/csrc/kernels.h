@@ -70,6 +70,9 @@ StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, i
 // The large tile kernel (kernels_gemm_large.hip, bf16): bm (256, 192 or 128) x 256 tiles, persistent on at most grid_max
 // workgroups, K in `splits` parts of k_per_split (every part at least 2 k-tiles of 64).
 hipError_t launch_gemm_large(const GemmArgs& a, int bm, int k_per_split, int splits, int grid_max, hipStream_t s);
+// The float tiles (kernels_gemm_f32.hip): K a multiple of 32, operands and bias 16-byte aligned.
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
+double gemm_f32_cost(int M, int N, int K);       // seconds
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t s);
 

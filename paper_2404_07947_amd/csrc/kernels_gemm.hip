@@ -1,10 +1,11 @@
 // GEMM kernels for the projections of a Transformer layer: out = epilogue(alpha * A[M,K] . W[N,K]^T + bias).
 //
-//  * gemm_tile_kernel    MFMA 16x16x32 (bf16) or 16x16x4 (float).  Macro tiles (BM x 256 or BM x 128, 128 bytes of K
+//  * gemm_tile_kernel    MFMA 16x16x32, bf16.  Macro tiles (BM x 256 or BM x 128, 128 bytes of K
 //                        per LDS stage) filled by direct global->LDS loads into a ring of stages; software-pipelined
-//                        fragment fetch; optional split-K into float partials (bf16), finished by splitk_reduce_kernel.
+//                        fragment fetch; optional split-K into float partials, finished by splitk_reduce_kernel.
 //  * gemm_large_kernel   (kernels_gemm_large.hip) bf16, tiles 256 features wide and 128 rows or more, K of 256 and more: encode,
 //                        and decode batches of 100 rows and more.
+//  * gemm_f32_kernel     (kernels_gemm_f32.hip) float, many rows.
 //  * gemm_stream_kernel  (kernels_gemm_stream.hip) few rows: streams the weights, the waves of a workgroup split K.
 //  * gemm_generic_kernel float or bf16 inputs, plain FMA in float, any shape (depths and widths the others do not take).
 //
@@ -59,7 +60,7 @@ constexpr int epilogue_cols(int BM, int BN, int WM, int WN, int ST)
 template <typename T, int BM, int BN, int WM, int WN, int ST>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
     int M, int N, int K, const T* __restrict__ A, const T* __restrict__ W, const T* __restrict__ bias, int act, float alpha, int out_mode, void* __restrict__ out, float* __restrict__ partial, int tiles_m, int tiles_n,
-    int k_per_split, int n_split, int flags, int lda, int ldw, KvStore kv)
+    int k_per_split, int n_split, int flags, int lda, int ldw)
 {
     // flags: bit 0 = spread the loads of a k-tile over the MFMAs (see below); bit 1 = the weights are read once
     // (a single row of output tiles): their loads are marked nontemporal so that they do not displace A in L2
@@ -188,9 +189,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
     using X3 = std::integral_constant<int, Q3>;
     using X4 = std::integral_constant<int, LPX>;
 
-    // MFMA operands: lane l holds 16-byte chunk 4*ks + l/16 of stage row l%16: the 8 k-values 8*(l/16) .. +7 of a 32-k step
-    // (16x16x32 bf16), or 4 k-values of a 16-k step, one for each of four MFMAs (16x16x4 float).  The W fragments of a step
-    // are kept for all its row parts.
+    // MFMA operands: lane l holds 16-byte chunk 4*ks + l/16 of stage row l%16: the 8 k-values 8*(l/16) .. +7 of a 32-k step.
+    // The W fragments of a step are kept for all its row parts.
     f32x4 acc[TN][TM];
     int frow = lane & 15, fk = lane >> 4;
     u32x4 fa[2][TMH], fw[2][TN];
@@ -303,8 +303,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
                 epilogue_tiles<T, TM, TN, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (out_mode == OUT_F32)
                 epilogue_tiles<T, TM, TN, EN, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
-            else if (sizeof(T) == 4 && kv.pool)
-                epilogue_tiles<T, TM, TN, EN, sizeof(T) == 4 ? EPI_T_KV : EPI_T>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out, kv);
             else if (act == 0)
                 epilogue_tiles<T, TM, TN, EN, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (T*)out);
             else if (act == 1)
@@ -432,6 +430,7 @@ static const Rates MODEL_RATES{44e9, 3.5e12, 6.5e12, 5.3e12, 4.5e-6}, OP_RATES{3
 
 static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, bool defer, bool model)
 {
+    if (dtype == DT_F32) return gemm_f32_cost(M, N, K);
     int bm = CFG[cfg].bm, bn = CFG[cfg].bn, bk = k_tile(dtype), esz = TROW / bk;
     const Rates& r = model ? MODEL_RATES : OP_RATES;
     int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -445,7 +444,7 @@ static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, boo
         t = rounds * (ktiles * per * (1.0 + 0.16 * busy) + fixed);
     } else {
         double fill = ktiles * (bm + bn) * TROW / r.fill;
-        double mfma = ktiles * 2.0 * bm * bn * bk / (dtype == DT_F32 ? 0.45e12 : cfg == C128x256 ? 2.8e12 : r.mfma);
+        double mfma = ktiles * 2.0 * bm * bn * bk / (cfg == C128x256 ? 2.8e12 : r.mfma);
         t = rounds * (fill > mfma ? fill : mfma);
     }
     double hbm = (double)N * K * esz / r.hbm;
@@ -660,15 +659,13 @@ static hipError_t launch_tile(const GemmArgs& a, const Plan& p, hipStream_t s)
     if (e != hipSuccess) return e;
     int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
     int items = tm * tn * p.splits;
-    constexpr int per_cu = 160 * 1024 / lds;         // float: 2 or 3 workgroups share a CU
-    int gmax = persistent_grid() * per_cu;
+    int gmax = persistent_grid();
     int grid = items < gmax ? items : gmax;
     int w_once = tm == 1 && a.M <= 64;      // measured: 7-10 % faster up to 32 rows, even from 96 rows on
     if (knobs().nt >= 0) w_once = knobs().nt != 0;
     kern<<<grid, threads, lds, s>>>(a.M, a.N, a.K, (const T*)a.A, (const T*)a.W, (const T*)a.bias, a.act, a.alpha, a.out_mode,
                                     a.out, a.workspace, tm, tn, p.k_per_split, p.splits,
-                                    (p.spread ? 1 : 0) | (w_once ? 2 : 0), a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K,
-                                    a.kv ? *a.kv : KvStore{});
+                                    (p.spread ? 1 : 0) | (w_once ? 2 : 0), a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K);
     return hipGetLastError();
 }
 
@@ -804,11 +801,7 @@ static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s)
     hipError_t e;
     if (p.route == 1) e = launch_gemm_stream(a, p.stream, s);
     else if (a.dtype == DT_F32) {
-        // Two or three workgroups on a CU hide each other's starts, epilogues and barriers (one, of 4 waves, ran at 60-70 TFLOP/s):
-        // 12288 x 768, K 256 81 -> 61 us, x 1024 93 -> 72; the smaller tile where the larger makes no more than a round:
-        // 12288 x 256, K 256 35 -> 23 (27 with the larger), K 1024 89 -> 63 (74).
-        int64_t tiles = (int64_t)((a.M + 63) / 64) * ((a.N + 127) / 128);
-        e = tiles <= 2 * persistent_grid() ? launch_tile<float, 64, 64, 32, 32, 2>(a, p, s) : launch_tile<float, 64, 128, 32, 32, 2>(a, p, s);
+        e = launch_gemm_f32(a, s);
     } else {
         switch (p.cfg) {
             case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;

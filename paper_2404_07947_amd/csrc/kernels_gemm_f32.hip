@@ -1,0 +1,210 @@
+// GEMM in float for many rows, on the bf16 matrix pipes.
+//
+// What bounds a float product: 16x16x4 float MFMAs, a sixteenth of the bf16 rate.  A float is the sum of three bf16 values without a
+// bit lost (h = x rounded, m = x - h rounded, l = x - h - m, 8 bits each), and a product of two floats their nine products, of
+// which the three smallest (m l, l m, l l; m l below 2^-26 of the product, of either sign) are left out: six bf16 MFMAs of 32 k in
+// the place of eight float ones of 4, at 16 times the rate.  Sums stay float, with fewer roundings on the way: error against 64
+// bits, 2-norm relative, of the float MFMAs -> now: see the table at launch_gemm_f32.
+//
+// A workgroup of 4 waves splits each operand tile once, on its way from registers to LDS (per wave and fragment it would be as much
+// vector work as the MFMAs take); two or three workgroups on a CU, so that one's splitting runs beside another's MFMAs.
+//
+// An infinite or NaN element, or one that rounds to infinity in bf16, makes its products NaN here: tiles with sums that are not
+// finite are computed again with float MFMAs (rare, so not for speed).  Elements below 2^-109 lose bits of l to bf16's range.
+#include <type_traits>
+
+#include "gemm_tile.h"
+#include "kernels.h"
+
+namespace exe {
+
+constexpr int F32_BK = 32, F32_THREADS = 256;
+constexpr int F32_ROW = F32_BK * 2;                          // bytes of a row of one plane
+constexpr int f32_lds(int BM, int BN) { return 3 * (BM + BN) * F32_ROW > 4 * 4096 ? 3 * (BM + BN) * F32_ROW : 4 * 4096; }
+
+// bf16 pairs in a dword: rounded to nearest even, and their values as floats
+__device__ __forceinline__ unsigned f32_round(float a, float b)
+{
+    unsigned r;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// A plane holds [rows][32 bf16]; 16-byte chunk c of row r at slot c ^ ((r >> 2) & 3): no bank conflicts on either side.
+template <int BM, int BN>
+__global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
+    const float* __restrict__ W, const float* __restrict__ bias, int act, float alpha, int out_mode, void* __restrict__ out, int tiles_n,
+    int lda, int ldw, KvStore kv)
+{
+    constexpr int TM = BM / 32, TN = BN / 32;                // 16-row and 16-feature tiles of a wave
+    constexpr int RA = BM * 8 / F32_THREADS, RW = BN * 8 / F32_THREADS;      // groups of 4 elements of a thread per operand and step
+    constexpr int PA = BM * F32_ROW, PW = BN * F32_ROW;      // bytes of a plane
+    constexpr int STAGE = 3 * (PA + PW);
+    extern __shared__ __align__(16) unsigned char lds[];     // two stages of A's planes h, m, l, then W's
+    int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int wm = wave >> 1, wn = wave & 1;
+    // an XCD's workgroups take neighbouring tiles, feature tiles fastest: they share activation rows in its L2
+    int total = gridDim.x, pid = blockIdx.x, chunk = total / 8;
+    if (pid < chunk * 8) pid = (pid % 8) * chunk + pid / 8;
+    int m0 = pid / tiles_n * BM, n0 = pid % tiles_n * BN;
+
+    // rows past the edge repeat the last one; their results are not stored
+    const float *src_a[RA], *src_w[RW];
+    unsigned dst_a[RA], dst_w[RW];
+    auto place = [&](int i) {
+        int u = i * F32_THREADS + tid, r = u >> 3, c = u & 7;
+        return (unsigned)(r * F32_ROW + (((c >> 1) ^ ((r >> 2) & 3)) << 4) + (c & 1) * 8);
+    };
+#pragma unroll
+    for (int i = 0; i < RA; ++i) {
+        int u = i * F32_THREADS + tid, r = m0 + (u >> 3);
+        src_a[i] = A + (int64_t)(r < M ? r : M - 1) * lda + (u & 7) * 4;
+        dst_a[i] = place(i);
+    }
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        int u = i * F32_THREADS + tid, r = n0 + (u >> 3);
+        src_w[i] = W + (int64_t)(r < N ? r : N - 1) * ldw + (u & 7) * 4;
+        dst_w[i] = 3 * PA + place(i);
+    }
+    f32x4 va[RA], vw[RW];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < RA; ++i) va[i] = *(const f32x4*)(src_a[i] + k);
+#pragma unroll
+        for (int i = 0; i < RW; ++i) vw[i] = *(const f32x4*)(src_w[i] + k);
+    };
+    auto put = [&](f32x4 v, unsigned dst, int plane) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            uint2 w = {f32_round(v[0], v[1]), f32_round(v[2], v[3])};
+            *(uint2*)(lds + dst + p * plane) = w;
+            if (p < 2) v -= f32x4{bf16lo(w.x), bf16hi(w.x), bf16lo(w.y), bf16hi(w.y)};
+        }
+    };
+
+    f32x4 acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int fr = lane & 15, g = lane >> 4;
+    const unsigned char* at = lds + fr * F32_ROW + ((g ^ ((fr >> 2) & 3)) << 4);       // rows 16 apart share their swizzle
+    const unsigned char *at_a = at + wm * (BM / 2) * F32_ROW, *at_w = at + 3 * PA + wn * (BN / 2) * F32_ROW;
+
+    fetch(0);
+    for (int k = 0; k < K; k += F32_BK) {
+#pragma unroll
+        for (int i = 0; i < RA; ++i) put(va[i], dst_a[i], PA);
+#pragma unroll
+        for (int i = 0; i < RW; ++i) put(vw[i], dst_w[i], PW);
+        __syncthreads();
+        if (k + F32_BK < K) fetch(k + F32_BK);
+        u32x4 fa[3][TM], fw[2][3];
+        auto read_a = [&](int p) {
+#pragma unroll
+            for (int j = 0; j < TM; ++j) fa[p][j] = *(const u32x4*)(at_a + p * PA + j * 16 * F32_ROW);
+        };
+        auto read_w = [&](int i, int p) { fw[i & 1][p] = *(const u32x4*)(at_w + p * PW + i * 16 * F32_ROW); };
+        // the smallest products first, and their operands
+        read_w(0, 2); read_a(0); read_w(0, 0); read_a(2); read_w(0, 1); read_a(1);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+            if (i + 1 < TN) { read_w(i + 1, 2); read_w(i + 1, 0); read_w(i + 1, 1); }
+            constexpr int ORDER[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+            for (int x = 0; x < 6; ++x)
+#pragma unroll
+                for (int j = 0; j < TM; ++j) acc[i][j] = HalfUnit<bf16_t>::mma(fw[i & 1][ORDER[x][0]], fa[ORDER[x][1]][j], acc[i][j]);
+        }
+        __syncthreads();
+    }
+
+    int row0 = m0 + wm * (BM / 2), col0 = n0 + wn * (BN / 2);
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            // 0 * x is NaN for a sum that is not finite
+            f32x4 z = acc[i][j] * 0.f;
+            float s = z[0] + z[1] + z[2] + z[3];
+            if (__builtin_amdgcn_ballot_w64(s != s) == 0) continue;
+            int r = row0 + j * 16 + fr, n = col0 + i * 16 + fr;
+            const float* pa = A + (int64_t)(r < M ? r : M - 1) * lda + g;
+            const float* pw = W + (int64_t)(n < N ? n : N - 1) * ldw + g;
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < K; k += 4) c = __builtin_amdgcn_mfma_f32_16x16x4f32(pw[k], pa[k], c, 0, 0, 0);
+            acc[i][j] = c;
+        }
+
+    unsigned stg = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds + wave * 4096;
+    if (out_mode == OUT_RESID)
+        epilogue_tiles<float, TM, TN, 32, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+    else if (out_mode == OUT_F32)
+        epilogue_tiles<float, TM, TN, 32, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+    else if (kv.pool)
+        epilogue_tiles<float, TM, TN, 32, EPI_T_KV>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (float*)out, kv);
+    else if (act == 0)
+        epilogue_tiles<float, TM, TN, 32, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (float*)out);
+    else if (act == 1)
+        epilogue_tiles<float, TM, TN, 32, EPI_T_GELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (float*)out);
+    else
+        epilogue_tiles<float, TM, TN, 32, EPI_T>(acc, stg, lane, row0, col0, M, N, bias, alpha, nullptr, (float*)out);
+}
+
+template <int BM, int BN> static hipError_t launch_f32(const GemmArgs& a, hipStream_t s)
+{
+    auto kern = gemm_f32_kernel<BM, BN>;
+    constexpr int lds = f32_lds(BM, BN);
+    static_assert(lds <= 64 * 1024, "no more than a launch takes without asking");
+    int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
+    kern<<<tm * tn, F32_THREADS, lds, s>>>(a.M, a.N, a.K, (const float*)a.A, (const float*)a.W, (const float*)a.bias, a.act, a.alpha,
+                                           a.out_mode, a.out, tn, a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K, a.kv ? *a.kv : KvStore{});
+    return hipGetLastError();
+}
+
+// The tile, and what a launch takes: n workgroups fall to the busiest CU, `resident` of them at a time; a step of 32 k takes them
+// `step` together and each `share` more (fitted, us within 10 % of the measured ones below).
+// us on one MI355X, the float MFMA kernel that this replaces / 128 x 128 / 64 x 128 / 64 x 64, and the 2-norm relative error against
+// 64 bits there and here:
+//   12288 x  768, K  256  51.8 / 42.6 / 37.0 / 38.5   2.9e-7 2.3e-7     12288 x 1024, K  256 (GELU)  65.8 / 47.9 / 47.4 / 53   3.2e-7 2.6e-7
+//   12288 x  256, K 1024  56.4 / 55.9 / 52.2 / 48.9   5.7e-7 4.9e-7      8000 x  512, K 2048   165 / 109 / 109 / 122           8.1e-7 7.0e-7
+//    3000 x  768, K  256  18.1 / 18.4 / 16.8 / 14.8   2.9e-7 2.3e-7     20000 x 1024, K  256 (GELU)  105 / 74 / 77 / 87        3.2e-7 2.6e-7
+// The last 128 x 128 step takes 1.1 us per workgroup where its MFMAs alone take 0.7: splitting overlaps with other waves' MFMAs only in
+// part.  Two stages in LDS with the splitting between a wave's own MFMAs were slower (8000 x 2048, K 512 103 -> 132).
+struct F32Tile { int bm, bn, resident; double step, share; };
+static const F32Tile F32_TILES[] = {{128, 128, 2, 0.55e-6, 1.05e-6}, {64, 128, 3, 0.6e-6, 0.53e-6}, {64, 64, 3, 0.4e-6, 0.32e-6}};
+static int f32_tile(int M, int N, int K, double* seconds)
+{
+    int best = 0;
+    for (int i = 0; i < 3; ++i) {
+        const F32Tile& t = F32_TILES[i];
+        int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        double n = (double)((tiles + 255) / 256), rounds = (double)(((int64_t)n + t.resident - 1) / t.resident);
+        double c = 4e-6 + (double)M * N * 4 / 6e12 + (double)(K / F32_BK) * (t.step * rounds + t.share * n);
+        if (i == 0 || c < *seconds) {
+            *seconds = c;
+            best = i;
+        }
+    }
+    return best;
+}
+
+double gemm_f32_cost(int M, int N, int K)
+{
+    double seconds = 0.0;
+    f32_tile(M, N, K, &seconds);
+    return seconds;
+}
+
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s)
+{
+    double seconds = 0.0;
+    switch (f32_tile(a.M, a.N, a.K, &seconds)) {
+        case 0: return launch_f32<128, 128>(a, s);
+        case 1: return launch_f32<64, 128>(a, s);
+        default: return launch_f32<64, 64>(a, s);
+    }
+}
+
+}  // namespace exe

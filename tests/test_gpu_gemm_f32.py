@@ -1,0 +1,76 @@
+"""Float products of many rows (gemm_f32_kernel): tile edges in either direction, depths of one step and more, every way of storing,
+and elements that its bf16 parts cannot hold."""
+import pytest
+import torch
+
+import paper_2404_07947_amd as exe
+import workload as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def product(A, W, bias=None, act=-1, alpha=1.0, out_mode=0, out=None):
+    M, K = A.shape
+    N = W.shape[0]
+    assert exe.exe_op_gemm_plan(wl.DTYPE_F32, M, N, K)["route"] == 0              # tiles, not the streaming kernel
+    out = torch.zeros((M, N), device=DEV) if out is None else out
+    exe.exe_op_gemm_model(wl.DTYPE_F32, M, N, K, A, W, bias, act, alpha, out_mode, out)
+    torch.cuda.synchronize()
+    return out.double().cpu()
+
+
+def bound(A, W, K):
+    """A sum's 6 additions per 32 k, each rounded to 2^-24 of at most the sum of magnitudes, and what is left out of the products."""
+    return (6 * ((K + 31) // 32) + 4) * 2.0 ** -24 * (A.double().abs() @ W.double().abs().T)
+
+
+# 64 x 64, 64 x 128 and 128 x 128 tiles by what a launch makes of them
+@pytest.mark.parametrize("M", [2049, 2111, 2175, 12289])
+@pytest.mark.parametrize("N,K", [(4, 32), (60, 64), (68, 96), (132, 256), (256, 2080), (772, 256), (1028, 32)])
+def test_edges(M, N, K):
+    g = torch.Generator().manual_seed(M + N + K)
+    A, W = torch.randn((M, K), generator=g), torch.randn((N, K), generator=g)
+    got = product(A.to(DEV), W.to(DEV))
+    assert bool(((got - A.double() @ W.double().T).abs() <= bound(A, W, K)).all())
+
+
+@pytest.mark.parametrize("mode", ["relu", "gelu", "resid", "f32", "alpha"])
+def test_stores(mode):
+    M, N, K = 2300, 324, 160
+    g = torch.Generator().manual_seed(5)
+    A, W, b = torch.randn((M, K), generator=g), torch.randn((N, K), generator=g) * 0.1, torch.randn((N,), generator=g)
+    ref, lim = A.double() @ W.double().T, bound(A, W, K) + 2.0 ** -22 * (8 + b.double().abs())
+    alpha, act, out_mode, out = 1.0, -1, 0, None
+    if mode == "alpha":
+        alpha = 0.37
+        ref = ref * float(torch.tensor(0.37))
+    ref = ref + b.double()
+    if mode == "relu":
+        act, ref = 0, ref.relu()
+    elif mode == "gelu":                                        # slope of at most 1.13
+        act, ref, lim = 1, torch.nn.functional.gelu(ref), 1.2 * lim
+    elif mode == "resid":
+        h = torch.randn((M, N), generator=g)
+        out_mode, out, ref = 1, h.to(DEV), ref + h.double()
+    elif mode == "f32":
+        out_mode = 2
+    got = product(A.to(DEV), W.to(DEV), b.to(DEV), act, alpha, out_mode, out)
+    assert bool(((got - ref).abs() <= lim).all())
+
+
+def test_values():
+    """Infinities, NaN, elements that round to infinity in bf16, and small ones."""
+    M, N, K = 2200, 100, 64
+    g = torch.Generator().manual_seed(6)
+    A, W = torch.randn((M, K), generator=g), torch.randn((N, K), generator=g) * 0.01
+    A[3, 5], A[70, 0], A[71, 63], A[2199, 7] = float("inf"), float("-inf"), float("nan"), 3.4e38
+    W[9, 2] = float("inf")
+    A[100:110] *= 1e-28
+    A[110, :2], W[11, :2] = 3e38, 10.0                           # overflows as a sum of floats does
+    got, ref = product(A.to(DEV), W.to(DEV)), A.double() @ W.double().T
+    ref = torch.where(ref.abs() > 3.4028235e38, torch.sign(ref) * float("inf"), ref)
+    assert torch.equal(got.isnan(), ref.isnan())
+    assert torch.equal(got.isinf(), ref.isinf()) and torch.equal(got[got.isinf()], ref[ref.isinf()])
+    ok = ref.isfinite()
+    assert bool(((got - ref).abs() <= bound(A, W, K))[ok].all())
