@@ -31,6 +31,24 @@ template <> struct HalfUnit<float> {
     }
 };
 
+// Floats as the sum of three bf16 parts, all of their bits: x rounded, what is left rounded, and the rest; bf16 pairs in dwords.  The
+// products of two such floats that count (see kernels_gemm_f32.hip) are PARTS of the one and the other, smallest first.
+constexpr int PARTS[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+__device__ __forceinline__ unsigned bf16_pair(float a, float b)
+{
+    unsigned r;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ void bf16_parts(f32x4 v, uint2 (&w)[3])
+{
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        w[p] = uint2{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])};
+        if (p < 2) v -= f32x4{bf16lo(w[p].x), bf16hi(w[p].x), bf16lo(w[p].y), bf16hi(w[p].y)};
+    }
+}
+
 // Stores 4 consecutive output features n..n+3 of row m.  v = raw accumulators.
 template <typename T>
 __device__ __forceinline__ void epilogue_store4(f32x4 v, int m, int n, int N, const T* __restrict__ bias, int act,

@@ -220,10 +220,12 @@ template <typename T, int DH, bool V2> constexpr int pf_lds()     // two key til
 {
     return (V2 ? 4 : 3) * pf_tile_bytes(DH * (int)sizeof(T));
 }
+// float x 64: three bf16 parts per key, value, query and probability, the parts of one key and one value tile in LDS
+template <typename T, int DH> constexpr bool pf_parted() { return sizeof(T) == 4 && DH == 64; }
 // workgroups per CU that the registers must leave room for (LDS does)
 template <typename T, int DH, bool V2> constexpr int pf_per_cu()
 {
-    if (sizeof(T) == 4) return DH == 128 ? 1 : V2 ? 2 : 3;
+    if (sizeof(T) == 4) return DH == 128 ? 1 : 3;
     return DH == 64 ? 5 : V2 ? 2 : 3;
 }
 
@@ -284,14 +286,21 @@ __device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* 
 // MFMAs hide behind the exponentials for the most part (one set more and a rounded rest, 2^-17 relative: 40 us where three
 // take 43).
 //
-// Float: the same tiles and softmax with 16x16x4 MFMAs, four per 16-byte fragment; the second product takes one key per lane
+// Float x 64: bf16 MFMAs too, six for the products that count of three bf16 parts per float (see kernels_gemm_f32.hip), an eighth
+// of whose time eight float MFMAs take.  Keys and values are parted by all threads on their way through registers into
+// LDS, one tile of either; the next tile's loads are in flight meanwhile.  A score, and a tile's share of an output, is the sum
+// of three numbers: the first parts' products of 32 features (keys) twice, and all the others'.  Error against 64 bits, 2-norm
+// relative, float MFMAs / row kernel / now: 200 rows 1.22e-7 / 1.09e-7 / 1.05e-7, 1000 1.38e-7 / 1.31e-7 / 1.20e-7, inputs three times
+// as large 3.95e-7 / 3.98e-7 / 3.71e-7, 4096 rows 1.62e-7 / 1.71e-7 / 1.45e-7; in one chain of additions 1.71e-7 at 1000.  What the parts
+// cannot hold (infinities, NaN, values that round to infinity) makes NaN, and such rows are computed again.
+//
+// Float x 128: the same tiles and softmax with 16x16x4 MFMAs, four per 16-byte fragment; the second product takes one key per lane
 // group and MFMA, so P again goes from accumulator to operand without moving, and V is read 4 bytes per lane.  A score is the
 // pairwise sum of sums of 8 features, an output of sums over 16 keys: with one chain of additions for either, the kernel erred
-// 2.3 to 3.3 times as much against 64 bits as the row kernel (1000 rows 6.5e-7 of the result, now and there 2.5e-7; 4096 rows
-// 9.4e-7, now 3.0e-7, there 3.2e-7), for 2 to 9 % less time.
+// 2.3 to 3.3 times as much against 64 bits as the row kernel, for 2 to 9 % less time.
 //
 // Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 34;
-// float x 64, 32 sequences of 384, 4 heads, 192 -> 56.
+// float x 64, 32 sequences of 384, 4 heads, 192 -> 36.
 template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB>
 __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_mfma_kernel(const T* __restrict__ qkv,
                                                                   const int32_t* __restrict__ cu,
@@ -306,6 +315,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
     constexpr int PF_TILE = pf_tile_bytes(RB);
     constexpr int DS = RB / 64, DT = DH / 16;                     // 64-byte steps of the first product, feature tiles of the second
     constexpr bool SPLIT_P = sizeof(T) == 2 && DH == 64;
+    constexpr bool PARTED = pf_parted<T, DH>();
+    constexpr int PLANE = PF_KT * 128;                            // PARTED: bytes of one part of a key or value tile
     extern __shared__ __align__(16) unsigned char pf_smem[];      // 2 key tiles, then the value tile(s), then the bias table
     float* sbias = (float*)(pf_smem + pf_lds<T, DH, V2>());
 
@@ -343,14 +354,28 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
     }
 
     // query fragments (B operand): lane (query qi, lane group g) holds 16-byte chunk 4*ds + g of its query row
-    u32x4 qf[QB][DS];
+    // (PARTED: parts 0 .. 2 of elements 8 * g .. +7 of its first and of its second 32)
+    constexpr int QF = PARTED ? 6 : DS;
+    u32x4 qf[QB][QF];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         int qr = wq0 + qb * 16 + qi;
         qr = qr < n ? qr : n - 1;
-        const u32x4* qp = (const u32x4*)(seq + (int64_t)qr * ld) + g;
+        if constexpr (PARTED) {
+            const f32x4* qp = (const f32x4*)(seq + (int64_t)qr * ld) + 2 * g;
 #pragma unroll
-        for (int ds = 0; ds < DS; ++ds) qf[qb][ds] = qp[ds * 4];
+            for (int ds = 0; ds < 2; ++ds) {
+                uint2 a[3], b[3];
+                bf16_parts(qp[ds * 8], a);
+                bf16_parts(qp[ds * 8 + 1], b);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) qf[qb][ds * 3 + p] = u32x4{a[p].x, a[p].y, b[p].x, b[p].y};
+            }
+        } else {
+            const u32x4* qp = (const u32x4*)(seq + (int64_t)qr * ld) + g;
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) qf[qb][ds] = qp[ds * 4];
+        }
     }
     // the softmax below takes the maximum of the raw scores, which wants a positive scale: the sign of a negative one goes to
     // the queries
@@ -358,7 +383,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-            for (int ds = 0; ds < DS; ++ds) qf[qb][ds] ^= sizeof(T) == 4 ? 0x80000000u : 0x80008000u;
+            for (int i = 0; i < QF; ++i) qf[qb][i] ^= sizeof(T) == 4 && !PARTED ? 0x80000000u : 0x80008000u;
     }
     int kend = n;
     if (CAUSAL) kend = q0 + QT < n ? q0 + QT : n;
@@ -399,6 +424,30 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
     auto load_k = [&](int kt) { load_tile((const char*)keys, kt, lds_base + (kt & 1) * PF_TILE); };
     auto load_v = [&](int kt) { load_tile((const char*)values, kt, lds_base + (2 + (V2 ? kt & 1 : 0)) * PF_TILE); };
 
+    // PARTED: a tile goes through registers, 4 groups of 4 elements per thread of keys and of values, and is parted on the way to LDS
+    f32x4 kv_reg[PARTED ? 8 : 1];
+    auto fetch_kv = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int u = i * PF_THREADS + tid, kg = kt * PF_KT + (u >> 4);
+            kg = kg < n ? kg : n - 1;
+            unsigned at = (unsigned)kg * kv_row + (u & 15) * 16;
+            kv_reg[i] = *(const f32x4*)((const char*)keys + at);
+            kv_reg[4 + i] = *(const f32x4*)((const char*)values + at);
+        }
+    };
+    auto put_kv = [&]() {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            int u = (i & 3) * PF_THREADS + tid, row = u >> 4, c = u & 15;
+            unsigned char* d = pf_smem + (i >> 2) * 3 * PLANE + row * 128 + (((c >> 1) ^ pf_swz<128>(row)) << 4) + (c & 1) * 8;
+            uint2 w[3];
+            bf16_parts(kv_reg[i], w);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *(uint2*)(d + p * PLANE) = w[p];
+        }
+    };
+
     f32x4 o_acc[QB][DT];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
@@ -426,11 +475,31 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
         // (With a bias, whose look-ups want registers too, all of a lane's offsets are.)
         int l = lane;
         if (BIAS) asm volatile("" : "+v"(l));
-        int qi = l & 15, g = l >> 4, qx = pf_swz<RB>(qi);
+        int qi = l & 15, g = l >> 4, qx = pf_swz<PARTED ? 128 : RB>(qi);
         if (!BIAS) asm volatile("" : "+v"(qx));
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
-            if constexpr (sizeof(T) == 4) {
+            if constexpr (PARTED) {
+                // The products of the first parts, 32 features each, and the others' sum (which is small, and so are its roundings)
+                // are added as three numbers.
+                f32x4 c[2][QB], rest[QB];
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) rest[qb] = c[0][qb] = c[1][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ds = 0; ds < 2; ++ds) {
+                    u32x4 fk[3];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) fk[p] = *(const u32x4*)(pf_smem + p * PLANE + (kb * 16 + qi) * 128 + (((ds * 4 + g) ^ qx) << 4));
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) {
+                        c[ds][qb] = HalfUnit<bf16_t>::mma(fk[0], qf[qb][ds * 3], c[ds][qb]);
+#pragma unroll
+                        for (int x = 0; x < 5; ++x) rest[qb] = HalfUnit<bf16_t>::mma(fk[PARTS[x][0]], qf[qb][ds * 3 + PARTS[x][1]], rest[qb]);
+                    }
+                }
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) s_acc[qb][kb] = c[0][qb] + c[1][qb] + rest[qb];
+            } else if constexpr (sizeof(T) == 4) {
                 // sums of 8 features each (two MFMAs), added pairwise: part x is half x % 2 of the 16-byte chunks 4 * (x / 2) + g
                 auto sum = [&](auto self, auto first, auto count, f32x4 (&c)[QB]) -> void {
                     constexpr int X = decltype(first)::value, N = decltype(count)::value;
@@ -565,7 +634,48 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
     int v_row = 4 * g + (qi >> 2), v_q = qi & 3;
     auto phase_pv = [&](int kt) {
         const unsigned char* tV = pf_smem + (2 + (V2 ? kt & 1 : 0)) * PF_TILE;
-        if constexpr (sizeof(T) == 4) {
+        if constexpr (PARTED) {
+            // probabilities in parts, as below, and a tile's sums added as one
+            const unsigned char* sV = pf_smem + 3 * PLANE + v_row * 128 + (v_q & 1) * 8;
+            bf16x8 pf[2][3][QB];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    uint2 a[3], b[3];
+                    bf16_parts(s_acc[qb][2 * ks], a);
+                    bf16_parts(s_acc[qb][2 * ks + 1], b);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) pf[ks][p][qb] = __builtin_bit_cast(bf16x8, u32x4{a[p].x, a[p].y, b[p].x, b[p].y});
+                }
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                f32x4 c[2][QB], rest[QB];
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) rest[qb] = c[0][qb] = c[1][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                int slot = ((2 * dt + (v_q >> 1)) ^ pf_swz<128>(v_row)) << 4;
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    bf16x8 fv[3];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        uint2 lo = pf_read_tr(sV + p * PLANE + ks * 32 * 128 + slot);
+                        uint2 hi = pf_read_tr(sV + p * PLANE + (ks * 32 + 16) * 128 + slot);
+                        fv[p] = __builtin_bit_cast(bf16x8, uint4{lo.x, lo.y, hi.x, hi.y});
+                    }
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) {
+                        c[ks][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv[0], pf[ks][0][qb], c[ks][qb], 0, 0, 0);
+#pragma unroll
+                        for (int x = 0; x < 5; ++x)
+                            rest[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fv[PARTS[x][0]], pf[ks][PARTS[x][1]][qb], rest[qb], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) o_acc[qb][dt] += c[0][qb] + c[1][qb] + rest[qb];
+            }
+            return;
+        } else if constexpr (sizeof(T) == 4) {
             // Lane group g supplies key 4*g + r of key block kb, for feature 16*dt + qi: chunk 4*dt + qi/4 of its row, at slot
             // 4 * (dt ^ g) + (qi/4 ^ r).  A sum per key block, added pairwise.  (The offsets are recomputed per tile: held, they spill.)
             int ga = g;
@@ -638,7 +748,20 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
         }
     };
 
-    if constexpr (V2) {
+    if constexpr (PARTED) {
+        fetch_kv(0);
+        for (int kt = 0; kt < n_tiles; ++kt) {
+            put_kv();
+            __syncthreads();
+            if (kt + 1 < n_tiles) fetch_kv(kt + 1);
+            if (active(kt)) {
+                phase_s(kt);
+                phase_softmax(kt);
+                phase_pv(kt);
+            }
+            __syncthreads();
+        }
+    } else if constexpr (V2) {
         load_k(0);
         load_v(0);
         for (int kt = 0; kt < n_tiles; ++kt) {
@@ -764,16 +887,13 @@ template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB> static hi
 //   not causal, T5's bias  128 12.6 / 12.0 / 10.1    384 23.7 / 23.6 / 25.5    768 60.6 / 71.2 / 81.3    13696 977 / 1137 / 1423
 //   QB 2 with two / QB 1 with two (/ with one)
 //   bf16 x 64   64 18.3 / 12.1    592 27.3 / 22.8    2672 62.4 / 57.6: half the registers, so five workgroups on a CU in place of four
-//   float x 64  148 60.0 / 40.8 / 41.6    292 73.2 / 45.0 / 51.7    452 81.0 / 63.4 / 58.6    804 122 / 106 / 100: MFMA-bound, so
-//               what counts is how evenly the CUs are loaded; one buffer and a third workgroup from three pieces per CU on
+//   float x 64, float MFMAs with QB 2 / with QB 1 / bf16 parts (one form: three workgroups on a CU)
+//               148 60.0 / 40.8 / 32.5    292 73.2 / 45.0 / 34.8    452 81.0 / 58.6 / 38.9    804 122 / 100 / 64.6
 template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
 {
     const int64_t wgs = (int64_t)a.n_tiles * a.H;
     if constexpr (DH == 64) {
-        if constexpr (sizeof(T) == 4) {
-            if (2 * wgs > 768) return launch_prefill<T, DH, CAUSAL, BIAS, false, 1>(a, s);
-        }
-        return launch_prefill<T, DH, CAUSAL, BIAS, true, 1>(a, s);
+        return launch_prefill<T, DH, CAUSAL, BIAS, !pf_parted<T, DH>(), 1>(a, s);
     } else if constexpr (sizeof(T) == 4) {
         return launch_prefill<T, DH, CAUSAL, BIAS, true, 2>(a, s);
     } else {
@@ -803,7 +923,7 @@ static bool prefill_mfma_pays(const AttnPackedArgs& a)
 {
     if (a.dtype == DT_BF16 && a.dh == 128) return true;
     struct Cost { double row_fixed, row, pair, mfma_fixed, chain, tile; };
-    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 1.9, 3.05, 2.8}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 2.5, 0.83, 0.8};
+    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 1.6, 2.8, 1.2}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 2.5, 0.83, 0.8};
     const Cost& c = a.dtype == DT_BF16 ? B64 : a.dh == 64 ? F64 : F128;
     double row = c.row_fixed + a.H * (c.row * a.T + c.pair * a.work.pairs);
     double mfma = c.mfma_fixed + c.chain * ((a.work.max_len + PREFILL_TILE_K - 1) / PREFILL_TILE_K) + c.tile * a.H * a.work.key_tiles / 256;

@@ -22,14 +22,6 @@ constexpr int F32_BK = 32, F32_THREADS = 256;
 constexpr int F32_ROW = F32_BK * 2;                          // bytes of a row of one plane
 constexpr int f32_lds(int BM, int BN) { return 3 * (BM + BN) * F32_ROW > 4 * 4096 ? 3 * (BM + BN) * F32_ROW : 4 * 4096; }
 
-// bf16 pairs in a dword: rounded to nearest even, and their values as floats
-__device__ __forceinline__ unsigned f32_round(float a, float b)
-{
-    unsigned r;
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 // A plane holds [rows][32 bf16]; 16-byte chunk c of row r at slot c ^ ((r >> 2) & 3): no bank conflicts on either side.
 template <int BM, int BN>
 __global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
@@ -75,12 +67,10 @@ __global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32
         for (int i = 0; i < RW; ++i) vw[i] = *(const f32x4*)(src_w[i] + k);
     };
     auto put = [&](f32x4 v, unsigned dst, int plane) {
+        uint2 w[3];
+        bf16_parts(v, w);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            uint2 w = {f32_round(v[0], v[1]), f32_round(v[2], v[3])};
-            *(uint2*)(lds + dst + p * plane) = w;
-            if (p < 2) v -= f32x4{bf16lo(w.x), bf16hi(w.x), bf16lo(w.y), bf16hi(w.y)};
-        }
+        for (int p = 0; p < 3; ++p) *(uint2*)(lds + dst + p * plane) = w[p];
     };
 
     f32x4 acc[TN][TM];
@@ -111,11 +101,10 @@ __global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
             if (i + 1 < TN) { read_w(i + 1, 2); read_w(i + 1, 0); read_w(i + 1, 1); }
-            constexpr int ORDER[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 #pragma unroll
             for (int x = 0; x < 6; ++x)
 #pragma unroll
-                for (int j = 0; j < TM; ++j) acc[i][j] = HalfUnit<bf16_t>::mma(fw[i & 1][ORDER[x][0]], fa[ORDER[x][1]][j], acc[i][j]);
+                for (int j = 0; j < TM; ++j) acc[i][j] = HalfUnit<bf16_t>::mma(fw[i & 1][PARTS[x][0]], fa[PARTS[x][1]][j], acc[i][j]);
         }
         __syncthreads();
     }
