@@ -1,6 +1,6 @@
 """exe: batched Transformer execution (encode once, decode iteratively over ragged K/V caches) on MI355X.
 
-Thin ctypes binding of libexe.so (include/exe.h).  Every step of the path runs in the library's HIP
+Thin binding of libexe.so (include/exe.h): ctypes, and csrc/call.c for the calls of a serving loop.  Every step of the path runs in the library's HIP
 kernels; this package only marshals arguments.  PyTorch is used by callers for device memory and
 streams.  Importing the package does not load the library; the first call does, and raises if the
 library has not been built (python -m paper_2404_07947_amd.build).

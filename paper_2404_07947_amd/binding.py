@@ -1,4 +1,4 @@
-"""ctypes marshalling for include/exe.h.  No arithmetic of the method lives here."""
+"""Marshalling for include/exe.h, by ctypes and (encode, decode_step, seq_release) csrc/call.c.  No arithmetic of the method lives here."""
 from __future__ import annotations
 
 import ctypes as C

@@ -1,4 +1,4 @@
-"""Builds libexe.so (HIP kernels + runtime + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libexe.so (HIP kernels + runtime + C ABI) for gfx950 with hipcc, and _call.so (Python's way to its serving calls), in-tree."""
 from __future__ import annotations
 
 import os

@@ -4,7 +4,7 @@
 // bit lost (h = x rounded, m = x - h rounded, l = x - h - m, 8 bits each), and a product of two floats their nine products, of
 // which the three smallest (m l, l m, l l; m l below 2^-26 of the product, of either sign) are left out: six bf16 MFMAs of 32 k in
 // the place of eight float ones of 4, at 16 times the rate.  Sums stay float, with fewer roundings on the way: error against 64
-// bits, 2-norm relative, of the float MFMAs -> now: see the table at launch_gemm_f32.
+// bits: see the table at f32_tile.
 //
 // A workgroup of 4 waves splits each operand tile once, on its way from registers to LDS (per wave and fragment it would be as much
 // vector work as the MFMAs take); two or three workgroups on a CU, so that one's splitting runs beside another's MFMAs.
