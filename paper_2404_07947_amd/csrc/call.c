@@ -7,7 +7,8 @@
 //
 // Each function takes the address of the library's function and the model handle as integers, then that function's arguments in
 // their order without the count, which is the length of the first array: int32 arrays as C-contiguous buffers, device pointers as
-// integers, either of them None for a null pointer.  It returns the library's status.
+// integers, either of them None for a null pointer (the first array excepted: without it there is no count).  It returns the
+// library's status.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
@@ -35,6 +36,15 @@ static int array(PyObject* o, int flags, Held* h, int32_t** p)
     return 1;
 }
 
+// the first array, whose length is the count
+static int first(PyObject* o, Held* h, int32_t** p, int* count)
+{
+    if (o == Py_None) PyErr_SetString(PyExc_TypeError, "expected an int32 array of sequence ids, got None");
+    if (o == Py_None || !array(o, PyBUF_ND, h, p)) return 0;
+    *count = (int)h->view[h->n - 1].shape[0];
+    return 1;
+}
+
 static int address(PyObject* o, void** p)
 {
     *p = o == Py_None ? NULL : PyLong_AsVoidPtr(o);
@@ -59,13 +69,14 @@ static PyObject* py_encode(PyObject* self, PyObject* const* a, Py_ssize_t n)
     typedef int (*Fn)(void*, int32_t, const int32_t*, const int32_t*, const int32_t*, const int32_t*, const void*, int32_t*, void*);
     void *fn, *model, *hidden, *out;
     int32_t *ids, *lens, *toks, *reserve, *next;
+    int count;
     Held h = {.n = 0};
     PyObject* r = NULL;
     if (!takes(n, 9)) return NULL;
-    if (function(a[0], &fn) && address(a[1], &model) && array(a[2], PyBUF_ND, &h, &ids) && array(a[3], PyBUF_ND, &h, &lens) &&
+    if (function(a[0], &fn) && address(a[1], &model) && first(a[2], &h, &ids, &count) && array(a[3], PyBUF_ND, &h, &lens) &&
         array(a[4], PyBUF_ND, &h, &toks) && array(a[5], PyBUF_ND, &h, &reserve) && address(a[6], &hidden) &&
         array(a[7], PyBUF_ND | PyBUF_WRITABLE, &h, &next) && address(a[8], &out)) {
-        int rc, count = ids ? (int)h.view[0].shape[0] : 0;
+        int rc;
         Py_BEGIN_ALLOW_THREADS
         rc = ((Fn)fn)(model, count, ids, lens, toks, reserve, hidden, next, out);
         Py_END_ALLOW_THREADS
@@ -80,13 +91,14 @@ static PyObject* py_decode_step(PyObject* self, PyObject* const* a, Py_ssize_t n
     typedef int (*Fn)(void*, int32_t, const int32_t*, const int32_t*, const int32_t*, const void*, int32_t*, void*);
     void *fn, *model, *hidden, *out;
     int32_t *ids, *toks, *lens, *next;
+    int count;
     Held h = {.n = 0};
     PyObject* r = NULL;
     if (!takes(n, 8)) return NULL;
-    if (function(a[0], &fn) && address(a[1], &model) && array(a[2], PyBUF_ND, &h, &ids) && array(a[3], PyBUF_ND, &h, &toks) &&
+    if (function(a[0], &fn) && address(a[1], &model) && first(a[2], &h, &ids, &count) && array(a[3], PyBUF_ND, &h, &toks) &&
         array(a[4], PyBUF_ND, &h, &lens) && address(a[5], &hidden) && array(a[6], PyBUF_ND | PyBUF_WRITABLE, &h, &next) &&
         address(a[7], &out)) {
-        int rc, count = ids ? (int)h.view[0].shape[0] : 0;
+        int rc;
         Py_BEGIN_ALLOW_THREADS
         rc = ((Fn)fn)(model, count, ids, toks, lens, hidden, next, out);
         Py_END_ALLOW_THREADS
@@ -101,11 +113,12 @@ static PyObject* py_seq_release(PyObject* self, PyObject* const* a, Py_ssize_t n
     typedef int (*Fn)(void*, int32_t, const int32_t*);
     void *fn, *model;
     int32_t* ids;
+    int count;
     Held h = {.n = 0};
     PyObject* r = NULL;
     if (!takes(n, 3)) return NULL;
-    if (function(a[0], &fn) && address(a[1], &model) && array(a[2], PyBUF_ND, &h, &ids)) {
-        int rc, count = ids ? (int)h.view[0].shape[0] : 0;
+    if (function(a[0], &fn) && address(a[1], &model) && first(a[2], &h, &ids, &count)) {
+        int rc;
         Py_BEGIN_ALLOW_THREADS
         rc = ((Fn)fn)(model, count, ids);
         Py_END_ALLOW_THREADS

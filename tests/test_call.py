@@ -88,3 +88,16 @@ def test_forms_of_a_call(call, ids):
     for f in (lambda: m.decode_step(ids, ids, ids), lambda: m.encode(ids, ids), lambda: m.seq_release(ids)):
         with pytest.raises(exe.ExeError, match="null model"):
             f()
+
+
+@pytest.mark.parametrize("want", [True, False])
+def test_a_call_without_ids(want):
+    """None for the ids is a TypeError, whatever else is given: the number of sequences is theirs."""
+    exe.lib()
+    m = object.__new__(exe.Model)
+    m._h = None
+    one = np.ones(1, dtype=np.int32)
+    for f in (lambda: m.encode(None, one, want_tokens=want), lambda: m.decode_step(None, one, one, want_tokens=want),
+              lambda: m.seq_release(None)):
+        with pytest.raises(TypeError):
+            f()
