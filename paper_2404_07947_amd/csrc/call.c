@@ -26,9 +26,12 @@ static int array(PyObject* o, int flags, Held* h, int32_t** p)
 {
     *p = NULL;
     if (o == Py_None) return 1;
-    if (PyObject_GetBuffer(o, &h->view[h->n], PyBUF_C_CONTIGUOUS | flags) < 0) return 0;
+    if (PyObject_GetBuffer(o, &h->view[h->n], PyBUF_C_CONTIGUOUS | PyBUF_FORMAT | flags) < 0) return 0;
     Py_buffer* v = &h->view[h->n++];
-    if (v->itemsize != 4 || v->ndim < 1) {
+    // "i" of 4 bytes in the machine's order, which may be said
+    const char* f = v->format ? v->format : "B";
+    if (*f == '@' || *f == '=' || *f == '<') ++f;
+    if (v->itemsize != 4 || v->ndim < 1 || (*f != 'i' && *f != 'l') || f[1]) {
         PyErr_SetString(PyExc_TypeError, "expected an int32 array");
         return 0;
     }

@@ -66,7 +66,8 @@ def test_refuses(call):
     def never(model, count, p):
         raise AssertionError
 
-    bad = [np.arange(4, dtype=np.int64), np.arange(8, dtype=np.int32)[::2], [1, 2], 3]
+    bad = [np.arange(4, dtype=np.int64), np.arange(8, dtype=np.int32)[::2], [1, 2], 3, np.arange(4, dtype=np.float32),
+           np.arange(4, dtype=np.uint32), np.arange(4, dtype=">i4")]
     for b in bad:
         with pytest.raises((TypeError, ValueError, BufferError)):
             call.seq_release(_at(never), 4096, b)
