@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sysconfig
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -112,7 +113,7 @@ def lib():
     if _lib is not None:
         return _lib
     p = lib_path()
-    for f in (p, os.path.join(_HERE, "_call.so")):
+    for f in (p, os.path.join(_HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))):
         if not os.path.exists(f):
             raise ImportError(f"{f} is not built; run `python -m paper_2404_07947_amd.build` (needs hipcc)")
     from . import _call

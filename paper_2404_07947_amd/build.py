@@ -1,4 +1,4 @@
-"""Builds libexe.so (HIP kernels + runtime + C ABI) for gfx950 with hipcc, and _call.so (Python's way to its serving calls), in-tree."""
+"""Builds libexe.so (HIP kernels + runtime + C ABI) for gfx950 with hipcc, and _call (Python's way to its serving calls), in-tree."""
 from __future__ import annotations
 
 import os
@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libexe.so")
-CALL = os.path.join(HERE, "_call.so")              # csrc/call.c: host code against Python's headers
+# csrc/call.c: host code against Python's headers, named for the Python that it is built for
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 CC = os.environ.get("CC", "gcc")
 SOURCES = ["kernels_elementwise.hip", "kernels_gemm.hip", "kernels_gemm_large.hip", "kernels_gemm_stream.hip", "kernels_gemm_f32.hip", "kernels_attn.hip", "kernels_small.hip", "runtime.hip", "probe.hip", "sched.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -102,3 +102,13 @@ def test_a_call_without_ids(want):
               lambda: m.seq_release(None)):
         with pytest.raises(TypeError):
             f()
+
+
+def test_the_extension_is_the_interpreters_own(call, monkeypatch):
+    """Built against one Python's headers, loaded by that Python: another one in the same tree is told to build its own."""
+    import sysconfig
+    assert call.__file__.endswith("_call" + sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(sysconfig, "get_config_var", lambda name: ".cpython-399-none.so")
+    with pytest.raises(ImportError, match="cpython-399"):
+        exe.lib()
