@@ -33,7 +33,13 @@ template <> struct HalfUnit<float> {
 
 // Floats as the sum of three bf16 parts, all of their bits: x rounded, what is left rounded, and the rest; bf16 pairs in dwords.  The
 // products of two such floats that count (see kernels_gemm_f32.hip) are PARTS of the one and the other, smallest first.
+//
+// What is parted is x * PART_SCALE: the lowest bit of a float is 2^-149 or more, of that 2^-125, a normal bf16, so no float is too
+// small for its parts (without the factor elements below 2^-109 lost bits: operands of 2^-115 gave products with errors of 1e-6,
+// of 2^-122 1e-4, where ordinary ones err 1e-7).  Sums of products carry the factor twice; where they, or a part of an element of
+// 2^104 and more, are too large for a float, they come out infinite or NaN, and who takes them looks for that.
 constexpr int PARTS[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+constexpr float PART_SCALE = 0x1p24f, PARTS_UNSCALE = 0x1p-48f;
 __device__ __forceinline__ unsigned bf16_pair(float a, float b)
 {
     unsigned r;

@@ -2,15 +2,19 @@
 //
 // What bounds a float product: 16x16x4 float MFMAs, a sixteenth of the bf16 rate.  A float is the sum of three bf16 values without a
 // bit lost (h = x rounded, m = x - h rounded, l = x - h - m, 8 bits each), and a product of two floats their nine products, of
-// which the three smallest (m l, l m, l l; m l below 2^-26 of the product, of either sign) are left out: six bf16 MFMAs of 32 k in
-// the place of eight float ones of 4, at 16 times the rate.  Sums stay float, with fewer roundings on the way: error against 64
-// bits: see the table at f32_tile.
+// which the three smallest are left out (m l and l m, below 2^-25 of the product each and of either sign, and l l, below 2^-34; all
+// three together below 2^-24): six bf16 MFMAs of 32 k in the place of eight float ones of 4, at 16 times the rate.  Sums stay float,
+// with fewer roundings on the way: error against 64 bits: see the table at f32_tile.  Where what is left out adds up with one sign, the
+// roundings outweigh it: rows of one random constant times features of another, rms (largest) error of the float MFMAs 2.3e-7 (5.1e-7)
+// at K 32, 1.9e-6 (3.8e-6) at 256, 1.5e-5 (3.1e-5) at 2048; here 2.8e-8 (1.1e-7), 6.0e-7 (2.8e-6), 4.1e-6 (2.0e-5), and the same with
+// m l and l m taken too, from K 64 on to all three digits, for 10 % more time.
 //
 // A workgroup of 4 waves splits each operand tile once, on its way from registers to LDS (per wave and fragment it would be as much
 // vector work as the MFMAs take); two or three workgroups on a CU, so that one's splitting runs beside another's MFMAs.
 //
-// An infinite or NaN element, or one that rounds to infinity in bf16, makes its products NaN here: tiles with sums that are not
-// finite are computed again with float MFMAs (rare, so not for speed).  Elements below 2^-109 lose bits of l to bf16's range.
+// What is split is the element times 2^24 (PART_SCALE), so that the parts of small ones stay in bf16's range.  An infinite or NaN
+// element, one of 2^104 and more, or a sum of 2^80 and more does not stay in it: tiles with sums that are not finite are computed
+// again with float MFMAs (rare, so not for speed).
 #include <type_traits>
 
 #include "gemm_tile.h"
@@ -31,8 +35,7 @@ __global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32
     constexpr int TM = BM / 32, TN = BN / 32;                // 16-row and 16-feature tiles of a wave
     constexpr int RA = BM * 8 / F32_THREADS, RW = BN * 8 / F32_THREADS;      // groups of 4 elements of a thread per operand and step
     constexpr int PA = BM * F32_ROW, PW = BN * F32_ROW;      // bytes of a plane
-    constexpr int STAGE = 3 * (PA + PW);
-    extern __shared__ __align__(16) unsigned char lds[];     // two stages of A's planes h, m, l, then W's
+    extern __shared__ __align__(16) unsigned char lds[];     // A's planes h, m, l, then W's
     int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int wm = wave >> 1, wn = wave & 1;
     // an XCD's workgroups take neighbouring tiles, feature tiles fastest: they share activation rows in its L2
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32
     };
     auto put = [&](f32x4 v, unsigned dst, int plane) {
         uint2 w[3];
-        bf16_parts(v, w);
+        bf16_parts(v * PART_SCALE, w);
 #pragma unroll
         for (int p = 0; p < 3; ++p) *(uint2*)(lds + dst + p * plane) = w[p];
     };
@@ -117,6 +120,7 @@ __global__ __launch_bounds__(F32_THREADS, (BM + BN > 192 ? 2 : 3)) void gemm_f32
             // 0 * x is NaN for a sum that is not finite
             f32x4 z = acc[i][j] * 0.f;
             float s = z[0] + z[1] + z[2] + z[3];
+            acc[i][j] *= PARTS_UNSCALE;
             if (__builtin_amdgcn_ballot_w64(s != s) == 0) continue;
             int r = row0 + j * 16 + fr, n = col0 + i * 16 + fr;
             const float* pa = A + (int64_t)(r < M ? r : M - 1) * lda + g;

@@ -74,3 +74,41 @@ def test_values():
     assert torch.equal(got.isinf(), ref.isinf()) and torch.equal(got[got.isinf()], ref[ref.isinf()])
     ok = ref.isfinite()
     assert bool(((got - ref).abs() <= bound(A, W, K))[ok].all())
+
+
+@pytest.mark.parametrize("M,N,K", [(2200, 100, 64), (12288, 768, 256)])
+@pytest.mark.parametrize("e", [-109, -115, -122, -130, -140, -149])
+def test_small_operands(M, N, K, e):
+    """Operands down to the smallest floats lose nothing to the parts: the ordinary relative bound, and results that are no normal
+    floats rounded once."""
+    g = torch.Generator().manual_seed(7)
+    A, W = torch.randn((M, K), generator=g), torch.randn((N, K), generator=g)
+    A, W = (A.double() * 2.0 ** e).float(), (W.double() * 2.0 ** (10 if e > -149 else 30)).float()
+    for a, w, flip in ((A, W, False), (W, A, True)) if M < 3000 else ((A, W, False),):
+        if flip:
+            w = w[:N].contiguous()                              # the weights are the small ones
+            a = a.repeat(-(-M // N), 1)[:M].contiguous()
+        got, ref = product(a.to(DEV), w.to(DEV)), a.double() @ w.double().T
+        assert bool(((got - ref).abs() <= bound(a, w, K) + 2.0 ** -150).all()), flip
+
+
+def test_small_elements_beside_large_ones():
+    """What a small element adds is kept where the row's large ones meet zeros."""
+    M, N, K = 2200, 100, 64
+    g = torch.Generator().manual_seed(8)
+    A, W = torch.randn((M, K), generator=g), torch.randn((N, K), generator=g)
+    A[:, ::2] = (A[:, ::2].double() * 2.0 ** -118).float()
+    W[:, 1::2] = 0.0
+    got, ref = product(A.to(DEV), W.to(DEV)), A.double() @ W.double().T
+    assert bool(((got - ref).abs() <= bound(A, W, K)).all())
+
+
+def test_large_sums():
+    """Sums and elements that are floats, but not with the parts' factor."""
+    M, N, K = 2200, 100, 64
+    g = torch.Generator().manual_seed(9)
+    for ea, ew in ((50, 40), (110, 0), (0, 110), (60, 60), (120, -60)):
+        A, W = torch.randn((M, K), generator=g) * 2.0 ** ea, torch.randn((N, K), generator=g) * 2.0 ** ew
+        got, ref = product(A.to(DEV), W.to(DEV)), A.double() @ W.double().T
+        # one addition per product in the float MFMAs that compute them again
+        assert bool(((got - ref).abs() <= (K + 4) * 2.0 ** -24 * (A.double().abs() @ W.double().abs().T)).all()), (ea, ew)
