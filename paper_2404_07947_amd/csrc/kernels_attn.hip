@@ -291,8 +291,9 @@ __device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* 
 // LDS, one tile of either; the next tile's loads are in flight meanwhile.  A score, and a tile's share of an output, is the sum
 // of three numbers: the first parts' products of 32 features (keys) twice, and all the others'.  Error against 64 bits, 2-norm
 // relative, float MFMAs / row kernel / now: 200 rows 1.22e-7 / 1.09e-7 / 1.05e-7, 1000 1.38e-7 / 1.31e-7 / 1.20e-7, inputs three times
-// as large 3.95e-7 / 3.98e-7 / 3.71e-7, 4096 rows 1.62e-7 / 1.71e-7 / 1.45e-7; in one chain of additions 1.71e-7 at 1000.  What the parts
-// cannot hold (infinities, NaN, values that round to infinity) makes NaN, and such rows are computed again.
+// as large 3.95e-7 / 3.98e-7 / 3.71e-7, 4096 rows 1.62e-7 / 1.71e-7 / 1.45e-7; in one chain of additions 1.71e-7 at 1000.  Parts are of
+// the values times PART_SCALE (see bf16_parts), so that small ones keep all of their bits, probabilities too.  What the parts or the
+// sums cannot hold (infinities, NaN, values of 2^104, scores and sums of 2^80 and more) makes NaN, and such rows are computed again.
 //
 // Float x 128: the same tiles and softmax with 16x16x4 MFMAs, four per 16-byte fragment; the second product takes one key per lane
 // group and MFMA, so P again goes from accumulator to operand without moving, and V is read 4 bytes per lane.  A score is the
@@ -300,7 +301,7 @@ __device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* 
 // 2.3 to 3.3 times as much against 64 bits as the row kernel, for 2 to 9 % less time.
 //
 // Measured, row kernel -> this kernel, us per layer: bf16 x 64, 16 ragged sequences of 512 on average, 16 heads, 442 -> 34;
-// float x 64, 32 sequences of 384, 4 heads, 192 -> 36.
+// float x 64, 32 sequences of 384, 4 heads, 192 -> 40.
 template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB>
 __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_mfma_kernel(const T* __restrict__ qkv,
                                                                   const int32_t* __restrict__ cu,
@@ -366,8 +367,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
 #pragma unroll
             for (int ds = 0; ds < 2; ++ds) {
                 uint2 a[3], b[3];
-                bf16_parts(qp[ds * 8], a);
-                bf16_parts(qp[ds * 8 + 1], b);
+                bf16_parts(qp[ds * 8] * PART_SCALE, a);
+                bf16_parts(qp[ds * 8 + 1] * PART_SCALE, b);
 #pragma unroll
                 for (int p = 0; p < 3; ++p) qf[qb][ds * 3 + p] = u32x4{a[p].x, a[p].y, b[p].x, b[p].y};
             }
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
             int u = (i & 3) * PF_THREADS + tid, row = u >> 4, c = u & 15;
             unsigned char* d = pf_smem + (i >> 2) * 3 * PLANE + row * 128 + (((c >> 1) ^ pf_swz<128>(row)) << 4) + (c & 1) * 8;
             uint2 w[3];
-            bf16_parts(kv_reg[i], w);
+            bf16_parts(kv_reg[i] * PART_SCALE, w);
 #pragma unroll
             for (int p = 0; p < 3; ++p) *(uint2*)(d + p * PLANE) = w[p];
         }
@@ -459,7 +460,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
         m_run[qb] = -INFINITY;
         l_run[qb] = 0.f;
     }
-    float sc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, fabsf(scale) * LOG2E)));
+    // (PARTED: of scores that carry PART_SCALE twice)
+    float sc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, fabsf(scale) * LOG2E * (PARTED ? PARTS_UNSCALE : 1.f))));
     f32x4 s_acc[QB][4];
 
     // a wave whose queries all lie before a tile's first key (causal) or past the sequence end has nothing to
@@ -498,7 +500,12 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
                     }
                 }
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) s_acc[qb][kb] = c[0][qb] + c[1][qb] + rest[qb];
+                for (int qb = 0; qb < QB; ++qb) {
+                    f32x4 v = s_acc[qb][kb] = c[0][qb] + c[1][qb] + rest[qb];
+                    // A score of 2^80 and more in magnitude is infinite with the parts' factor.  +infinity makes its row NaN below;
+                    // -infinity would only lose its key, so the row is made NaN here.
+                    l_run[qb] = fmaf(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])), 0.f, l_run[qb]);
+                }
             } else if constexpr (sizeof(T) == 4) {
                 // sums of 8 features each (two MFMAs), added pairwise: part x is half x % 2 of the 16-byte chunks 4 * (x / 2) + g
                 auto sum = [&](auto self, auto first, auto count, f32x4 (&c)[QB]) -> void {
@@ -643,8 +650,8 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
                     uint2 a[3], b[3];
-                    bf16_parts(s_acc[qb][2 * ks], a);
-                    bf16_parts(s_acc[qb][2 * ks + 1], b);
+                    bf16_parts(s_acc[qb][2 * ks] * PART_SCALE, a);
+                    bf16_parts(s_acc[qb][2 * ks + 1] * PART_SCALE, b);
 #pragma unroll
                     for (int p = 0; p < 3; ++p) pf[ks][p][qb] = __builtin_bit_cast(bf16x8, u32x4{a[p].x, a[p].y, b[p].x, b[p].y});
                 }
@@ -808,6 +815,15 @@ __global__ __launch_bounds__(PF_THREADS, (pf_per_cu<T, DH, V2>())) void prefill_
         int qpos = wq0 + qb * 16 + qi;
         float inv = 1.f / l_run[qb];
         float most = o_acc[qb][0][0];                              // NaN if one of them is
+        if constexpr (PARTED) {
+            // outputs carry PART_SCALE twice too, and an infinite one may not be infinite without
+            inv *= PARTS_UNSCALE;
+            most = l_run[qb];
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) most = fmaf(o_acc[qb][dt][j], 0.f, most);
+        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -888,7 +904,7 @@ template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB> static hi
 //   QB 2 with two / QB 1 with two (/ with one)
 //   bf16 x 64   64 18.3 / 12.1    592 27.3 / 22.8    2672 62.4 / 57.6: half the registers, so five workgroups on a CU in place of four
 //   float x 64, float MFMAs with QB 2 / with QB 1 / bf16 parts (one form: three workgroups on a CU)
-//               148 60.0 / 40.8 / 32.5    292 73.2 / 45.0 / 34.8    452 81.0 / 58.6 / 38.9    804 122 / 100 / 64.6
+//               148 60.0 / 40.8 / 35.5    292 73.2 / 45.0 / 38.6    452 81.0 / 58.6 / 42.8    804 122 / 100 / 67.8
 template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_prefill(const AttnPackedArgs& a, hipStream_t s)
 {
     const int64_t wgs = (int64_t)a.n_tiles * a.H;
@@ -934,7 +950,9 @@ hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
     if ((a.dtype != DT_F32 && a.dtype != DT_BF16) || (a.dh != 64 && a.dh != 128)) return hipErrorInvalidValue;
-    const bool mfma = a.force_generic <= 0 && a.n_tiles > 0 && (a.force_generic < 0 || prefill_mfma_pays(a));
+    // the scale of parted scores (float x 64) carries 2^-48: where that would be no normal float, the row kernel serves
+    const bool scale_fits = a.dtype != DT_F32 || a.dh != 64 || a.scale == 0.f || !(fabsf(a.scale) < 0x1p-70f);
+    const bool mfma = a.force_generic <= 0 && a.n_tiles > 0 && scale_fits && (a.force_generic < 0 || prefill_mfma_pays(a));
     // The key loader addresses the rows of one sequence with 32-bit byte offsets, and a head's bias table must fit
     // the kernel's LDS copy; a batch outside these limits runs on the row kernel, which is correct but far slower,
     // so say so (once).

@@ -105,3 +105,60 @@ def test_forms_agree(dtype, dh, copies, causal, use_bias, H):
     for n in copies:
         many = run(n)
         assert all(torch.equal(many[i], one[0]) for i in (0, n // 2, n - 1)), n
+
+
+def float64_attention(x, H, dh, scale):
+    q, k, v = (x.double()[:, j * H * dh:(j + 1) * H * dh].reshape(-1, H, dh).transpose(0, 1).contiguous() for j in range(3))
+    return (((q @ k.transpose(1, 2).contiguous()) * scale).softmax(dim=-1) @ v).transpose(0, 1).reshape(-1, H, dh)
+
+
+def float_rows(x, H, dh, scale):
+    out = torch.zeros((len(x), H * dh), device=DEV)
+    exe.exe_op_prefill_attention(F32, np.array([0, len(x)], dtype=np.int32), x.to(DEV), H, dh, scale, 0, None, 0, out, force_generic=-1)
+    torch.cuda.synchronize()
+    return out.double().cpu().reshape(-1, H, dh)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("qe,ke,ve", [(0, 0, -110), (0, 0, -118), (0, 0, -126), (-118, 0, 0), (0, -122, 0), (-60, -60, -122), (-110, 110, 0),
+                                      (0, 0, 90), (0, 0, 115), (40, 42, 0)])
+def test_float_range(dh, qe, ke, ve):
+    """Queries, keys and values of any size: as exact as ordinary ones.  The scale makes up for the scores'."""
+    n, H = 200, 2
+    g = torch.Generator().manual_seed(dh - qe)
+    x = torch.randn((n, 3 * H * dh), generator=g).double()
+    for j, e in enumerate((qe, ke, ve)):
+        x[:, j * H * dh:(j + 1) * H * dh] *= 2.0 ** e
+    x, scale = x.float(), float(np.float32(0.11)) * 2.0 ** -(qe + ke)
+    ref, got = float64_attention(x, H, dh, scale), float_rows(x, H, dh, scale)
+    err = (got - ref).abs().amax(dim=2) / ref.abs().amax(dim=2)
+    assert float(err.max()) < 1e-5, float(err.max())
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_float_small_probabilities(dh):
+    """A key that takes all but 2^-119 to 2^-125 of a row, with a value of zero: the row is what the others add."""
+    n = 64
+    x = torch.zeros((n, 3 * dh))
+    # scores of key 0: 82.5 to 86.6, the others' zero (from 87.4 on exp2 gives 2^-126 and less, zero in every form of the kernel)
+    x[:, 0] = 1.0 + torch.arange(n) / 1280.0
+    x[0, dh] = 82.5 / 0.125
+    x[1:, 2 * dh:] = torch.randn((n - 1, dh), generator=torch.Generator().manual_seed(1))
+    ref, got = float64_attention(x, 1, dh, 0.125), float_rows(x, 1, dh, 0.125)
+    # the exponent, 125 for exp2, is the product of three roundings: 3 * 125 * 2^-24 * ln 2, and the sums' own
+    err = (got - ref).abs().amax(dim=2) / ref.abs().amax(dim=2)
+    assert float(err.max()) < 2e-5, float(err.max())
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_float_scores_about_2_to_the_80(dh):
+    """Scores that are floats, but not with the factor that the parts carry, beside others that are: every key counts."""
+    n = 64
+    x = torch.zeros((n, 3 * dh), dtype=torch.float64)
+    x[:, 0] = 2.0 ** 40
+    x[:, dh] = -2.0 ** 40 * (1 + (torch.arange(n) - 2) * 2.0 ** -23)              # an eighth apart with the scale: keys 0 .. 2 are above
+    x[:, 2 * dh:] = torch.arange(n)[:, None]
+    x = x.float()
+    ref, got = float64_attention(x, 1, dh, 2.0 ** -60), float_rows(x, 1, dh, 2.0 ** -60)
+    # floats of 2^20 log2(e) are an eighth apart, so an exponent is off by up to a sixteenth: a weight by 2^(1/16), a ratio by 2^(1/8)
+    assert float((got / ref - 1).abs().max()) < 0.1 and float(ref.min()) > 5
