@@ -73,6 +73,7 @@ hipError_t launch_gemm_large(const GemmArgs& a, int bm, int k_per_split, int spl
 // The float tiles (kernels_gemm_f32.hip): K a multiple of 32, operands and bias 16-byte aligned.
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 double gemm_f32_cost(int M, int N, int K);       // seconds
+double stream_f32_seconds(const StreamPlan& p, int M, int N, int K);
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t s);
 

@@ -469,6 +469,13 @@ static bool split_ok(int dtype, int K, int s)
 // The streaming kernel is taken when its estimate is clearly below the tile kernel's (both are within 10-20 %): the tile
 // kernel's is a few per cent high where both stream from HBM.
 constexpr double STREAM_MARGIN = 0.92;
+// Float: both estimates are within 2 to 4 %, and the streaming kernel served these shapes before the float tiles were worth it, so
+// that near the line it stays.  Of 210 launches of up to 2048 rows (the weights named at f32_tile) the kernel taken is within 0.2 % of the faster
+// one on average, 4 % at worst.  us, streaming / the best tile, on either side of the line:
+//    512 x 3072, K 1024 36.4 / 38.2    1024 x 1536, K 512 20.5 / 21.4    768 x 2048, K 512 20.4 / 21.3    1024 x 1024, K 1024 23.5 / 29.4
+//    640 x 3072, K 1024 43.9 / 39.6    1152 x 1536, K 512 24.7 / 21.6   1024 x 2048, K 512 26.1 / 22.2   2048 x 1024, K 1024 44.3 / 39.8
+//    640 x 4096, K 1024 63.6 / 49.5     512 x 4096, K 256 17.2 / 13.4   1024 x 4096, K 256 33.7 / 19.8   2048 x 4096, K 256 60.4 / 30.0
+constexpr double F32_STREAM_MARGIN = 1.08;
 
 constexpr int64_t MANY_ROWS_PARTIALS = 128 << 20;
 constexpr int OP_RATE_ROWS = 192;
@@ -532,7 +539,8 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         p.cost = best;
         if ((mode & GEMM_FEW_ROWS) && M <= (dtype == DT_F32 ? 2048 : 256)) {
             p.stream = gemm_stream_plan(dtype, M, N, K, mode & GEMM_DEFER);
-            if (p.stream.nt && p.stream.cost > STREAM_MARGIN * best) p.stream = StreamPlan{};
+            if (p.stream.nt && (dtype == DT_F32 ? stream_f32_seconds(p.stream, M, N, K) > F32_STREAM_MARGIN * best
+                                                : p.stream.cost > STREAM_MARGIN * best)) p.stream = StreamPlan{};
             if (p.stream.nt) p.cost = p.stream.cost;
         }
         if (memo.size() > 4096) memo.clear();

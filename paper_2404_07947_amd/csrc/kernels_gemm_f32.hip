@@ -10,7 +10,7 @@
 // m l and l m taken too, from K 64 on to all three digits, for 10 % more time.
 //
 // A workgroup of 4 waves splits each operand tile once, on its way from registers to LDS (per wave and fragment it would be as much
-// vector work as the MFMAs take); two or three workgroups on a CU, so that one's splitting runs beside another's MFMAs.
+// vector work as the MFMAs take); two to four workgroups on a CU, so that one's splitting runs beside another's MFMAs.
 //
 // What is split is the element times 2^24 (PART_SCALE), so that the parts of small ones stay in bf16's range.  An infinite or NaN
 // element, one of 2^104 and more, or a sum of 2^80 and more does not stay in it: tiles with sums that are not finite are computed
@@ -156,17 +156,20 @@ template <int BM, int BN> static hipError_t launch_f32(const GemmArgs& a, hipStr
     return hipGetLastError();
 }
 
-// The tile, and what a launch takes: n workgroups fall to the busiest CU, `resident` of them at a time; a step of 32 k takes them
-// `step` together and each `share` more (fitted, us within 10 % of the measured ones below).
+// The tile, and what a launch takes: n workgroups fall to the busiest CU, `resident` of them at a time (what registers and LDS let in);
+// a launch takes `start`, and a step of 32 k takes the resident ones `step` together and each `share` more.  Fitted to 252 launches on one
+// MI355X, 14 weights (256 to 4096 features, K 256 to 4096) x 22 row counts from 32 to 16384: within 1.3, 2.0 and 2.4 % on average (9, 13
+// and 12 % at worst), and the tile taken is within 0.2 % of the fastest on average, 8 % at worst.
 // us on one MI355X, the float MFMA kernel that this replaces / 128 x 128 / 64 x 128 / 64 x 64, and the 2-norm relative error against
 // 64 bits there and here:
-//   12288 x  768, K  256  51.8 / 42.6 / 37.0 / 38.5   2.9e-7 2.3e-7     12288 x 1024, K  256 (GELU)  65.8 / 47.9 / 47.4 / 53   3.2e-7 2.6e-7
-//   12288 x  256, K 1024  56.4 / 55.9 / 52.2 / 48.9   5.7e-7 4.9e-7      8000 x  512, K 2048   165 / 109 / 109 / 122           8.1e-7 7.0e-7
-//    3000 x  768, K  256  18.1 / 18.4 / 16.8 / 14.8   2.9e-7 2.3e-7     20000 x 1024, K  256 (GELU)  105 / 74 / 77 / 87        3.2e-7 2.6e-7
+//   12288 x  768, K  256  51.2 / 43.2 / 38.0 / 40.3   2.9e-7 2.3e-7     12288 x 1024, K  256  60.9 / 44.5 / 43.5 / 50.7   2.9e-7 2.3e-7
+//   12288 x  256, K 1024  57.6 / 61.6 / 57.0 / 50.9   5.7e-7 4.9e-7      8192 x  512, K 2048   163 / 116 / 113 / 124      8.1e-7 7.0e-7
+//    3000 x  768, K  256  18.5 / 20.1 / 17.7 / 16.0   2.9e-7 2.3e-7     16384 x 1024, K  256  79.0 / 53.8 / 55.7 / 67.5   2.9e-7 2.3e-7
+//    2048 x 1024, K  256  14.5 (streaming kernel) / 19.9 / 14.6 / 12.5     1024 x 4096, K 1024  83.6 (streaming) / 62.8 / 58.1 / 64.8
 // The last 128 x 128 step takes 1.1 us per workgroup where its MFMAs alone take 0.7: splitting overlaps with other waves' MFMAs only in
 // part.  Two stages in LDS with the splitting between a wave's own MFMAs were slower (8000 x 2048, K 512 103 -> 132).
-struct F32Tile { int bm, bn, resident; double step, share; };
-static const F32Tile F32_TILES[] = {{128, 128, 2, 0.55e-6, 1.05e-6}, {64, 128, 3, 0.6e-6, 0.53e-6}, {64, 64, 3, 0.4e-6, 0.32e-6}};
+struct F32Tile { int bm, bn, resident; double start, step, share; };
+static const F32Tile F32_TILES[] = {{128, 128, 2, 5.5e-6, 0.90e-6, 0.76e-6}, {64, 128, 4, 3.3e-6, 0.74e-6, 0.48e-6}, {64, 64, 4, 2.7e-6, 0.45e-6, 0.32e-6}};
 static int f32_tile(int M, int N, int K, double* seconds)
 {
     int best = 0;
@@ -174,7 +177,7 @@ static int f32_tile(int M, int N, int K, double* seconds)
         const F32Tile& t = F32_TILES[i];
         int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         double n = (double)((tiles + 255) / 256), rounds = (double)(((int64_t)n + t.resident - 1) / t.resident);
-        double c = 4e-6 + (double)M * N * 4 / 6e12 + (double)(K / F32_BK) * (t.step * rounds + t.share * n);
+        double c = t.start + (double)M * N * 4 / 6e12 + (double)(K / F32_BK) * (t.step * rounds + t.share * n);
         if (i == 0 || c < *seconds) {
             *seconds = c;
             best = i;

@@ -337,6 +337,16 @@ static double stream_cost(int dtype, int nt, int ma, int splits, int M, int N, i
     return t;
 }
 
+// Seconds of a float launch, where it is compared with the float tiles: stream_cost, which ranks the candidates, is 14 % low there.
+// Fitted to the launches of up to 2048 rows (see F32_STREAM_MARGIN) that take more than 11.5 us: within 4.4 % on average, 13 % at worst.
+double stream_f32_seconds(const StreamPlan& p, int M, int N, int K)
+{
+    double wgs = (double)((N + p.nt * 16 - 1) / (p.nt * 16)) * ((M + p.ma * 8 - 1) / (p.ma * 8));
+    double rounds = (double)(int64_t)((wgs + 255) / 256);
+    double t = 3.9e-6 + rounds * (0.63e-6 + 2.0 * p.nt * 16 * ((p.ma + 1) / 2 * 16) * K / 0.427e12), w = (double)N * K * 4 / 6.9e12;
+    return t > w ? t : w;
+}
+
 // the parameters of one candidate; nt = 0 if the shape does not allow it.  Float is not split over workgroups (no workspace
 // is asked of its callers); a bf16 part keeps at least 16 units, 4 for each wave.
 StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K, bool defer)

@@ -83,3 +83,12 @@ def test_elements_of_a_head_beyond_32_bits(dh):
             for pos in (0, 1, cap - 1):
                 for base in (0, 1 << 33):
                     assert exe.exe_op_kv_store_index(base, cap, head, pos, dh) == base + (head * cap + pos) * dh
+
+
+# us measured, streaming kernel / the best float tile: see F32_STREAM_MARGIN in csrc/kernels_gemm.hip
+@pytest.mark.parametrize("M,N,K,route", [(512, 3072, 1024, 1), (1024, 1536, 512, 1), (768, 2048, 512, 1), (1024, 1024, 1024, 1),      # 36/38 20.5/21.4 20.4/21.3 24/29
+                                         (1024, 1024, 4096, 1), (2048, 512, 2048, 1), (64, 4096, 1024, 1),                            # 76/105 44/56 9/28
+                                         (1152, 1536, 512, 0), (2048, 1024, 1024, 0), (640, 4096, 1024, 0), (512, 4096, 256, 0),      # 24.7/21.6 44/40 64/50 17/13
+                                         (2048, 1024, 256, 0), (1024, 4096, 256, 0), (2048, 4096, 1024, 0), (2048, 4096, 256, 0)])    # 17/13 34/20 176/91 60/30
+def test_float_products_of_up_to_2048_rows_run_on_the_faster_kernel(M, N, K, route):
+    assert exe.exe_op_gemm_plan(F32, M, N, K)["route"] == route
