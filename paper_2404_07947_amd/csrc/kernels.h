@@ -72,6 +72,7 @@ StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, i
 hipError_t launch_gemm_large(const GemmArgs& a, int bm, int k_per_split, int splits, int grid_max, hipStream_t s);
 // The float tiles (kernels_gemm_f32.hip): K a multiple of 32, operands and bias 16-byte aligned.
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
+int gemm_f32_tile(int M, int N, int K, double* seconds);       // 0 128 x 128, 1 64 x 128, 2 64 x 64
 double gemm_f32_cost(int M, int N, int K);       // seconds
 double stream_f32_seconds(const StreamPlan& p, int M, int N, int K);
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);

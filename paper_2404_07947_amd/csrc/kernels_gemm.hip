@@ -470,7 +470,7 @@ static bool split_ok(int dtype, int K, int s)
 // kernel's is a few per cent high where both stream from HBM.
 constexpr double STREAM_MARGIN = 0.92;
 // Float: both estimates are within 2 to 4 %, and the streaming kernel served these shapes before the float tiles were worth it, so
-// that near the line it stays.  Of 210 launches of up to 2048 rows (the weights named at f32_tile) the kernel taken is within 0.2 % of the faster
+// that near the line it stays.  Of 210 launches of up to 2048 rows (the weights named at gemm_f32_tile) the kernel taken is within 0.2 % of the faster
 // one on average, 4 % at worst.  us, streaming / the best tile, on either side of the line:
 //    512 x 3072, K 1024 36.4 / 38.2    1024 x 1536, K 512 20.5 / 21.4    768 x 2048, K 512 20.4 / 21.3    1024 x 1024, K 1024 23.5 / 29.4
 //    640 x 3072, K 1024 43.9 / 39.6    1152 x 1536, K 512 24.7 / 21.6   1024 x 2048, K 512 26.1 / 22.2   2048 x 1024, K 1024 44.3 / 39.8
@@ -632,6 +632,11 @@ void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* s
     Plan p = make_plan(dtype, M1, N, K, op_mode(dtype));
     *route = p.route;
     *cfg = p.cfg;
+    if (dtype == DT_F32 && p.route == 0) {
+        const int tiles[] = {C128x128, C64x128, N_CFG};        // 64 x 64 is a float tile only
+        double seconds;
+        *cfg = tiles[gemm_f32_tile(M1, N, K, &seconds)];
+    }
     *splits = p.splits;
     *rows_first = M1;
 }

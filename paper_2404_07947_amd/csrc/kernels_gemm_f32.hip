@@ -4,7 +4,7 @@
 // bit lost (h = x rounded, m = x - h rounded, l = x - h - m, 8 bits each), and a product of two floats their nine products, of
 // which the three smallest are left out (m l and l m, below 2^-25 of the product each and of either sign, and l l, below 2^-34; all
 // three together below 2^-24): six bf16 MFMAs of 32 k in the place of eight float ones of 4, at 16 times the rate.  Sums stay float,
-// with fewer roundings on the way: error against 64 bits: see the table at f32_tile.  Where what is left out adds up with one sign, the
+// with fewer roundings on the way: error against 64 bits: see the table at gemm_f32_tile.  Where what is left out adds up with one sign, the
 // roundings outweigh it: rows of one random constant times features of another, rms (largest) error of the float MFMAs 2.3e-7 (5.1e-7)
 // at K 32, 1.9e-6 (3.8e-6) at 256, 1.5e-5 (3.1e-5) at 2048; here 2.8e-8 (1.1e-7), 6.0e-7 (2.8e-6), 4.1e-6 (2.0e-5), and the same with
 // m l and l m taken too, from K 64 on to all three digits, for 10 % more time.
@@ -170,7 +170,7 @@ template <int BM, int BN> static hipError_t launch_f32(const GemmArgs& a, hipStr
 // part.  Two stages in LDS with the splitting between a wave's own MFMAs were slower (8000 x 2048, K 512 103 -> 132).
 struct F32Tile { int bm, bn, resident; double start, step, share; };
 static const F32Tile F32_TILES[] = {{128, 128, 2, 5.5e-6, 0.90e-6, 0.76e-6}, {64, 128, 4, 3.3e-6, 0.74e-6, 0.48e-6}, {64, 64, 4, 2.7e-6, 0.45e-6, 0.32e-6}};
-static int f32_tile(int M, int N, int K, double* seconds)
+int gemm_f32_tile(int M, int N, int K, double* seconds)
 {
     int best = 0;
     for (int i = 0; i < 3; ++i) {
@@ -189,14 +189,14 @@ static int f32_tile(int M, int N, int K, double* seconds)
 double gemm_f32_cost(int M, int N, int K)
 {
     double seconds = 0.0;
-    f32_tile(M, N, K, &seconds);
+    gemm_f32_tile(M, N, K, &seconds);
     return seconds;
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s)
 {
     double seconds = 0.0;
-    switch (f32_tile(a.M, a.N, a.K, &seconds)) {
+    switch (gemm_f32_tile(a.M, a.N, a.K, &seconds)) {
         case 0: return launch_f32<128, 128>(a, s);
         case 1: return launch_f32<64, 128>(a, s);
         default: return launch_f32<64, 64>(a, s);

@@ -66,8 +66,8 @@ def test_large_gemm_every_row(cfg, M, N, K, mode):
 @pytest.mark.parametrize("M,N,K", [(8193, 1028, 64), (12289, 516, 96)])
 @pytest.mark.parametrize("mode", ["f32", "resid", "gelu"])
 def test_float_tiles_beyond_one_round(M, N, K, mode):
-    """The wider float tile (more tiles than two per CU; the smaller one is compared in test_gpu_gemm_stream.py)."""
-    assert exe.exe_op_gemm_plan(wl.DTYPE_F32, M, N, K)["route"] == 0
+    """Float tiles of 64 x 128, more of them than CUs (64 x 64 are compared in test_gpu_gemm_stream.py, all three in test_gpu_gemm_f32.py)."""
+    assert exe.exe_op_gemm_plan(wl.DTYPE_F32, M, N, K)["cfg"] == 3
     A, W, b = rnd((M, K), 1, 1.0, torch.float32), rnd((N, K), 2, 0.05, torch.float32), rnd((N,), 3, 0.5, torch.float32)
     prim = oracle.Primitives("double")
     ref, act, out_mode, out = prim.linear(A.numpy(), W.numpy(), None) + b.numpy(), -1, 2, torch.zeros((M, N), device=DEV)
