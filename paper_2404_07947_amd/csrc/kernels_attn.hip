@@ -896,11 +896,19 @@ template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB> static hi
 
 // The form of the MFMA kernel: query blocks per wave (QB; the other half of a listed tile goes to a workgroup of its own at QB 1)
 // and value buffers (V2), by how many workgroups of whole tiles there are.  One or two buffers do not change a row's result, nor do
-// the blocks.  us of a launch on one MI355X (by events, which add about 3):
-//   QB 2 with one value buffer / with two / QB 1 with two
-//   bf16 x 128, causal  160 workgroups (1 x 512, 40 heads) 24.9 / 19.7 / 17.5    320 36.8 / 31.0 / 26.2    600 36.8 / 28.7 / 33.2
-//                       1280 82 / 80 / 92    1536 (96 heads) 96.4 / 96.5 / 117    5800 205 / 212 / 258: the third workgroup on a CU
-//   not causal, T5's bias  128 12.6 / 12.0 / 10.1    384 23.7 / 23.6 / 25.5    768 60.6 / 71.2 / 81.3    13696 977 / 1137 / 1423
+// the blocks.
+//   QB 2 with one value buffer / with two / QB 1 with two, bf16 x 128, us of a launch on one MI355X, 12 in a row; 60 batches of 1 to 16
+//   ragged sequences of 96 to 1000 tokens, 40, 96 and 128 heads, table of radius 100; of whole tiles
+//     causal                160 21.6 / 17.5 / 14.9    320 35.0 / 29.2 / 24.1    400 27.9 / 24.8 / 20.0   600 33.3 / 26.3 / 29.4   720 34.1 / 31.3 / 30.6
+//                           768 39.7 / 42.0 / 44.5    960 36.5 / 37.9 / 41.3   1120 46.4 / 42.3 / 44.8  1200 63.7 / 59.7 / 70.6  1440 66.3 / 67.0 / 78.1
+//     causal, with a table  160 22.8 / 20.8 / 15.9    400 30.0 / 27.5 / 22.2    600 34.0 / 29.4 / 35.4   768 41.6 / 45.3 / 47.5  1080 54.1 / 56.1 / 60.3
+//     neither               120 14.5 / 13.5 /  9.6    256 13.2 / 12.4 / 10.6    320 42.3 / 40.7 / 44.5   600 43.0 / 48.7 / 48.7  2960 136 / 153 / 178
+//     table, not causal     120 16.1 / 15.0 / 10.7    256 14.6 / 13.3 / 11.5    320 44.7 / 43.3 / 48.0   600 43.8 / 50.2 / 49.8  13696 928 / 994 / 1268
+//   With one buffer three workgroups share a CU, so 768 are all there at once, with two 512: from 720 on one buffer is the faster, and
+//   without a table, where a tile's two barriers weigh more, two again while one buffer's second round fills less than two thirds of
+//   the chip.  Over these 240 launches the form taken is within 0.8 % of the fastest of the three on average, and none is slower than the
+//   form that all of them took before, QB 2 with one buffer.
+//   The same of other types (times by events around single launches, which add about 3):
 //   QB 2 with two / QB 1 with two (/ with one)
 //   bf16 x 64   64 18.3 / 12.1    592 27.3 / 22.8    2672 62.4 / 57.6: half the registers, so five workgroups on a CU in place of four
 //   float x 64, float MFMAs with QB 2 / with QB 1 / bf16 parts (one form: three workgroups on a CU)
@@ -915,7 +923,7 @@ template <typename T, int DH, bool CAUSAL, bool BIAS> static hipError_t launch_p
     } else {
         if (wgs <= (CAUSAL ? 400 : 256)) return launch_prefill<T, DH, CAUSAL, BIAS, true, 1>(a, s);
         if constexpr (CAUSAL) {
-            if (wgs <= 1280) return launch_prefill<T, DH, CAUSAL, BIAS, true, 2>(a, s);
+            if (wgs <= 720 || (!BIAS && wgs > 1024 && wgs <= 1280)) return launch_prefill<T, DH, CAUSAL, BIAS, true, 2>(a, s);
         }
         return launch_prefill<T, DH, CAUSAL, BIAS, false, 2>(a, s);
     }
