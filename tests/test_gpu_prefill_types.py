@@ -50,21 +50,24 @@ def test_every_row(dtype, dh, causal, use_bias, generic, H):
     assert worst < (1e-5 if dtype == F32 else 2.0 ** -8), worst
 
 
-@pytest.mark.parametrize("dtype,dh", [(BF16, 128), (BF16, 64), (F32, 64), (F32, 128)])
+# 22 workgroups a copy: bf16 x 128 in the form of few (64 rows each, two value buffers), of some (causal only: two buffers) and of many
+@pytest.mark.parametrize("dtype,dh,copies", [(BF16, 128, 1), (BF16, 128, 25), (BF16, 128, 60), (BF16, 64, 1), (F32, 64, 1), (F32, 128, 1)])
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("R", [1, 31, 64, 128, 511])              # radius of the bias table: none to all of the tiles look it up
-def test_bias_radius(dtype, dh, causal, R):
+def test_bias_radius(dtype, dh, copies, causal, R):
     td = torch.float32 if dtype == F32 else torch.bfloat16
     lens, H = [1, 65, 352, 700], 2
-    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
-    T, inner = int(cu[-1]), H * dh
+    cu = np.concatenate([[0], np.cumsum(lens * copies)]).astype(np.int32)
+    T, inner = sum(lens), H * dh
     g = torch.Generator().manual_seed(R + dh)
     qkv = torch.randn((T, 3 * inner), generator=g).to(td)
     tab = torch.randn((H, 2 * R + 1), generator=g)
-    out = torch.zeros((T, inner), dtype=td, device=DEV)
-    exe.exe_op_prefill_attention(dtype, cu, qkv.to(DEV), H, dh, 0.11, causal, tab.to(DEV), R, out, force_generic=-1)
+    out = torch.zeros((copies * T, inner), dtype=td, device=DEV)
+    exe.exe_op_prefill_attention(dtype, cu, qkv.to(DEV).repeat(copies, 1), H, dh, 0.11, causal, tab.to(DEV), R, out, force_generic=-1)
     torch.cuda.synchronize()
-    got, x = out.double().cpu(), qkv.double()
+    out = out.reshape(copies, T, inner)
+    assert all(torch.equal(out[i], out[0]) for i in range(copies))
+    got, x = out[0].double().cpu(), qkv.double()
     worst = 0.0
     for s, L in enumerate(lens):
         q, k, v = (x[cu[s]:cu[s + 1], j * inner:(j + 1) * inner].reshape(L, H, dh).transpose(0, 1).contiguous() for j in range(3))
