@@ -281,13 +281,14 @@ __device__ __forceinline__ void prefill_row(const T* q, const T* keys, const T* 
     for (int f = 0; f < DH / 64; ++f) out[lane + f * 64] = from_f32<T>(acc[f] / l);
 }
 
-// Head size 64: half the bytes per tile, so the value tiles are double buffered too.  Its probabilities enter the second product as the sum of three bf16 values, their first, second and third 8 bits, so no bit
-// of the float is lost: the row kernel, which served this head size before, multiplies floats too.  The two further sets of
+// Head size 64: half the bytes per tile, so the value tiles are double buffered too.  Its probabilities enter the second
+// product as the sum of three bf16 values, their first, second and third 8 bits, so no bit of the float is lost (from 2^-110 on; below,
+// bf16 holds fewer of them): the row kernel, which served this head size before, multiplies floats too.  The two further sets of
 // MFMAs hide behind the exponentials for the most part (one set more and a rounded rest, 2^-17 relative: 40 us where three
 // take 43).
 //
-// Float x 64: bf16 MFMAs too, six for the products that count of three bf16 parts per float (see kernels_gemm_f32.hip), an eighth
-// of whose time eight float MFMAs take.  Keys and values are parted by all threads on their way through registers into
+// Float x 64: bf16 MFMAs too, six for the products that count of three bf16 parts per float (see kernels_gemm_f32.hip), in 3/8
+// of the time that eight float MFMAs take.  Keys and values are parted by all threads on their way through registers into
 // LDS, one tile of either; the next tile's loads are in flight meanwhile.  A score, and a tile's share of an output, is the sum
 // of three numbers: the first parts' products of 32 features (keys) twice, and all the others'.  Error against 64 bits, 2-norm
 // relative, float MFMAs / row kernel / now: 200 rows 1.22e-7 / 1.09e-7 / 1.05e-7, 1000 1.38e-7 / 1.31e-7 / 1.20e-7, inputs three times
@@ -940,14 +941,14 @@ template <typename T, int DH> static hipError_t launch_prefill(const AttnPackedA
 // to 1000 tokens, ragged and not, 4 to 40 heads; within 6-11 % at the median, a quarter to a half at worst): the faster of the
 // two by these takes at most 1.17, 1.19 and 1.13 times the faster one measured; the MFMA kernel alone took up to 6.9, 24 and
 // 1.8 times (float x 64, float x 128, bf16 x 64; e.g. 64 sequences of one token, 16 heads, float x 128: 61 us, rows 4).  The MFMA
-// kernel's figures for head size 64 are of a later fit, of its 64-row workgroups over 47 batches: the slower of the two is
-// taken by at most 12 % there.
+// kernel's figures for head size 64 are of later fits, of its 64-row workgroups: bf16 over 47 batches, float over 69 (with and without
+// mask and bias table), where the faster of the two is taken every time (5 sequences of 87 tokens in all, 32 heads: rows 5.1, MFMA 6.2).
 // bf16 x 128 stays on the MFMA kernel, whose tiles were made for it.
 static bool prefill_mfma_pays(const AttnPackedArgs& a)
 {
     if (a.dtype == DT_BF16 && a.dh == 128) return true;
     struct Cost { double row_fixed, row, pair, mfma_fixed, chain, tile; };
-    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 1.6, 2.8, 1.2}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 2.5, 0.83, 0.8};
+    static constexpr Cost F64{3.1, 0.61e-3, 16.4e-6, 2.4, 2.5, 2.4}, F128{3.3, 0.59e-3, 35.1e-6, 4.5, 10.1, 11.1}, B64{3.4, 1.08e-3, 9.5e-6, 2.5, 0.83, 0.8};
     const Cost& c = a.dtype == DT_BF16 ? B64 : a.dh == 64 ? F64 : F128;
     double row = c.row_fixed + a.H * (c.row * a.T + c.pair * a.work.pairs);
     double mfma = c.mfma_fixed + c.chain * ((a.work.max_len + PREFILL_TILE_K - 1) / PREFILL_TILE_K) + c.tile * a.H * a.work.key_tiles / 256;
