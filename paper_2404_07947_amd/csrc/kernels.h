@@ -78,6 +78,9 @@ double stream_f32_seconds(const StreamPlan& p, int M, int N, int K);
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t s);
 
+// A launch counts its threads in 32 bits, and takes more modulo 2^32 without an error.
+constexpr int64_t MAX_LAUNCH_THREADS = 0xffffffff;
+
 // A kernel's dynamic LDS limit, raised once per kernel and device.
 constexpr int MAX_DEVICES = 64;
 struct LdsLimit {

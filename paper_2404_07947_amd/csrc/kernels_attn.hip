@@ -883,16 +883,21 @@ template <typename T, int DH, bool CAUSAL, bool BIAS, bool V2, int QB> static hi
 {
     auto kern = prefill_mfma_kernel<T, DH, CAUSAL, BIAS, V2, QB>;
     const int lds = pf_lds<T, DH, V2>() + (BIAS ? pf_bias_entries(a.bias_radius) * 4 : 0);
-    const int64_t wgs = (int64_t)a.n_tiles * (2 / QB) * a.H;
-    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
     static LdsLimit limit[MAX_DEVICES];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
     hipError_t e = limit[dev].raise((const void*)kern, pf_lds<T, DH, V2>() + (BIAS ? (PF_BIAS + 2 * PF_BIAS_PAD) * 4 : 0));
     if (e != hipSuccess) return e;
-    kern<<<(unsigned)wgs, PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
-                                                BIAS ? a.bias_radius : 0, (T*)a.out, (const T*)a.pool, a.base, a.cap, a.layer);
-    return hipGetLastError();
+    // a launch has fewer than 2^32 threads: very many short sequences take several
+    const int64_t per_tile = (int64_t)(2 / QB) * a.H, most = (MAX_LAUNCH_THREADS / PF_THREADS) / per_tile;
+    if (most < 1) return hipErrorInvalidValue;
+    for (int64_t t = 0; t < a.n_tiles; t += most) {
+        const int64_t n = a.n_tiles - t < most ? a.n_tiles - t : most;
+        kern<<<(unsigned)(n * per_tile), PF_THREADS, lds, s>>>((const T*)a.qkv, a.cu, a.tiles + 2 * t, a.H, a.scale, BIAS ? a.bias_by_dist : nullptr,
+                                                               BIAS ? a.bias_radius : 0, (T*)a.out, (const T*)a.pool, a.base, a.cap, a.layer);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // The form of the MFMA kernel: query blocks per wave (QB; the other half of a listed tile goes to a workgroup of its own at QB 1)

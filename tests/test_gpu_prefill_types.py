@@ -165,3 +165,17 @@ def test_float_scores_about_2_to_the_80(dh):
     ref, got = float64_attention(x, 1, dh, 2.0 ** -60), float_rows(x, 1, dh, 2.0 ** -60)
     # floats of 2^20 log2(e) are an eighth apart, so an exponent is off by up to a sixteenth: a weight by 2^(1/16), a ratio by 2^(1/8)
     assert float((got / ref - 1).abs().max()) < 0.1 and float(ref.min()) > 5
+
+
+def test_more_workgroups_than_a_launch_takes():
+    """Half a million sequences of 2 and 3 tokens, 16 heads: 2^32 threads and more, which are no single launch."""
+    n, H, dh, R = 1000, 16, 64, 530
+    cu = np.concatenate([[0], np.cumsum(np.tile([2, 3], n // 2 * R))]).astype(np.int32)
+    T = int(cu[-1]) // R
+    qkv = torch.randn((T, 3 * H * dh), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).to(DEV)
+    out = torch.zeros((R * T, H * dh), dtype=torch.bfloat16, device=DEV)
+    exe.exe_op_prefill_attention(BF16, cu, qkv.repeat(R, 1), H, dh, 0.125, 1, None, 0, out, force_generic=-1)
+    one = torch.zeros((T, H * dh), dtype=torch.bfloat16, device=DEV)
+    exe.exe_op_prefill_attention(BF16, cu[:n + 1], qkv, H, dh, 0.125, 1, None, 0, one, force_generic=-1)
+    torch.cuda.synchronize()
+    assert bool((one != 0).any(dim=1).all()) and bool((out.reshape(R, T, -1) == one).all())
