@@ -150,10 +150,22 @@ template <int BM, int BN> static hipError_t launch_f32(const GemmArgs& a, hipStr
     auto kern = gemm_f32_kernel<BM, BN>;
     constexpr int lds = f32_lds(BM, BN);
     static_assert(lds <= 64 * 1024, "no more than a launch takes without asking");
-    int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
-    kern<<<tm * tn, F32_THREADS, lds, s>>>(a.M, a.N, a.K, (const float*)a.A, (const float*)a.W, (const float*)a.bias, a.act, a.alpha,
-                                           a.out_mode, a.out, tn, a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K, a.kv ? *a.kv : KvStore{});
-    return hipGetLastError();
+    const int64_t tm = ((int64_t)a.M + BM - 1) / BM, tn = ((int64_t)a.N + BN - 1) / BN, most = MAX_LAUNCH_THREADS / F32_THREADS / tn;
+    if (most < 1) return hipErrorInvalidValue;
+    const int lda = a.lda ? a.lda : a.K;
+    KvStore kv = a.kv ? *a.kv : KvStore{};
+    for (int64_t t = 0; t < tm; t += most) {                 // one launch, but for some 10^9 rows
+        const int64_t row = t * BM, rows = t + most < tm ? most * BM : a.M - row;
+        kern<<<(unsigned)((t + most < tm ? most : tm - t) * tn), F32_THREADS, lds, s>>>((int)rows, a.N, a.K, (const float*)a.A + row * lda, (const float*)a.W,
+            (const float*)a.bias, a.act, a.alpha, a.out_mode, (float*)a.out + row * a.N, (int)tn, lda, a.ldw ? a.ldw : a.K, kv);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        if (kv.pool) {
+            kv.row += rows;
+            kv.cap += rows;
+        }
+    }
+    return hipSuccess;
 }
 
 // The tile, and what a launch takes: n workgroups fall to the busiest CU, `resident` of them at a time (what registers and LDS let in);
@@ -175,7 +187,7 @@ int gemm_f32_tile(int M, int N, int K, double* seconds)
     int best = 0;
     for (int i = 0; i < 3; ++i) {
         const F32Tile& t = F32_TILES[i];
-        int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        int64_t tiles = ((int64_t)M + t.bm - 1) / t.bm * (((int64_t)N + t.bn - 1) / t.bn);
         double n = (double)((tiles + 255) / 256), rounds = (double)(((int64_t)n + t.resident - 1) / t.resident);
         double c = t.start + (double)M * N * 4 / 6e12 + (double)(K / F32_BK) * (t.step * rounds + t.share * n);
         if (i == 0 || c < *seconds) {

@@ -129,3 +129,25 @@ def test_large_sums(shape):
         got, ref = product(A.to(DEV), W.to(DEV)), A.double() @ W.double().T
         # one addition per product in the float MFMAs that compute them again
         assert bool(((got - ref).abs() <= (K + 4) * 2.0 ** -24 * (A.double().abs() @ W.double().abs().T)).all()), (ea, ew)
+
+
+def test_more_tiles_than_a_launch_takes():
+    """2^30 rows and a few: 2^32 threads and more."""
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 180 << 30:
+        pytest.skip("needs 180 GB")
+    n, R, N, K, more = 1 << 20, 1 << 10, 4, 32, 65
+    g = torch.Generator().manual_seed(10)
+    block, W = torch.randn((n, K), generator=g).to(DEV), torch.randn((N, K), generator=g).to(DEV)
+    one, out = torch.zeros((n, N), device=DEV), torch.zeros((n * R + more, N), device=DEV)
+    A = torch.empty((n * R + more, K), device=DEV)
+    A[:n * R].view(R, n, K).copy_(block)
+    A[n * R:] = block[:more]
+    for x, o in ((block, one), (A, out)):
+        exe.exe_op_gemm(wl.DTYPE_F32, len(x), N, K, x, W, None, -1, 1.0, 0, o)
+    torch.cuda.synchronize()
+    ref = block.double() @ W.double().T
+    assert bool(((one.double() - ref).abs() <= bound(block, W, K)).all())
+    assert all(torch.equal(o, one) for o in out[:n * R].view(R, n, N)) and torch.equal(out[n * R:], one[:more])
+    del A, out
+    torch.cuda.empty_cache()
