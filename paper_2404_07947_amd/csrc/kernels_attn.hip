@@ -971,7 +971,7 @@ hipError_t launch_attn_packed(const AttnPackedArgs& a, hipStream_t s)
     // the kernel's LDS copy; a batch outside these limits runs on the row kernel, which is correct but far slower,
     // so say so (once).
     const int64_t longest = a.work.max_len, row_bytes = (int64_t)3 * a.H * a.dh * (a.dtype == DT_F32 ? 4 : 2);
-    const bool mfma_fits = longest * row_bytes < ((int64_t)1 << 32) && (!a.bias_by_dist || 2 * a.bias_radius + 1 <= PF_BIAS);
+    const bool mfma_fits = longest * row_bytes < ((int64_t)1 << 32) && (!a.bias_by_dist || (a.bias_radius >= 0 && a.bias_radius <= (PF_BIAS - 1) / 2));
     if (mfma && !mfma_fits) {
         static std::once_flag warned;
         std::call_once(warned, [&]() {

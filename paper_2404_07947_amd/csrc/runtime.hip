@@ -2121,6 +2121,7 @@ extern "C" int exe_op_prefill_attention(void* hip_stream, int32_t dtype, int32_t
                                         const float* bias_by_dist, int32_t bias_radius, void* out, int32_t force_generic)
 {
     if (n_seqs < 1 || !cu_seqlens || !qkv || !out || H < 1) return fail(EXE_ERR_ARG, "bad prefill arguments");
+    if (bias_by_dist && bias_radius < 0) return fail(EXE_ERR_ARG, "a bias table of radius %d", bias_radius);
     if (dh != 64 && dh != 128) return fail(EXE_ERR_SHAPE, "head_dim must be 64 or 128");
     hipStream_t s = (hipStream_t)hip_stream;
     int T = cu_seqlens[n_seqs];

@@ -100,3 +100,11 @@ def test_prefill_tile_list_covers_every_query_tile_once_in_launch_order():
     n = ctypes.c_int32()
     lens = (ctypes.c_int32 * 2)(300, 5)
     assert exe.lib().exe_op_prefill_tiles(2, lens, None, 0, ctypes.byref(n)) == -1 and n.value == 4
+
+
+@pytest.mark.parametrize("radius", [-1, -200, -(1 << 31)])
+def test_prefill_attention_refuses_negative_bias_radii(radius):
+    """The table is [heads, 2 * radius + 1]; refused before anything of the device is touched."""
+    with pytest.raises(exe.ExeError) as e:
+        exe.exe_op_prefill_attention(wl.DTYPE_BF16, [0, 4], 4096, 2, 128, 0.1, 0, 4096, radius, 4096, stream=1)
+    assert e.value.code == -1
