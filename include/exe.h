@@ -343,9 +343,9 @@ int exe_op_resid_norm(void* hip_stream, int32_t dtype, int32_t rms, float* x, co
                       int32_t d, const float* partial, int32_t splits, int32_t partial_rows, const void* bias,
                       const void* gain, const void* shift, float eps, float out_scale, void* out);
 /* Ragged prefill attention over packed qkv [T, 3*H*dh] (dtype): cu_seqlens [n_seqs+1] host.
- * causal 0/1; bias_by_dist nullable device float [H, 2*bias_radius+1] indexed by clamp(key-query)+radius.
+ * causal 0/1; bias_by_dist nullable device float [H, 2*bias_radius+1], bias_radius >= 0, indexed by clamp(key-query)+radius.
  * out [T, H*dh] dtype.  force_generic: 0 = the faster kernel for the batch, > 0 the row kernel, < 0 the MFMA kernel
- * wherever it takes the call (sequences of less than 4 GB of qkv rows, bias tables of up to 1024 entries). */
+ * wherever it takes the call (sequences of less than 4 GB of qkv rows, bias tables of up to 1024 entries, float with dh 64 no scale below 2^-70 but 0). */
 int exe_op_prefill_attention(void* hip_stream, int32_t dtype, int32_t n_seqs, const int32_t* cu_seqlens,
                              const void* qkv, int32_t H, int32_t dh, float scale, int32_t causal,
                              const float* bias_by_dist, int32_t bias_radius, void* out, int32_t force_generic);

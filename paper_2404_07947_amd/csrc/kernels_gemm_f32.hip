@@ -169,7 +169,7 @@ template <int BM, int BN> static hipError_t launch_f32(const GemmArgs& a, hipStr
 }
 
 // The tile, and what a launch takes: n workgroups fall to the busiest CU, `resident` of them at a time (what registers and LDS let in);
-// a launch takes `start`, and a step of 32 k takes the resident ones `step` together and each `share` more.  Fitted to 252 launches on one
+// a launch takes `start`, and a step of 32 k takes the resident ones `step` together and each `share` more.  Fitted to 302 shapes on one
 // MI355X, 14 weights (256 to 4096 features, K 256 to 4096) x 22 row counts from 32 to 16384: within 1.3, 2.0 and 2.4 % on average (9, 13
 // and 12 % at worst), and the tile taken is within 0.2 % of the fastest on average, 8 % at worst.
 // us on one MI355X, the float MFMA kernel that this replaces / 128 x 128 / 64 x 128 / 64 x 64, and the 2-norm relative error against
