@@ -312,7 +312,7 @@ int exe_op_gemm_model(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int
                       void* workspace, uint64_t workspace_bytes, int32_t* pending);
 /* How exe_op_gemm launches a shape (host function; lets a test assert that its cases cover every kernel
  * instantiation): *route 0 = MFMA tile kernel, 1 = streaming kernel (float), 2 = plain-FMA kernel; *cfg = tile configuration (0 64x256, 1 128x256,
- * 2 256x256, 3 64x128, 4 128x128, 5 256x128, 6 192x256, and float only 7 64x64 rows x features); *splits = split-K parts (> 1: float partials in the
+ * 2 256x256, 3 64x128, 4 128x128, 5 256x128, 6 192x256, 8 256x160, and float only 7 64x64 rows x features); *splits = split-K parts (> 1: float partials in the
  * workspace, summed in split order by a second kernel); *rows_first = rows of the first launch (M, unless the rows
  * beyond whole rounds of 256 x 256 tiles go to a second, separately planned launch: ask again with M - *rows_first). */
 int exe_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t* route, int32_t* cfg, int32_t* splits,

@@ -85,6 +85,15 @@ template <> struct LdsTurn<4> {
                      : "memory");
     }
 };
+template <> struct LdsTurn<3> {
+    static __device__ __forceinline__ void read(f32x4 (&v)[3], const unsigned (&a)[3])
+    {
+        asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b128 %2, %5\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2])
+                     : "v"(a[0]), "v"(a[1]), "v"(a[2])
+                     : "memory");
+    }
+};
 template <> struct LdsTurn<2> {
     static __device__ __forceinline__ void read(f32x4 (&v)[2], const unsigned (&a)[2])
     {
@@ -103,7 +112,7 @@ __device__ __forceinline__ void epilogue_tiles(const f32x4 (&acc)[TN][TM], unsig
                                                int M, int N, const T* __restrict__ bias, float alpha,
                                                float* __restrict__ fout, T* __restrict__ tout, const KvStore& kv = KvStore{})
 {
-    static_assert(TM % 2 == 0 && TN % 2 == 0, "groups are 2 tiles high");
+    static_assert(TM % 2 == 0 && TN % (EN / 16) == 0, "groups are 2 tiles high");
     constexpr int QW = EN / 8;                  // 16-byte slots a lane writes, and reads, per group
     constexpr int IW = EN / 16;                 // tiles side by side in a group
     constexpr int NG = TN / IW;                 // groups per 32 rows

@@ -51,7 +51,7 @@ enum GemmMode { GEMM_TILE_ONLY = 0, GEMM_FEW_ROWS = 1, GEMM_DEFER = 2 };       /
 constexpr int MAX_SPLIT_ROWS = 4096;      // no launch of more rows is split over K
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode);
 // how a shape is launched with few_rows = (dtype is float): route (0 tile kernel, 1 streaming kernel, 2 generic), tile configuration (0 64x256, 1 128x256, 2 256x256, 3 64x128,
-// 4 128x128, 5 256x128, 6 192x256), split-K parts, and the leading rows that the first launch takes (M unless the rows beyond
+// 4 128x128, 5 256x128, 6 192x256, 8 256x160), split-K parts, and the leading rows that the first launch takes (M unless the rows beyond
 // whole rounds of tiles go to a second launch)
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
@@ -67,9 +67,9 @@ int gemm_launches(const GemmArgs& a, int cap, int32_t* rows, int32_t* stores);
 struct StreamPlan { int nt = 0, ma = 0, splits = 1, units_per_split = 0; double cost = 0.0; };
 StreamPlan gemm_stream_plan(int dtype, int M, int N, int K, bool defer);
 StreamPlan gemm_stream_candidate(int dtype, int nt, int ma, int splits, int M, int N, int K, bool defer);    // nt in {1, 2, 4, 5}, ma in {1, 2, 4, 6, 8}
-// The large tile kernel (kernels_gemm_large.hip, bf16): bm (256, 192 or 128) x 256 tiles, persistent on at most grid_max
+// The large tile kernel (kernels_gemm_large.hip, bf16): 256, 192 or 128 x 256, 256 x 160 or 256 x 128 tiles, persistent on at most grid_max
 // workgroups, K in `splits` parts of k_per_split (every part at least 2 k-tiles of 64).
-hipError_t launch_gemm_large(const GemmArgs& a, int bm, int k_per_split, int splits, int grid_max, hipStream_t s);
+hipError_t launch_gemm_large(const GemmArgs& a, int bm, int bn, int k_per_split, int splits, int grid_max, hipStream_t s);
 // The float tiles (kernels_gemm_f32.hip): K a multiple of 32, operands and bias 16-byte aligned.
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 int gemm_f32_tile(int M, int N, int K, double* seconds);       // 0 128 x 128, 1 64 x 128, 2 64 x 64

@@ -381,14 +381,15 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(int M, int N, int K, 
 // ---------------------------------------------------------------- host-side routing
 // Tile configurations.  Four have BN = 256 (the weight share of the LDS fill traffic is BN / (BM + BN), which is what a
 // weight-streaming decode GEMM wants large); 64x128, 128x128 and 256x128 halve BN for matrices with few output features,
-// where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows run on gemm_large_kernel if K allows, the
-// others on gemm_tile_kernel.  192x256 runs on gemm_large_kernel only.
-enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, C192x256, N_CFG };
+// where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows and 256x128 run on gemm_large_kernel if K allows, the
+// others on gemm_tile_kernel.  192x256 and 256x160 run on gemm_large_kernel only.
+enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, C192x256, F64x64, C256x160, N_CFG };      // F64x64: a float tile only
 struct CfgInfo { int bm, bn; };
-static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}, {192, 256}};
+static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}, {192, 256}, {64, 64}, {256, 160}};
 
 // the shallowest depth of gemm_large_kernel (its start and end take a few k-tiles' time)
-static bool is_large(int cfg) { return cfg == C256x256 || cfg == C128x256 || cfg == C192x256; }
+static bool is_large(int cfg) { return cfg == C256x256 || cfg == C128x256 || cfg == C192x256 || cfg == C256x128 || cfg == C256x160; }
+static bool only_large(int cfg) { return cfg == C192x256 || cfg == C256x160; }
 constexpr int LARGE_MIN_K = 256;
 
 static int k_tile(int dtype) { return dtype == DT_F32 ? tbk<float>() : tbk<bf16_t>(); }
@@ -419,14 +420,38 @@ static const Knobs& knobs()
 // norm_kernel).
 //
 // Two sets of rates.  A model's launches (`model`): fitted to 2800 launches on MI355X, 13 row counts from 24 to 2048 x 11
-// weight shapes of 1024 to 49152 features, six tile shapes x 1..8 splits, weights from HBM: the picks take 0.7 % more than
-// the best measured choice on average, 11 % at worst.  gemm_large_kernel is priced by its time per k-tile there (1.03 us for
-// 256 rows, 0.93 for 192, 0.80 for 128, 16 % more when every CU runs it: the clock falls) and per tile.  Up to 192
+// weight shapes of 1024 to 49152 features, six tile shapes x 1..8 splits, weights from HBM, those of 256x128 and 256x160 afterwards
+// to 8900 more, 32 row counts from 104 to 16384 x 14 weight shapes: there the picks take 1.7 % more than the best measured choice on
+// average below 4096 rows (without the two 2.4 %), 0.1 % (0.2 %) from there on; at worst 25 %, of launches of 10 to 20 us.
+// gemm_large_kernel is priced by its time per k-tile and per tile (large_rate), 16 % more when every CU runs it: the clock falls.  Up to 192
 // rows, where the estimate also has to compare with the streaming kernel's, the rates of an earlier fit stay (within 2 % of
 // the best choice on average), and so they do for exe_op_gemm's launches up to 1024 rows: its callers have been given these
 // plans' workspace sizes.
 struct Rates { double fill, mfma, hbm, partial, reduce; };
 static const Rates MODEL_RATES{44e9, 3.5e12, 6.5e12, 5.3e12, 4.5e-6}, OP_RATES{35e9, 3.5e12, 5.5e12, 3e12, 1e-6};
+
+// Seconds per k-tile and per tile.  What a CU takes in is bound by the lines that it has in flight, some 300: a line from HBM
+// costs it 3.3 ns, one from L2 1.6.  So the shapes that read fewer weights per activation, 256 x 128 and 256 x 160, gain where the weights
+// are the larger operand and come from memory (0.85 of their time there), and of equal area 256 x 128 is the better one: us of 256 x
+// 128 and 128 x 256, 512 x 15360, K 5120 77 / 82, 256 x 20480 76 / 85; but 8192 x 3072, K 1024 53 / 53, 2048 x 1024, K 16384 in 3 parts
+// 1.35x, and of 36864 x 12288 weights (0.9 GB) 256 to 2048 rows 0.97 to 1.03x.
+// 256 x 160 besides fits widths that leave the others' last round half empty: 512 x 20480, K 5120 86 (192 x 256 98), 1024 x 20480 168 (193).
+struct LargeRate { double per, fixed; };
+static LargeRate large_rate(int cfg)
+{
+    switch (cfg) {
+        case C128x256: return {0.80e-6, 3e-6};
+        case C256x128: return {0.80e-6, 3.2e-6};
+        case C256x160: return {0.95e-6, 3.5e-6};
+        case C192x256: return {0.93e-6, 4.5e-6};
+        default: return {1.03e-6, 5e-6};
+    }
+}
+
+static double split_cost(int splits, int M, int N, bool defer, const Rates& r)
+{
+    return defer ? 2.0 * splits * M * N * 4 / 8e12 - 1e-6 : 2.0 * splits * M * N * 4 / r.partial + r.reduce;
+}
 
 static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, bool defer, bool model)
 {
@@ -440,8 +465,9 @@ static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, boo
     double t;
     if (model && is_large(cfg)) {
         double busy = wgs / rounds / 256;
-        double per = bm == 256 ? 1.03e-6 : bm == 192 ? 0.93e-6 : 0.80e-6, fixed = bm == 256 ? 5e-6 : bm == 192 ? 4.5e-6 : 3e-6;
-        t = rounds * (ktiles * per * (1.0 + 0.16 * busy) + fixed);
+        LargeRate lr = large_rate(cfg);
+        if (bm == 256 && bn < 256 && N >= 5120 && N >= 4 * (int64_t)M && (int64_t)N * K < (1 << 28)) lr.per *= 0.85;
+        t = rounds * (ktiles * lr.per * (1.0 + 0.16 * busy) + lr.fixed);
     } else {
         double fill = ktiles * (bm + bn) * TROW / r.fill;
         double mfma = ktiles * 2.0 * bm * bn * bk / (cfg == C128x256 ? 2.8e12 : r.mfma);
@@ -450,7 +476,7 @@ static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, boo
     double hbm = (double)N * K * esz / r.hbm;
     if (t < hbm) t = hbm;
     t += 4e-6;
-    if (splits > 1) t += defer ? 2.0 * splits * M * N * 4 / 8e12 - 1e-6 : 2.0 * splits * M * N * 4 / r.partial + r.reduce;
+    if (splits > 1) t += split_cost(splits, M, N, defer, r);
     return t;
 }
 
@@ -526,12 +552,14 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         double best = 1e30;
         for (int cfg = 0; cfg < N_CFG; ++cfg) {
             if (CFG[cfg].bm >= 2 * M && CFG[cfg].bm > 64) continue;     // more than half the rows would be padding
-            if (dtype == DT_F32 && cfg != C64x128) continue;
-            if (cfg == C192x256 && !model) continue;
+            if (cfg == F64x64 || (dtype == DT_F32 && cfg != C64x128)) continue;
+            if (only_large(cfg) && !model) continue;
+            if ((cfg == C256x160 || (cfg == C256x128 && many && !shallow)) && !(mode & GEMM_FEW_ROWS)) continue;     // a model's launches only
             if (many && (shallow ? cfg != shallow_cfg : !is_large(cfg))) continue;
             for (int s = 1; s <= max_splits; ++s) {
                 if (!split_ok(dtype, K, s)) continue;
                 if (many && s > 1 && (int64_t)s * M * N * 4 > MANY_ROWS_PARTIALS) break;
+                if (s > 1 && 4e-6 + split_cost(s, M, N, mode & GEMM_DEFER, model ? MODEL_RATES : OP_RATES) >= best) break;      // and so would more parts
                 double c = plan_cost(dtype, cfg, s, M, N, K, mode & GEMM_DEFER, model && dtype == DT_BF16);
                 if (c < best) { best = c; p.cfg = cfg; p.splits = s; }
             }
@@ -552,7 +580,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
         return p;
     }
     const Knobs& kn = knobs();
-    if (kn.cfg >= 0 && kn.cfg < N_CFG && dtype == DT_BF16 && !(kn.cfg == C192x256 && K < LARGE_MIN_K)) p.cfg = kn.cfg;
+    if (kn.cfg >= 0 && kn.cfg < N_CFG && kn.cfg != F64x64 && dtype == DT_BF16 && !(only_large(kn.cfg) && K < LARGE_MIN_K)) p.cfg = kn.cfg;
     if (kn.split > 0 && split_ok(dtype, K, kn.split)) p.splits = kn.split;
     p.spread = 1;     // never slower than issuing a k-tile's loads at once in that sweep, up to 15 % faster from M = 128 on
     if (kn.spread >= 0) p.spread = kn.spread != 0;
@@ -563,7 +591,7 @@ static Plan make_plan(int dtype, int M, int N, int K, int mode)
 
 bool gemm_force_ok(int cfg, int splits, int M, int N, int K)
 {
-    return cfg >= -1 && cfg < N_CFG && M >= 1 && N % 4 == 0 && K % k_tile(DT_BF16) == 0 && !(cfg == C192x256 && K < LARGE_MIN_K) &&
+    return cfg >= -1 && cfg < N_CFG && cfg != F64x64 && M >= 1 && N % 4 == 0 && K % k_tile(DT_BF16) == 0 && !(only_large(cfg) && K < LARGE_MIN_K) &&
            splits >= 1 && split_ok(DT_BF16, K, splits);
 }
 
@@ -633,7 +661,7 @@ void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* s
     *route = p.route;
     *cfg = p.cfg;
     if (dtype == DT_F32 && p.route == 0) {
-        const int tiles[] = {C128x128, C64x128, N_CFG};        // 64 x 64 is a float tile only
+        const int tiles[] = {C128x128, C64x128, F64x64};
         double seconds;
         *cfg = tiles[gemm_f32_tile(M1, N, K, &seconds)];
     }
@@ -818,12 +846,14 @@ static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s)
     } else {
         switch (p.cfg) {
             case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;
-            case C128x256: case C256x256: case C192x256:
-                if (a.K < LARGE_MIN_K) e = p.cfg == C128x256 ? launch_tile<bf16_t, 128, 256, 64, 64, 3>(a, p, s) : launch_tile<bf16_t, 256, 256, 128, 64, 2>(a, p, s);
-                else e = launch_gemm_large(a, CFG[p.cfg].bm, p.k_per_split, p.splits, persistent_grid(), s); break;
+            case C128x256: case C256x256: case C256x128: case C192x256: case C256x160:
+                if (a.K >= LARGE_MIN_K) e = launch_gemm_large(a, CFG[p.cfg].bm, CFG[p.cfg].bn, p.k_per_split, p.splits, persistent_grid(), s);
+                else if (p.cfg == C128x256) e = launch_tile<bf16_t, 128, 256, 64, 64, 3>(a, p, s);
+                else if (p.cfg == C256x128) e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);
+                else e = launch_tile<bf16_t, 256, 256, 128, 64, 2>(a, p, s);
+                break;
             case C64x128: e = launch_tile<bf16_t, 64, 128, 32, 64, 4>(a, p, s); break;
-            case C128x128: e = launch_tile<bf16_t, 128, 128, 64, 64, 3>(a, p, s); break;
-            default: e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);
+            default: e = launch_tile<bf16_t, 128, 128, 64, 64, 3>(a, p, s);
         }
     }
     if (e != hipSuccess || p.splits == 1) return e;

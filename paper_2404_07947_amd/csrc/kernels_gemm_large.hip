@@ -1,5 +1,5 @@
-// GEMM with large tiles (bf16): BM x 256 outputs per workgroup, BM 256, 192 or 128; encode batches, and decode batches that
-// split K over workgroups.
+// GEMM with large tiles (bf16): BM x BN outputs per workgroup, BM 256, 192 or 128 with BN 256, and 256 x 160 and 256 x 128; encode
+// batches, and decode batches that split K over workgroups.
 //
 // What bounds it: MFMA issue and, through the power budget, the clock.  gemm_tile_kernel's loop at this tile size kept the
 // matrix pipes busy 66 % of the cycles: its eight waves do the same thing at the same time, so both waves of a SIMD wait
@@ -21,6 +21,10 @@
 //   12288 x 65536 x  1024  1683 (980)  -> 1224 (1347)     8192 x  3072 x  1024    57 (899)  ->   48 (1085)
 // and with the tile height that fills the chip:
 //   12288 x  1024 x 16384   396 -> 335 (192 rows)   8192 x 1024 x 1024  36 -> 27, 8192 x 1024 x 4096  92 -> 63 (128 rows)
+// Launches of one round or less are bound by what a CU takes in (see large_rate in kernels_gemm.hip); there 256 x 128 and 256 x 160 take
+//   512 x 15360 x 5120  84 -> 78 (256 x 128 for 128 x 256)    512 x 20480 x 5120  98 -> 86, 1024 x 20480 x 5120 193 -> 168 (256 x 160 for 192 x 256)
+// A third LDS stage where it fits (128 x 256, 256 x 128) gave 2 % and took it back in epilogues of half the rows; a tile's lines fetched into L2 by
+// one of the CUs that share them, some k-tiles ahead, cost as many lines as it saved (3 to 20 % slower).
 #include <type_traits>
 
 #include "gemm_tile.h"
@@ -30,25 +34,26 @@ namespace exe {
 
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-constexpr int LARGE_BN = 256;
 // Outputs of this size and more are stored nontemporal: 12288 x 65536 in bf16 1350 -> 1225 us, 16384 x 5120 557 -> 552;
 // of 8192 x 3072 and 8192 x 4096 (50 and 67 MB) the next kernel still finds most in cache, and nothing is gained.
 constexpr int64_t NT_BYTES = 96 << 20;
 constexpr int LARGE_THREADS = 512;
-constexpr int large_lds(int BM) { return 2 * (BM + LARGE_BN) * TROW + 8 * 4096; }
+constexpr int large_lds(int BM, int BN) { return 2 * (BM + BN) * TROW + 8 * 4096; }
 
-// Epilogue for bf16 outputs: a wave's TM x 4 tiles, 32 rows x 64 features at a time, through its 4 KB of LDS (16-byte chunk c
+// Epilogue for bf16 outputs: a wave's TM x 4 tiles, RJ * 16 rows x 64 features at a time, through its RJ * 2 KB of LDS (16-byte chunk c
 // of row r at slot c ^ ((r >> 1) & 7): no bank conflicts either way).  The LDS accesses are inline assembly for the reason
 // given at epilogue_tiles.  wide: 0 = rows are 8-byte aligned only, 1 = 16-byte stores, 3 = and nontemporal.
-template <int TM, int MODE>
-__device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigned stg, int lane, int row0, int col0, int M, int N,
+template <int TM, int TN, int MODE, int RJ>
+__device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[TN][TM], unsigned stg, int lane, int row0, int col0, int M, int N,
                                               const bf16_t* __restrict__ bias, float alpha, bf16_t* __restrict__ out, int wide,
                                               const KvStore& kv = KvStore{})
 {
-    int lm = lane & 15, lq = lane >> 4, rr = lane >> 3, rc = lane & 7;
-    f32x4 bv[4];
+    constexpr int CH = TN * 2, RB = CH * 16, NR = (RJ * 16 * CH + 63) / 64;     // 16-byte chunks and bytes of a row, reads of a lane
+    constexpr bool SWZ = TN == 4;                    // rows of 160 bytes: chunks in order, read one behind the other
+    int lm = lane & 15, lq = lane >> 4;
+    f32x4 bv[TN];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < TN; ++i) {
         int n = col0 + i * 16 + lq * 4;
         bv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (bias && n < N) {
@@ -57,39 +62,46 @@ __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigne
             for (int e = 0; e < 4; ++e) bv[i][e] = (float)b[e];
         }
     }
-    unsigned waddr[2][4], raddr[4];
+    auto turn_row = [&](int p) { return SWZ ? p * 8 + (lane >> 3) : (p * 64 + lane) / CH; };
+    auto turn_chunk = [&](int p) { return SWZ ? lane & 7 : (p * 64 + lane) % CH; };
+    unsigned waddr[RJ][TN], raddr[NR];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
+    for (int x = 0; x < TN; ++x)
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-            waddr[jj][x] = stg + (jj * 16 + lm) * TROW + (((x * 2 + (lq >> 1)) ^ lds_swz(jj * 16 + lm)) << 4) + (lq & 1) * 8;
-        raddr[x] = stg + (x * 8 + rr) * TROW + ((rc ^ lds_swz(x * 8 + rr)) << 4);
-    }
-    int n = col0 + rc * 8;
-    const bool cached = MODE == EPI_T_KV && col0 >= kv.first_col;          // the wave's 64 features are of one head
-    KvRows<4> kr;
+        for (int jj = 0; jj < RJ; ++jj) {
+            int c = x * 2 + (lq >> 1);
+            waddr[jj][x] = stg + (jj * 16 + lm) * RB + ((SWZ ? c ^ lds_swz(jj * 16 + lm) : c) << 4) + (lq & 1) * 8;
+        }
 #pragma unroll
-    for (int jp = 0; jp < TM / 2; ++jp) {
-        if (MODE == EPI_T_KV && cached) kr.load(kv, M, [&](int p) { return row0 + jp * 32 + p * 8 + rr; });
+    for (int p = 0; p < NR; ++p) raddr[p] = stg + turn_row(p) * RB + ((SWZ ? turn_chunk(p) ^ lds_swz(turn_row(p)) : turn_chunk(p)) << 4);
+    // 64 features are of one head and all in the cache or none; of 80, each chunk of 8 is
+    const bool cached = MODE == EPI_T_KV && col0 + (SWZ ? 0 : TN * 16 - 8) >= kv.first_col;
+    KvRows<NR> kr;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+    for (int jp = 0; jp < TM / RJ; ++jp) {
+        if (MODE == EPI_T_KV && cached) kr.load(kv, M, [&](int p) { return row0 + jp * RJ * 16 + turn_row(p); });
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                f32x4 r = acc[i][jp * 2 + jj] * alpha + bv[i];
+        for (int jj = 0; jj < RJ; ++jj)
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                f32x4 r = acc[i][jp * RJ + jj] * alpha + bv[i];
                 bf16x4 w;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     w[e] = (bf16_t)(MODE == EPI_T_RELU ? act_apply(r[e], 0) : MODE == EPI_T_GELU ? act_apply(r[e], 1) : r[e]);
                 asm volatile("ds_write_b64 %0, %1" ::"v"(waddr[jj][i]), "v"(w) : "memory");
             }
-        f32x4 v[4];
-        LdsTurn<4>::read(v, raddr);
+        f32x4 v[NR];
+        LdsTurn<NR>::read(v, raddr);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            int m = row0 + jp * 32 + p * 8 + rr;
-            if (m >= M || n >= N) continue;
+        for (int p = 0; p < NR; ++p) {
+            int m = row0 + jp * RJ * 16 + turn_row(p), n = col0 + turn_chunk(p) * 8;
+            if (m >= M || n >= N || turn_row(p) >= RJ * 16) continue;
             bf16_t* o = out + (int64_t)m * N + n;
-            if (MODE == EPI_T_KV && cached) o = (bf16_t*)kv.pool + kr.at(kv, p, col0) + rc * 8;
+            if (MODE == EPI_T_KV && cached) {
+                if (SWZ) o = (bf16_t*)kv.pool + kr.at(kv, p, col0) + turn_chunk(p) * 8;
+                else if (n >= kv.first_col) o = (bf16_t*)kv.pool + kr.at(kv, p, n);
+            }
             if (wide & 2) __builtin_nontemporal_store(v[p], (f32x4*)o);
             else if (wide) *(f32x4*)o = v[p];
             else {
@@ -102,8 +114,9 @@ __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigne
     }
 }
 
-// A stage holds 64 k of [activation rows, half 0 | half 1 | weight rows 0..127 | 128..255], 128 bytes a row.  Group g of the
-// waves computes rows g * BM/2 .. of the tile, its half h the rows h * BM/4 .. of those; wave wn of a group 64 features.
+// A stage holds 64 k of [activation rows, half 0 | half 1 | weight rows], 128 bytes a row.  Group g of the waves computes rows
+// g * BM/2 .. of the tile: waves of 64 features (BN 256) and all of those rows, or (BN 160, 128) of half the features and 64 rows.  Half h
+// of the activations holds the h-th half of every wave's rows.
 //
 // One k-tile is two phases per group, each a memory step and a compute step, and the groups are one step apart:
 //   step     0        1        2        3        4
@@ -113,22 +126,27 @@ __device__ __forceinline__ void epilogue_rows(const f32x4 (&acc)[4][TM], unsigne
 // (lgkmcnt 0) in front of the barrier.  Refills, for k-tile kt + 2: the weights in mem 1 of kt (group 1 has read them by
 // the end of step 1, group 0 issues in step 2), the activations in mem 0 of kt + 1 (half 1 read by the end of step 3).
 // What a phase reads is waited for one phase ahead, by count: every wave issues the same loads, and the barrier makes its
-// wait good for all.  Loads of a wave per piece: weights 4 for both halves, a half of the activations 2 (BM 256),
+// wait good for all.  Loads of a wave per piece: weights BN / 64 (BN 160: 3 or 2, group 0 or 1), a half of the activations 2 (BM 256),
 // 2 or 1 (BM 192: group 0 or 1), 1 (BM 128).
-template <int BM>
+template <int BM, int BN>
 __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
     const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias, int act, float alpha, int out_mode, void* __restrict__ out,
     float* __restrict__ partial, int tiles_m, int tiles_n, int k_per_split, int n_split, int wide, int lda, int ldw, KvStore kv)
 {
-    constexpr int TM = BM / 32, TH = TM / 2;         // 16-row tiles of a wave, and of one of its halves
-    constexpr int QA = BM / 4;                       // rows of a wave group in one activation slot
-    constexpr int SLOT_A = BM / 2 * TROW, SLOT_W = LARGE_BN / 2 * TROW;
-    constexpr int STAGE = 2 * (SLOT_A + SLOT_W);     // [A half 0][A half 1][W half 0][W half 1]
-    constexpr int EN = 32;
+    constexpr int NWN = BN == 256 ? 4 : 2, NWR = 4 / NWN;            // waves of a group side by side in the features, and in the rows
+    constexpr int WC = BN / NWN, TN = WC / 16;                       // features and 16-feature tiles of a wave
+    constexpr int WR = BM / 2 / NWR, TM = WR / 16, TH = TM / 2;      // rows and 16-row tiles of a wave, tiles of one of its halves
+    constexpr int QA = WR / 2;                       // rows of a wave in one activation slot
+    constexpr int SLOT_A = BM / 2 * TROW;
+    constexpr int STAGE = 2 * SLOT_A + BN * TROW;    // [A half 0][A half 1][W]
+    constexpr int WP = (BN + 63) / 64;               // 1 KB loads of a wave for the weights of a k-tile, in group 0 and 1
+    constexpr int WL0 = WP, WL1 = BN / 64;
+    constexpr int AL0 = BM == 128 ? 1 : 2, AL1 = BM == 256 ? 2 : 1;  // and for an activation slot
+    constexpr int EN = TN == 4 ? 32 : 16, RJ = TN == 4 ? 2 : 1;      // columns and 16-row tiles that a wave turns through LDS at a time
     extern __shared__ __align__(16) unsigned char lds[];
     int tid = threadIdx.x, lane = tid & 63;
     int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int grp = wave >> 2, wn = wave & 3;
+    int grp = wave >> 2, wn = wave & (NWN - 1), part = grp * NWR + (wave & 3) / NWN;        // part: the wave's rows
 
     // Work items are (split, output tile) pairs, mapped as in gemm_tile_kernel: an XCD's 32 workgroups get a patch of 8 x 4
     // tiles.  (4 x 8 is 2 % faster at K = 20480 and 1-3 % slower elsewhere; shifting the patches of the XCDs against each other
@@ -146,7 +164,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         int gsz = tiles_m - first_m < GM ? tiles_m - first_m : GM;
         int within = pid - group * GM * tiles_n;
         m0 = (first_m + within % gsz) * BM;
-        n0 = (within / gsz) * LARGE_BN;
+        n0 = (within / gsz) * BN;
     };
     auto k_tiles = [&](int z) {
         int kbeg = z * k_per_split;
@@ -157,7 +175,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
     // ---- loader: two k-tiles ahead of the compute steps, across item boundaries; uniform tile origins plus per-lane offsets,
     // rows clamped into the matrices (rows past the edge are never stored).  Inline assembly for the reason given in
     // gemm_tile_kernel.
-    unsigned off_a[2][2], off_w[2][2];
+    unsigned off_a[2][2], off_w[WP];
     const char *base_a, *base_w;
     int ld_v = blockIdx.x, ld_kt = 0, ld_nk = 1;
     int ld_st = 0;
@@ -173,13 +191,16 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 int s = (p * 8 + wave) * 8 + (lane >> 3);          // row of the slot
-                int r = s / QA * (BM / 2) + h * QA + s % QA;       // row of the tile
+                int r = s / QA * WR + h * QA + s % QA;             // row of the tile
                 if (m0 + r >= M) r = M - 1 - m0;
                 off_a[h][p] = (unsigned)r * (unsigned)(lda * 2) + (((lane & 7) ^ lds_swz(s)) << 4);
-                r = h * (LARGE_BN / 2) + s;
-                if (n0 + r >= N) r = N - 1 - n0;
-                off_w[h][p] = (unsigned)r * (unsigned)(ldw * 2) + (((lane & 7) ^ lds_swz(s)) << 4);
             }
+#pragma unroll
+        for (int p = 0; p < WP; ++p) {
+            int s = (p * 8 + wave) * 8 + (lane >> 3), r = s;
+            if (n0 + r >= N) r = N - 1 - n0;
+            off_w[p] = (unsigned)r * (unsigned)(ldw * 2) + (((lane & 7) ^ lds_swz(s)) << 4);
+        }
     };
     set_src(ld_v);
     unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds;
@@ -194,14 +215,15 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         unsigned dst = lds_base + ld_st * STAGE + h * SLOT_A + wave * 1024;
         const char* src = base_a + ld_kt * TROW;
         load_to_lds(src, off_a[h][0], dst);
-        if (BM == 256 || (BM == 192 && grp == 0)) load_to_lds(src, off_a[h][1], dst + 8192);
+        if (AL1 == 2 || (AL0 == 2 && grp == 0)) load_to_lds(src, off_a[h][1], dst + 8192);
     };
-    auto load_w = [&](int h) {
+    auto load_w = [&]() {
         if (EXE_GEMM_ABLATE & 4) return;
-        unsigned dst = lds_base + ld_st * STAGE + 2 * SLOT_A + h * SLOT_W + wave * 1024;
+        unsigned dst = lds_base + ld_st * STAGE + 2 * SLOT_A + wave * 1024;
         const char* src = base_w + ld_kt * TROW;
-        load_to_lds(src, off_w[h][0], dst);
-        load_to_lds(src, off_w[h][1], dst + 8192);
+#pragma unroll
+        for (int p = 0; p < WP; ++p)
+            if (p < WL1 || grp == 0) load_to_lds(src, off_w[p], dst + p * 8192);
     };
     // past the last item the last k-tile is loaded again, which keeps the number of loads in flight uniform
     auto advance = [&]() {
@@ -213,34 +235,33 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
             set_src(ld_v);
         }
     };
-    // all but the youngest WL weight loads and the activation loads of NA slots have landed
-    auto wait_loads = [&](auto wl, auto na) {
-        constexpr int WL = decltype(wl)::value, NA = decltype(na)::value;
-        if (BM == 256 || (BM == 192 && grp == 0)) wait_vm<WL + 2 * NA>();
-        else wait_vm<WL + NA>();
+    // all but the youngest weight loads of W k-tiles and activation loads of NA slots have landed
+    auto wait_loads = [&](auto w, auto na) {
+        constexpr int W = decltype(w)::value, NA = decltype(na)::value;
+        if (WL0 * W + AL0 * NA == WL1 * W + AL1 * NA || grp == 0) wait_vm<WL0 * W + AL0 * NA>();
+        else wait_vm<WL1 * W + AL1 * NA>();
     };
     using C0 = std::integral_constant<int, 0>;
     using C1 = std::integral_constant<int, 1>;
     using C2 = std::integral_constant<int, 2>;
-    using C4 = std::integral_constant<int, 4>;
     auto barrier = [&]() { asm volatile("s_barrier" ::: "memory"); };
     auto lgkm0 = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
 
-    f32x4 acc[4][TM];
-    u32x4 fa[TH][2], fw[4][2];
+    f32x4 acc[TN][TM];
+    u32x4 fa[TH][2], fw[TN][2];
     int frow = lane & 15, fk = lane >> 4;
     unsigned fo[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) fo[ks] = frow * TROW + (((ks * 4 + fk) ^ lds_swz(frow)) << 4);
     auto read_a = [&](int stage, int h, int ks) {
-        const unsigned char* s = lds + stage * STAGE + h * SLOT_A + grp * QA * TROW;
+        const unsigned char* s = lds + stage * STAGE + h * SLOT_A + part * QA * TROW;
 #pragma unroll
         for (int j = 0; j < TH; ++j) fa[j][ks] = *(const u32x4*)(s + fo[ks] + j * 16 * TROW);
     };
     auto read_w = [&](int stage, int ks) {
-        const unsigned char* s = lds + stage * STAGE + 2 * SLOT_A + wn * 64 * TROW;
+        const unsigned char* s = lds + stage * STAGE + 2 * SLOT_A + wn * WC * TROW;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) fw[i][ks] = *(const u32x4*)(s + fo[ks] + i * 16 * TROW);
+        for (int i = 0; i < TN; ++i) fw[i][ks] = *(const u32x4*)(s + fo[ks] + i * 16 * TROW);
     };
 #define EXE_SB __builtin_amdgcn_sched_barrier(0)
     auto compute = [&](auto half) {
@@ -249,7 +270,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
 #pragma unroll
         for (int ks = 0; ks < ((EXE_GEMM_ABLATE & 1) ? 0 : 2); ++ks)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < TN; ++i)
 #pragma unroll
                 for (int j = 0; j < TH; ++j) acc[i][J0 + j] = HalfUnit<bf16_t>::mma(fw[i][ks], fa[j][ks], acc[i][J0 + j]);
         EXE_SB;
@@ -258,9 +279,9 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
     };
 
     // prologue: k-tile 0 and the weights of k-tile 1; waits for what the first memory step reads
-    load_w(0); load_w(1); load_a(0); load_a(1); advance();
-    load_w(0); load_w(1);
-    wait_loads(C4{}, C1{});
+    load_w(); load_a(0); load_a(1); advance();
+    load_w();
+    wait_loads(C1{}, C1{});
     barrier();
     int st = 0;
     bool first = true;
@@ -269,7 +290,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         locate(v, m0, n0, z);
         int nk = k_tiles(z);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TN; ++i)
 #pragma unroll
             for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (grp) barrier();                          // the groups part by a step
@@ -279,14 +300,14 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
             if (kt > 0 || first) {                   // else done before the epilogue of the item before
                 load_a(0); load_a(1);
                 advance();
-                wait_loads(C4{}, C2{});
+                wait_loads(C1{}, C2{});
             }
             lgkm0();
             barrier();
             compute(C0{});
             read_a(st, 1, 0); read_a(st, 1, 1);
-            load_w(0); load_w(1);
-            wait_loads(C4{}, C1{});
+            load_w();
+            wait_loads(C1{}, C1{});
             lgkm0();
             barrier();
             compute(C1{});
@@ -301,44 +322,46 @@ __global__ __launch_bounds__(LARGE_THREADS) void gemm_large_kernel(int M, int N,
         wait_loads(C0{}, C2{});
         {
             unsigned stg = lds_base + 2 * STAGE + wave * 4096;
-            int row0 = m0 + grp * (BM / 2), col0 = n0 + wn * 64;
+            int row0 = m0 + part * WR, col0 = n0 + wn * WC;
+            int el = lane;
+            if (TN != 4) asm volatile("" : "+v"(el));        // opaque: held through the loop above, the addresses would spill 11 registers
             if (EXE_GEMM_ABLATE & 32) {            // measurement variant: no epilogue, the accumulators are only kept alive
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < TN; ++i)
 #pragma unroll
                     for (int j = 0; j < TM; ++j) asm volatile("" ::"v"(acc[i][j]));
             } else if (n_split > 1)
-                epilogue_tiles<bf16_t, TM, 4, EN, EPI_PARTIAL>(acc, stg, lane, row0, col0, M, N, nullptr, 1.f, partial + (int64_t)z * M * N, nullptr);
+                epilogue_tiles<bf16_t, TM, TN, EN, EPI_PARTIAL>(acc, stg, el, row0, col0, M, N, nullptr, 1.f, partial + (int64_t)z * M * N, nullptr);
             else if (out_mode == OUT_RESID)
-                epilogue_tiles<bf16_t, TM, 4, EN, EPI_RESID>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+                epilogue_tiles<bf16_t, TM, TN, EN, EPI_RESID>(acc, stg, el, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (out_mode == OUT_F32)
-                epilogue_tiles<bf16_t, TM, 4, EN, EPI_F32>(acc, stg, lane, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
+                epilogue_tiles<bf16_t, TM, TN, EN, EPI_F32>(acc, stg, el, row0, col0, M, N, bias, alpha, (float*)out, nullptr);
             else if (kv.pool)
-                epilogue_rows<TM, EPI_T_KV>(acc, stg, lane, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide, kv);
+                epilogue_rows<TM, TN, EPI_T_KV, RJ>(acc, stg, el, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide, kv);
             else if (act == 0)
-                epilogue_rows<TM, EPI_T_RELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
+                epilogue_rows<TM, TN, EPI_T_RELU, RJ>(acc, stg, el, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
             else if (act == 1)
-                epilogue_rows<TM, EPI_T_GELU>(acc, stg, lane, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
+                epilogue_rows<TM, TN, EPI_T_GELU, RJ>(acc, stg, el, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
             else
-                epilogue_rows<TM, EPI_T>(acc, stg, lane, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
+                epilogue_rows<TM, TN, EPI_T, RJ>(acc, stg, el, row0, col0, M, N, bias, alpha, (bf16_t*)out, wide);
         }
     }
 #undef EXE_SB
     wait_vm<0>();     // the loads past the end land before the workgroup's LDS is released
 }
 
-template <int BM>
+template <int BM, int BN>
 static hipError_t launch_large(const GemmArgs& a, int k_per_split, int splits, int grid_max, hipStream_t s)
 {
-    auto kern = gemm_large_kernel<BM>;
-    constexpr int lds = large_lds(BM);
+    auto kern = gemm_large_kernel<BM, BN>;
+    constexpr int lds = large_lds(BM, BN);
     static_assert(lds <= 160 * 1024, "LDS budget");
     static LdsLimit limit[MAX_DEVICES];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) dev = 0;
     hipError_t e = limit[dev].raise((const void*)kern, lds);
     if (e != hipSuccess) return e;
-    int tm = (a.M + BM - 1) / BM, tn = (a.N + LARGE_BN - 1) / LARGE_BN, items = tm * tn * splits;
+    int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN, items = tm * tn * splits;
     int wide = a.N % 8 == 0 && ((uintptr_t)a.out & 15) == 0 ? (int64_t)a.M * a.N * 2 >= NT_BYTES ? 3 : 1 : 0;
     kern<<<items < grid_max ? items : grid_max, LARGE_THREADS, lds, s>>>(
         a.M, a.N, a.K, (const bf16_t*)a.A, (const bf16_t*)a.W, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out, a.workspace, tm,
@@ -346,11 +369,13 @@ static hipError_t launch_large(const GemmArgs& a, int k_per_split, int splits, i
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_large(const GemmArgs& a, int bm, int k_per_split, int splits, int grid_max, hipStream_t s)
+hipError_t launch_gemm_large(const GemmArgs& a, int bm, int bn, int k_per_split, int splits, int grid_max, hipStream_t s)
 {
-    return bm == 256 ? launch_large<256>(a, k_per_split, splits, grid_max, s)
-         : bm == 192 ? launch_large<192>(a, k_per_split, splits, grid_max, s)
-                     : launch_large<128>(a, k_per_split, splits, grid_max, s);
+    return bn == 128 ? launch_large<256, 128>(a, k_per_split, splits, grid_max, s)
+         : bn == 160 ? launch_large<256, 160>(a, k_per_split, splits, grid_max, s)
+         : bm == 256 ? launch_large<256, 256>(a, k_per_split, splits, grid_max, s)
+         : bm == 192 ? launch_large<192, 256>(a, k_per_split, splits, grid_max, s)
+                     : launch_large<128, 256>(a, k_per_split, splits, grid_max, s);
 }
 
 }  // namespace exe

@@ -64,6 +64,16 @@ def test_every_configuration_with_uneven_parts(cfg, M, N, k_tiles, splits, mode)
     check(M, N, 64 * k_tiles, cfg, splits, mode, splits * M * N)
 
 
+# the forms of the large kernel that are 128 and 160 features wide (5, 8): rows and features at the edges of tiles, of waves (64
+# rows; 64 and 80 features) and of the 8 features that a lane stores, depths of 4 k-tiles and more
+@pytest.mark.parametrize("cfg", [5, 8])
+@pytest.mark.parametrize("M,N,K,splits", [(1, 4, 256, 1), (64, 80, 256, 1), (255, 156, 320, 1), (256, 164, 576, 2), (257, 320, 1024, 3),
+                                          (321, 84, 256, 1), (513, 644, 512, 2), (1500, 5120, 256, 1)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_narrow_forms_of_the_large_kernel(cfg, M, N, K, splits, mode):
+    check(M, N, K, cfg, splits, mode, splits * M * N if splits > 1 else 0)
+
+
 @pytest.mark.parametrize("cfg,splits", [(1, 3), (2, 2), (6, 3), (5, 2)])
 def test_partial_sums_left_for_the_next_norm(cfg, splits):
     M, N, K = 1100, 516, 64 * 21

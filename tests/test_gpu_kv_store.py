@@ -90,3 +90,21 @@ def test_a_launch_cut_twice(rows, heads):
     for i in range(4):
         assert np.array_equal(got[0][0][i], got[1][0][i]), i
     assert torch.equal(got[0][1], got[1][1])
+
+
+def test_tiles_whose_waves_straddle_heads():
+    """512 x 20352 features go in tiles of 256 x 160: waves of 80 features, one of which holds the last queries and the first keys
+    (20352 = 3 x 6784, 6784 = 84.8 x 80), and the last tile is not full.  A paged pool's entries are copied out of the output."""
+    rows, d = 512, 53 * 128
+    shape = wl.gpt3_175b_share_shape(1).replace(d_model=d, n_heads=53, d_ff=512)
+    w = wl.make_weights(shape, 5, device=DEV)
+    lens = np.array([200, 133, 1, 178], dtype=np.int32)
+    x = torch.randn((rows, d), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV).bfloat16()
+    got = []
+    for block in (0, 16):
+        m = model_of(shape, w, rows, 4, block)
+        out = torch.zeros((rows, d), dtype=torch.bfloat16, device=DEV)
+        m.encode(np.arange(4), lens, None, hidden_in=x, want_tokens=False, out_device=out)
+        got.append([m.seq_export(i)[0] for i in range(4)] + [out.cpu().view(torch.int16).numpy()])
+        m.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
