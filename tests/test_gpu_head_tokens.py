@@ -49,3 +49,28 @@ def test_tokens_are_the_argmax_of_the_logits(n, vocab, dtype, kind):
     for t in range(2):
         check(m.decode_step(np.arange(n), rng.integers(0, used, size=n).astype(np.int32), lens + t + 1, out_device=out))
     m.close()
+
+
+@pytest.mark.parametrize("vocab,n", [(2048, 4), (1028, 15), (2048, 12), (32000, 5)])
+def test_outputs_are_complete_on_return(vocab, n):
+    """A call that returns tokens waits for them, not for its stream: another stream that reads the logits right behind it, and the
+    host, find all of them (entries of the LM head's workgroups, and argmax_kernel)."""
+    shape = wl.tiny_shape().replace(n_layers=1, vocab=vocab, max_pos=512)
+    w = [t.to(DEV) for t in wl.make_weights(shape, 3)]
+    cfg = exe.config_from_shape(shape, kv_pool_bytes=16384 * kv_bytes_per_token(shape), max_seqs=16, max_batch_tokens=256, max_batch_seqs=16)
+    m = exe.Model(cfg, w, stream=torch.cuda.Stream())
+    other = torch.cuda.Stream()
+    rng = np.random.default_rng(n)
+    lens = rng.integers(1, 8, size=n).astype(np.int32)
+    out = torch.empty((n, vocab), dtype=torch.float32, device=DEV)
+    m.encode(np.arange(n), lens, rng.integers(0, vocab, size=int(lens.sum())).astype(np.int32), reserve_lengths=lens + 100)
+    for t in range(100):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        tokens = m.decode_step(np.arange(n), rng.integers(0, vocab, size=n).astype(np.int32), lens + t + 1, out_device=out)
+        with torch.cuda.stream(other):
+            seen = out.clone()
+        assert np.array_equal(tokens, seen.cpu().numpy().argmax(axis=1)), t
+        torch.cuda.synchronize()
+        assert torch.equal(seen, out), t
+    m.close()
