@@ -646,12 +646,22 @@ static int head_launches(exe_model* m, const int32_t* row_index_dev, int n, floa
     return EXE_OK;
 }
 
-// A call that returns tokens waits for them, in pinned memory, instead of for the stream: they are the last thing that its last
+// A short call that returns tokens waits for them, in pinned memory, instead of for the stream: they are the last thing that its last
 // launch writes, behind the logits (argmax_kernel's come from a launch in front), so what is left of the call by then is the end of that
 // launch.  A word there is seen 5 us before hipStreamSynchronize returns (four launches of 30 us in all: 40.9 and 45.7; asked for
 // behind the word, it takes 11 more).  17 calls of 4 rows, two float layers 931 -> 873 us, 97 of 48 rows, six bf16 layers 35.8 -> 33.8 ms.
-// Calls of more than TOKENS_SPIN_US wait for the stream from then on, which also reports what may have gone wrong on it.
-constexpr int TOKENS_SPIN_US = 2000;
+// Calls that should take SHORT_CALL and more leave the processor to others and wait for the stream.  (Looking for the tokens for 2 ms
+// and waiting for the stream from then on made a call of 40 OPT-13B layers, one row, 1 to 2 % slower: 5.04 -> 5.12 ms.)
+constexpr double SHORT_CALL = 2e-3;
+constexpr int TOKENS_SPIN_US = 20000;        // then for the stream, which also reports what may have gone wrong on it
+// Seconds of a call of T rows, about: the weights' bytes or operations, the cached rows' bytes (one layer's), the launches.
+static double call_seconds(const exe_model* m, double T, double kv_bytes)
+{
+    const exe_config_t& c = m->c;
+    const double layers = (double)std::max(m->enc.size(), m->dec.size()), d = c.d_model;
+    const double weights = layers * (4 * d * m->inner + 2 * d * c.d_ff) + d * c.vocab;
+    return std::max(weights * m->esz / 6e12, 2 * weights * T / (c.dtype == EXE_DTYPE_F32 ? 1.5e14 : 1e15)) + layers * (kv_bytes / 6e12 + 20e-6);
+}
 constexpr int32_t NO_TOKEN = -1;
 static int32_t* token_word(const exe_model* m, int n, int i)      // the i-th word to wait for: the tokens, or the entries' indices
 {
@@ -669,8 +679,9 @@ static bool tokens_arrive(const exe_model* m, int n)
     return true;
 }
 
-// head, with the logits straight to out_device where its alignment allows the kernels' stores; returns when all of the call's work is done
-static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* next_tokens, void* out_device)
+// head, with the logits straight to out_device where its alignment allows the kernels' stores; returns when all of the call's work is
+// done.  seconds: what the call should take (call_seconds)
+static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* next_tokens, void* out_device, double seconds)
 {
     const exe_config_t& c = m->c;
     bool direct = out_device && ((uintptr_t)out_device & 15) == 0;
@@ -684,7 +695,7 @@ static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* 
     if (r) return r;
     if (out_device && !direct)
         HIP_TRY(hipMemcpyAsync(out_device, m->logits, (size_t)n * c.vocab * 4, hipMemcpyDeviceToDevice, m->stream));
-    if (!next_tokens || (out_device && !direct) || !tokens_arrive(m, n)) HIP_TRY(hipStreamSynchronize(m->stream));
+    if (!next_tokens || seconds >= SHORT_CALL || (out_device && !direct) || !tokens_arrive(m, n)) HIP_TRY(hipStreamSynchronize(m->stream));
     if (next_tokens) finish_tokens(m, n, next_tokens);
     return EXE_OK;
 }
@@ -984,7 +995,7 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
             HIP_TRY(hipStreamSynchronize(m->stream));
             return EXE_OK;
         }
-        if (c.has_lm_head) return run_head(m, d.last, n, next_tokens, out_device);
+        if (c.has_lm_head) return run_head(m, d.last, n, next_tokens, out_device, call_seconds(m, T, 0));
         if ((r = finish_resid(m))) return r;
         if (out_device)
             LAUNCH(m, EXE_K_OTHER, (double)T * c.d_model * (esz_of(m) + 4.0), 0.0,
@@ -1278,7 +1289,7 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
     }
     double e = esz_of(m);
     if (c.has_lm_head) {
-        if ((r = run_head(m, nullptr, n, next_tokens, out_device))) return r;
+        if ((r = run_head(m, nullptr, n, next_tokens, out_device, call_seconds(m, n, dd.self_bytes + dd.x_bytes)))) return r;
     } else {
         if ((r = finish_resid(m))) return r;
         if (out_device)
