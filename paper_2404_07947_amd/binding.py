@@ -346,7 +346,7 @@ def exe_op_gemm(dtype, M, N, K, A, W, bias, act, alpha, out_mode, out, workspace
                              _dev(out), _dev(workspace), ws_bytes))
 
 
-GEMM_CFG_NAMES = ["64x256", "128x256", "256x256", "64x128", "128x128", "256x128", "192x256", "64x64"]
+GEMM_CFG_NAMES = ["64x256", "128x256", "256x256", "64x128", "128x128", "256x128", "192x256", "64x64", "256x160"]
 
 
 def exe_op_gemm_plan(dtype: int, M: int, N: int, K: int) -> dict:

@@ -3,7 +3,7 @@
 //  * gemm_tile_kernel    MFMA 16x16x32, bf16.  Macro tiles (BM x 256 or BM x 128, 128 bytes of K
 //                        per LDS stage) filled by direct global->LDS loads into a ring of stages; software-pipelined
 //                        fragment fetch; optional split-K into float partials, finished by splitk_reduce_kernel.
-//  * gemm_large_kernel   (kernels_gemm_large.hip) bf16, tiles 256 features wide and 128 rows or more, K of 256 and more: encode,
+//  * gemm_large_kernel   (kernels_gemm_large.hip) bf16, tiles of 128 rows and 128 features or more, K of 256 and more: encode,
 //                        and decode batches of 100 rows and more.
 //  * gemm_f32_kernel     (kernels_gemm_f32.hip) float, many rows.
 //  * gemm_stream_kernel  (kernels_gemm_stream.hip) few rows: streams the weights, the waves of a workgroup split K.

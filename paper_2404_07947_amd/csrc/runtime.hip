@@ -617,6 +617,8 @@ static float attn_scale(const exe_model* m)
 // layers of 256 with argmax_kernel and so, by entries: 256 57.6 and 55.9, 512 58.3 and 56.7, 1024 61.7 and 60.1 (8 rows x 2048),
 // 1536 64.8 and 63.7, 2048 66.9 and 66.2, 3072 65.8 and 65.8, 4096 67.9 and 68.8.  The limit keeps what it takes of the host below a
 // microsecond; up to 2048 entries it gives away 0.7 to 1.1 us a call.
+// whether the LM head of n rows may leave its entries, each of 16 rows, in h_top
+static bool top_entries(const exe_model* m, int n) { return m->h_top && n <= 16 && n * ((m->c.vocab + 15) / 16) <= TOP_MAX; }
 static void finish_tokens(const exe_model* m, int n, int32_t* out)
 {
     if (!m->top_wgs) {
@@ -641,7 +643,7 @@ static int head_launches(exe_model* m, const int32_t* row_index_dev, int n, floa
     float out_scale = c.arch == EXE_ARCH_ENC_DEC ? 1.f / sqrtf((float)c.d_model) : 1.f;
     m->top_wgs = 0;
     if ((r = run_norm_gemm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last, c.vocab, m->tok_emb, nullptr, -1, OUT_F32, logits,
-                           nullptr, nullptr, true, tokens && m->h_top && (int64_t)n * ((c.vocab + 15) / 16) <= TOP_MAX))) return r;
+                           nullptr, nullptr, true, tokens && top_entries(m, n)))) return r;
     if (tokens && !m->top_wgs) LAUNCH(m, EXE_K_OTHER, (double)n * c.vocab * 4.0, 0.0, launch_argmax(logits, n, c.vocab, m->h_next, m->stream));
     return EXE_OK;
 }
@@ -687,7 +689,7 @@ static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* 
     bool direct = out_device && ((uintptr_t)out_device & 15) == 0;
     if (next_tokens) {
         std::fill(m->h_next, m->h_next + n, NO_TOKEN);
-        if (m->h_top && (int64_t)n * ((c.vocab + 15) / 16) <= TOP_MAX)
+        if (top_entries(m, n))
             for (int w = 0; w < (c.vocab + 15) / 16; ++w)
                 for (int i = 0; i < n; ++i) m->h_top[w * 16 + i].index = NO_TOKEN;
     }
