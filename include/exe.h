@@ -15,8 +15,8 @@
  *    input; exe_last_error() returns a thread-local description of the last failure.
  *  - "host" pointers are ordinary CPU memory read/written before the call returns.  "device" pointers
  *    are HIP device memory on the current device, owned by the caller.
- *  - Calls are synchronous: when they return, all of their work is done, host outputs are filled and device outputs are complete,
- *    for the host and for every stream.  (A call that returns tokens may do so before the stream reports its last launch as ended.)
+ *  - Calls are synchronous: when they return, host outputs are filled and device outputs are complete
+ *    on the model's stream (the stream has been synchronised).
  *  - A model handle is not thread-safe; use one handle per thread.
  *  - Linear weights are [out_features, in_features] row-major in the model's dtype.  The fused QKV
  *    weight's rows are [all query heads | all key heads | all value heads], head-major.

@@ -285,25 +285,13 @@ __device__ __forceinline__ void stream_body(
         for (int w = 1; w < NW; ++w) v += red[(w * NT * MT + x) * 64 + lane];
         int m = m0 + (x % MT) * 16 + fr, n = n0 + (x / MT) * 16 + 4 * g;
         if (NORM && norm.top) {                      // uniform
-            // The host takes the row's results once it sees this entry, so the logits have left for memory, past the caches, before it.
             float best = -INFINITY;
             int idx = 0x7fffffff;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (n + j < N) argmax_take(best, idx, v[j], n + j);
-            if (m < M && n < N && !(MA == 1 && fr >= 8)) {
-                uint64_t* o = (uint64_t*)((float*)out + (int64_t)m * N + n);
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    __hip_atomic_store(o + j, (uint64_t)__float_as_uint(v[2 * j]) | (uint64_t)__float_as_uint(v[2 * j + 1]) << 32, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_SYSTEM);
-            }
             argmax_column(best, idx);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (g == 0 && m < M)
-                __hip_atomic_store((uint64_t*)&norm.top[blockIdx.x * 16 + fr], (uint64_t)__float_as_uint(best) | (uint64_t)(unsigned)idx << 32,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            continue;
+            if (g == 0 && m < M) norm.top[blockIdx.x * 16 + fr] = TopLogit{best, idx};
         }
         if (m >= M || n >= N || (MA == 1 && fr >= 8)) continue;
         if (n_split > 1) *(f32x4*)(partial + ((int64_t)z * M + m) * N + n) = v;

@@ -612,13 +612,11 @@ static float attn_scale(const exe_model* m)
 }
 
 // Where the LM head of few rows takes the norm with it, its workgroups leave the largest logit of each row and 16 features in
-// pinned memory, and the host goes through those once all are there (see tokens_arrive), up to TOP_MAX of them, in place
+// pinned memory, and the host goes through those after the synchronisation that it waits in anyway, up to TOP_MAX of them, in place
 // of argmax_kernel's launch: 17 calls of 4 rows x 2048 logits 1058 -> 1039 us, 21 of 12 x 1024 1799 -> 1676.  us a call of two float
 // layers of 256 with argmax_kernel and so, by entries: 256 57.6 and 55.9, 512 58.3 and 56.7, 1024 61.7 and 60.1 (8 rows x 2048),
 // 1536 64.8 and 63.7, 2048 66.9 and 66.2, 3072 65.8 and 65.8, 4096 67.9 and 68.8.  The limit keeps what it takes of the host below a
 // microsecond; up to 2048 entries it gives away 0.7 to 1.1 us a call.
-// whether the LM head of n rows may leave its entries, each of 16 rows, in h_top
-static bool top_entries(const exe_model* m, int n) { return m->h_top && n <= 16 && n * ((m->c.vocab + 15) / 16) <= TOP_MAX; }
 static void finish_tokens(const exe_model* m, int n, int32_t* out)
 {
     if (!m->top_wgs) {
@@ -643,61 +641,21 @@ static int head_launches(exe_model* m, const int32_t* row_index_dev, int n, floa
     float out_scale = c.arch == EXE_ARCH_ENC_DEC ? 1.f / sqrtf((float)c.d_model) : 1.f;
     m->top_wgs = 0;
     if ((r = run_norm_gemm(m, row_index_dev, n, m->fin_g, m->fin_b, out_scale, m->a_last, c.vocab, m->tok_emb, nullptr, -1, OUT_F32, logits,
-                           nullptr, nullptr, true, tokens && top_entries(m, n)))) return r;
+                           nullptr, nullptr, true, tokens && m->h_top && (int64_t)n * ((c.vocab + 15) / 16) <= TOP_MAX))) return r;
     if (tokens && !m->top_wgs) LAUNCH(m, EXE_K_OTHER, (double)n * c.vocab * 4.0, 0.0, launch_argmax(logits, n, c.vocab, m->h_next, m->stream));
     return EXE_OK;
 }
 
-// A short call that returns tokens waits for them, in pinned memory, instead of for the stream: they are the last thing that its last
-// launch writes, behind the logits (argmax_kernel's come from a launch in front), so what is left of the call by then is the end of that
-// launch.  A word there is seen 5 us before hipStreamSynchronize returns (four launches of 30 us in all: 40.9 and 45.7; asked for
-// behind the word, it takes 11 more).  17 calls of 4 rows, two float layers 931 -> 873 us, 97 of 48 rows, six bf16 layers 35.8 -> 33.8 ms.
-// Calls that should take SHORT_CALL and more leave the processor to others and wait for the stream.  (Looking for the tokens for 2 ms
-// and waiting for the stream from then on made a call of 40 OPT-13B layers, one row, 1 to 2 % slower: 5.04 -> 5.12 ms.)
-constexpr double SHORT_CALL = 2e-3;
-constexpr int TOKENS_SPIN_US = 20000;        // then for the stream, which also reports what may have gone wrong on it
-// Seconds of a call of T rows, about: the weights' bytes or operations, the cached rows' bytes (one layer's), the launches.
-static double call_seconds(const exe_model* m, double T, double kv_bytes)
-{
-    const exe_config_t& c = m->c;
-    const double layers = (double)std::max(m->enc.size(), m->dec.size()), d = c.d_model;
-    const double weights = layers * (4 * d * m->inner + 2 * d * c.d_ff) + d * c.vocab;
-    return std::max(weights * m->esz / 6e12, 2 * weights * T / (c.dtype == EXE_DTYPE_F32 ? 1.5e14 : 1e15)) + layers * (kv_bytes / 6e12 + 20e-6);
-}
-constexpr int32_t NO_TOKEN = -1;
-static int32_t* token_word(const exe_model* m, int n, int i)      // the i-th word to wait for: the tokens, or the entries' indices
-{
-    return m->top_wgs ? &m->h_top[i / n * 16 + i % n].index : m->h_next + i;
-}
-static int token_words(const exe_model* m, int n) { return m->top_wgs ? m->top_wgs * n : n; }
-static bool tokens_arrive(const exe_model* m, int n)
-{
-    const auto start = std::chrono::steady_clock::now();
-    const int total = token_words(m, n);
-    unsigned polls = 0;
-    for (int i = 0; i < total; ++i)
-        while (__atomic_load_n(token_word(m, n, i), __ATOMIC_ACQUIRE) == NO_TOKEN)
-            if ((++polls & 255) == 0 && std::chrono::steady_clock::now() - start > std::chrono::microseconds(TOKENS_SPIN_US)) return false;
-    return true;
-}
-
-// head, with the logits straight to out_device where its alignment allows the kernels' stores; returns when all of the call's work is
-// done.  seconds: what the call should take (call_seconds)
-static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* next_tokens, void* out_device, double seconds)
+// head, with the logits straight to out_device where its alignment allows the kernels' stores; synchronises the stream
+static int run_head(exe_model* m, const int32_t* row_index_dev, int n, int32_t* next_tokens, void* out_device)
 {
     const exe_config_t& c = m->c;
     bool direct = out_device && ((uintptr_t)out_device & 15) == 0;
-    if (next_tokens) {
-        std::fill(m->h_next, m->h_next + n, NO_TOKEN);
-        if (top_entries(m, n))
-            for (int w = 0; w < (c.vocab + 15) / 16; ++w)
-                for (int i = 0; i < n; ++i) m->h_top[w * 16 + i].index = NO_TOKEN;
-    }
     int r = head_launches(m, row_index_dev, n, direct ? (float*)out_device : m->logits, next_tokens != nullptr);
     if (r) return r;
     if (out_device && !direct)
         HIP_TRY(hipMemcpyAsync(out_device, m->logits, (size_t)n * c.vocab * 4, hipMemcpyDeviceToDevice, m->stream));
-    if (!next_tokens || seconds >= SHORT_CALL || (out_device && !direct) || !tokens_arrive(m, n)) HIP_TRY(hipStreamSynchronize(m->stream));
+    HIP_TRY(hipStreamSynchronize(m->stream));
     if (next_tokens) finish_tokens(m, n, next_tokens);
     return EXE_OK;
 }
@@ -997,7 +955,7 @@ extern "C" int exe_encode(exe_model_t* m, int32_t n, const int32_t* seq_ids, con
             HIP_TRY(hipStreamSynchronize(m->stream));
             return EXE_OK;
         }
-        if (c.has_lm_head) return run_head(m, d.last, n, next_tokens, out_device, call_seconds(m, T, 0));
+        if (c.has_lm_head) return run_head(m, d.last, n, next_tokens, out_device);
         if ((r = finish_resid(m))) return r;
         if (out_device)
             LAUNCH(m, EXE_K_OTHER, (double)T * c.d_model * (esz_of(m) + 4.0), 0.0,
@@ -1291,7 +1249,7 @@ extern "C" int exe_decode_step(exe_model_t* m, int32_t n, const int32_t* seq_ids
     }
     double e = esz_of(m);
     if (c.has_lm_head) {
-        if ((r = run_head(m, nullptr, n, next_tokens, out_device, call_seconds(m, n, dd.self_bytes + dd.x_bytes)))) return r;
+        if ((r = run_head(m, nullptr, n, next_tokens, out_device))) return r;
     } else {
         if ((r = finish_resid(m))) return r;
         if (out_device)

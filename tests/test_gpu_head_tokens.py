@@ -53,24 +53,45 @@ def test_tokens_are_the_argmax_of_the_logits(n, vocab, dtype, kind):
 
 @pytest.mark.parametrize("vocab,n", [(2048, 4), (1028, 15), (2048, 12), (32000, 5)])
 def test_outputs_are_complete_on_return(vocab, n):
-    """A call that returns tokens waits for them, not for its stream: another stream that reads the logits right behind it, and the
-    host, find all of them (entries of the LM head's workgroups, and argmax_kernel)."""
+    """When a call that returns tokens is back, its stream is idle, and another stream that reads the logits right behind it finds
+    all of them (entries of the LM head's workgroups, and argmax_kernel)."""
     shape = wl.tiny_shape().replace(n_layers=1, vocab=vocab, max_pos=512)
     w = [t.to(DEV) for t in wl.make_weights(shape, 3)]
     cfg = exe.config_from_shape(shape, kv_pool_bytes=16384 * kv_bytes_per_token(shape), max_seqs=16, max_batch_tokens=256, max_batch_seqs=16)
-    m = exe.Model(cfg, w, stream=torch.cuda.Stream())
-    other = torch.cuda.Stream()
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    m = exe.Model(cfg, w, stream=stream)
     rng = np.random.default_rng(n)
     lens = rng.integers(1, 8, size=n).astype(np.int32)
     out = torch.empty((n, vocab), dtype=torch.float32, device=DEV)
     m.encode(np.arange(n), lens, rng.integers(0, vocab, size=int(lens.sum())).astype(np.int32), reserve_lengths=lens + 100)
+    assert stream.query(), "busy behind encode"
     for t in range(100):
         out.fill_(float("nan"))
         torch.cuda.synchronize()
         tokens = m.decode_step(np.arange(n), rng.integers(0, vocab, size=n).astype(np.int32), lens + t + 1, out_device=out)
+        idle = stream.query()
         with torch.cuda.stream(other):
-            seen = out.clone()
-        assert np.array_equal(tokens, seen.cpu().numpy().argmax(axis=1)), t
+            seen = out.clone().cpu()                       # on `other`, which the copy to the host waits for
+        assert idle, t
+        assert np.array_equal(tokens, seen.numpy().argmax(axis=1)), t
         torch.cuda.synchronize()
-        assert torch.equal(seen, out), t
+        assert torch.equal(seen, out.cpu()), t
+    m.close()
+
+
+def test_many_short_calls():
+    """Calls right behind one another, with no other synchronisation between them: every call's tokens are the argmax of its own logits."""
+    shape = wl.tiny_shape().replace(n_layers=1, vocab=2048, max_pos=512)
+    w = [t.to(DEV) for t in wl.make_weights(shape, 3)]
+    n, calls = 4, 400
+    cfg = exe.config_from_shape(shape, kv_pool_bytes=16384 * kv_bytes_per_token(shape), max_seqs=16, max_batch_tokens=256, max_batch_seqs=16)
+    m = exe.Model(cfg, w, stream=torch.cuda.Stream())
+    rng = np.random.default_rng(n)
+    lens = np.full(n, 5, dtype=np.int32)
+    fed = rng.integers(0, shape.vocab, size=(calls, n)).astype(np.int32)
+    out = torch.full((calls, n, shape.vocab), float("nan"), device=DEV)
+    torch.cuda.synchronize()
+    m.encode(np.arange(n), lens, rng.integers(0, shape.vocab, size=5 * n).astype(np.int32), reserve_lengths=lens + calls)
+    tokens = [m.decode_step(np.arange(n), fed[t], lens + t + 1, out_device=out[t]) for t in range(calls)]
+    assert np.array_equal(np.stack(tokens), out.cpu().numpy().argmax(axis=2))
     m.close()
