@@ -12,6 +12,7 @@
 // Both A and W are K-contiguous, so both MFMA operands are 16-byte vectors along K.  The MFMA "A" operand
 // is fed with weight rows and the "B" operand with activation rows: the accumulator then holds 4
 // consecutive output features per lane, which makes the epilogue's loads and stores 8/16-byte vectors.
+#include <algorithm>
 #include <stdlib.h>
 
 #include <mutex>
@@ -320,33 +321,32 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_tile_kernel(
 // Sums the split-K partials in split order (deterministic) and applies the epilogue.  (A reduction fused
 // into the GEMM through arrival counters was measured 3x slower: the device-scope fences it needs write
 // back and invalidate the L2 for every workgroup.)
-// What bounds it: the partial sums, read once, most of them from cache.  A workgroup takes REDUCE_COLS columns of a row, a row per grid
-// row, a thread 4 of them with three parts in flight: one index over all elements cost each thread a division by N in 64 bits (with
-// the product in front: 100 x 3072, K 1024 in 4 parts 12.3 -> 11.5 us, 128 x 15360, K 5120 in 4 46.0 -> 44.0, 256 rows in 2 58.3 -> 58.4).
-// Two groups of 4 a thread, or nontemporal loads, took 1 to 4 % of that time more.
-constexpr int REDUCE_COLS = 1024;
+// What bounds it: the partial sums, read once, most of them from cache.  One index over the rows' groups of 4 columns, of 32 bits: its division by
+// the row's groups runs under the loads, three parts of which are in flight.  us of this kernel with an index of 64 bits, with a row per grid row (in
+// workgroups of 1024 columns) and so: 4096 x 1028 in 4 parts 13.5, 19.7, 12.6, 4096 x 3076 in 2 21.7, 24.9, 20.8, 512 x 5120 in 3 5.7, 5.4, 5.3, 1000 x 3072 in
+// 2 4.5, 4.5, 4.5; a wave per 256 columns of a row is between them.  Two groups a thread, or nontemporal loads, took 1 to 4 % more with the product in front.
+constexpr int REDUCE_THREADS = 256;
+constexpr int64_t REDUCE_QUADS = (int64_t)1 << 31;       // of a launch
 template <typename T>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S, const float* __restrict__ partial,
-                                                            const T* __restrict__ bias, int act, float alpha, int out_mode,
-                                                            void* __restrict__ out)
+__global__ __launch_bounds__(REDUCE_THREADS) void splitk_reduce_kernel(unsigned quads, unsigned row_quads, int64_t slice, int S, const float* __restrict__ partial,
+                                                                       const T* __restrict__ bias, int act, float alpha, int out_mode,
+                                                                       void* __restrict__ out)
 {
-    const int64_t slice = (int64_t)M * N;
-    const int n = blockIdx.x * REDUCE_COLS + threadIdx.x * 4;
-    if (n >= N) return;
-    for (int m = blockIdx.y; m < M; m += gridDim.y) {
-        const float* p = partial + (int64_t)m * N + n;
-        f32x4 v = *(const f32x4*)p;
-        int s = 1;
-        for (; s + 3 <= S; s += 3) {
-            f32x4 t[3];
+    const unsigned q = blockIdx.x * REDUCE_THREADS + threadIdx.x;
+    if (q >= quads) return;
+    const float* p = partial + (int64_t)q * 4;
+    f32x4 v = *(const f32x4*)p;
+    for (int s = 1; s < S; s += 3) {
+        f32x4 t[3];
 #pragma unroll
-            for (int j = 0; j < 3; ++j) t[j] = *(const f32x4*)(p + (s + j) * slice);
+        for (int j = 0; j < 3; ++j)
+            if (s + j < S) t[j] = *(const f32x4*)(p + (s + j) * slice);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) v += t[j];
-        }
-        for (; s < S; ++s) v += *(const f32x4*)(p + s * slice);
-        epilogue_store4<T>(v, m, n, N, bias, act, alpha, out_mode, out);
+        for (int j = 0; j < 3; ++j)
+            if (s + j < S) v += t[j];
     }
+    const unsigned m = q / row_quads;
+    epilogue_store4<T>(v, (int)m, (int)(q - m * row_quads) * 4, (int)row_quads * 4, bias, act, alpha, out_mode, out);
 }
 
 // ---------------------------------------------------------------- generic kernel (float math, any shape)
@@ -693,14 +693,26 @@ size_t gemm_workspace_bytes(int dtype, int M, int N, int K, int mode)
     return p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
 }
 
+template <typename T>
+static void reduce_rows(const GemmArgs& a, int splits, int64_t first, int rows, hipStream_t s)
+{
+    const unsigned quads = (unsigned)((int64_t)rows * (a.N / 4));
+    void* out = (char*)a.out + first * a.N * (a.out_mode == OUT_T ? sizeof(T) : sizeof(float));
+    splitk_reduce_kernel<T><<<(quads + REDUCE_THREADS - 1) / REDUCE_THREADS, REDUCE_THREADS, 0, s>>>(
+        quads, a.N / 4, (int64_t)a.M * a.N, splits, a.workspace + first * a.N, (const T*)a.bias, a.act, a.alpha, a.out_mode, out);
+}
+
 hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s)
 {
-    const dim3 grid((a.N + REDUCE_COLS - 1) / REDUCE_COLS, a.M < 65535 ? a.M : 65535);
-    if (a.dtype == DT_F32)
-        splitk_reduce_kernel<float><<<grid, 256, 0, s>>>(a.M, a.N, splits, a.workspace, (const float*)a.bias, a.act, a.alpha, a.out_mode, a.out);
-    else
-        splitk_reduce_kernel<bf16_t><<<grid, 256, 0, s>>>(a.M, a.N, splits, a.workspace, (const bf16_t*)a.bias, a.act, a.alpha, a.out_mode, a.out);
-    return hipGetLastError();
+    const int most = (int)std::min<int64_t>(a.M, REDUCE_QUADS / (a.N / 4));
+    for (int64_t first = 0; first < a.M; first += most) {
+        const int rows = (int)std::min<int64_t>(most, a.M - first);
+        if (a.dtype == DT_F32) reduce_rows<float>(a, splits, first, rows, s);
+        else reduce_rows<bf16_t>(a, splits, first, rows, s);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int ST>

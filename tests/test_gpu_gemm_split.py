@@ -74,6 +74,15 @@ def test_narrow_forms_of_the_large_kernel(cfg, M, N, K, splits, mode):
     check(M, N, K, cfg, splits, mode, splits * M * N if splits > 1 else 0)
 
 
+# the reduction: rows of one group of 4 columns, of a group more than its workgroups' threads, and others that end inside one; 2 to 8
+# parts, three of which it adds at a time
+@pytest.mark.parametrize("M,N", [(1, 4), (257, 4), (65, 260), (33, 1028), (70, 3076)])
+@pytest.mark.parametrize("splits", range(2, 9))
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_reduction_of_the_parts(M, N, splits, mode):
+    check(M, N, 64 * 4 * splits, 4, splits, mode, splits * M * N)
+
+
 @pytest.mark.parametrize("cfg,splits", [(1, 3), (2, 2), (6, 3), (5, 2)])
 def test_partial_sums_left_for_the_next_norm(cfg, splits):
     M, N, K = 1100, 516, 64 * 21
