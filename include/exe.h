@@ -317,6 +317,11 @@ int exe_op_gemm_model(void* hip_stream, int32_t dtype, int32_t M, int32_t N, int
  * beyond whole rounds of 256 x 256 tiles go to a second, separately planned launch: ask again with M - *rows_first). */
 int exe_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t* route, int32_t* cfg, int32_t* splits,
                      int32_t* rows_first);
+/* How exe_op_gemm_model launches a shape, with its cfg and splits, where the workspace holds what is planned (host function; defer: as with
+ * its pending): *n_launches in the order of their rows, and of the first `cap` of them five numbers each in plans: rows, route, tile
+ * configuration and split-K parts as exe_op_gemm_plan has them, and 1 if the large-tile kernel runs (bf16). */
+int exe_op_gemm_model_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t cfg, int32_t splits, int32_t defer, int32_t cap,
+                           int32_t* plans, int32_t* n_launches);
 /* How the model calls launch a projection whose last features are keys and values (host function): *n_launches in the order
  * of their rows, of the first `cap` of them rows[i] and stores[i] = 1 if such a launch can store keys and values in the cache
  * itself; *kv_rows = the leading rows that an encode call counts on being stored so (it copies the others' keys and values). */

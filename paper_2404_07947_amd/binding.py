@@ -15,7 +15,7 @@ _call = None                                     # csrc/call.c
 DECLARED_SYMBOLS = [
     "exe_expected_weights", "exe_model_load", "exe_model_free", "exe_encode", "exe_decode_step",
     "exe_seq_release", "exe_seq_length", "exe_kv_stats", "exe_seq_export_bytes", "exe_seq_export", "exe_seq_import", "exe_seq_reserve", "exe_kv_compact", "exe_profile", "exe_run_rra", "exe_kernel_timing",
-    "exe_kernel_times", "exe_op_gemm", "exe_op_gemm_workspace", "exe_op_gemm_plan", "exe_op_gemm_kv_plan", "exe_op_kv_store_index", "exe_op_gemm_stream", "exe_op_gemm_model", "exe_op_gemm_ld", "exe_op_gemm_noalloc", "exe_op_gemm_noalloc_max_workspace", "exe_op_paged_index_check", "exe_op_norm", "exe_op_resid_norm", "exe_op_prefill_attention", "exe_op_prefill_tiles",
+    "exe_kernel_times", "exe_op_gemm", "exe_op_gemm_workspace", "exe_op_gemm_plan", "exe_op_gemm_model_plan", "exe_op_gemm_kv_plan", "exe_op_kv_store_index", "exe_op_gemm_stream", "exe_op_gemm_model", "exe_op_gemm_ld", "exe_op_gemm_noalloc", "exe_op_gemm_noalloc_max_workspace", "exe_op_paged_index_check", "exe_op_norm", "exe_op_resid_norm", "exe_op_prefill_attention", "exe_op_prefill_tiles",
     "exe_op_decode_attention", "exe_op_decode_attention_paged", "exe_probe_peaks", "exe_probe_ingest", "exe_op_argmax", "exe_rel_bucket", "exe_last_error", "exe_version",
     # exe_sched.h (host only)
     "exe_sim_completion", "exe_sim_step_ms", "exe_sim_rra", "exe_sim_waa", "exe_sched_search", "exe_sched_rra",
@@ -142,6 +142,7 @@ def lib():
     L.exe_op_gemm_workspace.argtypes = [i32, i32, i32, i32]
     L.exe_op_gemm_workspace.restype = C.c_uint64
     L.exe_op_gemm_plan.argtypes = [i32, i32, i32, i32, ip, ip, ip, ip]
+    L.exe_op_gemm_model_plan.argtypes = [i32, i32, i32, i32, i32, i32, i32, i32, ip, ip]
     L.exe_op_gemm_kv_plan.argtypes = [i32, i32, i32, i32, i32, ip, ip, ip, ip]
     L.exe_op_kv_store_index.argtypes, L.exe_op_kv_store_index.restype = [C.c_int64, i32, i32, i32, i32], C.c_int64
     L.exe_op_gemm_ld.argtypes = [vp, i32, i32, i32, i32, vp, i32, vp, i32, vp, i32, C.c_float, i32, vp, vp, C.c_uint64]
@@ -353,6 +354,14 @@ def exe_op_gemm_plan(dtype: int, M: int, N: int, K: int) -> dict:
     r, c, s, f = C.c_int32(), C.c_int32(), C.c_int32(), C.c_int32()
     _check(lib().exe_op_gemm_plan(dtype, M, N, K, C.byref(r), C.byref(c), C.byref(s), C.byref(f)))
     return {"route": r.value, "cfg": c.value, "splits": s.value, "rows_first": f.value}
+
+
+def exe_op_gemm_model_plan(dtype: int, M: int, N: int, K: int, cfg: int = -1, splits: int = 0, defer: bool = False) -> list:
+    """Every launch of exe_op_gemm_model, in the order of their rows."""
+    plans, n = (C.c_int32 * 320)(), C.c_int32()
+    _check(lib().exe_op_gemm_model_plan(dtype, M, N, K, cfg, splits, defer, 64, plans, C.byref(n)))
+    assert n.value <= 64
+    return [dict(zip(("rows", "route", "cfg", "splits", "large"), plans[5 * i:5 * i + 5])) for i in range(n.value)]
 
 
 def exe_op_gemm_kv_plan(dtype: int, M: int, N: int, K: int):

@@ -60,6 +60,8 @@ int gemm_kv_rows(const GemmArgs& a);
 // the launches of launch_gemm(a) in the order of their rows: how many there are, and of the first `cap` the rows and whether such a
 // launch can store through a.kv
 int gemm_launches(const GemmArgs& a, int cap, int32_t* rows, int32_t* stores);
+// and five numbers of each as exe_op_gemm_model_plan has them
+int gemm_launch_plans(const GemmArgs& a, bool defer, int cap, int32_t* plans);
 
 // The streaming kernel (kernels_gemm_stream.hip): nt * 16 output features of ma * 8 rows per workgroup, K in `splits` parts of
 // units_per_split units (128 bytes of a row each); nt = 0: a shape it does not take.  launch_gemm_stream leaves float

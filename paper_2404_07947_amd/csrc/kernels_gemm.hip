@@ -670,17 +670,21 @@ static int split_rows(int dtype, int M, int N, int K, int mode)
 // exe_op_gemm's mode: bf16 by the tile kernel alone
 static int op_mode(int dtype) { return dtype == DT_F32 ? GEMM_FEW_ROWS : GEMM_TILE_ONLY; }
 
+// the tile configuration that a plan's launch takes
+static int reported_cfg(int dtype, const Plan& p, int M, int N, int K)
+{
+    if (dtype != DT_F32 || p.route != 0) return p.cfg;
+    const int tiles[] = {C128x128, C64x128, F64x64};
+    double seconds;
+    return tiles[gemm_f32_tile(M, N, K, &seconds)];
+}
+
 void gemm_plan_info(int dtype, int M, int N, int K, int* route, int* cfg, int* splits, int* rows_first)
 {
     int M1 = split_rows(dtype, M, N, K, op_mode(dtype));
     Plan p = make_plan(dtype, M1, N, K, op_mode(dtype));
     *route = p.route;
-    *cfg = p.cfg;
-    if (dtype == DT_F32 && p.route == 0) {
-        const int tiles[] = {C128x128, C64x128, F64x64};
-        double seconds;
-        *cfg = tiles[gemm_f32_tile(M1, N, K, &seconds)];
-    }
+    *cfg = reported_cfg(dtype, p, M1, N, K);
     *splits = p.splits;
     *rows_first = M1;
 }
@@ -796,6 +800,34 @@ int gemm_launches(const GemmArgs& a, int cap, int32_t* rows, int32_t* stores)
     return n;
 }
 
+static Plan forced_plan(Plan p, int dtype, int K, int cfg, int splits)
+{
+    p.route = 0;
+    if (cfg >= 0) p.cfg = cfg;
+    p.splits = splits;
+    p.k_per_split = split_k_tiles(dtype, K, splits) * k_tile(dtype);
+    p.spread = 1;
+    return p;
+}
+
+int gemm_launch_plans(const GemmArgs& a, bool defer, int cap, int32_t* plans)
+{
+    const int mode = GEMM_FEW_ROWS | (defer ? GEMM_DEFER : 0);
+    int n = 0;
+    auto put = [&](int rows, const Plan& p) {
+        if (n < cap) {
+            const int32_t plan[] = {rows, p.route, reported_cfg(a.dtype, p, rows, a.N, a.K), p.splits, a.dtype == DT_BF16 && p.route == 0 && is_large(p.cfg) && a.K >= LARGE_MIN_K};
+            std::copy(plan, plan + 5, plans + 5 * n);
+        }
+        ++n;
+    };
+    if (a.force_splits) put(a.M, forced_plan(make_plan(a.dtype, a.M, a.N, a.K, mode), a.dtype, a.K, a.force_cfg, a.force_splits));
+    else each_launch(a.dtype, 0, a.M, a.N, a.K, mode, [&](int, int rows) {
+        put(rows, make_plan(a.dtype, rows, a.N, a.K, rows == a.M ? mode : mode & ~GEMM_DEFER));
+    });
+    return n;
+}
+
 static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s);
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
@@ -837,13 +869,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
 static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s)
 {
     Plan p = make_plan(a.dtype, a.M, a.N, a.K, mode);
-    if (a.force_splits) {
-        p.route = 0;
-        if (a.force_cfg >= 0) p.cfg = a.force_cfg;
-        p.splits = a.force_splits;
-        p.k_per_split = split_k_tiles(a.dtype, a.K, p.splits) * k_tile(a.dtype);
-        p.spread = 1;
-    }
+    if (a.force_splits) p = forced_plan(p, a.dtype, a.K, a.force_cfg, a.force_splits);
     if (needs_generic(a)) p.route = 2;
     if (p.route == 2) {
         dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);

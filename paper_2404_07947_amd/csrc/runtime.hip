@@ -2049,6 +2049,20 @@ extern "C" int exe_op_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, 
     return EXE_OK;
 }
 
+extern "C" int exe_op_gemm_model_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t cfg, int32_t splits, int32_t defer,
+                                      int32_t cap, int32_t* plans, int32_t* n_launches)
+{
+    if (M < 1 || N < 1 || K < 1 || cap < 0 || (cap > 0 && !plans) || !n_launches || splits < 0 || (splits == 0 && cfg != -1))
+        return fail(EXE_ERR_ARG, "bad gemm plan arguments");
+    if (splits && (dtype != DT_BF16 || !gemm_force_ok(cfg, splits, M, N, K)))
+        return fail(EXE_ERR_SHAPE, "shape not served in configuration %d with %d parts", cfg, splits);
+    GemmArgs g{dtype, M, N, K, nullptr, nullptr, nullptr, -1, 1.f, OUT_RESID, nullptr, nullptr, 0};
+    g.force_cfg = cfg;
+    g.force_splits = splits;
+    *n_launches = gemm_launch_plans(g, defer != 0, cap, plans);
+    return EXE_OK;
+}
+
 extern "C" int exe_op_gemm_kv_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t cap, int32_t* rows, int32_t* stores,
                                    int32_t* n_launches, int32_t* kv_rows)
 {

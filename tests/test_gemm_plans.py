@@ -75,6 +75,21 @@ def test_launches_that_the_cache_tests_run():
     assert exe.exe_op_gemm_kv_plan(BF16, 16385, 17664, 5888) == ([(16128, 1), (256, 0), (1, 0)], 16128)
 
 
+@pytest.mark.parametrize("dtype", [BF16, F32])
+def test_model_plans_are_the_launches(dtype):
+    """The rows of exe_op_gemm_model_plan are those of the launches that are made, and forced plans are what was asked for."""
+    for M, N, K in [(1, 1024, 1024), (300, 3072, 1024), (2049, 36864, 12288), (5377, 3072, 512), (16385, 17664, 5888)]:
+        plans = exe.exe_op_gemm_model_plan(dtype, M, N, K)
+        assert [p["rows"] for p in plans] == [r for r, _ in exe.exe_op_gemm_kv_plan(dtype, M, N, K)[0]]
+        assert [p["route"] == 0 and p["splits"] == 1 and (dtype == F32 or p["large"] == 1) for p in plans] == \
+            [bool(s) for _, s in exe.exe_op_gemm_kv_plan(dtype, M, N, K)[0]]
+    assert exe.exe_op_gemm_model_plan(BF16, 300, 1024, 1024, 8, 2) == [{"rows": 300, "route": 0, "cfg": 8, "splits": 2, "large": 1}]
+    assert exe.exe_op_gemm_model_plan(BF16, 300, 1024, 192, 5, 1) == [{"rows": 300, "route": 0, "cfg": 5, "splits": 1, "large": 0}]
+    for bad in ((BF16, 300, 1024, 1024, 7, 1), (BF16, 300, 1024, 192, 8, 1), (F32, 300, 1024, 1024, 2, 1)):
+        with pytest.raises(exe.ExeError):
+            exe.exe_op_gemm_model_plan(*bad)
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 def test_elements_of_a_head_beyond_32_bits(dh):
     """Extents are as long as the pool: 2^31 elements a head and more."""

@@ -92,11 +92,15 @@ def test_a_launch_cut_twice(rows, heads):
     assert torch.equal(got[0][1], got[1][1])
 
 
-def test_tiles_whose_waves_straddle_heads():
-    """512 x 20352 features go in tiles of 256 x 160: waves of 80 features, one of which holds the last queries and the first keys
-    (20352 = 3 x 6784, 6784 = 84.8 x 80), and the last tile is not full.  A paged pool's entries are copied out of the output."""
-    rows, d = 512, 53 * 128
-    shape = wl.gpt3_175b_share_shape(1).replace(d_model=d, n_heads=53, d_ff=512)
+# 512 rows in one launch that stores.  Tiles of 256 x 160 (configuration 8): waves of 80 features, one of which holds the last queries
+# and the first keys (20352 = 3 x 6784, 6784 = 84.8 x 80); of 256 x 128 (5): waves of 64, keys begin inside a tile.  The last tile is not full.
+@pytest.mark.parametrize("dh,heads,cfg", [(128, 53, 8), (64, 106, 8), (64, 81, 5)])
+def test_tiles_whose_waves_straddle_heads(dh, heads, cfg):
+    """A paged pool's entries are copied out of the output."""
+    rows, d = 512, heads * dh
+    assert exe.exe_op_gemm_model_plan(wl.DTYPE_BF16, rows, 3 * d, d) == [{"rows": rows, "route": 0, "cfg": cfg, "splits": 1, "large": 1}]
+    assert exe.exe_op_gemm_kv_plan(wl.DTYPE_BF16, rows, 3 * d, d) == ([(rows, 1)], rows)
+    shape = wl.gpt3_175b_share_shape(1).replace(d_model=d, n_heads=heads, head_dim=dh, d_ff=512)
     w = wl.make_weights(shape, 5, device=DEV)
     lens = np.array([200, 133, 1, 178], dtype=np.int32)
     x = torch.randn((rows, d), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV).bfloat16()
