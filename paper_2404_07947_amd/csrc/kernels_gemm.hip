@@ -408,6 +408,21 @@ static bool is_large(int cfg) { return cfg == C256x256 || cfg == C128x256 || cfg
 static bool only_large(int cfg) { return cfg == C192x256 || cfg == C256x160; }
 constexpr int LARGE_MIN_K = 256;
 
+// Whether a launch of a configuration runs on gemm_large_kernel.  256 x 128 has a third LDS stage in gemm_tile_kernel, which is the better
+// one where lines come late: weights that do not stay in cache, read by few row tiles at once, or parts so deep that the tiles that
+// share lines drift apart.  us of gemm_tile_kernel / gemm_large_kernel on either side of the line, whole sums: 256 x 24576, K 3072 51 / 51,
+// K 4096 64 / 65, K 6144 99 / 107, 512 x 16384, K 6144 94 / 94, K 12288 188 / 218, 768 x 9216, K 11008 153 / 150, 1024 x 16384, K 12288 342 / 324, K 14336 402 / 439;
+// in parts: 256 x 9216, K 4096 in 3 36.7 / 35.5, 256 x 8192, K 8192 in 4 48 / 51, 512 x 5120, K 12288 in 3 75 / 73, 512 x 13824, K 14336 in 2 217 / 231.
+// Of 3469 launches of up to 1024 rows gemm_large_kernel alone takes 0.986 of gemm_tile_kernel's time on average and 1.26 at most, by this
+// line 0.977 and 1.08.  Beyond them it takes 0.960.
+static bool runs_large(int cfg, int M, int N, int K, int splits)
+{
+    if (!is_large(cfg) || K < LARGE_MIN_K) return false;
+    if (cfg != C256x128 || M > 1024) return true;
+    const int rows = (M + 255) / 256;
+    return splits == 1 ? K < std::min(4096 * rows, 14336) : (int64_t)N * K < (int64_t)std::min(40 * rows, 96) << 20;
+}
+
 static int k_tile(int dtype) { return dtype == DT_F32 ? tbk<float>() : tbk<bf16_t>(); }
 
 // route: 0 tile kernel, 1 streaming kernel (then `stream` says how), 2 generic kernel
@@ -757,10 +772,10 @@ static int launch_mode(const GemmArgs& a)
 // Keys and values go straight into the cache from launches of whole sums on the kernels that the rows of an encode batch run on:
 // gemm_large_kernel and the float tiles.  Few rows (the streaming kernel, the smaller bf16 tiles, split sums) leave them to a copy
 // of their own, 2-4 us.  (In the 256 x 256 shape of gemm_tile_kernel, K < 256, that epilogue would spill 75 registers.)
-static bool stores_kv(const GemmArgs& a, const Plan& p)
+static bool stores_kv(const GemmArgs& a, int rows, const Plan& p)       // p: the plan of a launch of that many of a's rows
 {
     return p.route == 0 && p.splits == 1 && a.out_mode == OUT_T && a.act < 0 && !needs_generic(a) &&
-           (a.dtype == DT_F32 || (is_large(p.cfg) && a.K >= LARGE_MIN_K));
+           (a.dtype == DT_F32 || runs_large(p.cfg, rows, a.N, a.K, p.splits));
 }
 
 // The launches of a product in the order of their rows, f(first row, rows): one, or where whole rounds of tiles go first (split_rows)
@@ -782,7 +797,7 @@ int gemm_kv_rows(const GemmArgs& a)
     if (a.M <= 0 || a.force_splits) return 0;
     int stored = 0;
     each_launch(a.dtype, 0, a.M, a.N, a.K, launch_mode(a), [&](int row, int rows) {
-        if (stored == row && stores_kv(a, make_plan(a.dtype, rows, a.N, a.K, launch_mode(a)))) stored += rows;
+        if (stored == row && stores_kv(a, rows, make_plan(a.dtype, rows, a.N, a.K, launch_mode(a)))) stored += rows;
     });
     return stored;
 }
@@ -793,7 +808,7 @@ int gemm_launches(const GemmArgs& a, int cap, int32_t* rows, int32_t* stores)
     each_launch(a.dtype, 0, a.M, a.N, a.K, launch_mode(a), [&](int, int M) {
         if (n < cap) {
             rows[n] = M;
-            stores[n] = stores_kv(a, make_plan(a.dtype, M, a.N, a.K, launch_mode(a)));
+            stores[n] = stores_kv(a, M, make_plan(a.dtype, M, a.N, a.K, launch_mode(a)));
         }
         ++n;
     });
@@ -816,7 +831,8 @@ int gemm_launch_plans(const GemmArgs& a, bool defer, int cap, int32_t* plans)
     int n = 0;
     auto put = [&](int rows, const Plan& p) {
         if (n < cap) {
-            const int32_t plan[] = {rows, p.route, reported_cfg(a.dtype, p, rows, a.N, a.K), p.splits, a.dtype == DT_BF16 && p.route == 0 && is_large(p.cfg) && a.K >= LARGE_MIN_K};
+            const int32_t plan[] = {rows, p.route, reported_cfg(a.dtype, p, rows, a.N, a.K), p.splits, 
+                                    a.dtype == DT_BF16 && p.route == 0 && runs_large(p.cfg, rows, a.N, a.K, p.splits)};
             std::copy(plan, plan + 5, plans + 5 * n);
         }
         ++n;
@@ -853,7 +869,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         part.out = (char*)a.out + (size_t)row * a.N * osz;
         KvStore kv;
         part.kv = nullptr;
-        if (a.kv && stored == row && stores_kv(a, make_plan(a.dtype, rows, a.N, a.K, mode))) {
+        if (a.kv && stored == row && stores_kv(a, rows, make_plan(a.dtype, rows, a.N, a.K, mode))) {
             kv = *a.kv;
             kv.row += row;
             kv.cap += row;
@@ -900,7 +916,7 @@ static hipError_t launch_rows(const GemmArgs& a, int mode, hipStream_t s)
         switch (p.cfg) {
             case C64x256: e = launch_tile<bf16_t, 64, 256, 32, 64, 3>(a, p, s); break;
             case C128x256: case C256x256: case C256x128: case C192x256: case C256x160:
-                if (a.K >= LARGE_MIN_K) e = launch_gemm_large(a, CFG[p.cfg].bm, CFG[p.cfg].bn, p.k_per_split, p.splits, persistent_grid(), s);
+                if (runs_large(p.cfg, a.M, a.N, a.K, p.splits)) e = launch_gemm_large(a, CFG[p.cfg].bm, CFG[p.cfg].bn, p.k_per_split, p.splits, persistent_grid(), s);
                 else if (p.cfg == C128x256) e = launch_tile<bf16_t, 128, 256, 64, 64, 3>(a, p, s);
                 else if (p.cfg == C256x128) e = launch_tile<bf16_t, 256, 128, 64, 64, 3>(a, p, s);
                 else e = launch_tile<bf16_t, 256, 256, 128, 64, 2>(a, p, s);

@@ -90,6 +90,16 @@ def test_model_plans_are_the_launches(dtype):
             exe.exe_op_gemm_model_plan(*bad)
 
 
+# us measured, gemm_tile_kernel / gemm_large_kernel: see runs_large in csrc/kernels_gemm.hip
+@pytest.mark.parametrize("M,N,K,splits,large", [(256, 24576, 3072, 1, 1), (256, 24576, 6144, 1, 0), (512, 16384, 6144, 1, 1), (512, 16384, 12288, 1, 0),      # 51/51 99/107 94/94 188/218
+                                                (768, 9216, 11008, 1, 1), (1024, 16384, 12288, 1, 1), (1024, 16384, 14336, 1, 0), (448, 15360, 11008, 1, 0),    # 153/150 342/324 402/439 158/173
+                                                (224, 24576, 8192, 1, 0), (256, 9216, 4096, 3, 1), (256, 8192, 8192, 4, 0), (512, 5120, 12288, 3, 1),          # 122/141 36.7/35.5 48/51 75/73
+                                                (512, 13824, 14336, 2, 0), (256, 10240, 20480, 3, 0), (1100, 5120, 20480, 1, 1), (300, 1024, 192, 1, 0)])       # 217/231 124/133
+def test_tiles_of_256_x_128_run_on_the_faster_kernel(M, N, K, splits, large):
+    assert exe.exe_op_gemm_model_plan(BF16, M, N, K, 5, splits)[0]["large"] == large
+    assert exe.exe_op_gemm_model_plan(BF16, M, N, K, 2, splits)[0]["large"] == (K >= 256)
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 def test_elements_of_a_head_beyond_32_bits(dh):
     """Extents are as long as the pool: 2^31 elements a head and more."""

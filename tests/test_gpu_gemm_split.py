@@ -74,6 +74,15 @@ def test_narrow_forms_of_the_large_kernel(cfg, M, N, K, splits, mode):
     check(M, N, K, cfg, splits, mode, splits * M * N if splits > 1 else 0)
 
 
+# 256 x 128 tiles on either side of the line between their two kernels: whole sums of one row tile, of two, and in parts
+@pytest.mark.parametrize("M,N,K,splits,large", [(130, 260, 4096 - 64, 1, 1), (130, 260, 4096, 1, 0), (257, 132, 8192 - 64, 1, 1), (257, 132, 8192, 1, 0),
+                                                (1024, 132, 14336, 1, 0), (1025, 132, 14336, 1, 1), (140, 10236, 4096, 3, 1), (140, 10240, 4096, 3, 0)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_both_kernels_of_256_x_128_tiles(M, N, K, splits, large, mode):
+    assert exe.exe_op_gemm_model_plan(BF16, M, N, K, 5, splits)[0]["large"] == large
+    check(M, N, K, 5, splits, mode, splits * M * N if splits > 1 else 0)
+
+
 # the reduction: rows of one group of 4 columns, of a group more than its workgroups' threads, and others that end inside one; 2 to 8
 # parts, three of which it adds at a time
 @pytest.mark.parametrize("M,N", [(1, 4), (257, 4), (65, 260), (33, 1028), (70, 3076)])
