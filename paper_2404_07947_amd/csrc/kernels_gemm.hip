@@ -451,9 +451,11 @@ static const Knobs& knobs()
 // norm_kernel).
 //
 // Two sets of rates.  A model's launches (`model`): fitted to 2800 launches on MI355X, 13 row counts from 24 to 2048 x 11
-// weight shapes of 1024 to 49152 features, six tile shapes x 1..8 splits, weights from HBM, those of 256x128 and 256x160 afterwards
-// to 8900 more, 32 row counts from 104 to 16384 x 14 weight shapes: there the picks take 1.7 % more than the best measured choice on
-// average below 4096 rows (without the two 2.4 %), 0.1 % (0.2 %) from there on; at worst 25 %, of launches of 10 to 20 us.
+// weight shapes of 1024 to 49152 features, six tile shapes x 1..8 splits, weights from HBM; those of 256x128 and 256x160 afterwards
+// to 26100 launches of 2950 shapes, rows 193 to 16384, features 500 to 65536, depths 512 to 20480 (a sixteenth of the shapes at weights of the
+// models that the benchmarks name): there the picks take 0.9 % more than the best measured choice on average (without the two 1.8 %; at up to
+// 3000 features 1.8 and 2.2 %, wider 0.5 and 1.7 %), 21 % at worst.  On 900 other shapes of these ranges the launches as planned take 0.989 of the time that they
+// take without the two, 1.10 at most.
 // gemm_large_kernel is priced by its time per k-tile and per tile (large_rate), 16 % more when every CU runs it: the clock falls.  Up to 192
 // rows, where the estimate also has to compare with the streaming kernel's, the rates of an earlier fit stay (within 2 % of
 // the best choice on average), and so they do for exe_op_gemm's launches up to 1024 rows: its callers have been given these
@@ -461,19 +463,21 @@ static const Knobs& knobs()
 struct Rates { double fill, mfma, hbm, partial, reduce; };
 static const Rates MODEL_RATES{44e9, 3.5e12, 6.5e12, 5.3e12, 4.5e-6}, OP_RATES{35e9, 3.5e12, 5.5e12, 3e12, 1e-6};
 
-// Seconds per k-tile and per tile.  What a CU takes in is bound by the lines that it has in flight, some 300: a line from HBM
-// costs it 3.3 ns, one from L2 1.6.  So the shapes that read fewer weights per activation, 256 x 128 and 256 x 160, gain where the weights
-// are the larger operand and come from memory (0.85 of their time there), and of equal area 256 x 128 is the better one: us of 256 x
-// 128 and 128 x 256, 512 x 15360, K 5120 77 / 82, 256 x 20480 76 / 85; but 8192 x 3072, K 1024 53 / 53, 2048 x 1024, K 16384 in 3 parts
-// 1.35x, and of 36864 x 12288 weights (0.9 GB) 256 to 2048 rows 0.97 to 1.03x.
-// 256 x 160 besides fits widths that leave the others' last round half empty: 512 x 20480, K 5120 86 (192 x 256 98), 1024 x 20480 168 (193).
+// Seconds per k-tile and per tile.  What a CU takes in is bound by the lines that it has in flight, whatever the instructions, and a line
+// from HBM takes about twice as long as one from L2.  So the shapes that read fewer weights per activation, 256 x 128 and 256 x 160, gain the
+// more, the more of the lines are weights, which come from memory.  Of 2600 pairs of 256 x 128 and 128 x 256, of equal area and the same parts, the
+// former takes 0.94 to 0.97 of the latter's time where N is 4 M and more (512 x 15360, K 5120 74 / 84 us), 1.00 where they are equal, and in
+// parts 1.03 to 1.06 where M is 2 N and more (1024 x 1024, K 16384 in 8 54 / 46): their prices follow M / (M + N).  That of 256 x 160 follows the
+// weights' size besides, without which it was 0.93 of the time at 0.5 GB and 0.87 at 1 GB.  256 x 160 also fits widths that leave the others'
+// last round half empty: 512 x 20480, K 5120 86 (192 x 256 98), 1024 x 20480 168 (193).
 struct LargeRate { double per, fixed; };
-static LargeRate large_rate(int cfg)
+static LargeRate large_rate(int cfg, int M, int N, int K)
 {
+    const double share = M / ((double)M + N), weights = (double)N * K;
     switch (cfg) {
         case C128x256: return {0.80e-6, 3e-6};
-        case C256x128: return {0.80e-6, 3.2e-6};
-        case C256x160: return {0.95e-6, 3.5e-6};
+        case C256x128: return {0.76e-6 * (1 + 0.25 * share), 2e-6};
+        case C256x160: return {0.78e-6 * (1 + 0.25 * share) * (1 + 0.3 * weights / (weights + (1 << 28))), 3.6e-6};
         case C192x256: return {0.93e-6, 4.5e-6};
         default: return {1.03e-6, 5e-6};
     }
@@ -496,8 +500,7 @@ static double plan_cost(int dtype, int cfg, int splits, int M, int N, int K, boo
     double t;
     if (model && is_large(cfg)) {
         double busy = wgs / rounds / 256;
-        LargeRate lr = large_rate(cfg);
-        if (bm == 256 && bn < 256 && N >= 5120 && N >= 4 * (int64_t)M && (int64_t)N * K < (1 << 28)) lr.per *= 0.85;
+        const LargeRate lr = large_rate(cfg, M, N, K);
         t = rounds * (ktiles * lr.per * (1.0 + 0.16 * busy) + lr.fixed);
     } else {
         double fill = ktiles * (bm + bn) * TROW / r.fill;

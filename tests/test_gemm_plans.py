@@ -100,6 +100,24 @@ def test_tiles_of_256_x_128_run_on_the_faster_kernel(M, N, K, splits, large):
     assert exe.exe_op_gemm_model_plan(BF16, M, N, K, 2, splits)[0]["large"] == (K >= 256)
 
 
+# us measured, the tiles taken / the best of another form: see large_rate in csrc/kernels_gemm.hip.  Weights that no benchmarked model has
+@pytest.mark.parametrize("M,N,K,cfg,splits", [(384, 4096, 3072, 5, 4), (1144, 524, 640, 5, 1), (2130, 1096, 640, 5, 1), (440, 12288, 6144, 2, 2),      # 24.3/25.0 11.7/14.2 12.2/14.1 79/87
+                                              (700, 12288, 20480, 2, 3), (1711, 5480, 2560, 8, 1), (2700, 7168, 1536, 8, 1), (2120, 640, 4352, 1, 5),  # 300/340 45/50 58/64 26/29
+                                              (300, 12288, 1536, 0, 1), (1500, 1536, 512, 5, 1), (900, 5120, 4096, 8, 2)])     # 24/26 11.6/12.9 50/55
+def test_models_products_take_the_faster_tiles(M, N, K, cfg, splits):
+    assert [(p["cfg"], p["splits"]) for p in exe.exe_op_gemm_model_plan(BF16, M, N, K)] == [(cfg, splits)]
+
+
+# the same tiles of every form on both sides: 5120 features, N = 4 M, weights of 2^28 elements
+@pytest.mark.parametrize("widths,depths,rows", [((5116, 5120), range(512, 20481, 512), range(208, 1281, 16)), ((6396, 6400), range(512, 20481, 512), (1600,)),
+                                                ((26212, 26216), (10240,), range(208, 1281, 16))])
+def test_four_features_more_do_not_change_the_tiles(widths, depths, rows):
+    for K in depths:
+        for M in rows:
+            a, b = ([(p["rows"], p["cfg"], p["splits"]) for p in exe.exe_op_gemm_model_plan(BF16, M, N, K)] for N in widths)
+            assert a == b, (M, K)
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 def test_elements_of_a_head_beyond_32_bits(dh):
     """Extents are as long as the pool: 2^31 elements a head and more."""
