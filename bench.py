@@ -92,8 +92,8 @@ def accumulate(acc, rows):
 # HBM-side bytes (rocprofv3 FETCH_SIZE x 2 + WRITE_SIZE, factors from a plain copy) per algorithmic byte, measured
 # per kernel at the OPT-13B bench shapes by a separate counter run (profiles/traffic_opt13b_kernels.md gives the
 # command and the table; regenerate it whenever a kernel it covers changes).  gemm_skinny: at the job's mean decode
-# batch of 153 rows (1.06 at 64 rows, 1.45 at 256: the split-K partial sums).  A class not listed reports null.
-TRAFFIC_RATIO = {"gemm_tile": 4.83, "gemm_skinny": 1.27, "decode_attn": 1.0, "cross_attn": 1.0, "prefill_attn": 1.02}
+# batch of 153 rows (1.06 at 64 rows, 1.37 at 256: the split-K partial sums).  A class not listed reports null.
+TRAFFIC_RATIO = {"gemm_tile": 4.79, "gemm_skinny": 1.27, "decode_attn": 1.0, "cross_attn": 1.0, "prefill_attn": 1.02}
 
 
 def roofline_entry(kind, a):
