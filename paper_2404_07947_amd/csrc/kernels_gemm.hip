@@ -397,8 +397,8 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(int M, int N, int K, 
 // ---------------------------------------------------------------- host-side routing
 // Tile configurations.  Four have BN = 256 (the weight share of the LDS fill traffic is BN / (BM + BN), which is what a
 // weight-streaming decode GEMM wants large); 64x128, 128x128 and 256x128 halve BN for matrices with few output features,
-// where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows and 256x128 run on gemm_large_kernel if K allows, the
-// others on gemm_tile_kernel.  192x256 and 256x160 run on gemm_large_kernel only.
+// where more tiles beat deeper split-K.  The BN = 256 shapes of 128 and more rows run on gemm_large_kernel if K allows, 256x128 on
+// either (runs_large), the others on gemm_tile_kernel.  192x256 and 256x160 run on gemm_large_kernel only.
 enum Cfg { C64x256 = 0, C128x256, C256x256, C64x128, C128x128, C256x128, C192x256, F64x64, C256x160, N_CFG };      // F64x64: a float tile only
 struct CfgInfo { int bm, bn; };
 static const CfgInfo CFG[N_CFG] = {{64, 256}, {128, 256}, {256, 256}, {64, 128}, {128, 128}, {256, 128}, {192, 256}, {64, 64}, {256, 160}};

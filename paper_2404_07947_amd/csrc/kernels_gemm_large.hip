@@ -22,8 +22,9 @@
 // and with the tile height that fills the chip:
 //   12288 x  1024 x 16384   396 -> 335 (192 rows)   8192 x 1024 x 1024  36 -> 27, 8192 x 1024 x 4096  92 -> 63 (128 rows)
 // Launches of one round or less are bound by what a CU takes in (see large_rate in kernels_gemm.hip); there 256 x 128 and 256 x 160 take
-//   512 x 15360 x 5120  84 -> 78 (256 x 128 for 128 x 256)    512 x 20480 x 5120  98 -> 86, 1024 x 20480 x 5120 193 -> 168 (256 x 160 for 192 x 256)
-// A third LDS stage where it fits (128 x 256, 256 x 128) gave 2 % and took it back in epilogues of half the rows; a tile's lines fetched into L2 by
+//   512 x 15360 x 5120  84 -> 75 (256 x 128 for 128 x 256)    512 x 20480 x 5120  98 -> 86, 1024 x 20480 x 5120 193 -> 168 (256 x 160 for 192 x 256)
+// A third LDS stage where it fits (128 x 256, 256 x 128) gave 2 % and took it back in epilogues of half the rows (where it gives more, 256 x 128
+// runs on gemm_tile_kernel's three: runs_large in kernels_gemm.hip); a tile's lines fetched into L2 by
 // one of the CUs that share them, some k-tiles ahead, cost as many lines as it saved (3 to 20 % slower).
 #include <type_traits>
 
